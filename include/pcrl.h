@@ -273,7 +273,7 @@ typedef struct {
 } PcrlQuery;
 
 typedef struct {
-    int32_t tile_rays;          /* ray slots per work item (multiple of 64); <= 0 -> 1024 */
+    int32_t tile_rays;          /* ray slots per work item (multiple of 64); <= 0 -> 64..1024, eight per wave */
     float   compact_threshold;  /* theta: a bounce keeps survivors in place when the predicted density of live
                                    rays is >= theta, else compacts them; > 1 always compacts; < 0 -> 0.6 */
     int32_t waves_per_cu;       /* persistent waves per compute unit; <= 0 -> 16 */
