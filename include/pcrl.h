@@ -100,11 +100,12 @@ typedef struct {
     int32_t flags;                        /* 0, or PCRL_VOXEL_COMPACT */
 } PcrlVoxelParams;
 
-/* PcrlVoxelParams.flags: keep no dense cell table of the leaves' parent bricks
- * (8 bytes per leaf cell of every occupied parent); the traversal then reads
- * the bricks' occupancy masks (less device memory, slower).  The table is
- * also left out when the parent-to-leaf ratio exceeds 16 or it would exceed
- * 256 MiB (beyond the last-level cache it slows the traversal down). */
+/* PcrlVoxelParams.flags: the implicit surface (sdf_intersect, PCRL_LAUNCH_SDF)
+ * keeps no dense cell table of the leaves' parent bricks (8 bytes per leaf
+ * cell of every occupied parent) but walks the bricks' occupancy masks (less
+ * device memory, slower).  The table is also left out when the
+ * parent-to-leaf ratio exceeds 16 or it would exceed 256 MiB.  The launcher
+ * keeps no such table. */
 #define PCRL_VOXEL_COMPACT 1
 
 typedef struct {
@@ -206,15 +207,15 @@ typedef struct {
     /* PCRL_LAUNCH_STATS only (else 0) */
     int64_t dda_steps;                             /* cells entered at any level */
     int64_t leaves_visited;                        /* occupied leaves whose points were tested */
-    int64_t node_lookups;                          /* hierarchy lookups (level-0 map and brick words) */
+    int64_t node_lookups;                          /* hierarchy lookups (top cells and block records) */
     int64_t surfel_tests;                          /* ray-disk tests */
     int64_t hits;                                  /* segments ending on a surfel */
     int64_t algo_bytes;                            /* algorithmic bytes of the trace kernels: hierarchy
-                                                      reads (4 B level-0, 8-12 B per brick word, 8 B per
+                                                      reads (8 B per top cell, 16 B per block, 8 B per
                                                       leaf), 32 B per surfel tested, 36 B ray state read per
                                                       later segment, 52 B per reflection, 16 B per record */
     int64_t empty_leaf_steps;                      /* DDA steps into empty leaves of occupied parents */
-    int64_t uniform_leaf_visits;                   /* leaf visits shared by every walking lane of the wave */
+    int64_t uniform_leaf_visits;                   /* leaf visits shared by every lane of the wave at a leaf */
     int64_t wave_dda_iters;                        /* DDA loop iterations per wave, summed over waves */
     int64_t wave_test_iters;                       /* surfel-test loop iterations per wave, summed over waves */
     int64_t algo_bytes_bounce[PCRL_MAX_REFLECTIONS + 1];  /* algo_bytes of each bounce kernel */
@@ -470,7 +471,8 @@ typedef struct {
  * A ray with a zero or non-finite direction or origin, or t_lo > t_hi, has
  * no intersection.  Asynchronous on `stream`, except that the first call on
  * a scene builds and keeps with the scene an index of each point in the leaf
- * of its centre (16 B per point twice, 4 B per entry) and waits for it.  Calls
+ * of its centre (16 B per point twice, 4 B per entry) with the structures of its leaf
+ * walk (a table or skip radii of the leaf cells), and waits for it.  Calls
  * of 65536 rays or more sort the rays by origin and direction first (outputs
  * stay in the caller's order).  PCRL_EINVAL on NULL arrays, out-of-range
  * parameters, or a scene holding dynamic points (update_points): the surface

@@ -169,8 +169,8 @@ class Scene:
 def build_voxels(xyz, normal, label, levels, surfel_radius, t_eps=0.0, device=None, compact=False) -> Scene:
     """Voxelise a labeled point cloud (positions [N,3], normals [N,3], labels [N]).
 
-    ``compact`` keeps no dense cell table of the leaves' parent bricks (less
-    device memory, slower traversal)."""
+    ``compact`` keeps no dense cell table for the implicit surface (less
+    device memory, slower ``sdf_intersect``)."""
     device = _dev(device)
     xyz = _as_tensor(xyz, torch.float32, device, 3)
     normal = _as_tensor(normal, torch.float32, device, 3)

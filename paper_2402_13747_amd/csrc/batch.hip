@@ -102,11 +102,13 @@ __global__ __launch_bounds__(TILE_BLOCK) void k_batch_tiles(BatchCtl* c, int b) 
     }
 }
 
-// One persistent kernel per group of queries with the same number of voxel
-// levels NL and overlay presence OV (the specialisations of the bounce body).
-template <bool FIRST, bool STATS, int NL, bool OV>
+// One persistent kernel per group of queries with the same top-grid depth TD
+// and overlay presence OV (the specialisations of the bounce body).
+template <bool FIRST, bool STATS, int TD, bool OV>
 __global__ __launch_bounds__(TRACE_BLOCK) void k_trace_batch(BatchCtl* c, int b) {
-    __shared__ LeafTestLds lds[TRACE_BLOCK / 64];
+    __shared__ TraceLds<TRACE_BLOCK / 64> lds;
+    ahead_init(lds.ahead, threadIdx.x, TRACE_BLOCK);
+    __syncthreads();
     stat_t cnt[ST_COUNT] = {};
     const uint32_t n_tiles = c->n_tiles;
     const uint32_t n_q = c->n_q;
@@ -124,13 +126,14 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace_batch(BatchCtl* c, int b)
             else hi = mid;
         }
         const uint32_t q = __builtin_amdgcn_readfirstlane(lo);
-        const TraceArgs& a = c->qs[q];
+        const ArgsPtr args = uniform_args(c->qs + q);
+        const TraceArgs& a = *(const TraceArgs*)args;
         const uint32_t range = c->range[q];
         const bool ip = c->in_place[q] != 0u;
         const uint32_t start = (t - c->tile_off[q]) * tile;
         const uint32_t end = min(start + tile, range);
         for (uint32_t base = start; base < end; base += 64)
-            trace_chunk<FIRST, STATS, NL, OV>(a, lds[threadIdx.x >> 6], b, base, range, ip, cnt);
+            trace_chunk<FIRST, STATS, TD, OV>(args, lds.ahead, lds.w[threadIdx.x >> 6], b, base, 64, range, ip, cnt);
         if (STATS) flush_stats<STATS>(cnt, a.stats ? a.stats + (size_t)b * PCRL_NSTATS : nullptr);
     }
 }
@@ -152,24 +155,24 @@ struct BatchShared {
 
 // Queries of one kernel specialisation, contiguous in the query table.
 struct BatchGroup {
-    int nl;
+    int depth;
     bool ov;
 };
 
-template <bool FIRST, bool STATS, int NL>
-static void launch_group_nl(bool ov, BatchCtl* ctl, int b, unsigned grid, hipStream_t s) {
-    if (ov) hipLaunchKernelGGL((k_trace_batch<FIRST, STATS, NL, true>), dim3(grid), dim3(TRACE_BLOCK), 0, s, ctl, b);
-    else hipLaunchKernelGGL((k_trace_batch<FIRST, STATS, NL, false>), dim3(grid), dim3(TRACE_BLOCK), 0, s, ctl, b);
+template <bool FIRST, bool STATS, int TD>
+static void launch_group_td(bool ov, BatchCtl* ctl, int b, unsigned grid, hipStream_t s) {
+    if (ov) hipLaunchKernelGGL((k_trace_batch<FIRST, STATS, TD, true>), dim3(grid), dim3(TRACE_BLOCK), 0, s, ctl, b);
+    else hipLaunchKernelGGL((k_trace_batch<FIRST, STATS, TD, false>), dim3(grid), dim3(TRACE_BLOCK), 0, s, ctl, b);
 }
 
 template <bool FIRST, bool STATS>
 static void launch_group(const BatchGroup& g, BatchCtl* ctl, int b, unsigned grid, hipStream_t s) {
-    static_assert(PCRL_MAX_LEVELS == 4, "one kernel specialisation per level count");
-    switch (g.nl) {
-    case 1: launch_group_nl<FIRST, STATS, 1>(g.ov, ctl, b, grid, s); break;
-    case 2: launch_group_nl<FIRST, STATS, 2>(g.ov, ctl, b, grid, s); break;
-    case 3: launch_group_nl<FIRST, STATS, 3>(g.ov, ctl, b, grid, s); break;
-    default: launch_group_nl<FIRST, STATS, 4>(g.ov, ctl, b, grid, s); break;
+    static_assert(PCRL_MAX_LEVELS == 4, "one kernel specialisation per top-grid depth");
+    switch (g.depth) {
+    case -1: launch_group_td<FIRST, STATS, -1>(g.ov, ctl, b, grid, s); break;
+    case 0: launch_group_td<FIRST, STATS, 0>(g.ov, ctl, b, grid, s); break;
+    case 1: launch_group_td<FIRST, STATS, 1>(g.ov, ctl, b, grid, s); break;
+    default: launch_group_td<FIRST, STATS, 2>(g.ov, ctl, b, grid, s); break;
     }
 }
 
@@ -207,7 +210,7 @@ static int run_graph(const std::vector<BatchCtl>& host_ctl, const std::vector<Ba
         char head[96];
         snprintf(head, sizeof head, "%d/%p/%d/%u/%d", dev, (void*)s, kmax, grid, stats ? 1 : 0);
         key = head;
-        for (const auto& g : groups) key += "/" + std::to_string(g.nl) + (g.ov ? "o" : "b");
+        for (const auto& g : groups) key += "/" + std::to_string(g.depth) + (g.ov ? "o" : "b");
     }
     std::lock_guard<std::mutex> lock(g_graph_mu);
     GraphEntry& e = g_graphs[key];
@@ -288,20 +291,20 @@ static int batch_impl(const PcrlQuery* q, int32_t n_q, const PcrlBatchParams* bp
             set_error("%s", msg);
         }
     }
-    // query table ordered by kernel specialisation (levels, overlay); one group per run
+    // query table ordered by kernel specialisation (top-grid depth, overlay); one group per run
     std::vector<BatchGroup> groups;
     std::vector<uint32_t> g_first, g_count;
     if (!rc) {
         std::vector<int> order((size_t)n_q);
         for (int i = 0; i < n_q; ++i) order[(size_t)i] = i;
-        auto cls = [&](int i) { return args[(size_t)i].v.nlev * 2 + (args[(size_t)i].has_ov ? 1 : 0); };
+        auto cls = [&](int i) { return (args[(size_t)i].v.depth + 1) * 2 + (args[(size_t)i].has_ov ? 1 : 0); };
         std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cls(x) < cls(y); });
         std::vector<TraceArgs> sorted((size_t)n_q);
         for (int k = 0; k < n_q; ++k) {
             const TraceArgs& a = args[(size_t)order[(size_t)k]];
             sorted[(size_t)k] = a;
             if (k == 0 || cls(order[(size_t)k]) != cls(order[(size_t)k - 1])) {
-                groups.push_back(BatchGroup{a.v.nlev, a.has_ov != 0});
+                groups.push_back(BatchGroup{a.v.depth, a.has_ov != 0});
                 g_first.push_back((uint32_t)k);
                 g_count.push_back(0);
             }

@@ -5,11 +5,15 @@
 // that becomes a hierarchy of 1..4 levels, each level dividing the previous
 // one by an integer ratio:
 //
-//   level 0          dense int32 map over the coarse grid (node index or -1)
-//   levels 1..L-1    occupancy bricks: per occupied parent a bitmask over its
-//                    ratio^3 children plus, per 64-bit word, the index of the
-//                    first child of that word (child = base + popcount)
-//   leaves           (first entry, count) ranges into leaf-ordered surfels
+//   top grid         dense, over the cells of the leaves' parents (or a coarser
+//                    level when that grid would be too large): the node of an
+//                    occupied cell with the box of its leaves, or the empty
+//                    boxes that start at an empty one, per direction octant
+//   blocks           per leaves' parent one 16-byte record per 4 x 4 x 4 leaves
+//   bricks           per occupied cell of every level a bitmask over its
+//                    ratio^3 children (linear order)
+//   leaves           (first entry, count) ranges into leaf-ordered surfels, in
+//                    key order and once more block by block
 //   surfels          two 16-byte streams per entry, in leaf order:
 //                    (x, y, z, point id) and (unit normal, label rank)
 //
@@ -19,8 +23,9 @@
 //
 // Pipeline: ingest (normalise normals, validate, AABB, max label) -> sync ->
 // label ranks -> per-point leaf counts -> scan -> sync -> emit (key, id) ->
-// radix sort -> per-tile node-start counts + their scan -> sync -> level-0
-// map, bricks, leaf ranges (one pass over the sorted keys) -> surfel gather.
+// radix sort -> per-tile node-start counts + their scan -> sync -> bricks,
+// leaf ranges, occupied top cells (one pass over the sorted keys) -> skip
+// codes of the top grid, blocks -> surfel gather.
 #include "internal.h"
 
 #include <algorithm>
@@ -334,6 +339,11 @@ struct HierOut {
     uint32_t* first_child[PCRL_MAX_LEVELS - 1];
     uint2* leaf;
     uint64_t* leaf_key;
+    int32_t F;                // level of the top grid
+    int32_t words;            // 64-bit words per row of `occ`
+    uint2* top;
+    uint64_t* occ;            // occupied top cells, one bit each, rows along x
+    uint32_t* tcell;          // top cell of every level-F node
 };
 
 // Node starts of every level from the sorted keys: an entry opens a node of
@@ -410,6 +420,27 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_link(const uint64_t* keys, int6
                 const uint64_t top = k >> ls.sh[0];
                 h.map0[h.unmap0 ? (uint64_t)h.unmap0[top] : top] = (int32_t)node[0];
             }
+            if (l == h.F) {
+                // the node's cell of the top grid: its level-0 cell, then the local cells down to level F
+                const uint64_t top = k >> ls.sh[0];
+                const uint32_t c0 = (uint32_t)(h.unmap0 ? (uint64_t)h.unmap0[top] : top);
+                uint32_t x = c0 % (uint32_t)v.dim0[0], y = c0 / (uint32_t)v.dim0[0], z = y / (uint32_t)v.dim0[1];
+                y -= z * (uint32_t)v.dim0[1];
+#pragma unroll
+                for (int i = 1; i < PCRL_MAX_LEVELS; ++i) {
+                    if (i > h.F) break;
+                    const uint32_t r = (uint32_t)v.ratio[i - 1];
+                    const uint32_t loc = (uint32_t)((k >> ls.sh[i]) & ((uint64_t(1) << v.lbits[i]) - 1));
+                    x = x * r + loc % r;
+                    y = y * r + (loc / r) % r;
+                    z = z * r + loc / (r * r);
+                }
+                const size_t row = (size_t)y + (size_t)v.tdim[1] * z;
+                const size_t cell = row * (size_t)v.tdim[0] + x;
+                h.top[cell].x = node[l];
+                if (h.tcell) h.tcell[node[l]] = (uint32_t)cell;
+                atomicOr((unsigned long long*)&h.occ[row * (size_t)h.words + (x >> 6)], 1ull << (x & 63u));
+            }
             if (l == L - 1) {
                 const uint64_t top = k >> ls.sh[0];
                 const uint64_t cell0 = h.unmap0 ? (uint64_t)h.unmap0[top] : top;
@@ -441,252 +472,10 @@ __global__ void k_brick_base(const uint64_t* mask, const uint32_t* first_child, 
     }
 }
 
-// Box of the occupied children of every brick, in the brick's local child
-// coordinates (x + r (y + r z) order of the mask bits): lo x, y, z in bits
-// 0-14 and hi x, y, z in bits 15-29, 5 bits each (r <= 32).  Every child
-// outside the box is empty, so a ray in such a child crosses the brick's
-// empty rest up to the box or the brick's exit in one step.
-__global__ void k_brick_aabb(const uint64_t* mask, int64_t n_nodes, int nw, int r, uint32_t* aabb) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_nodes) return;
-    int lo0 = 31, lo1 = 31, lo2 = 31, hi0 = 0, hi1 = 0, hi2 = 0;
-    for (int w = 0; w < nw; ++w) {
-        uint64_t m = mask[(size_t)p * nw + w];
-        while (m) {
-            const int loc = 64 * w + __ffsll((long long)m) - 1;
-            m &= m - 1;
-            const int x = loc % r, y = (loc / r) % r, z = loc / (r * r);
-            lo0 = min(lo0, x); lo1 = min(lo1, y); lo2 = min(lo2, z);
-            hi0 = max(hi0, x); hi1 = max(hi1, y); hi2 = max(hi2, z);
-        }
-    }
-    aabb[p] = (uint32_t)lo0 | ((uint32_t)lo1 << 5) | ((uint32_t)lo2 << 10) | ((uint32_t)hi0 << 15) |
-              ((uint32_t)hi1 << 20) | ((uint32_t)hi2 << 25);
-}
-
-// Empty-space skip radius of every leaf cell of an occupied parent brick
-// (r^3 cells, r <= 16): R = 0 for an occupied leaf; otherwise the largest k
-// such that the cube of cells within Chebyshev distance k - 1 is empty and
-// inside the brick.  This is the per-voxel march distance of Section 2.2.4
-// (the longest per-axis distance to the closest voxel with content), limited
-// to the brick.  The cells within Chebyshev distance k of an occupied cell
-// are the occupancy dilated k times by the 3 x 3 x 3 cube, and the dilation
-// is separable: with the brick held as r^2 rows of r bits (row y + r z, bit
-// x), one step ORs each row with its shifts along x, then with its y and z
-// neighbour rows.  A cell first reached at step k is at distance k; the
-// border limits every radius to at most (r - 1) / 2 + 1, so that many steps
-// suffice.  One wave per brick (rows and distances in the wave's LDS).
-// RC > 0: the ratio is the compile-time constant RC (index arithmetic by
-// constants); RC = 0: the runtime r.
-constexpr int BDIST_RMAX = 16;
-
-__device__ __forceinline__ void build_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <int RC>
-__global__ __launch_bounds__(BUILD_BLOCK) void k_brick_dist(const uint64_t* mask, int nw, int r_rt, int64_t n_bricks,
-                                                            uint8_t* dist) {
-    __shared__ uint32_t rows_s[BUILD_BLOCK / 64][2][BDIST_RMAX * BDIST_RMAX];
-    __shared__ uint8_t d_s[BUILD_BLOCK / 64][BDIST_RMAX * BDIST_RMAX * BDIST_RMAX];
-    const int r = RC > 0 ? RC : r_rt;
-    const int n2 = r * r, n3 = n2 * r;
-    const int w = threadIdx.x >> 6;
-    const int lane = (int)lane_id();
-    const int64_t P = (int64_t)blockIdx.x * (BUILD_BLOCK / 64) + w;
-    if (P >= n_bricks) return;  // the whole wave: no block-wide barrier follows
-    uint32_t* cur = rows_s[w][0];
-    uint32_t* tmp = rows_s[w][1];
-    uint8_t* D = d_s[w];
-    const uint32_t full = (1u << r) - 1u;
-    // row j holds bits [r j, r j + r) of the brick's mask
-    for (int j = lane; j < n2; j += 64) {
-        const int b0 = r * j;
-        const uint64_t* m = mask + (size_t)P * nw + (b0 >> 6);
-        uint64_t bits = m[0] >> (b0 & 63);
-        if ((b0 & 63) + r > 64) bits |= m[1] << (64 - (b0 & 63));
-        cur[j] = (uint32_t)bits & full;
-    }
-    build_wave_sync();
-    for (int c = lane; c < n3; c += 64) D[c] = ((cur[c / r] >> (c % r)) & 1u) ? 0 : 255;
-    const int K = (r - 1) / 2 + 1;
-    for (int k = 1; k <= K; ++k) {
-        // along x, then y
-        for (int j = lane; j < n2; j += 64) {
-            const int y = j % r;
-            const uint32_t a = cur[j];
-            uint32_t t = a | (a << 1) | (a >> 1);
-            if (y > 0) {
-                const uint32_t b = cur[j - 1];
-                t |= b | (b << 1) | (b >> 1);
-            }
-            if (y < r - 1) {
-                const uint32_t b = cur[j + 1];
-                t |= b | (b << 1) | (b >> 1);
-            }
-            tmp[j] = t & full;
-        }
-        build_wave_sync();
-        // along z; the cells reached now are at distance k
-        for (int j = lane; j < n2; j += 64) {
-            const int z = j / r;
-            uint32_t t = tmp[j];
-            if (z > 0) t |= tmp[j - r];
-            if (z < r - 1) t |= tmp[j + r];
-            uint32_t nb = t & ~cur[j];
-            while (nb) {
-                const int x = __ffs(nb) - 1;
-                nb &= nb - 1u;
-                D[x + r * j] = (uint8_t)k;
-            }
-            cur[j] = t;
-        }
-        build_wave_sync();
-    }
-    for (int c = lane; c < n3; c += 64) {
-        const int x = c % r, y = (c / r) % r, z = c / n2;
-        const int db = min(min(min(x, r - 1 - x), min(y, r - 1 - y)), min(z, r - 1 - z));
-        dist[P * n3 + c] = (uint8_t)min((int)D[c], db + 1);
-    }
-}
-
-// Empty-space skip radii of the level-0 grid: for every cell the Chebyshev
-// distance (in cells, at most DIST0_CAP + 1) to the nearest occupied cell, so
-// the cube of radius d - 1 around an empty cell holds no occupied cell.  The
-// same march distance as inside the bricks, one level up.  Separable: one
-// pass per axis of out(c) = min over |t| <= DIST0_CAP of max(|t|, in(c + t e)),
-// starting from 0 (occupied) / 255 (empty).  A window that misses the
-// nearest occupied cell only lowers the result (conservative).
-constexpr int DIST0_CAP = 15;
-
-// Largest dense cell table built: the table pays off while it stays resident
-// in the 256 MB last-level (MALL) cache; a larger one (3.3 GB for a 20M-point
-// street canyon) turns every DDA step into an HBM round trip and doubled that
-// scene's trace time.  Beyond it the traversal reads the bricks' masks.
-constexpr int64_t CELL_TABLE_MAX_BYTES = (int64_t)256 << 20;
-
-__global__ void k_dist0_pass(const int32_t* map0, const uint8_t* in, uint8_t* out, int dx, int dy, int dz, int axis) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t n = (int64_t)dx * dy * dz;
-    if (c >= n) return;
-    const int x = (int)(c % dx), y = (int)((c / dx) % dy), z = (int)(c / ((int64_t)dx * dy));
-    const int pos = axis == 0 ? x : (axis == 1 ? y : z);
-    const int len = axis == 0 ? dx : (axis == 1 ? dy : dz);
-    const int64_t stride = axis == 0 ? 1 : (axis == 1 ? dx : (int64_t)dx * dy);
-    int m = 255;
-    const int t0 = max(-DIST0_CAP, -pos), t1 = min(DIST0_CAP, len - 1 - pos);
-    for (int t = t0; t <= t1; ++t) {
-        const int64_t q = c + t * stride;
-        const int a = map0 ? (map0[q] >= 0 ? 0 : 255) : (int)in[q];
-        m = min(m, max(abs(t), a));
-    }
-    out[c] = (uint8_t)min(m, DIST0_CAP + 1);
-}
-
-// Dense cell table of the leaves' parent bricks: one 8-byte load per DDA
-// step gives an occupied leaf's entry range, or, for an empty leaf, its skip
-// radii per direction octant.  Radius s of octant (sx, sy, sz) (bit a set:
-// the ray's component a is negative) means the box of s x s x s cells that
-// starts at the cell and extends along the octant's signs is empty and inside
-// the brick; a ray whose direction lies in that octant crosses the box in one
-// step.  s is the octant-restricted Chebyshev distance to the nearest
-// occupied cell, capped by the brick's far faces and by 15 (4 bits per
-// octant, 8 octants in the first word).
-// Computed on bit rows (the r <= 16 cells of a brick row along x in one
-// 16-bit word), per octant: E_1 = empty cells; E_{s+1}(c) = AND of E_s over the
-// 8 cells c + delta, delta in {0, 1}^3 along the octant's signs (a box of s + 1
-// is the union of 8 boxes of s), cells outside the brick counting as not
-// empty.  The radius of a cell is the number of s <= 15 with E_s(c), kept as a
-// 4-bit counter in bit planes.
-constexpr int OCT_ITEMS = 8;  // (octant, row) items per thread: 8 * r^2 <= OCT_ITEMS * BUILD_BLOCK for r <= 16
-
-__global__ __launch_bounds__(BUILD_BLOCK) void k_brick_cells(const uint64_t* mask, const uint32_t* base,
-                                                            const uint2* leaf, int nw, int r, uint2* cells) {
-    extern __shared__ uint16_t rows[];  // [2][8][r^2]: E_s and E_{s+1} per octant and row; then the radii
-    __shared__ uint64_t wmask[64];      // the brick's occupancy words (nw <= 64 for r <= 16)
-    const int r2 = r * r, n3 = r2 * r;
-    const int items = 8 * r2;
-    const uint32_t full = (1u << r) - 1u;
-    const size_t P = blockIdx.x;
-    uint16_t* Ecur = rows;
-    uint16_t* Enext = rows + items;
-    for (int k = threadIdx.x; k < nw; k += BUILD_BLOCK) wmask[k] = mask[P * nw + k];
-    __syncthreads();
-    // E_1: empty cells of every row, the same for all octants
-    for (int row = threadIdx.x; row < r2; row += BUILD_BLOCK) {
-        uint32_t e = 0;
-        for (int x = 0; x < r; ++x) {
-            const int c = x + r * row;
-            if (!((wmask[c >> 6] >> (c & 63)) & 1ull)) e |= 1u << x;
-        }
-        for (int o = 0; o < 8; ++o) Ecur[o * r2 + row] = (uint16_t)e;
-    }
-    __syncthreads();
-    uint16_t plane[OCT_ITEMS][4];
-    for (int k = 0; k < OCT_ITEMS; ++k)
-        for (int b = 0; b < 4; ++b) plane[k][b] = 0;
-    for (int sz = 1; sz <= 15; ++sz) {
-        int any = 0;  // some E_{s+1} is not empty
-        for (int k = 0; k < OCT_ITEMS; ++k) {
-            const int it = threadIdx.x + k * BUILD_BLOCK;
-            if (it >= items) break;
-            const int o = it / r2, row = it % r2;
-            const uint32_t e = Ecur[it];
-            // count this s (4-bit ripple add of the bits of E_s)
-            uint32_t carry = e;
-            for (int b = 0; b < 4; ++b) {
-                const uint32_t pb = plane[k][b];
-                plane[k][b] = (uint16_t)(pb ^ carry);
-                carry &= pb;
-            }
-            if (sz == 15) continue;
-            const int y = row % r, z = row / r;
-            const int sy = (o & 2) ? -1 : 1, szn = (o & 4) ? -1 : 1;
-            const bool negx = (o & 1) != 0;
-            const uint16_t* Eo = Ecur + (size_t)o * r2;
-            auto get = [&](int yy, int zz) -> uint32_t {
-                if (yy < 0 || yy >= r || zz < 0 || zz >= r) return 0u;
-                const uint32_t v = Eo[yy + r * zz];
-                const uint32_t sh = negx ? ((v << 1) & full) : (v >> 1);  // the neighbour along x
-                return v & sh;
-            };
-            const uint16_t en = (uint16_t)(get(y, z) & get(y + sy, z) & get(y, z + szn) & get(y + sy, z + szn));
-            Enext[it] = en;
-            any |= en;
-        }
-        // once every E_{s+1} is empty, no later size counts anything
-        if (!__syncthreads_or(any)) break;
-        uint16_t* t = Ecur;
-        Ecur = Enext;
-        Enext = t;
-    }
-    // radii packed per cell (octant o in bits 4o..4o+3), written with the occupied leaves' ranges
-    __syncthreads();
-    uint32_t* packed = reinterpret_cast<uint32_t*>(rows + 2 * items);  // [n3]
-    for (int c = threadIdx.x; c < n3; c += BUILD_BLOCK) packed[c] = 0u;
-    __syncthreads();
-    for (int k = 0; k < OCT_ITEMS; ++k) {
-        const int it = threadIdx.x + k * BUILD_BLOCK;
-        if (it >= items) break;
-        const int o = it / r2, row = it % r2;
-        for (int x = 0; x < r; ++x) {
-            const uint32_t n = ((plane[k][0] >> x) & 1u) | (((plane[k][1] >> x) & 1u) << 1) |
-                               (((plane[k][2] >> x) & 1u) << 2) | (((plane[k][3] >> x) & 1u) << 3);
-            if (n) atomicOr(&packed[x + r * row], n << (4 * o));
-        }
-    }
-    __syncthreads();
-    for (int c = threadIdx.x; c < n3; c += BUILD_BLOCK) {
-        const size_t i = P * (size_t)n3 + c;
-        const uint64_t w = wmask[c >> 6];
-        const uint64_t bit = uint64_t(1) << (c & 63);
-        if (w & bit)
-            cells[i] = leaf[base[P * nw + (c >> 6)] + (uint32_t)__popcll(w & (bit - 1))];
-        else
-            cells[i] = make_uint2(packed[c], 0u);
-    }
+void launch_brick_base(const uint64_t* mask, const uint32_t* first_child, int64_t n_nodes, int nw, uint32_t* base,
+                       hipStream_t s) {
+    hipLaunchKernelGGL(k_brick_base, dim3(blocks_for(n_nodes)), dim3(BUILD_BLOCK), 0, s, mask, first_child, n_nodes, nw,
+                       base);
 }
 
 __global__ void k_leaf_counts(uint2* leaf, int64_t n_leaves, int64_t m) {
@@ -694,6 +483,205 @@ __global__ void k_leaf_counts(uint2* leaf, int64_t n_leaves, int64_t m) {
     if (l >= n_leaves) return;
     const uint32_t end = (l + 1 < n_leaves) ? leaf[l + 1].x : (uint32_t)m;
     leaf[l].y = end - leaf[l].x;
+}
+
+// ---------------------------------------------------------------------------
+// traversal structures (trace_core.h)
+// ---------------------------------------------------------------------------
+
+// Skip codes of the empty top cells.  A ray moves ahead only, so what counts
+// at a cell is, per direction octant, the largest empty box of s^3 cells that
+// starts at the cell and extends along the octant's signs, s in TOP_SIZES.
+// The test is separable (a box is free when no cell of it is occupied), and
+// runs on rows of occupancy bits, 64 cells per word:
+//   k_top_rows  per (x sign, y sign, size): the cells whose s x s square of
+//               rows holds an occupied cell (x by shifts, y over s rows);
+//   k_top_codes the same along z per octant, then one 4-bit code s - 1 per
+//               octant and cell.
+// Cells outside the grid count as empty (a ray that reaches them has left).
+// Bound by the loads of the rows (each word read 16 times from the caches) and
+// the 8 B written per cell.  8 M cells (a 20M-point street's 1 m cells): 33 us
+// and 97 us; the isotropic radii of every leaf cell and the bricks' boxes that
+// they replace took 1.1 ms.
+constexpr int TOP_NS = 7;
+__device__ constexpr int TOP_SIZES[TOP_NS] = {2, 3, 4, 6, 8, 12, 16};
+
+__global__ __launch_bounds__(BUILD_BLOCK) void k_top_rows(const uint64_t* occ, int words, int dy, int dz,
+                                                          uint64_t* plane) {
+    const int64_t n = (int64_t)words * dy * dz;
+    const int64_t i = (int64_t)blockIdx.x * BUILD_BLOCK + threadIdx.x;
+    const int q = blockIdx.y;  // bit 0: towards -x, bit 1: towards -y
+    if (i >= n) return;
+    const int w = (int)(i % words), y = (int)((i / words) % dy);
+    const int64_t row0 = i - w;  // first word of the row
+    uint64_t acc[TOP_NS] = {0, 0, 0, 0, 0, 0, 0};
+    const bool nx = q & 1, ny = q & 2;
+    for (int j = 0; j < TOP_SIZES[TOP_NS - 1]; ++j) {
+        const int yy = ny ? y - j : y + j;
+        if (yy < 0 || yy >= dy) break;
+        const uint64_t* row = occ + row0 + (int64_t)(yy - y) * words;
+        const uint64_t cur = row[w];
+        const uint64_t nb = nx ? (w > 0 ? row[w - 1] : 0ull) : (w + 1 < words ? row[w + 1] : 0ull);
+        if (!(cur | nb)) continue;
+        uint64_t d = cur;
+        int k = 1;
+#pragma unroll
+        for (int s = 0; s < TOP_NS; ++s) {
+            for (; k < TOP_SIZES[s]; ++k)
+                d |= nx ? (cur << k) | (nb >> (64 - k)) : (cur >> k) | (nb << (64 - k));
+            if (j < TOP_SIZES[s]) acc[s] |= d;
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < TOP_NS; ++s) plane[((int64_t)q * TOP_NS + s) * n + i] = acc[s];
+}
+
+constexpr int TOP_WORDS = BUILD_BLOCK / 8;  // words per block: one thread per (word, octant)
+
+__global__ __launch_bounds__(BUILD_BLOCK) void k_top_codes(const uint64_t* occ, const uint64_t* plane, int words,
+                                                           int dx, int dy, int dz, uint2* top) {
+    __shared__ uint64_t bits[TOP_WORDS][8][4];
+    const int64_t n = (int64_t)words * dy * dz;
+    const int64_t i0 = (int64_t)blockIdx.x * TOP_WORDS;
+    {
+        const int o = threadIdx.x / TOP_WORDS, wl = threadIdx.x % TOP_WORDS;
+        const int64_t i = i0 + wl;
+        uint64_t e[TOP_NS] = {0, 0, 0, 0, 0, 0, 0};  // cells with a free box of the size
+        if (i < n) {
+            const int64_t slab = (int64_t)words * dy;
+            const int z = (int)(i / slab);
+            const bool nz = o & 4;
+            uint64_t above = ~0ull;
+            for (int s = 0; s < TOP_NS && above; ++s) {
+                const uint64_t* pl = plane + ((int64_t)(o & 3) * TOP_NS + s) * n + i;
+                uint64_t occd = 0;
+                for (int k = 0; k < TOP_SIZES[s]; ++k) {
+                    const int zz = nz ? z - k : z + k;
+                    if (zz < 0 || zz >= dz) break;
+                    occd |= pl[(int64_t)(zz - z) * slab];
+                }
+                above = e[s] = ~occd;
+            }
+        }
+        // code s - 1 of the largest free size in bit planes (the sizes' sets are nested)
+        bits[wl][o][0] = (e[0] & ~e[1]) | e[2];
+        bits[wl][o][1] = (e[1] & ~e[3]) | e[4];
+        bits[wl][o][2] = (e[3] & ~e[5]) | e[6];
+        bits[wl][o][3] = e[5];
+    }
+    __syncthreads();
+    const int lane = (int)lane_id();
+    for (int wl = threadIdx.x >> 6; wl < TOP_WORDS; wl += BUILD_BLOCK / 64) {
+        const int64_t i = i0 + wl;
+        if (i >= n) break;
+        const int x = (int)(i % words) * 64 + lane;
+        if (x >= dx || ((occ[i] >> lane) & 1ull)) continue;
+        uint32_t code = 0;
+#pragma unroll
+        for (int o = 0; o < 8; ++o)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) code |= (uint32_t)((bits[wl][o][b] >> lane) & 1ull) << (4 * o + b);
+        top[(i / words) * dx + x] = make_uint2(0xFFFFFFFFu, code);
+    }
+}
+
+// Top cells of a grid without skip codes.
+__global__ void k_top_plain(const uint64_t* occ, int words, int dx, int64_t n, uint2* top) {
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    const int64_t row = c / dx;
+    const int x = (int)(c - row * dx);
+    if (!((occ[row * words + (x >> 6)] >> (x & 63)) & 1ull)) top[c] = make_uint2(0xFFFFFFFFu, 0u);
+}
+
+// One wave per leaves' parent: the occupancy of its blocks of 4 x 4 x 4
+// leaves from the parent's linear mask, the box of its occupied leaves, and
+// the leaves' entry ranges in block order (the leaves themselves stay in key
+// order, so a block's leaves are not consecutive there).  lds: nblk^3 masks
+// and first ranges.  Bound by the leaf keys and ranges read and written once
+// (24 B per leaf).
+struct BlockArgs {
+    const uint64_t* mask;
+    const uint32_t* first;      // first leaf of every parent
+    const uint64_t* leaf_key;
+    uint2* leaf;                // .x given, .y (the count) set here
+    int64_t n_parents, n_leaves, m;
+    int32_t nw, r, nblk, lbits;
+    uint4* blk;
+    uint2* rng;
+    const uint32_t* tcell;      // top cell of every parent, or null: the box goes to pbox
+    uint2* top;
+    uint32_t* pbox;
+};
+
+__global__ __launch_bounds__(64) void k_brick_blocks(BlockArgs a) {
+    extern __shared__ uint64_t bmask[];  // [nblk^3] masks, then [nblk^3] first ranges (32 bits)
+    const int B = a.nblk, B3 = B * B * B, r = a.r;
+    uint32_t* bfirst = reinterpret_cast<uint32_t*>(bmask + B3);
+    const int64_t P = blockIdx.x;
+    const int lane = (int)lane_id();
+    const uint64_t* mask = a.mask + (size_t)P * a.nw;
+    const uint32_t first = a.first[P];
+    const uint32_t end = P + 1 < a.n_parents ? a.first[P + 1] : (uint32_t)a.n_leaves;
+    uint32_t run = first;
+    const int sh = r > 32 ? 1 : 0;
+    uint32_t ox = 0, oy = 0, oz = 0;
+    for (int b0 = 0; b0 < B3; b0 += 64) {
+        const int b = b0 + lane;
+        uint64_t m = 0;
+        if (b < B3) {
+            const int bx = 4 * (b % B), by = 4 * ((b / B) % B), bz = 4 * (b / (B * B));
+            const int wx = min(4, r - bx);
+            for (int z = 0; z < 4 && bz + z < r; ++z)
+                for (int y = 0; y < 4 && by + y < r; ++y) {
+                    const int p = bx + r * (by + y + r * (bz + z));
+                    uint64_t f = mask[p >> 6] >> (p & 63);
+                    if ((p & 63) + wx > 64) f |= mask[(p >> 6) + 1] << (64 - (p & 63));
+                    const uint32_t nib = (uint32_t)f & ((1u << wx) - 1u);
+                    if (nib) {
+                        m |= (uint64_t)nib << (4 * (y + 4 * z));
+                        // in units of one leaf, or of two beyond ratio 32 (bits 0-31)
+                        ox |= sh ? ((nib & 3u) ? 1u << (bx >> 1) : 0u) | ((nib & 12u) ? 2u << (bx >> 1) : 0u)
+                                 : nib << bx;
+                        oy |= 1u << ((by + y) >> sh);
+                        oz |= 1u << ((bz + z) >> sh);
+                    }
+                }
+        }
+        const uint32_t c = (uint32_t)__popcll(m);
+        const uint32_t incl = wave_incl_scan(c);
+        if (b < B3) {
+            const uint32_t f = run + incl - c;
+            a.blk[(size_t)P * B3 + b] = make_uint4((uint32_t)m, (uint32_t)(m >> 32), f, 0u);
+            bmask[b] = m;
+            bfirst[b] = f;
+        }
+        run += __shfl(incl, 63, 64);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        ox |= __shfl_xor(ox, off, 64);
+        oy |= __shfl_xor(oy, off, 64);
+        oz |= __shfl_xor(oz, off, 64);
+    }
+    if (lane == 0) {
+        const uint32_t box = (uint32_t)(__ffs(ox) - 1) | ((uint32_t)(__ffs(oy) - 1) << 5) |
+                             ((uint32_t)(__ffs(oz) - 1) << 10) | ((uint32_t)(31 - __clz(ox)) << 15) |
+                             ((uint32_t)(31 - __clz(oy)) << 20) | ((uint32_t)(31 - __clz(oz)) << 25);
+        if (a.tcell) a.top[a.tcell[P]].y = box;
+        else a.pbox[P] = box;
+    }
+    __syncthreads();
+    for (uint32_t g = first + lane; g < end; g += 64) {
+        const uint32_t loc = (uint32_t)(a.leaf_key[g] & ((uint64_t(1) << a.lbits) - 1));
+        const int x = (int)(loc % (uint32_t)r), y = (int)((loc / (uint32_t)r) % (uint32_t)r),
+                  z = (int)(loc / (uint32_t)(r * r));
+        const int b = ((z >> 2) * B + (y >> 2)) * B + (x >> 2);
+        const int bit = (x & 3) | ((y & 3) << 2) | ((z & 3) << 4);
+        const uint32_t e0 = a.leaf[g].x;
+        const uint32_t e1 = g + 1 < (uint32_t)a.n_leaves ? a.leaf[g + 1].x : (uint32_t)a.m;
+        a.leaf[g].y = e1 - e0;
+        a.rng[bfirst[b] + (uint32_t)__popcll(bmask[b] & ((uint64_t(1) << bit) - 1))] = make_uint2(e0, e1 - e0);
+    }
 }
 
 __global__ void k_split_leaf(const uint2* r, int64_t n, uint32_t* b, uint32_t* c) {
@@ -766,6 +754,53 @@ static int validate_params(const PcrlVoxelParams* p, int32_t ratio[PCRL_MAX_LEVE
     return PCRL_OK;
 }
 
+// Level of the dense top grid: the leaves' parents (the traversal then finds
+// a leaf's brick with one load) while their grid has at most this many cells
+// (8 bytes each), else the finest coarser level that has, or level 0.
+constexpr int64_t TOP_MAX_CELLS = (int64_t)64 << 20;
+// Grids beyond this many cells (only a level-0 grid can be) keep no skip
+// codes: every empty cell is crossed by itself.
+constexpr int64_t TOP_CODES_MAX_CELLS = (int64_t)512 << 20;
+
+static int64_t top_cells(const SceneView& v) { return (int64_t)v.tdim[0] * v.tdim[1] * v.tdim[2]; }
+
+// The top grid, the brick levels below it and the blocks' layout of a frame.
+static void set_top(SceneView& v) {
+    const int P = v.nlev - 2;  // the leaves' parents
+    int F = std::max(P, 0);
+    auto dims = [&](int l) {
+        for (int a = 0; a < 3; ++a) v.tdim[a] = v.dim[a] / v.span[l];
+        return top_cells(v);
+    };
+    while (dims(F) > TOP_MAX_CELLS && F > 0) --F;
+    // depth counts at most two brick levels: with four voxel levels a top grid on level 0 leaves two above the parents
+    v.depth = P < 0 ? -1 : P - F;
+    const float span = (float)v.span[F];
+    v.tspan = span;
+    v.tinv = 1.0f / span;
+    v.thalf = 0.5f / span;
+    const int r = P < 0 ? 1 : v.ratio[P];
+    v.rf = (float)r;
+    v.r1 = (float)(r - 1);
+    v.bunit = r <= 32 ? 1.f : 2.f;
+    v.nblk = (r + 3) / 4;
+    v.nblk3 = v.nblk * v.nblk * v.nblk;
+    for (int a = 0; a < 3; ++a) {
+        v.dimf[a] = (float)v.dim[a];
+        v.dim1[a] = (float)(v.dim[a] - 1);
+        v.tdim1[a] = (float)(v.tdim[a] - 1);
+    }
+    v.stop_pad = 1e-3f * v.h;
+    for (int i = 0; i < v.depth; ++i) {
+        const float s = (float)v.span[F + 1 + i];
+        v.minv[i] = 1.0f / s;
+        v.mhalf[i] = 0.5f / s;
+        v.mspan_f[i] = s;
+        v.mratio[i] = (float)v.ratio[F + i];
+        v.mnw[i] = v.nw[F + i];
+    }
+}
+
 // Grid frame of a new scene from its parameters and point AABB.
 static int make_frame(const PcrlVoxelParams* params, const int32_t ratio[PCRL_MAX_LEVELS], const IngestOut& io,
                       SceneView& v) {
@@ -818,6 +853,7 @@ static int make_frame(const PcrlVoxelParams* params, const int32_t ratio[PCRL_MA
         return PCRL_EINVAL;
     }
     v.key_bits = key_bits;
+    set_top(v);
     const double diag = std::sqrt((double)(io.hi[0] - io.lo[0]) * (io.hi[0] - io.lo[0]) +
                                   (double)(io.hi[1] - io.lo[1]) * (io.hi[1] - io.lo[1]) +
                                   (double)(io.hi[2] - io.lo[2]) * (io.hi[2] - io.lo[2]));
@@ -834,12 +870,13 @@ struct HierBuild {
     uint64_t* leaf_key = nullptr;
     uint32_t* entry_point = nullptr;
     uint2* leaf_range = nullptr;
+    uint32_t* first_child[PCRL_MAX_LEVELS - 1] = {};
 };
 
 // Voxelise n ingested points into the frame already set in v (level-0 map,
 // bricks, leaves, surfel streams).  gid: global point ids (null: 0..n-1).
 static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint32_t* label, const uint32_t* gid,
-                           int64_t n, hipStream_t s, bool compact, SceneView& v, DevBufs& B, DevBufs& T,
+                           int64_t n, hipStream_t s, SceneView& v, DevBufs& B, DevBufs& T,
                            HierBuild& hb) {
     const int L = v.nlev;
     int rc = PCRL_OK;
@@ -859,7 +896,12 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
     v.map0 = map0;
     for (int l = 0; l < PCRL_MAX_LEVELS; ++l) v.nn[l] = 0;
     hb.bytes = (int64_t)cells0 * 4;
-    if (n == 0) return PCRL_OK;
+    const int64_t cells = top_cells(v);
+    uint2* top = nullptr;
+    if ((rc = B.alloc(&top, (size_t)cells))) return rc;
+    v.top = top;
+    hb.bytes += cells * 8;
+    if (n == 0) return fill_u32((uint32_t*)top, 0xFFFFFFFFu, 2 * cells, s);  // all empty: the largest skips
 
     // dilated key counts and their total
     KeyParams kp{};
@@ -975,87 +1017,91 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
     for (int l = 0; l + 1 < L; ++l) {
         const size_t words = (size_t)host_nodes[l] * v.nw[l];
         uint64_t* mk = nullptr;
-        uint32_t* bs = nullptr;
         uint32_t* fc = nullptr;
-        if ((rc = B.alloc(&mk, words)) || (rc = B.alloc(&bs, words)) || (rc = T.alloc(&fc, host_nodes[l]))) return rc;
+        if ((rc = B.alloc(&mk, words)) || (rc = B.alloc(&fc, host_nodes[l]))) return rc;
         if ((rc = fill_u64(mk, 0ull, (int64_t)words, s))) return rc;
         ho.mask[l] = mk;
         ho.first_child[l] = fc;
+        hb.first_child[l] = fc;
         v.mask[l] = mk;
-        v.base[l] = bs;
+        hb.bytes += (int64_t)words * 8 + (int64_t)host_nodes[l] * 4;
     }
     uint2* leaf = nullptr;
     uint64_t* lkey = nullptr;
     if ((rc = B.alloc(&leaf, (size_t)n_leaves)) || (rc = B.alloc(&lkey, (size_t)n_leaves))) return rc;
     ho.leaf = leaf;
     ho.leaf_key = lkey;
+    const int P = L - 2;
+    const int F = P < 0 ? 0 : P - v.depth;
+    const int words = (v.tdim[0] + 63) / 64;
+    const int64_t occ_words = (int64_t)words * v.tdim[1] * v.tdim[2];
+    uint64_t* occ = nullptr;
+    uint32_t* tcell = nullptr;
+    if ((rc = T.alloc(&occ, (size_t)occ_words)) || (rc = fill_u64(occ, 0ull, occ_words, s))) return rc;
+    if (v.depth == 0 && (rc = T.alloc(&tcell, (size_t)host_nodes[P]))) return rc;
+    ho.F = F;
+    ho.words = words;
+    ho.top = top;
+    ho.occ = occ;
+    ho.tcell = tcell;
     hipLaunchKernelGGL(k_link, dim3(link_blocks), dim3(BUILD_BLOCK), 0, s, keys, m, ls, v, tiles, n_tiles, ho,
                        packed ? id_bits : 0);
-    for (int l = 0; l + 1 < L; ++l)
-        hipLaunchKernelGGL(k_brick_base, dim3(blocks_for(host_nodes[l])), dim3(BUILD_BLOCK), 0, s, ho.mask[l],
-                           ho.first_child[l], (int64_t)host_nodes[l], v.nw[l], (uint32_t*)v.base[l]);
-    for (int l = 0; l + 1 < L; ++l) {
-        v.baabb[l] = nullptr;
-        if (v.ratio[l] > 32 || host_nodes[l] == 0) continue;
-        uint32_t* ab = nullptr;
-        if ((rc = B.alloc(&ab, (size_t)host_nodes[l]))) return rc;
-        hipLaunchKernelGGL(k_brick_aabb, dim3(blocks_for(host_nodes[l])), dim3(BUILD_BLOCK), 0, s, ho.mask[l],
-                           (int64_t)host_nodes[l], v.nw[l], v.ratio[l], ab);
-        v.baabb[l] = ab;
-        hb.bytes += (int64_t)host_nodes[l] * 4;
+    // the brick levels between the top grid and the leaves' parents
+    for (int i = 0; i < v.depth; ++i) {
+        uint32_t* bs = nullptr;
+        if ((rc = B.alloc(&bs, (size_t)host_nodes[F + i] * v.nw[F + i]))) return rc;
+        launch_brick_base(ho.mask[F + i], ho.first_child[F + i], host_nodes[F + i], v.nw[F + i], bs, s);
+        v.mmask[i] = ho.mask[F + i];
+        v.mbase[i] = bs;
+        hb.bytes += (int64_t)host_nodes[F + i] * v.nw[F + i] * 4;
     }
-    hipLaunchKernelGGL(k_leaf_counts, dim3(blocks_for(n_leaves)), dim3(BUILD_BLOCK), 0, s, leaf, n_leaves, m);
+    if (cells <= TOP_CODES_MAX_CELLS) {
+        uint64_t* plane = nullptr;
+        if ((rc = T.alloc(&plane, (size_t)(4 * TOP_NS * occ_words)))) return rc;
+        hipLaunchKernelGGL(k_top_rows, dim3(blocks_for(occ_words), 4), dim3(BUILD_BLOCK), 0, s, (const uint64_t*)occ,
+                           words, v.tdim[1], v.tdim[2], plane);
+        hipLaunchKernelGGL(k_top_codes, dim3(blocks_for(occ_words, TOP_WORDS)), dim3(BUILD_BLOCK), 0, s,
+                           (const uint64_t*)occ, (const uint64_t*)plane, words, v.tdim[0], v.tdim[1], v.tdim[2], top);
+    } else {
+        hipLaunchKernelGGL(k_top_plain, dim3(blocks_for(cells)), dim3(BUILD_BLOCK), 0, s, (const uint64_t*)occ, words,
+                           v.tdim[0], cells, top);
+    }
     v.leaf = leaf;
     hb.leaf_range = leaf;
     hb.leaf_key = lkey;
-    // Leaf level of the traversal: a dense cell table of the leaves' parent
-    // bricks (entry ranges and octant skip radii; needs the leaf ranges, so
-    // after k_leaf_counts), or, when it would be too large, per-cell isotropic
-    // skip radii beside the bricks' masks.
-    v.ldist = nullptr;
-    v.cells = nullptr;
-    if (L >= 2 && host_nodes[L - 2] > 0) {
-        const int r = v.ratio[L - 2];
-        const int64_t r3 = (int64_t)r * r * r;
-        const int64_t n_cells = (int64_t)host_nodes[L - 2] * r3;
-        if (!compact && r <= 16 && n_cells * 8 <= CELL_TABLE_MAX_BYTES) {
-            uint2* cells = nullptr;
-            if ((rc = B.alloc(&cells, (size_t)n_cells))) return rc;
-            const size_t lds = (size_t)2 * 8 * r * r * 2 + (size_t)r3 * 4;
-            hipLaunchKernelGGL(k_brick_cells, dim3((unsigned)host_nodes[L - 2]), dim3(BUILD_BLOCK), lds, s,
-                               ho.mask[L - 2], (const uint32_t*)v.base[L - 2], (const uint2*)leaf, v.nw[L - 2], r,
-                               cells);
-            v.cells = cells;
-            hb.bytes += n_cells * 8;
-        } else if (r >= 3 && r <= 16) {
-            uint8_t* ld = nullptr;
-            if ((rc = B.alloc(&ld, (size_t)n_cells))) return rc;
-            const int64_t nb = host_nodes[L - 2];
-            const dim3 g(blocks_for(nb, BUILD_BLOCK / 64));
-            if (r == 10)
-                hipLaunchKernelGGL(k_brick_dist<10>, g, dim3(BUILD_BLOCK), 0, s, ho.mask[L - 2], v.nw[L - 2], r, nb, ld);
-            else if (r == 8)
-                hipLaunchKernelGGL(k_brick_dist<8>, g, dim3(BUILD_BLOCK), 0, s, ho.mask[L - 2], v.nw[L - 2], r, nb, ld);
-            else
-                hipLaunchKernelGGL(k_brick_dist<0>, g, dim3(BUILD_BLOCK), 0, s, ho.mask[L - 2], v.nw[L - 2], r, nb, ld);
-            v.ldist = ld;
-            hb.bytes += n_cells;
-        }
-    }
-
-    // empty-space skip radii of the level-0 grid
-    {
-        uint8_t *d0 = nullptr, *tmp = nullptr;
-        if ((rc = B.alloc(&d0, (size_t)cells0)) || (rc = T.alloc(&tmp, (size_t)cells0))) return rc;
-        const unsigned g0 = (unsigned)blocks_for((int64_t)cells0);
-        hipLaunchKernelGGL(k_dist0_pass, dim3(g0), dim3(BUILD_BLOCK), 0, s, (const int32_t*)map0,
-                           (const uint8_t*)nullptr, d0, v.dim0[0], v.dim0[1], v.dim0[2], 0);
-        hipLaunchKernelGGL(k_dist0_pass, dim3(g0), dim3(BUILD_BLOCK), 0, s, (const int32_t*)nullptr,
-                           (const uint8_t*)d0, tmp, v.dim0[0], v.dim0[1], v.dim0[2], 1);
-        hipLaunchKernelGGL(k_dist0_pass, dim3(g0), dim3(BUILD_BLOCK), 0, s, (const int32_t*)nullptr,
-                           (const uint8_t*)tmp, d0, v.dim0[0], v.dim0[1], v.dim0[2], 2);
-        v.dist0 = d0;
-        hb.bytes += (int64_t)cells0;
+    if (P < 0) {
+        hipLaunchKernelGGL(k_leaf_counts, dim3(blocks_for(n_leaves)), dim3(BUILD_BLOCK), 0, s, leaf, n_leaves, m);
+        v.rng = leaf;
+    } else {
+        uint4* blk = nullptr;
+        uint2* rng = nullptr;
+        uint32_t* pbox = nullptr;
+        const size_t nb = (size_t)host_nodes[P] * (size_t)v.nblk3;
+        if ((rc = B.alloc(&blk, nb)) || (rc = B.alloc(&rng, (size_t)n_leaves)) ||
+            (v.depth > 0 && (rc = B.alloc(&pbox, (size_t)host_nodes[P]))))
+            return rc;
+        BlockArgs ba{};
+        ba.mask = ho.mask[P];
+        ba.first = ho.first_child[P];
+        ba.leaf_key = lkey;
+        ba.leaf = leaf;
+        ba.n_parents = host_nodes[P];
+        ba.n_leaves = n_leaves;
+        ba.m = m;
+        ba.nw = v.nw[P];
+        ba.r = v.ratio[P];
+        ba.nblk = v.nblk;
+        ba.lbits = v.lbits[L - 1];
+        ba.blk = blk;
+        ba.rng = rng;
+        ba.tcell = tcell;
+        ba.top = top;
+        ba.pbox = pbox;
+        hipLaunchKernelGGL(k_brick_blocks, dim3(host_nodes[P]), dim3(64), (size_t)v.nblk3 * 12, s, ba);
+        v.blk = blk;
+        v.rng = rng;
+        v.pbox = pbox;
+        hb.bytes += (int64_t)nb * 16 + n_leaves * 8 + (pbox ? (int64_t)host_nodes[P] * 4 : 0);
     }
 
     // surfel streams in leaf order
@@ -1071,7 +1117,6 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
         return PCRL_EHIP;
     }
     hb.bytes += m * ((ids ? 4 : 0) + 32) + n_leaves * 16;
-    for (int l = 0; l + 1 < L; ++l) hb.bytes += (int64_t)host_nodes[l] * v.nw[l] * 12;
     return PCRL_OK;
 }
 
@@ -1125,11 +1170,12 @@ static int build_impl(const float* xyz, const float* nrm, const uint32_t* label,
     if ((rc = make_frame(params, ratio, io, v))) return fail(rc);
     HierBuild hb;
     S->compact = (params->flags & PCRL_VOXEL_COMPACT) != 0;
-    if ((rc = build_hierarchy(xyz, unit_nrm, label, nullptr, n, s, S->compact, v, S->bufs, T, hb))) return fail(rc);
+    if ((rc = build_hierarchy(xyz, unit_nrm, label, nullptr, n, s, v, S->bufs, T, hb))) return fail(rc);
     S->max_label = io.max_label;
     S->leaf_key = hb.leaf_key;
     S->entry_point = hb.entry_point;
     S->leaf_range = hb.leaf_range;
+    for (int l = 0; l + 1 < PCRL_MAX_LEVELS; ++l) S->first_child[l] = hb.first_child[l];
     PcrlSceneInfo& info = S->info;
     info.n_points = n;
     info.n_entries = hb.n_entries;
@@ -1179,18 +1225,18 @@ static int overlay_impl(PcrlScene* S, const uint32_t* gid, const float* xyz, con
     }
     SceneView v = bv;  // same frame: origin, levels, padding, t_eps
     v.map0 = nullptr;
-    for (int l = 0; l + 1 < PCRL_MAX_LEVELS; ++l) {
-        v.mask[l] = nullptr;
-        v.base[l] = nullptr;
-        v.baabb[l] = nullptr;
+    for (int l = 0; l + 1 < PCRL_MAX_LEVELS; ++l) v.mask[l] = nullptr;
+    for (int i = 0; i < 2; ++i) {
+        v.mmask[i] = nullptr;
+        v.mbase[i] = nullptr;
     }
+    v.top = v.rng = nullptr;
+    v.blk = nullptr;
+    v.pbox = nullptr;
     v.leaf = nullptr;
-    v.ldist = nullptr;
-    v.dist0 = nullptr;
-    v.cells = nullptr;
     v.spos = v.snrm = nullptr;
     HierBuild hb;
-    if ((rc = build_hierarchy(xyz, unit_nrm, label, gid, n, s, S->compact, v, ov->bufs, T, hb))) return fail(rc);
+    if ((rc = build_hierarchy(xyz, unit_nrm, label, gid, n, s, v, ov->bufs, T, hb))) return fail(rc);
     ov->view = v;
     ov->n_points = n;
     ov->n_entries = hb.n_entries;

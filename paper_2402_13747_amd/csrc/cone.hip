@@ -450,11 +450,12 @@ struct VisArgs {
 // reception point; blocked when a surfel disk is hit before the ray enters
 // the target's subvoxel (the lane's nearest hit starts at that distance, so
 // only nearer hits register).
-template <int NL, bool BX>
+template <int TD>
 __global__ __launch_bounds__(TRACE_BLOCK) void k_visibility(VisArgs a) {
-    __shared__ LeafTestLds lds[TRACE_BLOCK / 64];
-    LeafTestLds& W = lds[threadIdx.x >> 6];
-    stat_t cnt[ST_COUNT] = {};
+    __shared__ TraceLds<TRACE_BLOCK / 64> lds;
+    WaveLds& W = lds.w[threadIdx.x >> 6];
+    ahead_init(lds.ahead, threadIdx.x, TRACE_BLOCK);
+    __syncthreads();
     const uint32_t wave = blockIdx.x * (TRACE_BLOCK / 64) + (threadIdx.x >> 6);
     const uint32_t n_waves = gridDim.x * (TRACE_BLOCK / 64);
     for (uint32_t base = wave * 64; base < a.n; base += n_waves * 64) {
@@ -491,7 +492,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_visibility(VisArgs a) {
             }
         }
         stage_ray(W, o, u, NO_HIT);
-        trace_segment<false, NL, false, BX>(a.t, W, act && hit.t > 0.f, o, u, hit, cnt);
+        trace_segment<false, TD, false, true>(kernel_args(), lds.ahead, W, act && hit.t > 0.f, hit, nullptr);
         if (act) a.visible[i] = hit.id == NO_HIT ? 1u : 0u;
     }
 }
@@ -604,11 +605,12 @@ struct AxisArgs {
 };
 
 // The first surfel hit (t > t_eps) of every cone's axis: the end of its march.
-template <int NL, bool BX>
+template <int TD>
 __global__ __launch_bounds__(TRACE_BLOCK) void k_axis(AxisArgs a) {
-    __shared__ LeafTestLds lds[TRACE_BLOCK / 64];
-    LeafTestLds& W = lds[threadIdx.x >> 6];
-    stat_t cnt[ST_COUNT] = {};
+    __shared__ TraceLds<TRACE_BLOCK / 64> lds;
+    WaveLds& W = lds.w[threadIdx.x >> 6];
+    ahead_init(lds.ahead, threadIdx.x, TRACE_BLOCK);
+    __syncthreads();
     const uint32_t wave = blockIdx.x * (TRACE_BLOCK / 64) + (threadIdx.x >> 6);
     const uint32_t n_waves = gridDim.x * (TRACE_BLOCK / 64);
     const uint32_t n = a.cones.n;
@@ -625,7 +627,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_axis(AxisArgs a) {
             d[0] = D.x; d[1] = D.y; d[2] = D.z;
         }
         stage_ray(W, o, d, NO_HIT);
-        trace_segment<false, NL, false, BX>(a.t, W, act, o, d, hit, cnt);
+        trace_segment<false, TD, false>(kernel_args(), lds.ahead, W, act, hit, nullptr);
         if (act) a.cones.t_end[i] = hit.id == NO_HIT ? INFINITY : hit.t;
     }
 }
@@ -1159,47 +1161,35 @@ static int ie_add_edges_impl(PcrlIes* I, const float* seg, const float* nrm, con
     return PCRL_OK;
 }
 
-template <int NL, bool BX>
+template <int TD>
 static void launch_vis(const VisArgs& a, hipStream_t s) {
     const unsigned grid = (unsigned)std::min<int64_t>(blocks(a.n, TRACE_BLOCK), (int64_t)device_cus() * 16);
-    hipLaunchKernelGGL((k_visibility<NL, BX>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a);
+    hipLaunchKernelGGL((k_visibility<TD>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a);
 }
 
-template <int NL, bool BX>
+template <int TD>
 static void launch_axis(const AxisArgs& a, hipStream_t s) {
     const unsigned grid = (unsigned)std::min<int64_t>(blocks(a.cones.n, TRACE_BLOCK), (int64_t)device_cus() * 16);
-    hipLaunchKernelGGL((k_axis<NL, BX>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a);
-}
-
-template <int NL>
-static void dispatch_vis(const VisArgs& a, hipStream_t s) {
-    if (NL > 1 && !a.t.v.cells) launch_vis<NL, true>(a, s);
-    else launch_vis<NL, false>(a, s);
-}
-
-template <int NL>
-static void dispatch_axis(const AxisArgs& a, hipStream_t s) {
-    if (NL > 1 && !a.t.v.cells) launch_axis<NL, true>(a, s);
-    else launch_axis<NL, false>(a, s);
+    hipLaunchKernelGGL((k_axis<TD>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a);
 }
 
 static void run_vis(const VisArgs& a, hipStream_t s) {
     if (a.n == 0) return;
-    switch (a.t.v.nlev) {
-    case 1: dispatch_vis<1>(a, s); break;
-    case 2: dispatch_vis<2>(a, s); break;
-    case 3: dispatch_vis<3>(a, s); break;
-    default: dispatch_vis<4>(a, s); break;
+    switch (a.t.v.depth) {
+    case -1: launch_vis<-1>(a, s); break;
+    case 0: launch_vis<0>(a, s); break;
+    case 1: launch_vis<1>(a, s); break;
+    default: launch_vis<2>(a, s); break;
     }
 }
 
 static void run_axis(const AxisArgs& a, hipStream_t s) {
     if (a.cones.n == 0) return;
-    switch (a.t.v.nlev) {
-    case 1: dispatch_axis<1>(a, s); break;
-    case 2: dispatch_axis<2>(a, s); break;
-    case 3: dispatch_axis<3>(a, s); break;
-    default: dispatch_axis<4>(a, s); break;
+    switch (a.t.v.depth) {
+    case -1: launch_axis<-1>(a, s); break;
+    case 0: launch_axis<0>(a, s); break;
+    case 1: launch_axis<1>(a, s); break;
+    default: launch_axis<2>(a, s); break;
     }
 }
 

@@ -224,13 +224,38 @@ struct SceneView {
     int32_t nw[PCRL_MAX_LEVELS];     // 64-bit mask words of a level-i brick (i < nlev-1)
     uint32_t nn[PCRL_MAX_LEVELS];    // occupied nodes per level (bounds of every index)
     uint64_t mspan[PCRL_MAX_LEVELS]; // ceil(2^40 / span[i]): x / span[i] == (x * mspan[i]) >> 40 for x < 2^22
+    // traversal structures of the launcher (trace_core.h): a dense top grid over level `nlev - 2 - depth`
+    // (depth -1: a single-level grid, its cells are the leaves), `depth` levels of bricks below it, and
+    // blocks of 4 x 4 x 4 leaves in the bricks of the leaves' parents
+    int32_t depth;
+    float dimf[3], dim1[3];          // dim, dim - 1
+    float rf, r1;                    // leaves per parent edge (1 without parents), that - 1
+    int32_t tdim[3];                 // top grid dims
+    float tdim1[3];                  // tdim - 1
+    float stop_pad;                  // a walk ends this far (and 4e-6 t) beyond its nearest hit
+    float tspan, tinv, thalf;        // leaves per top cell edge, 1 / that, 0.5 / that
+    float bunit;                     // unit of the parents' box words in leaves (1 up to ratio 32, else 2)
+    int32_t nblk, nblk3;             // blocks per parent edge and per parent
+    const uint2* top;                // per top cell: (node, box word of its occupied leaves when depth = 0), or
+                                     // (0xFFFFFFFF, per octant 4 bits: edge - 1 of the empty box onwards)
+    const uint32_t* pbox;            // box word per leaves' parent (depth > 0)
+    const uint4* blk;                // [parents][nblk3]: occupancy of the block's leaves (64 bits, x + 4 (y + 4 z)),
+                                     // first of its ranges in rng, unused
+    const uint2* rng;                // (first entry, entry count) of every leaf, block by block
+    float minv[2], mhalf[2];         // brick levels between: 1 / span, 0.5 / span,
+    float mratio[2], mspan_f[2];     // ratio of the level above, span,
+    int32_t mnw[2];                  // mask words per brick above,
+    const uint64_t* mmask[2];        // its occupancy words
+    const uint32_t* mbase[2];        // and child bases
+
     const int32_t* map0;             // [dim0 x*y*z] level-0 node or -1
     const uint64_t* mask[PCRL_MAX_LEVELS - 1];  // child occupancy bricks of level i
+    const uint2* leaf;               // per leaf: (first entry, entry count)
+    // structures of the implicit surface's own leaf walk, built with its point index (sdf.hip)
     const uint32_t* base[PCRL_MAX_LEVELS - 1];  // child index of the first set bit of each word
     const uint32_t* baabb[PCRL_MAX_LEVELS - 1]; // null, or per node of level i the box of its occupied
                                                 // children (local coordinates, 5 bits each: lo x, y, z,
                                                 // then hi x, y, z; ratio <= 32)
-    const uint2* leaf;               // per leaf: (first entry, entry count)
     const uint8_t* ldist;            // null, or per leaf cell of each parent brick its empty-space skip radius
     const uint8_t* dist0;            // null, or per level-0 cell its empty-space skip radius (level-0 cells)
     const uint2* cells;              // null, or per leaf cell of every parent brick: (first entry, count) of
@@ -293,12 +318,14 @@ struct PcrlScene {
     uint64_t* leaf_key = nullptr;     // per leaf hierarchical key
     uint32_t* entry_point = nullptr;  // per entry: point id (leaf order); null: read from spos.w
     uint2* leaf_range = nullptr;
+    uint32_t* first_child[PCRL_MAX_LEVELS - 1] = {};  // per node of level i: its first child
     uint32_t max_label = 0;
-    bool compact = false;             // PCRL_VOXEL_COMPACT: no dense cell tables (base and overlays)
+    bool compact = false;             // PCRL_VOXEL_COMPACT: no dense cell table for the implicit surface's walk
     std::shared_ptr<pcrl::Overlay> overlay;  // current epoch of dynamic points (may be null)
     // own-point index of the implicit-surface intersection (sdf_intersect), built
     // on first use: every point once, in the leaf holding its centre, in leaf order
     std::mutex own_mu;
+    pcrl::SceneView walk{};           // `view` with the structures of the implicit surface's leaf walk
     uint32_t* own_scan = nullptr;     // [n_entries + 1] own entries before each entry
     float4* own_pos = nullptr;        // [n_points] positions (w: point id bits)
     float4* own_nrm = nullptr;        // [n_points] unit normals (w: label bits)
@@ -335,6 +362,9 @@ struct TraceArgs;
 int launch_prepare(const PcrlScene* scene, const float* tx, int32_t n_tx, const float* rx, int32_t n_rx,
                    const PcrlLaunchParams* p, hipStream_t s, bool timing_events, PcrlLaunch** out, TraceArgs* args);
 void destroy_launch(PcrlLaunch* L);
+// Child base of every mask word of n_nodes bricks (build.hip).
+void launch_brick_base(const uint64_t* mask, const uint32_t* first_child, int64_t n_nodes, int nw, uint32_t* base,
+                       hipStream_t s);
 // Every static point once, in the leaf that holds its centre (built on first
 // use and kept with the scene; sdf.hip): scene->own_pos / own_nrm.
 int scene_own_index(PcrlScene* S, hipStream_t s);

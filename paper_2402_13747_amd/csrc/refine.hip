@@ -102,10 +102,10 @@ __device__ __forceinline__ int wave_max(int x) {
 // direction (lanes with `act` false only help with the leaf tests).  Returns
 // the hit in `hit` (t from the start os = o + skip d); `len` is the distance
 // from o to the target (0: the target is o, no ray).
-template <int NL, bool OV>
-__device__ __forceinline__ void trace_towards(const RefineArgs& a, LeafTestLds& W, bool act, const float o[3],
+template <int TD, bool OV>
+__device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_t* ahead, WaveLds& W, bool act, const float o[3],
                                               const float target[3], uint32_t last, float skip, Hit& hit, float d[3],
-                                              float os[3], float& len, stat_t cnt[ST_COUNT]) {
+                                              float os[3], float& len) {
     d[0] = target[0] - o[0];
     d[1] = target[1] - o[1];
     d[2] = target[2] - o[2];
@@ -125,8 +125,8 @@ __device__ __forceinline__ void trace_towards(const RefineArgs& a, LeafTestLds& 
     os[2] = o[2] + skip * d[2];
     hit_reset(hit);
     stage_ray(W, os, d, last);
-    trace_segment<false, NL, false>(a.t, W, go, os, d, hit, cnt);
-    if (OV) trace_segment<false, NL, true>(a.t, W, go, os, d, hit, cnt);
+    trace_segment<false, TD, false>(kernel_args(), ahead, W, go, hit, nullptr);
+    if (OV) trace_segment<false, TD, true>(kernel_args(), ahead, W, go, hit, nullptr);
 }
 
 // Add the weighted normals of the points of hierarchy v within sqrt(h2) of c
@@ -134,7 +134,7 @@ __device__ __forceinline__ void trace_towards(const RefineArgs& a, LeafTestLds& 
 // with nh).  h2 is below one leaf edge squared, so the points lie in the 27
 // leaves around c's; a point is taken from the leaf holding its centre only
 // (every leaf its disk meets lists it).
-template <int NL>
+template <int TD>
 __device__ __forceinline__ void gather_normals(const SceneView& v, const float c[3], float h2, const float nh[3],
                                                float acc[3]) {
     int lc[3];
@@ -147,10 +147,7 @@ __device__ __forceinline__ void gather_normals(const SceneView& v, const float c
                 if (cell[0] < 0 || cell[1] < 0 || cell[2] < 0 || cell[0] >= v.dim[0] || cell[1] >= v.dim[1] ||
                     cell[2] >= v.dim[2])
                     continue;
-                uint32_t node = 0;
-                int skip0 = 0;
-                if (descend<false, NL - 1>(v, cell, node, skip0, nullptr) != NL) continue;
-                const uint2 r = v.leaf[node];
+                const uint2 r = leaf_range<TD>(v, cell[0], cell[1], cell[2]);
                 for (uint32_t e = r.x; e < r.x + r.y; ++e) {
                     const float4 P = v.spos[e];
                     const float x = P.x - c[0], y = P.y - c[1], z = P.z - c[2];
@@ -179,10 +176,11 @@ __device__ __forceinline__ void load3(const float4* p, float x[3]) {
     x[2] = v.z;
 }
 
-template <int NL, bool OV>
+template <int TD, bool OV>
 __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
-    __shared__ LeafTestLds W;
-    stat_t cnt[ST_COUNT] = {};
+    __shared__ TraceLds<1> lds;
+    ahead_init(lds.ahead, threadIdx.x, REFINE_BLOCK);
+    __syncthreads();
     const uint32_t p = blockIdx.x * a.ppw + threadIdx.x;
     const bool in = threadIdx.x < a.ppw && p < a.n;
     const size_t n = a.n;
@@ -226,7 +224,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
             float tg[3] = {0.f, 0.f, 0.f}, d[3], os[3], len;
             if (act) load3(&a.tgt[k * n + p], tg);
             Hit hit;
-            trace_towards<NL, OV>(a, W, act && e < 0, o, tg, last, skip, hit, d, os, len, cnt);
+            trace_towards<TD, OV>(a, lds.ahead, lds.w[0], act && e < 0, o, tg, last, skip, hit, d, os, len);
             if (act && e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
                 const float t = a.tgt[k * n + p].w;
@@ -253,8 +251,8 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                     float nr[3] = {hit.nx, hit.ny, hit.nz};
                     if (a.smooth_h2 > 0.f) {
                         float acc[3] = {0.f, 0.f, 0.f};
-                        gather_normals<NL>(a.t.v, o, a.smooth_h2, nr, acc);
-                        if (OV) gather_normals<NL>(a.t.ov, o, a.smooth_h2, nr, acc);
+                        gather_normals<TD>(a.t.v, o, a.smooth_h2, nr, acc);
+                        if (OV) gather_normals<TD>(a.t.ov, o, a.smooth_h2, nr, acc);
                         const float l = sqrtf(acc[0] * acc[0] + acc[1] * acc[1] + acc[2] * acc[2]);
                         if (l > 0.f) {
                             nr[0] = acc[0] / l;
@@ -392,7 +390,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
             }
             float d[3], os[3], len;
             Hit hit;
-            trace_towards<NL, OV>(a, W, act, o, tg, last, skip, hit, d, os, len, cnt);
+            trace_towards<TD, OV>(a, lds.ahead, lds.w[0], act, o, tg, last, skip, hit, d, os, len);
             if (act) {
                 if (!(len > 0.f)) status = PCRL_REFINE_DEGENERATE;
                 else if (hit.id != NO_HIT && skip + hit.t < len - a.clear) status = PCRL_REFINE_OCCLUDED;
@@ -415,7 +413,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         }
         float d[3], os[3], len;
         Hit hit;
-        trace_towards<NL, OV>(a, W, act, o, R, last, skip, hit, d, os, len, cnt);
+        trace_towards<TD, OV>(a, lds.ahead, lds.w[0], act, o, R, last, skip, hit, d, os, len);
         if (act) {
             if (!(len > 0.f)) status = PCRL_REFINE_DEGENERATE;
             else if (hit.id != NO_HIT && skip + hit.t < len) status = PCRL_REFINE_OCCLUDED;
@@ -575,11 +573,11 @@ __global__ __launch_bounds__(64) void k_refine_sweep(const uint64_t* skey, const
     }
 }
 
-template <int NL>
-static void launch_refine_nl(const RefineArgs& a, hipStream_t s) {
+template <int TD>
+static void launch_refine_td(const RefineArgs& a, hipStream_t s) {
     const unsigned grid = (a.n + a.ppw - 1) / a.ppw;
-    if (a.t.has_ov) hipLaunchKernelGGL((k_refine<NL, true>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
-    else hipLaunchKernelGGL((k_refine<NL, false>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
+    if (a.t.has_ov) hipLaunchKernelGGL((k_refine<TD, true>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
+    else hipLaunchKernelGGL((k_refine<TD, false>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
 }
 
 }  // namespace pcrl
@@ -741,11 +739,11 @@ extern "C" int refine_paths(const PcrlScene* scene, const float* tx, int32_t n_t
         T.release();
         return rc;
     }
-    switch (scene->view.nlev) {
-    case 1: launch_refine_nl<1>(a, s); break;
-    case 2: launch_refine_nl<2>(a, s); break;
-    case 3: launch_refine_nl<3>(a, s); break;
-    default: launch_refine_nl<4>(a, s); break;
+    switch (scene->view.depth) {
+    case -1: launch_refine_td<-1>(a, s); break;
+    case 0: launch_refine_td<0>(a, s); break;
+    case 1: launch_refine_td<1>(a, s); break;
+    default: launch_refine_td<2>(a, s); break;
     }
     const unsigned g = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_refine_keys, dim3(g), dim3(256), 0, s, paths->tx, paths->rx, paths->n_refl, out->status,

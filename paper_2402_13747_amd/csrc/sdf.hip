@@ -13,14 +13,16 @@
 // by h / 2 and compares no sign across that sample.  The ray's intersection is
 // the nearest over the leaves; its normal is n at the final sample.
 //
-// Lane = ray.  The leaves come from the launcher's hierarchical DDA
-// (trace_core.h), walked per lane; the walk stops once the next cell starts
+// Lane = ray.  The leaves come from a hierarchical DDA
+// (sdf_walk.h), walked per lane; the walk stops once the next cell starts
 // more than 1.5 leaf diagonals beyond the nearest intersection found (no
 // later leaf's segment starts before that).  The neighbours of x are the
 // entries of the 27 leaves around x's leaf (h is at most 0.98 leaf edges)
 // whose centre lies in that leaf, so each point is counted once.
+#include "sdf_walk.h"
 #include "trace_core.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace pcrl {
@@ -131,7 +133,7 @@ __device__ __forceinline__ bool sdf_eval(const SdfArgs& a, const float x[3], flo
             continue;
         DdaCell k;
         dda_cell_reset(k);
-        dda_locate<false, NL>(a.ov, N, k, nullptr);
+        dda_locate<NL>(a.ov, N, k);
         if (k.lvl != NL || k.range.y == 0u) continue;
         reads += k.range.y;
         sdf_accumulate(a, x, k.range.x, k.range.x + k.range.y, sw, sp, sn);
@@ -182,12 +184,12 @@ __global__ void k_own_flags(SceneView v, uint32_t m, uint32_t* flag) {
         N.cq[0] = N.cq[1] = N.cq[2] = -1;
         N.cres = 0;
         N.cskip0 = 1;
-    N.cbox = NO_BOX;
+        N.cbox = NO_BOX;
         N.cnode = 0;
         N.oct_shift = 0;
         DdaCell k;
         dda_cell_reset(k);
-        dda_locate<false, NL>(v, N, k, nullptr);
+        dda_locate<NL>(v, N, k);
         own = (k.lvl == NL && k.range.x <= e && e - k.range.x < k.range.y) ? 1u : 0u;
     }
     flag[e] = own;
@@ -273,7 +275,7 @@ __device__ __forceinline__ void sdf_first_hit(const SdfArgs& a, const float o[3]
     while (walking) {
         DdaCell k;
         dda_cell_reset(k);
-        dda_locate<false, NL>(v, S, k, nullptr);
+        dda_locate<NL>(v, S, k);
         const bool at_leaf = k.lvl == NL;
         float c[3];
         uint32_t o0 = 0u, o1 = 0u;
@@ -426,7 +428,7 @@ __device__ __forceinline__ bool nearest_own(const SdfArgs& a, const float x[3], 
             continue;
         DdaCell k;
         dda_cell_reset(k);
-        dda_locate<false, NL>(a.ov, N, k, nullptr);
+        dda_locate<NL>(a.ov, N, k);
         if (k.lvl != NL || k.range.y == 0u) continue;
         const uint32_t e1 = k.range.x + k.range.y;
         for (uint32_t e = k.range.x; e < e1; ++e) {
@@ -579,7 +581,7 @@ struct OwnLayout {
 };
 
 static OwnLayout own_layout(const PcrlScene* S) {
-    const SceneView& v = S->view;
+    const SceneView& v = S->walk;
     OwnLayout L{};
     L.leaf_off = ((size_t)(S->info.n_entries + 1) * sizeof(uint32_t) + 7) / 8 * 8;
     L.n_leaves = v.nn[v.nlev - 1];
@@ -595,7 +597,7 @@ static OwnLayout own_layout(const PcrlScene* S) {
 // The scene's view with its leaf and cell ranges pointing into the own entries.
 static SceneView own_view(const PcrlScene* S) {
     const OwnLayout L = own_layout(S);
-    SceneView ov = S->view;
+    SceneView ov = S->walk;
     char* base = (char*)S->own_scan;
     ov.leaf = (const uint2*)(base + L.leaf_off);
     if (L.n_cells) ov.cells = (const uint2*)(base + L.cells_off);
@@ -607,6 +609,65 @@ static void launch_own_flags(const SceneView& v, uint32_t m, uint32_t* flag, hip
     hipLaunchKernelGGL((k_own_flags<NL>), dim3((unsigned)(((uint64_t)m + 255) / 256)), dim3(256), 0, s, v, m, flag);
 }
 
+// The structures of the leaf walk for scene S (S->walk), owned by B: child
+// bases and boxes of every brick, the leaves' skip radii (a dense cell table
+// where it fits, else isotropic radii) and those of the level-0 grid.
+static int build_walk(PcrlScene* S, hipStream_t s, DevBufs& B) {
+    SceneView v = S->view;
+    const int L = v.nlev;
+    int rc;
+    auto blocks = [](int64_t n, int block) { return dim3((unsigned)std::max<int64_t>(1, (n + block - 1) / block)); };
+    for (int l = 0; l + 1 < L; ++l) {
+        const int64_t nodes = v.nn[l];
+        uint32_t *bs = nullptr, *ab = nullptr;
+        if ((rc = B.alloc(&bs, (size_t)nodes * v.nw[l]))) return rc;
+        launch_brick_base(v.mask[l], S->first_child[l], nodes, v.nw[l], bs, s);
+        v.base[l] = bs;
+        if (v.ratio[l] > 32 || nodes == 0) continue;
+        if ((rc = B.alloc(&ab, (size_t)nodes))) return rc;
+        hipLaunchKernelGGL(k_brick_aabb, blocks(nodes, WALK_BLOCK), dim3(WALK_BLOCK), 0, s, v.mask[l], nodes, v.nw[l],
+                           v.ratio[l], ab);
+        v.baabb[l] = ab;
+    }
+    if (L >= 2 && v.nn[L - 2] > 0) {
+        const int r = v.ratio[L - 2];
+        const int64_t r3 = (int64_t)r * r * r, nb = v.nn[L - 2], n_cells = nb * r3;
+        if (!S->compact && r <= 16 && n_cells * 8 <= CELL_TABLE_MAX_BYTES) {
+            uint2* cells = nullptr;
+            if ((rc = B.alloc(&cells, (size_t)n_cells))) return rc;
+            const size_t lds = (size_t)2 * 8 * r * r * 2 + (size_t)r3 * 4;
+            hipLaunchKernelGGL(k_brick_cells, dim3((unsigned)nb), dim3(WALK_BLOCK), lds, s, v.mask[L - 2],
+                               v.base[L - 2], v.leaf, v.nw[L - 2], r, cells);
+            v.cells = cells;
+        } else if (r >= 3 && r <= 16) {
+            uint8_t* ld = nullptr;
+            if ((rc = B.alloc(&ld, (size_t)n_cells))) return rc;
+            const dim3 g = blocks(nb, WALK_BLOCK / 64);
+            if (r == 10)
+                hipLaunchKernelGGL(k_brick_dist<10>, g, dim3(WALK_BLOCK), 0, s, v.mask[L - 2], v.nw[L - 2], r, nb, ld);
+            else if (r == 8)
+                hipLaunchKernelGGL(k_brick_dist<8>, g, dim3(WALK_BLOCK), 0, s, v.mask[L - 2], v.nw[L - 2], r, nb, ld);
+            else
+                hipLaunchKernelGGL(k_brick_dist<0>, g, dim3(WALK_BLOCK), 0, s, v.mask[L - 2], v.nw[L - 2], r, nb, ld);
+            v.ldist = ld;
+        }
+    }
+    const int64_t cells0 = (int64_t)v.dim0[0] * v.dim0[1] * v.dim0[2];
+    uint8_t *d0 = nullptr, *tmp = nullptr;
+    if ((rc = B.alloc(&d0, (size_t)cells0)) || (rc = dalloc((void**)&tmp, (size_t)cells0, s))) return rc;
+    const dim3 g0 = blocks(cells0, WALK_BLOCK);
+    hipLaunchKernelGGL(k_dist0_pass, g0, dim3(WALK_BLOCK), 0, s, v.map0, (const uint8_t*)nullptr, d0, v.dim0[0],
+                       v.dim0[1], v.dim0[2], 0);
+    hipLaunchKernelGGL(k_dist0_pass, g0, dim3(WALK_BLOCK), 0, s, (const int32_t*)nullptr, (const uint8_t*)d0, tmp,
+                       v.dim0[0], v.dim0[1], v.dim0[2], 1);
+    hipLaunchKernelGGL(k_dist0_pass, g0, dim3(WALK_BLOCK), 0, s, (const int32_t*)nullptr, (const uint8_t*)tmp, d0,
+                       v.dim0[0], v.dim0[1], v.dim0[2], 2);
+    v.dist0 = d0;
+    dfree(tmp, s);
+    S->walk = v;
+    return hipGetLastError() == hipSuccess ? PCRL_OK : PCRL_EHIP;
+}
+
 // The scene's own-point index, built on the first call (under the scene's
 // lock) and kept with the scene.  The build waits for its stream, so calls on
 // any stream find the index complete.
@@ -614,42 +675,42 @@ static int own_index(PcrlScene* S, hipStream_t s) {
     std::lock_guard<std::mutex> lock(S->own_mu);
     if (S->own_scan) return PCRL_OK;
     const int64_t m = S->info.n_entries, np = S->info.n_points;
+    DevBufs B;  // handed to the scene when complete
+    B.stream = s;
+    int rc = build_walk(S, s, B);
     const OwnLayout lay = own_layout(S);
+    char* block = nullptr;
     uint32_t* scan = nullptr;
     float4 *pos = nullptr, *nrm = nullptr;
-    int rc = dalloc((void**)&scan, lay.bytes, s);
-    if (!rc) rc = dalloc((void**)&pos, (size_t)(np > 0 ? np : 1) * sizeof(float4), s);
-    if (!rc) rc = dalloc((void**)&nrm, (size_t)(np > 0 ? np : 1) * sizeof(float4), s);
+    if (!rc) rc = B.alloc(&block, lay.bytes);
+    if (!rc) rc = B.alloc(&pos, (size_t)(np > 0 ? np : 1));
+    if (!rc) rc = B.alloc(&nrm, (size_t)(np > 0 ? np : 1));
+    scan = (uint32_t*)block;
     if (!rc) {
         switch (S->view.nlev) {
-        case 1: launch_own_flags<1>(S->view, (uint32_t)m, scan, s); break;
-        case 2: launch_own_flags<2>(S->view, (uint32_t)m, scan, s); break;
-        case 3: launch_own_flags<3>(S->view, (uint32_t)m, scan, s); break;
-        default: launch_own_flags<4>(S->view, (uint32_t)m, scan, s); break;
+        case 1: launch_own_flags<1>(S->walk, (uint32_t)m, scan, s); break;
+        case 2: launch_own_flags<2>(S->walk, (uint32_t)m, scan, s); break;
+        case 3: launch_own_flags<3>(S->walk, (uint32_t)m, scan, s); break;
+        default: launch_own_flags<4>(S->walk, (uint32_t)m, scan, s); break;
         }
         rc = hipGetLastError() == hipSuccess ? scan_u32(scan, scan, m, scan + m, s) : PCRL_EHIP;
     }
     if (!rc) {
         hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, S->view.spos,
                            S->view.snrm, scan, (uint32_t)m, (uint32_t)np, pos, nrm);
-        char* base = (char*)scan;
         hipLaunchKernelGGL(k_own_ranges, dim3((unsigned)((lay.n_leaves + 255) / 256)), dim3(256), 0, s,
-                           S->view.leaf, (uint32_t)lay.n_leaves, scan, (uint2*)(base + lay.leaf_off));
+                           S->walk.leaf, (uint32_t)lay.n_leaves, scan, (uint2*)(block + lay.leaf_off));
         if (lay.n_cells)
             hipLaunchKernelGGL(k_own_ranges, dim3((unsigned)((lay.n_cells + 255) / 256)), dim3(256), 0, s,
-                               S->view.cells, (uint32_t)lay.n_cells, scan, (uint2*)(base + lay.cells_off));
+                               S->walk.cells, (uint32_t)lay.n_cells, scan, (uint2*)(block + lay.cells_off));
         rc = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? PCRL_OK : PCRL_EHIP;
     }
     if (rc) {
-        dfree(scan, s);
-        dfree(pos, s);
-        dfree(nrm, s);
+        B.release();
         if (rc == PCRL_EHIP) set_error("sdf_intersect: building the own-point index failed");
         return rc;
     }
-    S->bufs.ptrs.push_back(scan);
-    S->bufs.ptrs.push_back(pos);
-    S->bufs.ptrs.push_back(nrm);
+    S->bufs.ptrs.insert(S->bufs.ptrs.end(), B.ptrs.begin(), B.ptrs.end());
     S->own_scan = scan;
     S->own_pos = pos;
     S->own_nrm = nrm;
@@ -663,7 +724,6 @@ int scene_own_index(PcrlScene* S, hipStream_t s) { return own_index(S, s); }
 static void sdf_defaults(const PcrlScene* scene, SdfArgs& a) {
     const float leaf = scene->view.h;
     const float h = 0.95f * leaf;
-    a.v = scene->view;
     a.max_steps = 64;
     a.h2 = h * h;
     a.hl2 = (h / leaf + 1e-3f) * (h / leaf + 1e-3f);
@@ -695,6 +755,7 @@ int sdf_launch_run(PcrlLaunch* L, const TraceArgs& t) {
         A.s.oscan = scene->own_scan;
         A.s.opos = scene->own_pos;
         A.s.onrm = scene->own_nrm;
+        A.s.v = scene->walk;
         A.s.ov = own_view(scene);
     }
     A.tx = t.tx;
@@ -777,7 +838,6 @@ extern "C" int sdf_intersect(const PcrlScene* scene, const float* o, const float
     }
     if (n_rays == 0) return PCRL_OK;
     SdfArgs a{};
-    a.v = scene->view;
     a.o = o;
     a.d = d;
     a.tr = t_range;
@@ -804,6 +864,7 @@ extern "C" int sdf_intersect(const PcrlScene* scene, const float* o, const float
         a.oscan = scene->own_scan;
         a.opos = scene->own_pos;
         a.onrm = scene->own_nrm;
+        a.v = scene->walk;
         a.ov = own_view(scene);
     }
     DevBufs T;

@@ -1,11 +1,10 @@
 // trace.hip -- uniform ray launching over the voxel hierarchy (paper, Section 2.2).
 //
 // One kernel launch per bounce b = 0..K.  Lane = ray.  Per segment a lane
-//   1. walks the hierarchy by DDA in finest-leaf integer coordinates: at every
-//      step it looks the current leaf up top-down (level-0 map, then one brick
-//      word per level); an empty cell at level i is skipped whole (its exit
-//      along the ray is computed at level i's size), an occupied leaf has
-//      all its surfels tested;
+//   1. walks the hierarchy by DDA in leaf coordinates (trace_core.h): an empty
+//      top cell's skip box, or a brick's box of occupied leaves, is crossed in
+//      one step; inside, blocks of 4 x 4 x 4 leaves are stepped through in
+//      registers; an occupied leaf has all its surfels tested;
 //   2. keeps the nearest surfel hit (ties: smaller point id) and stops once
 //      the next cell starts beyond it;
 //   3. tests every RX sphere on [0, t_hit] (rho grows with unfolded length);
@@ -22,23 +21,49 @@
 
 namespace pcrl {
 
-// Specialised on the number of voxel levels NL and on the presence of an
-// overlay OV, so every level index in the traversal is a compile-time constant.
-// Each wave traces 64 consecutive slots in lockstep (neighbouring slots hold
-// coherent rays: their lookups share cache lines), grid-stride over the
-// active slots; with an overlay, the base hierarchy and then the overlay.
-// BX: the traversal uses the bricks' occupied-children boxes (scenes without
-// a dense cell table; the table's octant radii already skip empty leaves, and
-// the box code's registers would cost those scenes a wave per SIMD).
-template <bool FIRST, bool STATS, int NL, bool OV, bool BX>
+// Rays a wave traces together when n rays are active.  A wave lasts as long as
+// its longest ray and tests its lanes' leaves together, so while the waves do
+// not fill the GPU fewer rays per wave end sooner; once they do, every extra
+// wave costs its own instructions.  The line is at 8,192 waves (8 per SIMD).
+// 16 k rays in a room, four segments: 0.391 ms with 64 rays a wave, 0.352
+// with 32, 0.318 with 16, 0.304 with 8, 0.357 with 4.  766 k rays in a street:
+// 0.338 ms with 64, 0.452 with 32; 196 k: 0.525 and 0.401 ms.  Every wave runs
+// the receivers' loop once, about 14 instructions each, so many receivers
+// move the line down: 200 k rays and 1,024 of them take 1.08 ms with 64 rays
+// a wave, 1.42 with 32.
+constexpr uint32_t RPW_MIN = 8, RPW_WAVES = 8192, RPW_RX = 512;
+__host__ __device__ __forceinline__ uint32_t rays_per_wave(uint32_t n, uint32_t n_rx) {
+    const uint32_t waves = RPW_WAVES * RPW_RX / (RPW_RX + n_rx);
+    uint32_t r = 64;
+    while (r > RPW_MIN && n / (r / 2) <= waves) r /= 2;
+    return r;
+}
+
+// Specialised on the depth TD of the traversal's top grid and on the presence
+// of an overlay OV, so every level index in the traversal is a compile-time
+// constant.  Each wave traces `rpw` consecutive slots in lockstep
+// (neighbouring slots hold coherent rays: their lookups share cache lines),
+// grid-stride over the active slots; with an overlay, the base hierarchy and
+// then the overlay.  The grid is a multiple of 8: the blocks that the active
+// slots need are spread over all 8 XCDs (workgroups are dispatched to them
+// round-robin), each XCD working on one contiguous range of slots so that
+// neighbouring, coherent rays share its L2; the other blocks end at once.
+template <bool FIRST, bool STATS, int TD, bool OV>
 __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(TraceArgs a, int b) {
+    constexpr uint32_t WAVES = TRACE_BLOCK / 64;
+    __shared__ TraceLds<WAVES> lds;
     const uint32_t n_act = FIRST ? a.n_total : a.counters[b];
-    const uint32_t wave = xcd_block() * (TRACE_BLOCK / 64) + (threadIdx.x >> 6);
-    const uint32_t n_waves = gridDim.x * (TRACE_BLOCK / 64);
-    __shared__ LeafTestLds lds[TRACE_BLOCK / 64];
+    const uint32_t rpw = rays_per_wave(n_act, (uint32_t)a.n_rx);
+    const uint32_t blocks = min((uint32_t)gridDim.x, (n_act + rpw * WAVES - 1) / (rpw * WAVES));
+    const uint32_t per = (blocks + 7) >> 3, block = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= per || block >= blocks) return;
+    ahead_init(lds.ahead, threadIdx.x, TRACE_BLOCK);
+    __syncthreads();
+    const uint32_t wave = block * WAVES + (threadIdx.x >> 6);
     stat_t cnt[ST_COUNT] = {};
-    for (uint32_t base = wave * 64; base < n_act; base += n_waves * 64)
-        trace_chunk<FIRST, STATS, NL, OV, BX>(a, lds[threadIdx.x >> 6], b, base, n_act, false, cnt);
+    for (uint32_t base = wave * rpw; base < n_act; base += blocks * WAVES * rpw)
+        trace_chunk<FIRST, STATS, TD, OV>(kernel_args(), lds.ahead, lds.w[threadIdx.x >> 6], b, base, rpw, n_act, false,
+                                          cnt);
     flush_stats<STATS>(cnt, a.stats ? a.stats + (size_t)b * PCRL_NSTATS : nullptr);
 }
 
@@ -113,30 +138,23 @@ __global__ void k_unpack_records(const uint4* rec, const uint32_t* count, uint32
 // host side
 // ---------------------------------------------------------------------------
 
-template <bool FIRST, bool STATS, int NL, bool BX>
-static void launch_trace_bx(const TraceArgs& a, int b, unsigned grid, hipStream_t s) {
-    if (a.has_ov) hipLaunchKernelGGL((k_trace<FIRST, STATS, NL, true, BX>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a, b);
-    else hipLaunchKernelGGL((k_trace<FIRST, STATS, NL, false, BX>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a, b);
-}
-
-template <bool FIRST, bool STATS, int NL>
-static void launch_trace_nl(const TraceArgs& a, int b, unsigned grid, hipStream_t s) {
-    if constexpr (NL == 1) {
-        launch_trace_bx<FIRST, STATS, NL, false>(a, b, grid, s);   // no bricks
-    } else {
-        if (a.v.cells) launch_trace_bx<FIRST, STATS, NL, false>(a, b, grid, s);
-        else launch_trace_bx<FIRST, STATS, NL, true>(a, b, grid, s);
-    }
+template <bool FIRST, bool STATS, int TD>
+static void launch_trace_td(const TraceArgs& a, int b, unsigned grid, hipStream_t s) {
+    grid = (grid + 7) / 8 * 8;
+    if (a.has_ov)
+        hipLaunchKernelGGL((k_trace<FIRST, STATS, TD, true>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a, b);
+    else
+        hipLaunchKernelGGL((k_trace<FIRST, STATS, TD, false>), dim3(grid), dim3(TRACE_BLOCK), 0, s, a, b);
 }
 
 template <bool FIRST, bool STATS>
 static void launch_trace(const TraceArgs& a, int b, unsigned grid, hipStream_t s) {
-    static_assert(PCRL_MAX_LEVELS == 4, "one kernel specialisation per level count");
-    switch (a.v.nlev) {
-    case 1: launch_trace_nl<FIRST, STATS, 1>(a, b, grid, s); break;
-    case 2: launch_trace_nl<FIRST, STATS, 2>(a, b, grid, s); break;
-    case 3: launch_trace_nl<FIRST, STATS, 3>(a, b, grid, s); break;
-    default: launch_trace_nl<FIRST, STATS, 4>(a, b, grid, s); break;
+    static_assert(PCRL_MAX_LEVELS == 4, "one kernel specialisation per top-grid depth");
+    switch (a.v.depth) {
+    case -1: launch_trace_td<FIRST, STATS, -1>(a, b, grid, s); break;
+    case 0: launch_trace_td<FIRST, STATS, 0>(a, b, grid, s); break;
+    case 1: launch_trace_td<FIRST, STATS, 1>(a, b, grid, s); break;
+    default: launch_trace_td<FIRST, STATS, 2>(a, b, grid, s); break;
     }
 }
 
@@ -306,8 +324,12 @@ static int launch_run(PcrlLaunch* L, const TraceArgs& a) {
     const uint32_t n_total = (uint32_t)L->n_total;
     const bool stats = L->stats != nullptr;
     const bool timing = !L->events.empty();
-    const unsigned full = (unsigned)((n_total + TRACE_BLOCK - 1) / TRACE_BLOCK);
-    const unsigned capped = std::min<unsigned>(full, (unsigned)device_cus() * 16);
+    // bounce 0 runs as many blocks as its rays need; later ones, whose count is on the device,
+    // at most 16 per CU (the blocks they do not need end at once)
+    const uint32_t per_block = rays_per_wave(n_total, (uint32_t)a.n_rx) * (TRACE_BLOCK / 64);
+    const unsigned full = (n_total + per_block - 1) / per_block;
+    const unsigned most = (n_total + RPW_MIN * (TRACE_BLOCK / 64) - 1) / (RPW_MIN * (TRACE_BLOCK / 64));
+    const unsigned capped = std::min<unsigned>(most, (unsigned)device_cus() * 16);
     for (int b = 0; b <= K; ++b) {
         if (timing) PCRL_TRY_HIP(hipEventRecord(L->events[2 * b], s));
         if (b == 0) {

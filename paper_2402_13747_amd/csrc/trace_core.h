@@ -13,10 +13,10 @@ constexpr int TRACE_BLOCK = 256;
 constexpr uint32_t NO_HIT = 0xFFFFFFFFu;
 
 // Statistics of the PCRL_LAUNCH_STATS kernel variant.  ST_BYTES is the exact
-// algorithmic traffic of the trace kernels: 4 B per level-0 map read, 8 B per
-// brick mask word (+4 B base when the bit is set), 8 B per leaf range, 32 B
-// per surfel tested, 36 B of ray state read per segment after the first,
-// 36 B of ray state + 16 B of history per reflection, 16 B per record.
+// algorithmic traffic of the trace kernels: 8 B per top cell and 16 B per block
+// record read (12 B per brick word between), 8 B per leaf range, 32 B per
+// surfel tested, 36 B of ray state read per segment after the first, 36 B of
+// ray state + 16 B of history per reflection, 16 B per record.
 enum StatSlot {
     ST_SEGMENTS = 0, ST_DDA, ST_LEAVES, ST_NODES, ST_TESTS, ST_HITS, ST_BYTES, ST_EMPTY_LEAF, ST_UNIFORM,
     ST_WAVE_DDA, ST_WAVE_TESTS, ST_COUNT
@@ -67,101 +67,46 @@ struct Hit {
     float nx, ny, nz;
 };
 
-// Level-indexed constants for a per-lane level index.  The values are
-// selected arithmetically after loading all NL of them: a select between
-// loads of argument fields would become a pointer select into the argument
-// struct and keep the struct in scratch memory.
-template <int NL>
-__device__ __forceinline__ int span_at(const SceneView& v, int lvl) {
-    int s = 0;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) s += v.span[i] * (int)(lvl == i);
-    return s;
-}
-
-template <int NL>
-__device__ __forceinline__ uint64_t mspan_at(const SceneView& v, int lvl) {
-    uint64_t m = 0;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) m += v.mspan[i] * (uint64_t)(lvl == i);
-    return m;
-}
-
-// Box word that no child lies outside of (lo 0, hi 31 on every axis): the
-// value used where a brick has no box.
-constexpr uint32_t NO_BOX = (31u << 15) | (31u << 20) | (31u << 25);
-
-// Descend from level 0 to level TO (< nlev) for leaf cell c.  Returns the
-// level at which the path is empty, or TO + 1 when the level-TO node exists
-// (its index in `node`).  Quotients c / span[i] use the precomputed magics.
-// BOX: `box` receives the occupied-children box of the brick that holds the
-// empty cell (empty at level i >= 1: the level-(i-1) brick), or of the
-// level-TO node's own brick when the path exists (TO < nlev - 1); NO_BOX
-// where there is none.  The box of a brick is loaded with its mask word.
-template <bool STATS, int TO, bool BOX = false>
-__device__ __forceinline__ int descend(const SceneView& v, const int c[3], uint32_t& node, int& skip0,
-                                       stat_t* cnt, uint32_t* box = nullptr) {
-    int p[3] = {span_div(c[0], v.mspan[0]), span_div(c[1], v.mspan[0]), span_div(c[2], v.mspan[0])};
-    const size_t i0 = (size_t)p[0] + (size_t)v.dim0[0] * ((size_t)p[1] + (size_t)v.dim0[1] * p[2]);
-    // the level-0 node and the cell's skip radius are loaded together
-    const int32_t n0 = v.map0[i0];
-    const int d0 = v.dist0 ? (int)v.dist0[i0] : 1;
-    if (STATS) {
-        ++cnt[ST_NODES];
-        cnt[ST_BYTES] += (n0 < 0 && v.dist0) ? 5 : 4;
-    }
-    if (BOX) *box = NO_BOX;
-    if (n0 < 0 || (uint32_t)n0 >= v.nn[0]) {
-        skip0 = d0;
-        return 0;
-    }
-    uint32_t n = (uint32_t)n0;
-#pragma unroll
-    for (int i = 1; i <= TO; ++i) {
-        const int q[3] = {span_div(c[0], v.mspan[i]), span_div(c[1], v.mspan[i]), span_div(c[2], v.mspan[i])};
-        const int r = v.ratio[i - 1];
-        const int loc = (q[0] - r * p[0]) + r * ((q[1] - r * p[1]) + r * (q[2] - r * p[2]));
-        const size_t wi = (size_t)n * v.nw[i - 1] + (loc >> 6);
-        const uint64_t w = v.mask[i - 1][wi];
-        const uint32_t bx = (BOX && v.baabb[i - 1]) ? v.baabb[i - 1][n] : NO_BOX;
-        const uint64_t bit = uint64_t(1) << (loc & 63);
-        if (STATS) {
-            ++cnt[ST_NODES];
-            cnt[ST_BYTES] += ((w & bit) ? 12 : 8) + ((BOX && v.baabb[i - 1]) ? 4 : 0);
-        }
-        if (!(w & bit)) {
-            if (BOX) *box = bx;
-            return i;
-        }
-        n = v.base[i - 1][wi] + (uint32_t)__popcll(w & (bit - 1));
-        if (n >= v.nn[i]) return i;
-        p[0] = q[0];
-        p[1] = q[1];
-        p[2] = q[2];
-    }
-    node = n;
-    if constexpr (BOX) {
-        if (v.baabb[TO]) {
-            *box = v.baabb[TO][n];
-            if (STATS) cnt[ST_BYTES] += 4;
-        }
-    }
-    return TO + 1;
-}
-
-// Per-wave LDS of the cooperative leaf test: the rays of the wave's lanes and,
-// per lane, the pending leaf, its running nearest hit and the hit's normal.
-struct alignas(16) LeafTestLds {
-    float4 hn[64];                 // normal + label bits of a new nearest hit
+// Per-wave LDS of a trace: the rays of the wave's lanes (read by every lane in
+// the cooperative leaf tests) and their running nearest hits.
+struct alignas(16) WaveLds {
+    float4 o[64];                  // origin, point the ray left (bits; excluded)
+    float4 d[64];                  // unit direction, length travelled before the segment
+    uint32_t g[64];                // global ray id
     unsigned long long best[64];   // (t bits << 32) | point id: lexicographic min = nearest, ties by id
-    float ox[64], oy[64], oz[64], dx[64], dy[64], dz[64];
-    uint32_t last[64];             // point the ray left (excluded)
-    uint32_t begin[64];            // first entry of the lane's pending leaf
-    uint32_t excl[64];             // exclusive prefix of the pending entry counts over lanes
-    uint32_t win[64];              // a test of this pass found a new nearest hit for the lane
-    int32_t mark[64];              // lane whose entries start at this position of the current chunk
+    uint32_t entry[64];            // entry that set `best` in this trace
+    uint32_t delta[64];            // first entry of the lane's leaf minus its first pair
+    int32_t mark[64];              // 1 + the lane whose pairs start at this position of the chunk
 };
 
+// Occupancy ahead of a ray in a block of 4 x 4 x 4 leaves: bit j of
+// ahead[64 o + i] is set when leaf j lies at or after leaf i along every axis
+// in direction octant o (bit a: component a negative).  A ray only moves
+// ahead, so a block whose mask has no bit there is crossed in one step.
+constexpr int AHEAD_WORDS = 8 * 64;
+
+__device__ __forceinline__ void ahead_init(uint64_t* ahead, uint32_t first, uint32_t stride) {
+    for (uint32_t i = first; i < (uint32_t)AHEAD_WORDS; i += stride) {
+        const uint32_t o = i >> 6, x = i & 3u, y = (i >> 2) & 3u, z = (i >> 4) & 3u;
+        const uint32_t nx = (o & 1u) ? 0xFu >> (3u - x) : (0xFu << x) & 0xFu;
+        const uint32_t ny = (o & 2u) ? 0xFu >> (3u - y) : (0xFu << y) & 0xFu;
+        const uint32_t nz = (o & 4u) ? 0xFu >> (3u - z) : (0xFu << z) & 0xFu;
+        const uint32_t sy = (ny & 1u) | ((ny & 2u) << 3) | ((ny & 4u) << 6) | ((ny & 8u) << 9);
+        const uint64_t sz = (uint64_t)(nz & 1u) | ((uint64_t)(nz & 2u) << 15) | ((uint64_t)(nz & 4u) << 30) |
+                            ((uint64_t)(nz & 8u) << 45);
+        ahead[i] = (uint64_t)(nx * sy) * sz;
+    }
+}
+
+// LDS of a block of `WAVES` waves.
+template <int WAVES>
+struct alignas(16) TraceLds {
+    uint64_t ahead[AHEAD_WORDS];
+    WaveLds w[WAVES];
+};
+
+// Orders this wave's LDS accesses in the program; the hardware runs the LDS
+// instructions of one wave in order, so no wait is needed.
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -191,138 +136,360 @@ __device__ __forceinline__ int wave_scan_max_dpp(int x) {
     return x;
 }
 
-// Test the pending leaves of all lanes of the wave together: the wave's
+__device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+
+__device__ __forceinline__ unsigned long long hit_word(float t, uint32_t id) {
+    return ((unsigned long long)__float_as_uint(t) << 32) | id;
+}
+
+// Test the leaves (entries r) of all lanes of the wave together: the wave's
 // (lane, entry) pairs are dealt out 64 at a time, so every lane tests a
 // surfel in every pass whatever the leaves' sizes, and consecutive lanes read
 // consecutive entries of a leaf.  Each pair is tested against its owner
 // lane's ray and the owner's nearest hit is the minimum of (t, id) over its
 // previous hit and all accepted pairs: the same result as testing the
 // leaf's entries one after another in the owner's lane.  Called by every
-// lane of the wave; `has` marks lanes with a pending leaf (entries r).
+// lane of the wave (r.y 0: no leaf).
 template <bool STATS>
-__device__ __forceinline__ void leaf_tests(const SceneView& v, LeafTestLds& W, bool has, uint2 r, Hit& hit,
-                                           stat_t cnt[ST_COUNT]) {
+__device__ __forceinline__ void leaf_tests(const SceneView& v, WaveLds& W, uint2 r, stat_t* cnt) {
     const uint32_t lane = lane_id();
-    const uint32_t n = has ? r.y : 0u;
+    const uint32_t n = r.y;
     const uint32_t incl = wave_scan_add_dpp(n);
-    const uint32_t total = __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     const uint32_t excl = incl - n;
-    W.begin[lane] = r.x;
-    W.excl[lane] = excl;
-    W.best[lane] = ((unsigned long long)__float_as_uint(hit.t) << 32) | hit.id;
-    W.win[lane] = 0u;
+    W.delta[lane] = r.x - excl;
     for (uint32_t base = 0; base < total; base += 64) {
         if (STATS && lane == 0) ++cnt[ST_WAVE_TESTS];
-        W.mark[lane] = -1;
+        W.mark[lane] = 0;
         wave_sync();
-        if (n && excl < base + 64 && incl > base) W.mark[excl > base ? excl - base : 0] = (int)lane;
+        if (n && excl < base + 64 && incl > base) W.mark[excl > base ? excl - base : 0] = (int)lane + 1;
         wave_sync();
-        const int own = wave_scan_max_dpp(W.mark[lane] + 1) - 1;  // marks + 1 >= 0
-        const uint32_t pi = base + lane;
-        bool ok = false;
-        unsigned long long cand = 0;
-        float4 N = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (pi < total && own >= 0) {  // own >= 0 always: the pair at `base` has an owner
-            const uint32_t k = W.begin[own] + (pi - W.excl[own]);
-            const float4 P4 = v.spos[k];
-            N = v.snrm[k];
-            const float o0 = W.ox[own], o1 = W.oy[own], o2 = W.oz[own];
-            const float d0 = W.dx[own], d1 = W.dy[own], d2 = W.dz[own];
-            const uint32_t id = __float_as_uint(P4.w);
-            const float wx = P4.x - o0, wy = P4.y - o1, wz = P4.z - o2;
-            const float den = d0 * N.x + d1 * N.y + d2 * N.z;
-            const float num = wx * N.x + wy * N.y + wz * N.z;
-            const float t = num * __builtin_amdgcn_rcpf(den);
-            const float qx = t * d0 - wx, qy = t * d1 - wy, qz = t * d2 - wz;
-            const float dist2 = qx * qx + qy * qy + qz * qz;
-            ok = fabsf(den) > 1e-7f && t > v.t_eps && id != W.last[own] && dist2 <= v.rs2;
-            if (ok) {
-                cand = ((unsigned long long)__float_as_uint(t) << 32) | id;
-                atomicMin(&W.best[own], cand);
-            }
+        const uint32_t own = (uint32_t)max(wave_scan_max_dpp(W.mark[lane]), 1) - 1u;  // the pair at `base` has an owner
+        // lanes past the last pair repeat it (same loads, no branch)
+        const uint32_t pi = min(base + lane, total - 1u);
+        const uint32_t k = W.delta[own] + pi;
+        const float4 P = v.spos[k];
+        const float4 N = v.snrm[k];
+        const float4 O = W.o[own];
+        const float4 Dd = W.d[own];
+        const uint32_t id = __float_as_uint(P.w);
+        const float wx = P.x - O.x, wy = P.y - O.y, wz = P.z - O.z;
+        // the fused forms are written out: results must not depend on the compiler's choice
+        const float den = fmaf(N.z, Dd.z, fmaf(N.x, Dd.x, N.y * Dd.y));
+        const float num = fmaf(N.z, wz, fmaf(N.x, wx, N.y * wy));
+        const float t = num * __builtin_amdgcn_rcpf(den);
+        const float qx = fmaf(t, Dd.x, -wx), qy = fmaf(t, Dd.y, -wy), qz = fmaf(t, Dd.z, -wz);
+        const float dist2 = fmaf(qz, qz, fmaf(qx, qx, qy * qy));
+        // no short circuit: the id is then loaded with the position
+        const bool ok = (fabsf(den) > 1e-7f) & (t > v.t_eps) & (id != __float_as_uint(O.w)) & (dist2 <= v.rs2);
+        const unsigned long long cand = hit_word(t, id);
+        if (ok) atomicMin(&W.best[own], cand);
+        if (ballot(ok)) {
+            wave_sync();
+            // the pair that holds the minimum names its entry (pairs with equal
+            // (t, id) are the same point: same normal and label)
+            if (ok && W.best[own] == cand) W.entry[own] = k;
+            wave_sync();
         }
-        wave_sync();
-        // the pair that holds the minimum publishes the hit's normal and label
-        // (pairs with equal (t, id) are the same point: same normal)
-        if (ok && W.best[own] == cand) {
-            W.hn[own] = N;
-            W.win[own] = 1u;
-        }
-        wave_sync();
     }
-    if (has && W.win[lane]) {
-        const unsigned long long b = W.best[lane];
-        const float4 hn = W.hn[lane];
-        hit.t = __uint_as_float((uint32_t)(b >> 32));
-        hit.id = (uint32_t)b;
-        hit.nx = hn.x;
-        hit.ny = hn.y;
-        hit.nz = hn.z;
-        hit.lab = __float_as_uint(hn.w);
-    }
-    wave_sync();
 }
 
-// DDA state of one lane's segment.
-struct Seg {
-    float inv[3];   // 1 / d (0 on axes the ray does not move along)
-    int c[3];       // current leaf cell
-    int cq[3];      // parent cell of the cached descent
-    int cres;       // cached descent result
-    int cskip0;     // cached skip radius of an empty level-0 cell (cres == 0)
-    uint32_t cnode; // cached parent node
-    uint32_t cbox;  // cached box word: of the parent node's brick (cres > P), or of the brick holding
-                    // the empty cell (0 < cres <= P)
-    int it;         // DDA steps taken
-    int oct_shift;  // 4 x the ray's direction octant (bit a: component a negative)
-};
+__device__ __forceinline__ float clampf(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+__device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+__device__ __forceinline__ float min3(float a, float b, float c) { return fminf(fminf(a, b), c); }
 
-__device__ __forceinline__ int dir_step(float x) { return x > 0.f ? 1 : (x < 0.f ? -1 : 0); }
-
-// Start a segment from o along d: clip to the grid and find the first cell.
-// Returns false when the ray misses the grid.
-__device__ __forceinline__ bool seg_begin(const SceneView& v, const float o[3], const float d[3], Seg& S) {
-    float t0 = 0.f, t1 = INFINITY;
-    // slab test; both faces are read on every path (a choice between two
-    // argument fields would be turned into a pointer select into the argument
-    // struct, which then stays in scratch memory)
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float lo_a = v.org[a], hi_a = v.hi[a];
-        if (d[a] != 0.f) {
-            S.inv[a] = 1.0f / d[a];
-            const float ta = (lo_a - o[a]) * S.inv[a], tb = (hi_a - o[a]) * S.inv[a];
-            t0 = fmaxf(t0, fminf(ta, tb));
-            t1 = fminf(t1, fmaxf(ta, tb));
-        } else {
-            S.inv[a] = 0.f;
-            if (o[a] < lo_a || o[a] > hi_a) t1 = -1.f;
-        }
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int ci = (int)floorf((o[a] + t0 * d[a] - v.org[a]) * v.inv_h);
-        S.c[a] = min(max(ci, 0), v.dim[a] - 1);
-        S.cq[a] = -1;
-    }
-    S.cres = 0;
-    S.cskip0 = 1;
-    S.cbox = NO_BOX;
-    S.oct_shift = 4 * ((d[0] < 0.f ? 1 : 0) | (d[1] < 0.f ? 2 : 0) | (d[2] < 0.f ? 4 : 0));
-    S.cnode = 0;
-    S.it = 0;
-    return t0 <= t1;
+// Index of a top cell: coordinates below 2^22, rows below 2^32.
+__device__ __forceinline__ size_t top_index(const SceneView& v, uint32_t x, uint32_t y, uint32_t z) {
+    return (uint64_t)(__umul24(z, (uint32_t)v.tdim[1]) + y) * (uint32_t)v.tdim[0] + x;
 }
 
-__device__ __forceinline__ void stage_ray(LeafTestLds& W, const float o[3], const float d[3], uint32_t last) {
+// Walk every active lane's ray (staged in W) through one hierarchy, testing
+// the surfels of the leaves it crosses until no nearer hit can follow.  The
+// lane's nearest hit so far is W.best; ANY: a lane stops at its first hit
+// nearer than that.  Called by every lane of the wave.
+//
+// The walk runs in units of leaves, mirrored along every axis on which the
+// ray moves backwards, so it only moves towards larger coordinates: a step
+// crosses the box from the lane's cell up to hi, te is the distance at which
+// it leaves the box and c the next cell.  Cells are whole numbers below 2^22
+// held in floats.
+//   - TD < 0: the top grid's cells are leaves.  TD >= 0: they are bricks of
+//     r^3 leaves (TD = 0), or TD levels of bricks above those.
+//   - an empty top cell holds, per direction octant, the edge of the largest
+//     empty box of top cells (of 1, 2, 3, 4, 6, 8, 12, 16) from it onwards;
+//   - an occupied one holds its brick and the box of its occupied leaves: the
+//     ray goes straight to that box, or past the brick when it misses it;
+//   - inside, one 16-byte record per 4 x 4 x 4 leaves holds their occupancy:
+//     the lane steps leaf by leaf in registers while occupied leaves lie
+//     ahead in the block, else to the block's end.
+// Every distance is computed from the ray's origin (no accumulation), and a
+// surfel is listed in every leaf within the build's rounding pad of its disk,
+// so no leaf holding the nearest hit is passed by.
+//
+// Bound by latency: a wave's chain of steps, each with one to three dependent
+// loads, and by instruction issue.  Against a per-step descent through the
+// levels with 64-bit divisions (36 then 16 steps a segment, 250 instructions
+// each, spilled scalar registers): street canyon, 4 x 4 M rays, 10.2 steps a
+// segment, 21.6 -> 11.1 ms of kernels a launch; furnished room, 1 M rays, 9.5
+// steps, 2.25 -> 1.41 ms; 16 k rays in a room 0.74 -> 0.30 ms.  The leaves of
+// a step are tested at once: letting lanes wait at their leaves until 8, 24 or
+// 48 of them did (fuller tests) took 1.53, 1.66 and 1.90 ms in the room
+// against 1.49.
+template <bool STATS, int TD, bool ANY = false>
+__device__ __forceinline__ void walk(const SceneView& v, const uint64_t* ahead, WaveLds& W, bool active, stat_t* cnt) {
     const uint32_t lane = lane_id();
-    W.ox[lane] = o[0];
-    W.oy[lane] = o[1];
-    W.oz[lane] = o[2];
-    W.dx[lane] = d[0];
-    W.dy[lane] = d[1];
-    W.dz[lane] = d[2];
-    W.last[lane] = last;
+    float og[3], dg[3], ig[3], c[3], te = 0.f, ts;
+    bool neg[3], walking;
+    {
+        const float4 O = W.o[lane], Dd = W.d[lane];
+        const float o[3] = {O.x, O.y, O.z}, d[3] = {Dd.x, Dd.y, Dd.z};
+        float t1 = INFINITY, sum = 0.f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float x = (o[a] - v.org[a]) * v.inv_h, g = d[a] * v.inv_h;
+            neg[a] = g < 0.f;
+            og[a] = neg[a] ? v.dimf[a] - x : x;
+            dg[a] = fabsf(g);
+            ig[a] = dg[a] > 1e-30f ? __builtin_amdgcn_rcpf(dg[a]) : 1e30f;
+            te = fmaxf(te, -og[a] * ig[a]);
+            t1 = fminf(t1, (v.dimf[a] - og[a]) * ig[a]);
+            sum += fabsf(x) + dg[a];
+        }
+        walking = active && te <= t1 && sum < INFINITY;  // false for a non-finite ray
+#pragma unroll
+        for (int a = 0; a < 3; ++a) c[a] = clampf(floorf(fmaf(te, dg[a], og[a])), 0.f, v.dim1[a]);
+        const float t = __uint_as_float((uint32_t)(W.best[lane] >> 32));
+        ts = t + (t * 4e-6f + v.stop_pad);
+    }
+    const uint32_t oct = (neg[0] ? 1u : 0u) | (neg[1] ? 2u : 0u) | (neg[2] ? 4u : 0u);
+    const float r = v.rf, r1 = v.r1;
+    float plo[3] = {0.f, 0.f, 0.f}, lhi[3] = {0.f, 0.f, 0.f};  // the brick's low corner, its box's far faces (local)
+    uint32_t node = 0, cb = 0xFFFFFFFFu, mbase = 0;
+    uint64_t mask = 0;
+    bool inb = false;
+    while (ballot(walking)) {
+        if (STATS && lane == 0) ++cnt[ST_WAVE_DDA];
+        uint2 rg = make_uint2(0u, 0u);  // the leaf at c: its surfels are tested in this step
+        if (walking) {
+            if (STATS) ++cnt[ST_DDA];
+            float hi[3] = {c[0] + 1.f, c[1] + 1.f, c[2] + 1.f};
+            float l[3] = {c[0] - plo[0], c[1] - plo[1], c[2] - plo[2]};
+            if (TD < 0 || !inb || max3(l[0], l[1], l[2]) >= r) {
+                // the top cell holding c
+                float q[3];
+                uint32_t u[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    q[a] = TD < 0 ? c[a] : floorf(fmaf(c[a], v.tinv, v.thalf));
+                    u[a] = (uint32_t)(neg[a] ? v.tdim1[a] - q[a] : q[a]);
+                }
+                const uint2 T = v.top[top_index(v, u[0], u[1], u[2])];
+                if (STATS) {
+                    ++cnt[ST_NODES];
+                    cnt[ST_BYTES] += 8;
+                }
+                inb = false;
+                if ((int32_t)T.x < 0) {
+                    // empty: the box of (s + 1)^3 top cells onwards is empty
+                    const float s = (float)(((T.y >> (4u * oct)) & 15u) + 1u);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) hi[a] = (q[a] + s) * v.tspan;
+                } else if (TD < 0) {
+                    rg = v.rng[T.x];
+                    if (STATS) cnt[ST_BYTES] += 8;
+                } else {
+                    node = T.x;
+                    uint32_t box = T.y;
+                    bool found = true;
+                    if constexpr (TD > 0) {
+                        // down the brick levels between the top grid and the leaves' parents
+                        float pq[3] = {q[0], q[1], q[2]};
+#pragma unroll
+                        for (int i = 0; i < TD; ++i) {
+                            float qi[3];
+                            uint32_t w[3];
+#pragma unroll
+                            for (int a = 0; a < 3; ++a) {
+                                qi[a] = floorf(fmaf(c[a], v.minv[i], v.mhalf[i]));
+                                const float m = qi[a] - pq[a] * v.mratio[i];
+                                w[a] = (uint32_t)(neg[a] ? v.mratio[i] - 1.f - m : m);
+                            }
+                            if (found) {
+                                const uint32_t rr = (uint32_t)v.mratio[i];
+                                const uint32_t loc = w[0] + rr * (w[1] + rr * w[2]);
+                                const size_t wi = (size_t)node * v.mnw[i] + (loc >> 6);
+                                const uint64_t m = v.mmask[i][wi];
+                                if (STATS) {
+                                    ++cnt[ST_NODES];
+                                    cnt[ST_BYTES] += 12;
+                                }
+                                found = (m >> (loc & 63u)) & 1ull;
+                                node = v.mbase[i][wi] + (uint32_t)__popcll(m & ((uint64_t(1) << (loc & 63u)) - 1ull));
+                                if (!found) {
+#pragma unroll
+                                    for (int a = 0; a < 3; ++a) hi[a] = (qi[a] + 1.f) * v.mspan_f[i];
+                                }
+                            }
+#pragma unroll
+                            for (int a = 0; a < 3; ++a) {
+                                pq[a] = qi[a];
+                                q[a] = qi[a];
+                            }
+                        }
+                        if (found) box = v.pbox[node];
+                    }
+                    if (found) {
+                        // to the box of the brick's occupied leaves, or past the brick
+                        float tn = te, tf = INFINITY, b0[3], b1[3];
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            plo[a] = q[a] * r;
+                            // box in units of v.bunit leaves, mirrored with the ray
+                            const float x0 = (float)((box >> (5 * a)) & 31u) * v.bunit;
+                            const float x1 = fminf(fmaf((float)((box >> (15 + 5 * a)) & 31u), v.bunit, v.bunit), r);
+                            const float m0 = r - x1, m1 = r - x0;
+                            const float y0 = neg[a] ? m0 : x0;
+                            lhi[a] = neg[a] ? m1 : x1;
+                            b0[a] = plo[a] + y0;
+                            b1[a] = plo[a] + lhi[a];
+                            tn = fmaxf(tn, (b0[a] - og[a]) * ig[a]);
+                            tf = fminf(tf, (b1[a] - og[a]) * ig[a]);
+                        }
+                        if (tn > tf) {
+#pragma unroll
+                            for (int a = 0; a < 3; ++a) hi[a] = plo[a] + r;
+                        } else {
+                            inb = true;
+                            cb = 0xFFFFFFFFu;
+#pragma unroll
+                            for (int a = 0; a < 3; ++a) {
+                                const float n = floorf(fmaf(tn, dg[a], og[a]));
+                                c[a] = fmaxf(c[a], clampf(n, b0[a], b1[a] - 1.f));
+                                l[a] = c[a] - plo[a];
+                                hi[a] = c[a] + 1.f;
+                            }
+                        }
+                    }
+                }
+            }
+            if (TD >= 0 && inb) {
+                if (max3(l[0] - lhi[0], l[1] - lhi[1], l[2] - lhi[2]) >= 0.f) {
+                    // past the box on some axis: the rest of the brick ahead is empty
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) hi[a] = plo[a] + r;
+                    inb = false;
+                } else {
+                    uint32_t u[3];
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) u[a] = (uint32_t)(neg[a] ? r1 - l[a] : l[a]);
+                    const uint32_t B = (uint32_t)v.nblk;
+                    const uint32_t b = __umul24(__umul24(u[2] >> 2, B) + (u[1] >> 2), B) + (u[0] >> 2);
+                    if (b != cb) {
+                        const uint4 k = v.blk[(uint64_t)node * (uint32_t)v.nblk3 + b];
+                        cb = b;
+                        mask = ((uint64_t)k.y << 32) | k.x;
+                        mbase = k.z;
+                        if (STATS) {
+                            ++cnt[ST_NODES];
+                            cnt[ST_BYTES] += 16;
+                        }
+                    }
+                    const uint32_t bit = (u[0] & 3u) | ((u[1] & 3u) << 2) | ((u[2] & 3u) << 4);
+                    const uint64_t m = mask & ahead[64u * oct + bit];
+                    if (m == 0) {
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            const float lo4 = (float)(u[a] & ~3u);
+                            hi[a] = plo[a] + (neg[a] ? r - lo4 : fminf(lo4 + 4.f, r));
+                        }
+                    } else if ((mask >> bit) & 1ull) {
+                        rg = v.rng[mbase + (uint32_t)__popcll(mask & ((uint64_t(1) << bit) - 1ull))];
+                        if (STATS) cnt[ST_BYTES] += 8;
+                    } else if (STATS) {
+                        ++cnt[ST_EMPTY_LEAF];
+                    }
+                }
+            }
+            if (STATS && rg.y) {
+                ++cnt[ST_LEAVES];
+                cnt[ST_TESTS] += rg.y;
+                cnt[ST_BYTES] += 32ull * rg.y;
+            }
+            // leave the box [c, hi): the axis (or axes) left first move to hi
+            float ta[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) ta[a] = (hi[a] - og[a]) * ig[a];
+            te = min3(ta[0], ta[1], ta[2]);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float n = clampf(floorf(fmaf(te, dg[a], og[a])), c[a], hi[a] - 1.f);
+                c[a] = ta[a] <= te ? hi[a] : n;
+            }
+            walking = c[0] <= v.dim1[0] && c[1] <= v.dim1[1] && c[2] <= v.dim1[2];
+        }
+        const uint64_t at_leaf = ballot(rg.y != 0u);
+        if (at_leaf) {
+            if (STATS) {
+                // leaf visits in which every lane at a leaf is in the same one
+                const uint32_t lead = (uint32_t)__builtin_amdgcn_readlane((int)rg.x, __ffsll((long long)at_leaf) - 1);
+                if (rg.y && ballot(rg.y && rg.x == lead) == at_leaf) ++cnt[ST_UNIFORM];
+            }
+            leaf_tests<STATS>(v, W, rg, cnt);
+            const float t = __uint_as_float((uint32_t)(W.best[lane] >> 32));
+            const float before = ts;
+            ts = t + (t * 4e-6f + v.stop_pad);
+            if (ANY) walking = walking && !(ts < before);
+        }
+        walking = walking && te <= ts;  // no later cell holds a nearer hit
+    }
+}
+
+// The range of entries of leaf (x, y, z) (inside the grid; not mirrored), or
+// a count of 0 when it is empty.
+template <int TD>
+__device__ __forceinline__ uint2 leaf_range(const SceneView& v, int x, int y, int z) {
+    const float c[3] = {(float)x, (float)y, (float)z};
+    float q[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) q[a] = TD < 0 ? c[a] : floorf(fmaf(c[a], v.tinv, v.thalf));
+    const uint2 T = v.top[top_index(v, (uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2])];
+    if ((int32_t)T.x < 0) return make_uint2(0u, 0u);
+    if constexpr (TD < 0) return v.rng[T.x];
+    uint32_t node = T.x;
+    if constexpr (TD > 0) {
+#pragma unroll
+        for (int i = 0; i < TD; ++i) {
+            uint32_t w[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float qi = floorf(fmaf(c[a], v.minv[i], v.mhalf[i]));
+                w[a] = (uint32_t)(qi - q[a] * v.mratio[i]);
+                q[a] = qi;
+            }
+            const uint32_t rr = (uint32_t)v.mratio[i];
+            const uint32_t loc = w[0] + rr * (w[1] + rr * w[2]);
+            const size_t wi = (size_t)node * v.mnw[i] + (loc >> 6);
+            const uint64_t m = v.mmask[i][wi];
+            if (!((m >> (loc & 63u)) & 1ull)) return make_uint2(0u, 0u);
+            node = v.mbase[i][wi] + (uint32_t)__popcll(m & ((uint64_t(1) << (loc & 63u)) - 1ull));
+        }
+    }
+    uint32_t u[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) u[a] = (uint32_t)(c[a] - q[a] * v.rf);
+    const uint32_t B = (uint32_t)v.nblk;
+    const uint4 k = v.blk[(uint64_t)node * (uint32_t)v.nblk3 + ((u[2] >> 2) * B + (u[1] >> 2)) * B + (u[0] >> 2)];
+    const uint64_t mask = ((uint64_t)k.y << 32) | k.x;
+    const uint32_t bit = (u[0] & 3u) | ((u[1] & 3u) << 2) | ((u[2] & 3u) << 4);
+    if (!((mask >> bit) & 1ull)) return make_uint2(0u, 0u);
+    return v.rng[k.z + (uint32_t)__popcll(mask & ((uint64_t(1) << bit) - 1ull))];
+}
+
+__device__ __forceinline__ void stage_ray(WaveLds& W, const float o[3], const float d[3], uint32_t last,
+                                          float L = 0.f) {
+    const uint32_t lane = lane_id();
+    W.o[lane] = make_float4(o[0], o[1], o[2], __uint_as_float(last));
+    W.d[lane] = make_float4(d[0], d[1], d[2], L);
 }
 
 __device__ __forceinline__ void hit_reset(Hit& hit) {
@@ -332,298 +499,51 @@ __device__ __forceinline__ void hit_reset(Hit& hit) {
     hit.nx = hit.ny = hit.nz = 0.f;
 }
 
-// Whether local child coordinates (x, y, z) of a brick lie outside its box word.
-__device__ __forceinline__ bool box_outside(uint32_t box, int x, int y, int z) {
-    return x < (int)(box & 31u) || y < (int)((box >> 5) & 31u) || z < (int)((box >> 10) & 31u) ||
-           x > (int)((box >> 15) & 31u) || y > (int)((box >> 20) & 31u) || z > (int)((box >> 25) & 31u);
+// The launch arguments, read again from where they lie (the kernel's argument
+// segment, or a batch's query table): what the segment's end needs is loaded
+// after the walk instead of being held in scalar registers through it.
+typedef const TraceArgs __attribute__((address_space(4)))* ArgsPtr;
+// The same pointer on every lane, as scalar registers (arguments in device
+// memory are read by scalar loads then; nothing writes them in the kernel).
+__device__ __forceinline__ ArgsPtr uniform_args(const TraceArgs* p) {
+    const uint64_t x = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return (ArgsPtr)(((uint64_t)hi << 32) | lo);
 }
-
-// What the DDA found at the current cell: an occupied leaf (lvl == NL, its
-// node and entry range) or an empty cell of level lvl with the empty region
-// around it that the ray may skip.
-struct DdaCell {
-    uint32_t node;
-    uint2 range;    // entries of an occupied leaf
-    int skip;       // > 1: an empty cube of 2 skip - 1 units centred on the unit holding c
-    int oct;        // > 1: an empty box of oct leaves from c along the ray's octant; -1: an empty cell
-                    // of level lvl whose brick's occupied-children box is `node` (a box word)
-    int unit;       // edge of a skip unit in leaves (1, or a level-0 cell)
-    int lvl;        // level of the empty cell containing c, or NL for an occupied leaf
-};
-
-__device__ __forceinline__ void dda_cell_reset(DdaCell& k) {
-    k.node = 0;
-    k.range = make_uint2(0u, 0u);
-    k.skip = 1;
-    k.oct = 1;
-    k.unit = 1;
-    k.lvl = 0;
-}
-
-// Look the lane's current cell S.c up top-down through a hierarchy of NL
-// levels (NL == v.nlev).  Per lane; no cross-lane operations.
-template <bool STATS, int NL, bool BX = true>
-__device__ __forceinline__ void dda_locate(const SceneView& v, Seg& S, DdaCell& k, stat_t* cnt) {
-    constexpr int L = NL;
-    constexpr int P = L - 2;  // level of the leaves' parents (-1: single-level grid)
-    const int* c = S.c;
-    if constexpr (P < 0) {
-        const size_t i0 = (size_t)c[0] + (size_t)v.dim0[0] * ((size_t)c[1] + (size_t)v.dim0[1] * c[2]);
-        const int32_t n0 = v.map0[i0];
-        const int d0 = v.dist0 ? (int)v.dist0[i0] : 1;
-        if (STATS) {
-            ++cnt[ST_NODES];
-            cnt[ST_BYTES] += (n0 < 0 && v.dist0) ? 5 : 4;
-        }
-        k.lvl = (n0 < 0 || (uint32_t)n0 >= v.nn[0]) ? 0 : L;
-        k.node = (uint32_t)n0;
-        if (k.lvl == 0) k.skip = max(1, d0);
-        if (k.lvl == L) {
-            k.range = v.leaf[k.node];
-            if (STATS) cnt[ST_BYTES] += 8;
-        }
-    } else {
-        // the descent from level 0 runs only when the parent cell changes
-        const int q[3] = {span_div(c[0], v.mspan[P]), span_div(c[1], v.mspan[P]), span_div(c[2], v.mspan[P])};
-        if (q[0] != S.cq[0] || q[1] != S.cq[1] || q[2] != S.cq[2]) {
-            S.cq[0] = q[0];
-            S.cq[1] = q[1];
-            S.cq[2] = q[2];
-            S.cres = descend<STATS, P, BX>(v, c, S.cnode, S.cskip0, cnt, &S.cbox);
-        }
-        if (S.cres <= P) {
-            k.lvl = S.cres;
-            if (k.lvl == 0) {
-                // empty level-0 cell: the cube of radius cskip0 - 1 level-0 cells around it is empty
-                k.skip = max(1, S.cskip0);
-                k.unit = v.span[0];
-            } else if (BX && S.cbox != NO_BOX) {
-                // empty cell of a brick: the rest of the brick outside its box may be empty too
-                k.oct = -1;
-                k.node = S.cbox;
-            }
-        } else if (BX && S.cbox != NO_BOX && !v.cells &&
-                   box_outside(S.cbox, c[0] - v.ratio[P] * q[0], c[1] - v.ratio[P] * q[1],
-                               c[2] - v.ratio[P] * q[2])) {
-            // a leaf outside its parent brick's occupied box: empty, no lookup
-            k.lvl = L - 1;
-            k.oct = -1;
-            k.node = S.cbox;
-        } else if (v.cells) {
-            // one load: the leaf's entry range, or its skip radius
-            const int r = v.ratio[P];
-            const int loc = (c[0] - r * q[0]) + r * ((c[1] - r * q[1]) + r * (c[2] - r * q[2]));
-            const uint2 cl = v.cells[(size_t)S.cnode * (size_t)(r * r * r) + loc];
-            if (STATS) {
-                ++cnt[ST_NODES];
-                cnt[ST_BYTES] += 8;
-            }
-            if (cl.y) {
-                k.lvl = L;
-                k.range = cl;
-                k.node = cl.x;
-            } else {
-                // empty leaf: the box of oct cells from it along the ray's octant is empty
-                k.lvl = L - 1;
-                k.oct = (int)((cl.x >> S.oct_shift) & 15u);
-            }
-        } else {
-            const int r = v.ratio[P];
-            const int loc = (c[0] - r * q[0]) + r * ((c[1] - r * q[1]) + r * (c[2] - r * q[2]));
-            const size_t wi = (size_t)S.cnode * v.nw[P] + (loc >> 6);
-            // the mask word, the word's child base and the leaf's skip radius are
-            // loaded together (one memory round trip); only one of the last two is used
-            const uint64_t w = v.mask[P][wi];
-            const uint32_t wbase = v.base[P][wi];
-            const int ld = v.ldist ? (int)v.ldist[(size_t)S.cnode * (size_t)(r * r * r) + loc] : 1;
-            const uint64_t bit = uint64_t(1) << (loc & 63);
-            if (STATS) {
-                ++cnt[ST_NODES];
-                cnt[ST_BYTES] += (w & bit) ? 12 : (v.ldist ? 9 : 8);
-            }
-            k.lvl = L - 1;
-            if (w & bit) {
-                k.node = wbase + (uint32_t)__popcll(w & (bit - 1));
-                if (k.node < v.nn[L - 1]) {
-                    k.lvl = L;
-                    k.range = v.leaf[k.node];
-                    if (STATS) cnt[ST_BYTES] += 8;
-                }
-            } else {
-                // empty leaf: the whole cube of radius skip - 1 around it is empty
-                k.skip = max(1, ld);
-            }
-        }
-    }
-}
-
-// Move the lane past the cell (or empty region) `k` describes: S.c becomes
-// the next cell along the ray, and `te` the distance at which the ray enters
-// it.  Clears `walking` when the next cell starts beyond t_stop or the ray
-// leaves the grid.  Per lane; no cross-lane operations.
-template <int NL, bool BX = true>
-__device__ __forceinline__ void dda_advance(const SceneView& v, bool& walking, const float o[3], const float d[3],
-                                            Seg& S, const DdaCell& k, bool at_leaf, float t_stop, float& te) {
-    int* c = S.c;
-    const int Sz = at_leaf ? 1 : span_at<NL>(v, k.lvl);
-    // An empty cell of a brick with an occupied-children box: when the cell is
-    // outside the box along some axes, each such axis a bounds an empty slab
-    // of the brick (the brick cut at the box's face on a); the ray crosses the
-    // slab that it leaves last in one step.
-    // The slab along a ends at the box's near face when the ray moves towards
-    // the box, else at the brick's face; the ray leaves the slab at
-    // min(that face, T) with T its exit from the whole brick.
-    int slab = -1, bs = 0;
-    bool below = false;
-    if (BX && NL > 1 && k.oct < 0) {
-        const int us = span_at<NL>(v, k.lvl);
-        bs = span_at<NL>(v, k.lvl - 1);
-        const uint64_t um = mspan_at<NL>(v, k.lvl), bm = mspan_at<NL>(v, k.lvl - 1);
-        const uint32_t box = k.node;
-        float T = INFINITY;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int blo = span_div(c[a], bm) * bs;
-            if (d[a] != 0.f) T = fminf(T, ((float)(d[a] > 0.f ? blo + bs : blo) * v.h + v.org[a] - o[a]) * S.inv[a]);
-        }
-        float best = -INFINITY;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int blo = span_div(c[a], bm) * bs;
-            const int lc = span_div(c[a] - blo, um);
-            const int alo = (int)((box >> (5 * a)) & 31u), ahi = (int)((box >> (15 + 5 * a)) & 31u);
-            float t_a = T;
-            if (d[a] > 0.f && lc < alo) t_a = fminf(T, ((float)(blo + alo * us) * v.h + v.org[a] - o[a]) * S.inv[a]);
-            if (d[a] < 0.f && lc > ahi)
-                t_a = fminf(T, ((float)(blo + (ahi + 1) * us) * v.h + v.org[a] - o[a]) * S.inv[a]);
-            if ((lc < alo || lc > ahi) && t_a > best) {
-                best = t_a;
-                slab = a;
-                below = lc < alo;
-            }
-        }
-    }
-    // exit of the current cell (size Sz leaves)
-    int lo[3], hi[3];
-    te = INFINITY;
-    int axis = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (BX && slab >= 0) {
-            // the brick's range, cut at the box's face along the slab axis
-            lo[a] = span_div(c[a], mspan_at<NL>(v, k.lvl - 1)) * bs;
-            hi[a] = lo[a] + bs;
-            if (a == slab) {
-                const int us = span_at<NL>(v, k.lvl);
-                const int alo = (int)((k.node >> (5 * a)) & 31u), ahi = (int)((k.node >> (15 + 5 * a)) & 31u);
-                if (below)
-                    hi[a] = lo[a] + alo * us;
-                else
-                    lo[a] = lo[a] + (ahi + 1) * us;
-            }
-        } else if (k.oct > 1) {
-            // the octant box (inside its brick)
-            lo[a] = d[a] < 0.f ? c[a] - (k.oct - 1) : c[a];
-            hi[a] = d[a] < 0.f ? c[a] + 1 : c[a] + k.oct;
-        } else if (k.skip > 1) {
-            // the skip cube, clipped to the grid (beyond it the ray leaves)
-            const int uc = (k.unit == 1) ? c[a] : span_div(c[a], v.mspan[0]);
-            lo[a] = max((uc - (k.skip - 1)) * k.unit, 0);
-            hi[a] = min((uc + k.skip) * k.unit, v.dim[a]);
-        } else {
-            lo[a] = (Sz == 1) ? c[a] : span_div(c[a], mspan_at<NL>(v, k.lvl)) * Sz;
-            hi[a] = lo[a] + Sz;
-        }
-        float ta = INFINITY;
-        if (d[a] > 0.f)
-            ta = ((float)hi[a] * v.h + v.org[a] - o[a]) * S.inv[a];
-        else if (d[a] < 0.f)
-            ta = ((float)lo[a] * v.h + v.org[a] - o[a]) * S.inv[a];
-        if (ta < te) {
-            te = ta;
-            axis = a;
-        }
-    }
-    // next cell along the exit axis (selects, no dynamic indexing of private arrays)
-    int nc = 0, dim_ax = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        if (a == axis) {
-            nc = d[a] > 0.f ? hi[a] : lo[a] - 1;
-            dim_ax = v.dim[a];
-        }
-    const int max_iter = v.dim[0] + v.dim[1] + v.dim[2] + 8;
-    // no later cell can hold a nearer hit; or the ray leaves the grid
-    if (te > t_stop || nc < 0 || nc >= dim_ax || ++S.it >= max_iter) {
-        walking = false;
-    } else {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            if (a == axis) {
-                c[a] = nc;
-                continue;
-            }
-            const int sg = dir_step(d[a]);
-            if (sg == 0) continue;
-            int j = (int)floorf((o[a] + te * d[a] - v.org[a]) * v.inv_h);
-            j = min(max(j, lo[a]), hi[a] - 1);
-            j = sg > 0 ? max(j, c[a]) : min(j, c[a]);
-            c[a] = j;
-        }
-    }
-}
-
-// One DDA step of every walking lane through a hierarchy of NL levels
-// (NL == v.nlev): look the current cell up top-down, test an occupied leaf
-// (cooperatively, with the other lanes' leaves), then move to the next cell
-// or stop.  Called by every lane of the wave; `walking` is cleared when the
-// lane's segment ends.  The lane's ray must be staged in W.
-template <bool STATS, int NL, bool BX = true>
-__device__ __forceinline__ void dda_step(const SceneView& v, LeafTestLds& W, bool& walking, const float o[3],
-                                         const float d[3], Hit& hit, Seg& S, stat_t cnt[ST_COUNT]) {
-    constexpr int L = NL;
-    DdaCell k;
-    dda_cell_reset(k);
-    if (walking) dda_locate<STATS, NL, BX>(v, S, k, cnt);
-    const bool at_leaf = walking && k.lvl == L;
-    if (STATS) {
-        const uint64_t m_walk = __ballot(walking);
-        if (walking) {
-            ++cnt[ST_DDA];
-            if (k.lvl == L - 1 && L > 1) ++cnt[ST_EMPTY_LEAF];
-        }
-        // leaf visits where every lane of the wave still walking is in the same leaf
-        const uint64_t m_leaf = __ballot(at_leaf);
-        const int first = m_leaf ? __ffsll((long long)m_leaf) - 1 : 0;
-        const uint32_t lead = __shfl(k.node, first, 64);
-        if (at_leaf && __ballot(at_leaf && k.node == lead) == m_walk) ++cnt[ST_UNIFORM];
-        if (lane_id() == 0) ++cnt[ST_WAVE_DDA];
-    }
-    if (STATS && at_leaf) {
-        ++cnt[ST_LEAVES];
-        cnt[ST_TESTS] += k.range.y;
-        cnt[ST_BYTES] += 32ull * k.range.y;
-    }
-    if (__ballot(at_leaf && k.range.y != 0u)) leaf_tests<STATS>(v, W, at_leaf, k.range, hit, cnt);
-    if (walking) {
-        float te;
-        dda_advance<NL, BX>(v, walking, o, d, S, k, at_leaf, hit.t + (hit.t * 4e-6f + 1e-3f * v.h), te);
-    }
+// The arguments of a kernel whose first parameter is, or starts with, a
+// TraceArgs.
+__device__ __forceinline__ ArgsPtr kernel_args() { return (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); }
+__device__ __forceinline__ const TraceArgs& reread(ArgsPtr p) {
+    asm volatile("" : "+s"(p));
+    return *(const TraceArgs*)p;
 }
 
 // One whole segment of every active lane (lanes with `active` false only
 // help with the cooperative leaf tests) through the base hierarchy, or the
-// overlay when OVL.  The hierarchy is picked by a compile-time member, never
-// by a runtime reference: two such calls merged over a reference would keep
-// the whole argument struct in scratch memory.  Called by every lane of the
-// wave.
-template <bool STATS, int NL, bool OVL, bool BX = true>
-__device__ __forceinline__ void trace_segment(const TraceArgs& a, LeafTestLds& W, bool active, const float o[3],
-                                              const float d[3], Hit& hit, stat_t cnt[ST_COUNT]) {
+// overlay when OVL, from the staged ray and the nearest hit so far.  Called by
+// every lane of the wave.
+template <bool STATS, int TD, bool OVL, bool ANY = false>
+__device__ __forceinline__ void trace_segment(ArgsPtr args, const uint64_t* ahead, WaveLds& W, bool active, Hit& hit,
+                                              stat_t* cnt) {
+    const TraceArgs& a = reread(args);
     const SceneView& v = OVL ? a.ov : a.v;
-    Seg S;
-    bool walking = seg_begin(v, o, d, S) && active;
-    while (__ballot(walking)) dda_step<STATS, NL, BX>(v, W, walking, o, d, hit, S, cnt);
+    const uint32_t lane = lane_id();
+    const unsigned long long before = hit_word(hit.t, hit.id);
+    W.best[lane] = before;
+    wave_sync();
+    walk<STATS, TD, ANY>(v, ahead, W, active, cnt);
+    const unsigned long long b = W.best[lane];
+    if (active && b != before) {
+        const float4 N = v.snrm[W.entry[lane]];
+        hit.t = __uint_as_float((uint32_t)(b >> 32));
+        hit.id = (uint32_t)b;
+        hit.nx = N.x;
+        hit.ny = N.y;
+        hit.nz = N.z;
+        hit.lab = __float_as_uint(N.w);
+    }
+    wave_sync();
 }
 
 // Load slot i of bounce b: the ray, its global id, polyline length and the
@@ -756,9 +676,9 @@ __device__ __forceinline__ void finish_segment(const TraceArgs& a, int b, bool d
         const float qx = o[0] + hit.t * d[0], qy = o[1] + hit.t * d[1], qz = o[2] + hit.t * d[2];
         a.hist[(size_t)b * a.n_total + g] = make_float4(qx, qy, qz, __uint_as_float(hit.lab));
         L += hit.t;
-        const float dn = d[0] * hit.nx + d[1] * hit.ny + d[2] * hit.nz;
-        const float ex = d[0] - 2.f * dn * hit.nx, ey = d[1] - 2.f * dn * hit.ny, ez = d[2] - 2.f * dn * hit.nz;
-        const float inv = 1.0f / sqrtf(ex * ex + ey * ey + ez * ez);
+        const float dn2 = 2.f * fmaf(d[2], hit.nz, fmaf(d[1], hit.ny, d[0] * hit.nx));
+        const float ex = fmaf(-hit.nx, dn2, d[0]), ey = fmaf(-hit.ny, dn2, d[1]), ez = fmaf(-hit.nz, dn2, d[2]);
+        const float inv = 1.0f / sqrtf(fmaf(ez, ez, fmaf(ex, ex, ey * ey)));
         d[0] = ex * inv; d[1] = ey * inv; d[2] = ez * inv;
         o[0] = qx; o[1] = qy; o[2] = qz;
         last = hit.id;
@@ -791,27 +711,34 @@ __device__ __forceinline__ void finish_segment(const TraceArgs& a, int b, bool d
     }
 }
 
-// One wave's 64 consecutive slots [base, base + 64) of bounce b of one query,
-// traced in lockstep (base hierarchy, then the overlay).  Slots at or past
-// `range` are idle; a slot whose ray id is NO_HIT (left by an in-place
-// bounce) is idle too.  Every lane of the wave must call this (ballots).
-template <bool FIRST, bool STATS, int NL, bool OV, bool BX = true>
-__device__ __forceinline__ void trace_chunk(const TraceArgs& a, LeafTestLds& W, int b, uint32_t base, uint32_t range,
-                                            bool in_place, stat_t cnt[ST_COUNT]) {
+// `rpw` (1..64) consecutive slots from `base` of bounce b of one query, one
+// per lane, traced in lockstep (base hierarchy, then the overlay).  Slots at
+// or past `range` are idle; a slot whose ray id is NO_HIT (left by an
+// in-place bounce) is idle too.  Every lane of the wave must call this
+// (ballots).
+template <bool FIRST, bool STATS, int TD, bool OV>
+__device__ __forceinline__ void trace_chunk(ArgsPtr args, const uint64_t* ahead, WaveLds& W, int b, uint32_t base,
+                                            uint32_t rpw, uint32_t range, bool in_place, stat_t* cnt) {
     const uint32_t i = base + lane_id();
-    float o[3] = {0.f, 0.f, 0.f}, d[3] = {1.f, 0.f, 0.f};
-    float L = 0.f;
-    uint32_t last = NO_HIT, g = NO_HIT;
-    const bool act = i < range && load_ray<FIRST>(a, b, i, in_place, o, d, L, last, g);
+    bool act;
+    {
+        float o[3] = {0.f, 0.f, 0.f}, d[3] = {1.f, 0.f, 0.f}, L = 0.f;
+        uint32_t last = NO_HIT, g = NO_HIT;
+        act = lane_id() < rpw && i < range && load_ray<FIRST>(reread(args), b, i, in_place, o, d, L, last, g);
+        stage_ray(W, o, d, last, L);
+        W.g[lane_id()] = g;
+    }
     Hit hit;
     hit_reset(hit);
-    stage_ray(W, o, d, last);
-    trace_segment<STATS, NL, false, BX>(a, W, act, o, d, hit, cnt);
+    trace_segment<STATS, TD, false>(args, ahead, W, act, hit, cnt);
     // dynamic points: the nearest hit over base and overlay is the nearest
     // hit of the union (ties again by point id); the overlay shares the
     // base's frame and levels
-    if (OV) trace_segment<STATS, NL, true, BX>(a, W, act, o, d, hit, cnt);
-    finish_segment<FIRST, STATS>(a, b, act, in_place, i, g, o, d, L, last, hit, cnt);
+    if (OV) trace_segment<STATS, TD, true>(args, ahead, W, act, hit, cnt);
+    const float4 O = W.o[lane_id()], Dd = W.d[lane_id()];
+    float o[3] = {O.x, O.y, O.z}, d[3] = {Dd.x, Dd.y, Dd.z};
+    finish_segment<FIRST, STATS>(reread(args), b, act, in_place, i, W.g[lane_id()], o, d, Dd.w, __float_as_uint(O.w), hit,
+                                 cnt);
 }
 
 template <bool STATS>
@@ -823,15 +750,6 @@ __device__ __forceinline__ void flush_stats(stat_t cnt[ST_COUNT], unsigned long 
         if (stats && lane_id() == 0 && sum) atomicAdd(&stats[k], (unsigned long long)sum);
         cnt[k] = 0;
     }
-}
-
-// Renumber workgroups so that each of the 8 XCDs (workgroups are dispatched
-// round-robin over them: block b -> XCD b % 8) works on one contiguous range
-// of slots: neighbouring, coherent rays then share that XCD's L2.
-__device__ __forceinline__ uint32_t xcd_block() {
-    const uint32_t nb = gridDim.x, bx = blockIdx.x;
-    const uint32_t xcd = bx & 7u, per = nb >> 3, extra = nb & 7u;
-    return xcd * per + min(xcd, extra) + (bx >> 3);
 }
 
 // A launch whose segments end at the implicit surface of Eq. 1 instead of the
