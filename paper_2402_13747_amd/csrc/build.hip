@@ -782,6 +782,8 @@ static void set_top(SceneView& v) {
     const int r = P < 0 ? 1 : v.ratio[P];
     v.rf = (float)r;
     v.r1 = (float)(r - 1);
+    v.pinv = 1.0f / v.rf;
+    v.phalf = 0.5f / v.rf;
     v.bunit = r <= 32 ? 1.f : 2.f;
     v.nblk = (r + 3) / 4;
     v.nblk3 = v.nblk * v.nblk * v.nblk;

@@ -164,11 +164,11 @@ __device__ __forceinline__ float box_entry(const float o[3], const float u[3], c
 // IE table (Section 2.1)
 // ---------------------------------------------------------------------------
 
-__global__ void k_ie_keys(const float4* pos, const float4* nrm, uint32_t n, IeGrid g, uint64_t* key, uint32_t* id,
-                          uint32_t* bad) {
+// own: per point a pair (position, id bits), (unit normal, label bits).
+__global__ void k_ie_keys(const float4* own, uint32_t n, IeGrid g, uint64_t* key, uint32_t* id, uint32_t* bad) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float4 p = pos[i];
+    const float4 p = own[2 * (size_t)i];
     const float pc[3] = {p.x, p.y, p.z};
     int s[3];
     bool ok = true;
@@ -183,7 +183,7 @@ __global__ void k_ie_keys(const float4* pos, const float4* nrm, uint32_t n, IeGr
     const uint64_t vox = (uint64_t)(s[0] / dv) + (uint64_t)g.dims[0] * ((uint64_t)(s[1] / dv) +
                                                                        (uint64_t)g.dims[1] * (uint64_t)(s[2] / dv));
     const uint64_t loc = (uint64_t)(s[0] % dv) + (uint64_t)dv * ((uint64_t)(s[1] % dv) + (uint64_t)dv * (s[2] % dv));
-    key[i] = ((vox * (uint64_t)(dv * dv * dv) + loc) << 32) | (uint64_t)__float_as_uint(nrm[i].w);
+    key[i] = ((vox * (uint64_t)(dv * dv * dv) + loc) << 32) | (uint64_t)__float_as_uint(own[2 * (size_t)i + 1].w);
     id[i] = i;
 }
 
@@ -195,8 +195,8 @@ __global__ void k_ie_flags(const uint64_t* key, uint32_t n, uint32_t* flag) {
 
 // Per IE (one thread): its range of sorted points, the means in FP64.
 __global__ void k_ie_reduce(const uint64_t* key, const uint32_t* id, const uint32_t* scan, uint32_t n,
-                            const float4* pos, const float4* nrm, IeGrid g, uint32_t n_ie, uint64_t* ie_key,
-                            int32_t* sub, uint32_t* label, uint32_t* count, float4* ie_pos, float4* ie_nrm) {
+                            const float4* own, IeGrid g, uint32_t n_ie, uint64_t* ie_key, int32_t* sub,
+                            uint32_t* label, uint32_t* count, float4* ie_pos, float4* ie_nrm) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     if (!(i == 0 || key[i] != key[i - 1])) return;
@@ -205,8 +205,8 @@ __global__ void k_ie_reduce(const uint64_t* key, const uint32_t* id, const uint3
     uint32_t j = i;
     double px = 0, py = 0, pz = 0, nx = 0, ny = 0, nz = 0;
     for (; j < n && key[j] == key[i]; ++j) {
-        const float4 p = pos[id[j]];
-        const float4 q = nrm[id[j]];
+        const float4 p = own[2 * (size_t)id[j]];
+        const float4 q = own[2 * (size_t)id[j] + 1];
         px += p.x; py += p.y; pz += p.z;
         nx += q.x; ny += q.y; nz += q.z;
     }
@@ -998,7 +998,7 @@ static int ie_build_impl(PcrlScene* S, const PcrlIeGrid* params, hipStream_t s, 
             (rc = T.alloc(&bad, 1)))
             return fail(rc);
         if ((rc = fill_u32(bad, 0u, 1, s))) return fail(rc);
-        hipLaunchKernelGGL(k_ie_keys, dim3(blocks(n)), dim3(256), 0, s, S->own_pos, S->own_nrm, n, g, key, id, bad);
+        hipLaunchKernelGGL(k_ie_keys, dim3(blocks(n)), dim3(256), 0, s, S->own, n, g, key, id, bad);
         uint32_t h_bad = 0;
         if ((rc = read_u32(bad, &h_bad, s))) return fail(rc);
         if (h_bad) {
@@ -1018,7 +1018,7 @@ static int ie_build_impl(PcrlScene* S, const PcrlIeGrid* params, hipStream_t s, 
             (rc = I->bufs.alloc(&I->label, n_ie)) || (rc = I->bufs.alloc(&I->count, n_ie)) ||
             (rc = I->bufs.alloc(&I->pos, n_ie)) || (rc = I->bufs.alloc(&I->nrm, n_ie)))
             return fail(rc);
-        hipLaunchKernelGGL(k_ie_reduce, dim3(blocks(n)), dim3(256), 0, s, key, id, flag, n, S->own_pos, S->own_nrm, g,
+        hipLaunchKernelGGL(k_ie_reduce, dim3(blocks(n)), dim3(256), 0, s, key, id, flag, n, S->own, g,
                            n_ie, I->key, I->sub, I->label, I->count, I->pos, I->nrm);
         if ((rc = I->bufs.alloc(&I->type, n_ie)) || (rc = I->bufs.alloc(&I->eid, n_ie)) ||
             (rc = fill_u32(I->type, 0u, n_ie, s)) || (rc = fill_u32(I->eid, 0xFFFFFFFFu, n_ie, s)))

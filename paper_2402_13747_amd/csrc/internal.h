@@ -234,6 +234,7 @@ struct SceneView {
     float tdim1[3];                  // tdim - 1
     float stop_pad;                  // a walk ends this far (and 4e-6 t) beyond its nearest hit
     float tspan, tinv, thalf;        // leaves per top cell edge, 1 / that, 0.5 / that
+    float pinv, phalf;               // 1 / rf, 0.5 / rf
     float bunit;                     // unit of the parents' box words in leaves (1 up to ratio 32, else 2)
     int32_t nblk, nblk3;             // blocks per parent edge and per parent
     const uint2* top;                // per top cell: (node, box word of its occupied leaves when depth = 0), or
@@ -327,8 +328,10 @@ struct PcrlScene {
     std::mutex own_mu;
     pcrl::SceneView walk{};           // `view` with the structures of the implicit surface's leaf walk
     uint32_t* own_scan = nullptr;     // [n_entries + 1] own entries before each entry
-    float4* own_pos = nullptr;        // [n_points] positions (w: point id bits)
-    float4* own_nrm = nullptr;        // [n_points] unit normals (w: label bits)
+    float4* own = nullptr;            // [n_points] pairs: position (w: point id bits), unit normal (w: label bits)
+    float4* own_box = nullptr;        // [n_points] at a leaf's first own entry: centre of the box around its points
+    uint32_t* own_first = nullptr;    // [n_leaves + 1] own entries before each leaf
+    uint32_t* own_cells = nullptr;    // null, or own entries before each leaf cell (sdf.hip)
 };
 
 struct PcrlLaunch {
@@ -366,6 +369,6 @@ void destroy_launch(PcrlLaunch* L);
 void launch_brick_base(const uint64_t* mask, const uint32_t* first_child, int64_t n_nodes, int nw, uint32_t* base,
                        hipStream_t s);
 // Every static point once, in the leaf that holds its centre (built on first
-// use and kept with the scene; sdf.hip): scene->own_pos / own_nrm.
+// use and kept with the scene; sdf.hip): scene->own.
 int scene_own_index(PcrlScene* S, hipStream_t s);
 }

@@ -13,17 +13,20 @@
 // by h / 2 and compares no sign across that sample.  The ray's intersection is
 // the nearest over the leaves; its normal is n at the final sample.
 //
-// Lane = ray.  The leaves come from a hierarchical DDA
-// (sdf_walk.h), walked per lane; the walk stops once the next cell starts
-// more than 1.5 leaf diagonals beyond the nearest intersection found (no
-// later leaf's segment starts before that).  The neighbours of x are the
-// entries of the 27 leaves around x's leaf (h is at most 0.98 leaf edges)
-// whose centre lies in that leaf, so each point is counted once.
+// Lane = ray.  The leaves come from a hierarchical DDA (sdf_walk.h), walked per
+// lane; the walk stops once the next cell starts more than 1.5 leaf diagonals
+// beyond the nearest intersection found (no later leaf's segment starts before
+// that).  Every lane walks to its next sample, then the wave evaluates f for
+// all of them.  The neighbours of x are the points of the 27 leaves around x's
+// leaf (h is at most 0.98 leaf edges); each point is listed once, in the leaf
+// that holds its centre, so the leaves of a row along x lie next to each other
+// and a sample reads at most 9 such runs (18 across bricks).
 #include "sdf_walk.h"
 #include "trace_core.h"
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace pcrl {
 
@@ -31,18 +34,21 @@ constexpr int SDF_BLOCK = 64;  // one wave per block: the lanes finish unevenly,
 constexpr int64_t SDF_ORDER_MIN = 65536;  // rays from which a call sorts them into a coherent order
 
 struct SdfArgs {
-    SceneView v;
-    SceneView ov;          // v with leaf and cell ranges into the own entries (neighbour lookups)
+    SceneView v;           // the scene with its leaf-walk structures
     const float* o;        // [n][3]
     const float* d;        // [n][3]
     const float* tr;       // [n][2] (t_lo, t_hi), or null for (0, inf)
     const uint32_t* order; // null, or lane -> ray (a coherent order of the rays)
     const uint32_t* oscan; // [n_entries + 1] own entries before each entry of the hierarchy
-    const float4* opos;    // own entries (each point once, in the leaf of its centre), leaf order
-    const float4* onrm;
+    const float4* own;     // own entries (each point once, in the leaf of its centre, leaf order): pairs of
+                           // (position, id bits) and (unit normal, label bits)
+    const float4* lbox;    // [n_points] at the first own entry of a leaf: centre of the box around its own points
+    const uint32_t* first; // [n_leaves + 1] own entries before each leaf
+    const uint32_t* cells; // own entries before each cell: [parents][r^3 + 1], or [cells + 1] without parents
     uint32_t n;
     int32_t max_steps;
     float h2;              // h^2
+    float rh2;             // 1 / h2
     float hl2;             // (h / leaf edge + 1e-3)^2: leaves farther than this from x hold no neighbour
     float half_h;          // step over an undefined sample
     float eps;
@@ -56,115 +62,223 @@ struct SdfArgs {
     unsigned long long* stats;  // null, or [2]: evaluations of f, entries read
 };
 
-__device__ __forceinline__ bool in_leaf(const SceneView& v, const float4& P, const int cell[3]) {
-    return (int)floorf((P.x - v.org[0]) * v.inv_h) == cell[0] && (int)floorf((P.y - v.org[1]) * v.inv_h) == cell[1] &&
-           (int)floorf((P.z - v.org[2]) * v.inv_h) == cell[2];
+// a . b with the fused form written out (results must not depend on the
+// compiler's choice).
+__device__ __forceinline__ float dot3(float ax, float ay, float az, float bx, float by, float bz) {
+    return fmaf(az, bz, fmaf(ax, bx, ay * by));
 }
 
-// Accumulate the weighted sums of f(x) over the own entries [e0, e1) that
-// lie within h of x.  Four entries' positions are loaded before any is used
-// (more loads in flight per lane).
-__device__ __forceinline__ void sdf_accumulate(const SdfArgs& a, const float x[3], uint32_t e0, uint32_t e1,
-                                               float& sw, float sp[3], float sn[3]) {
-    const float h2 = a.h2;
-    uint32_t e = e0;
-    for (; e < e1; e += 4) {
-        float4 P[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) P[k] = a.opos[min(e + k, e1 - 1)];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float ex = P[k].x - x[0], ey = P[k].y - x[1], ez = P[k].z - x[2];
-            const float d2 = ex * ex + ey * ey + ez * ez;
-            if (e + k >= e1 || !(d2 < h2)) continue;
-            const float4 N = a.onrm[e + k];
-            float w = 1.0f - d2 / h2;
-            w *= w;
-            w *= w;
-            sw += w;
-            sp[0] += w * ex;
-            sp[1] += w * ey;
-            sp[2] += w * ez;
-            sn[0] += w * N.x;
-            sn[1] += w * N.y;
-            sn[2] += w * N.z;
-        }
-    }
+// The kernel's arguments (its first parameter is, or starts with, a SdfArgs),
+// read again where they are needed: holding all of them through the march
+// spilled 150 scalar registers.
+typedef const SdfArgs __attribute__((address_space(4)))* SdfArgsPtr;
+__device__ __forceinline__ const SdfArgs& reread_sdf() {
+    uint32_t zero;
+    asm volatile("s_mov_b32 %0, 0" : "=s"(zero));  // unknown to the compiler: the loads stay behind it
+    const char __attribute__((address_space(4)))* p =
+        (const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr() + zero;
+    return *(const SdfArgs*)(SdfArgsPtr)p;
 }
 
-// f(x) of Eq. 1 and the unit normal n(x); false where f is undefined.  The
-// offset p(x) - x is accumulated relative to x.  The 27 leaves are looked up
-// with the DDA's own cell lookup (the cell table where the scene has one),
-// whose descent is cached per parent cell: neighbouring leaves mostly share
-// their parent.
-template <int NL>
-__device__ __forceinline__ bool sdf_eval(const SdfArgs& a, const float x[3], float& f, float n[3], uint32_t& reads) {
+constexpr int SDF_RUNS = 18;  // (y, z) rows x the two bricks a row may cross
+typedef uint2 SdfRuns[SDF_RUNS][64];
+
+// Own entries before the position p of brick `node` (p < r^3): those of the
+// leaves before it.
+__device__ __forceinline__ uint32_t own_before(const SdfArgs& a, int P, uint32_t node, uint32_t p) {
+    const size_t w = (size_t)node * a.v.nw[P] + (p >> 6);
+    return a.first[a.v.base[P][w] + (uint32_t)__popcll(a.v.mask[P][w] & ((uint64_t(1) << (p & 63u)) - 1ull))];
+}
+
+// The runs of own entries of the up to 27 leaves around x that may hold a
+// point within h, in the order of the leaves (x fastest, then y, z): run s of
+// this lane in runs[s][lane] for every bit s of the result, [first, end).
+// NL voxel levels; FAST: bricks from the dense top grid and per-cell prefixes
+// (one load each); else by descent and the bricks' masks (scenes whose
+// prefixes would be too large).
+template <int NL, bool FAST>
+__device__ __forceinline__ uint32_t sdf_runs(const float x[3], SdfRuns& runs, uint32_t& reads) {
+    constexpr int P = NL - 2;
+    const SdfArgs& a = reread_sdf();
     const SceneView& v = a.v;
-    int lc[3];
-    float fr[3];  // position of x inside its leaf, in leaf edges
+    const uint32_t lane = lane_id();
+    int lc[3], ql[3], qh[3];   // x's cell; parents of the cells below and above it per axis
+    float g[3][3];             // squared distance (leaf edges) from x to the cells below, at and above
+    bool in[3][3];
+    const int r = P < 0 ? 1 : v.ratio[P < 0 ? 0 : P];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const float u = (x[k] - v.org[k]) * v.inv_h;
-        lc[k] = (int)floorf(u);
-        fr[k] = u - (float)lc[k];
+        const float f = floorf(u), fr = u - f;
+        lc[k] = (int)f;
+        g[k][0] = fr * fr;
+        g[k][1] = 0.f;
+        g[k][2] = (1.f - fr) * (1.f - fr);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) in[k][d] = lc[k] + d - 1 >= 0 && lc[k] + d - 1 < v.dim[k];
+        if (P >= 0) {
+            ql[k] = (int)floorf(fmaf(f - 1.f, v.pinv, v.phalf));
+            qh[k] = (int)floorf(fmaf(f + 1.f, v.pinv, v.phalf));
+        }
     }
+    uint32_t found = 0;
+    // per (z, y): the cells along x within reach
+    auto reach = [&](int dz, int dy, int& x0, int& x1) -> bool {
+        const float gyz = g[2][dz] + g[1][dy];
+        const bool c = in[0][1] && gyz < a.hl2;
+        const bool lo = in[0][0] && gyz + g[0][0] < a.hl2, hi = in[0][2] && gyz + g[0][2] < a.hl2;
+        x0 = lo ? -1 : (c ? 0 : 1);
+        x1 = hi ? 1 : (c ? 0 : -1);
+        return in[2][dz] && in[1][dy] && (lo || c || hi);
+    };
+    if constexpr (P < 0) {
+        uint2 e[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            int x0, x1;
+            e[q] = make_uint2(0u, 0u);
+            if (!reach(q / 3, q % 3, x0, x1)) continue;
+            const size_t p = (size_t)(lc[0] + x0) +
+                             (size_t)v.dim[0] * ((size_t)(lc[1] + q % 3 - 1) + (size_t)v.dim[1] * (lc[2] + q / 3 - 1));
+            e[q] = make_uint2(a.cells[p], a.cells[p + (x1 - x0 + 1)]);
+        }
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            if (e[q].x < e[q].y) {
+                runs[2 * q][lane] = e[q];
+                found |= 1u << (2 * q);
+                reads += e[q].y - e[q].x;
+            }
+        }
+    } else {
+        // the up to eight bricks around x
+        int32_t node[2][2][2];
+#pragma unroll
+        for (int iz = 0; iz < 2; ++iz)
+#pragma unroll
+            for (int iy = 0; iy < 2; ++iy)
+#pragma unroll
+                for (int ix = 0; ix < 2; ++ix) {
+                    const int q[3] = {ix ? qh[0] : ql[0], iy ? qh[1] : ql[1], iz ? qh[2] : ql[2]};
+                    int32_t n = -1;
+                    if (FAST) {
+                        if (q[0] >= 0 && q[1] >= 0 && q[2] >= 0 && q[0] < v.tdim[0] && q[1] < v.tdim[1] &&
+                            q[2] < v.tdim[2])
+                            n = (int32_t)v.top[(size_t)q[0] + (size_t)v.tdim[0] * (q[1] + v.tdim[1] * q[2])].x;
+                    } else {
+                        const int c[3] = {q[0] * r, q[1] * r, q[2] * r};
+                        uint32_t m = 0, box;
+                        int skip;
+                        if (q[0] >= 0 && q[1] >= 0 && q[2] >= 0 && c[0] < v.dim[0] && c[1] < v.dim[1] &&
+                            c[2] < v.dim[2] && descend<P>(v, c, m, skip, box) == P + 1)
+                            n = (int32_t)m;
+                    }
+                    node[iz][iy][ix] = n;
+                }
+        // runs of the rows' parts in the lower and (where a row crosses into it) the upper brick along x
+        const int bx = qh[0] * r - lc[0];  // the first cell (relative to x's) of the upper brick
+        const bool two = qh[0] != ql[0];
+        auto part_runs = [&](auto part_c, int32_t n00, int32_t n01, int32_t n10, int32_t n11) {
+            constexpr int part = decltype(part_c)::value;
+            uint2 e[9];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                const int dz = q / 3, dy = q % 3;
+                int x0, x1;
+                e[q] = make_uint2(0u, 0u);
+                if (!reach(dz, dy, x0, x1)) continue;
+                const int cz = lc[2] + dz - 1, cy = lc[1] + dy - 1;
+                const bool hz = cz >= qh[2] * r, hy = cy >= qh[1] * r;
+                const int32_t ny = hy ? n01 : n00, nz = hy ? n11 : n10, n = hz ? nz : ny;
+                if (two) {
+                    if (part == 0) x1 = min(x1, bx - 1);
+                    else x0 = max(x0, bx);
+                } else if (part == 1) {
+                    continue;
+                }
+                if (n < 0 || x0 > x1) continue;
+                const int lz = cz - (hz ? qh[2] : ql[2]) * r, ly = cy - (hy ? qh[1] : ql[1]) * r;
+                const int lx = lc[0] + x0 - (part ? qh[0] : ql[0]) * r;
+                const uint32_t p = (uint32_t)(lx + r * (ly + r * lz));
+                const uint32_t len = (uint32_t)(x1 - x0 + 1);
+                if (FAST) {
+                    const uint32_t* c = a.cells + (uint64_t)(uint32_t)n * (uint32_t)(r * r * r + 1) + p;
+                    e[q] = make_uint2(c[0], c[len]);
+                } else {
+                    const uint32_t l = p + len - 1;
+                    const size_t w = (size_t)n * v.nw[P] + (l >> 6);
+                    const uint32_t last = v.base[P][w] + (uint32_t)__popcll(v.mask[P][w] & (~0ull >> (63u - (l & 63u))));
+                    e[q] = make_uint2(own_before(a, P, (uint32_t)n, p), a.first[last]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                if (e[q].x < e[q].y) {
+                    runs[2 * q + part][lane] = e[q];
+                    found |= 1u << (2 * q + part);
+                    reads += e[q].y - e[q].x;
+                }
+            }
+        };
+        part_runs(std::integral_constant<int, 0>{}, node[0][0][0], node[0][1][0], node[1][0][0], node[1][1][0]);
+        if (__ballot(two))
+            part_runs(std::integral_constant<int, 1>{}, node[0][0][1], node[0][1][1], node[1][0][1], node[1][1][1]);
+    }
+    return found;
+}
+
+// f(x) of Eq. 1 and the unit normal n(x); false where f is undefined.  The
+// offset p(x) - x is accumulated relative to x.  Four points (32 bytes each)
+// are loaded before any is used.
+template <int NL, bool FAST>
+__device__ __forceinline__ bool sdf_eval(const float x[3], SdfRuns& runs, float& f, float n[3], uint32_t& reads) {
+    const uint32_t lane = lane_id();
+    uint32_t todo = sdf_runs<NL, FAST>(x, runs, reads);
+    const SdfArgs& a = reread_sdf();
     float sw = 0.f, sp[3] = {0.f, 0.f, 0.f}, sn[3] = {0.f, 0.f, 0.f};
-    Seg N;
-    N.cq[0] = N.cq[1] = N.cq[2] = -1;
-    N.cres = 0;
-    N.cskip0 = 1;
-    N.cbox = NO_BOX;
-    N.cnode = 0;
-    N.oct_shift = 0;
-    // one rolled loop over the 27 leaves (unrolled, the lookups would multiply the registers)
-#pragma unroll 1
-    for (int q = 0; q < 27; ++q) {
-        const int dx = q % 3 - 1, dy = (q / 3) % 3 - 1, dz = q / 9 - 1;
-        // distance (in leaf edges) from x to the neighbour leaf: skip leaves beyond h
-        const float gx = dx < 0 ? fr[0] : (dx > 0 ? 1.f - fr[0] : 0.f);
-        const float gy = dy < 0 ? fr[1] : (dy > 0 ? 1.f - fr[1] : 0.f);
-        const float gz = dz < 0 ? fr[2] : (dz > 0 ? 1.f - fr[2] : 0.f);
-        if (gx * gx + gy * gy + gz * gz >= a.hl2) continue;
-        N.c[0] = lc[0] + dx;
-        N.c[1] = lc[1] + dy;
-        N.c[2] = lc[2] + dz;
-        if (N.c[0] < 0 || N.c[1] < 0 || N.c[2] < 0 || N.c[0] >= v.dim[0] || N.c[1] >= v.dim[1] ||
-            N.c[2] >= v.dim[2])
-            continue;
-        DdaCell k;
-        dda_cell_reset(k);
-        dda_locate<NL>(a.ov, N, k);
-        if (k.lvl != NL || k.range.y == 0u) continue;
-        reads += k.range.y;
-        sdf_accumulate(a, x, k.range.x, k.range.x + k.range.y, sw, sp, sn);
+    uint32_t e = 0, end = 0;
+    for (;;) {
+        if (e >= end) {
+            if (!todo) break;
+            const uint2 run = runs[__ffs((int)todo) - 1][lane];
+            todo &= todo - 1u;
+            e = run.x;
+            end = run.y;
+        }
+        float4 Q[4], N[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float4* r = a.own + 2 * (size_t)min(e + k, end - 1u);
+            Q[k] = r[0];
+            N[k] = r[1];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float ex = Q[k].x - x[0], ey = Q[k].y - x[1], ez = Q[k].z - x[2];
+            const float d2 = dot3(ex, ey, ez, ex, ey, ez);
+            if (e + k < end && d2 < a.h2) {
+                // d2 / h2, correctly rounded (rh2 is the correctly rounded reciprocal)
+                const float q = d2 * a.rh2;
+                const float u = 1.0f - fmaf(fmaf(-q, a.h2, d2), a.rh2, q);
+                const float u2 = u * u, w = u2 * u2;
+                sw = fmaf(u2, u2, sw);
+                sp[0] = fmaf(ex, w, sp[0]);
+                sp[1] = fmaf(ey, w, sp[1]);
+                sp[2] = fmaf(ez, w, sp[2]);
+                sn[0] = fmaf(w, N[k].x, sn[0]);
+                sn[1] = fmaf(w, N[k].y, sn[1]);
+                sn[2] = fmaf(w, N[k].z, sn[2]);
+            }
+        }
+        e += 4;
     }
-    const float ln = sqrtf(sn[0] * sn[0] + sn[1] * sn[1] + sn[2] * sn[2]);
+    const float ln = sqrtf(dot3(sn[0], sn[1], sn[2], sn[0], sn[1], sn[2]));
     if (!(sw > 0.f) || !(ln > 0.f)) return false;
     const float inv = 1.0f / ln;
     n[0] = sn[0] * inv;
     n[1] = sn[1] * inv;
     n[2] = sn[2] * inv;
-    f = -(sp[0] * n[0] + sp[1] * n[1] + sp[2] * n[2]) / sw;
-    return true;
-}
-
-// Centre of the box around the own entries [e0, e1) of a leaf; false when
-// there is none.
-__device__ __forceinline__ bool own_box_centre(const SdfArgs& a, uint32_t e0, uint32_t e1, float c[3]) {
-    float lo0 = INFINITY, lo1 = INFINITY, lo2 = INFINITY, hi0 = -INFINITY, hi1 = -INFINITY, hi2 = -INFINITY;
-    for (uint32_t e = e0; e < e1; ++e) {
-        const float4 P = a.opos[e];
-        lo0 = fminf(lo0, P.x);
-        lo1 = fminf(lo1, P.y);
-        lo2 = fminf(lo2, P.z);
-        hi0 = fmaxf(hi0, P.x);
-        hi1 = fmaxf(hi1, P.y);
-        hi2 = fmaxf(hi2, P.z);
-    }
-    if (!(e0 < e1)) return false;
-    c[0] = 0.5f * (lo0 + hi0);
-    c[1] = 0.5f * (lo1 + hi1);
-    c[2] = 0.5f * (lo2 + hi2);
+    f = -dot3(sp[0], sp[1], sp[2], n[0], n[1], n[2]) / sw;
     return true;
 }
 
@@ -196,14 +310,53 @@ __global__ void k_own_flags(SceneView v, uint32_t m, uint32_t* flag) {
 }
 
 // Copy the own entries to their compacted slots.
-__global__ void k_own_scatter(const float4* spos, const float4* snrm, const uint32_t* scan, uint32_t m,
-                              uint32_t cap, float4* opos, float4* onrm) {
+__global__ void k_own_scatter(const float4* spos, const float4* snrm, const uint32_t* scan, uint32_t m, uint32_t cap,
+                              float4* own) {
     const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const uint32_t j = scan[e];
     if (scan[e + 1] == j || j >= cap) return;
-    opos[j] = spos[e];
-    onrm[j] = snrm[e];
+    own[2 * (size_t)j] = spos[e];
+    own[2 * (size_t)j + 1] = snrm[e];
+}
+
+// Own entries before each leaf, and the centre of the box around each leaf's
+// own points (at its first own entry).
+__global__ void k_own_leaves(const uint2* leaf, uint32_t n, const uint32_t* scan, const float4* own, uint32_t* first,
+                             float4* lbox, uint32_t* single, const uint64_t* leaf_key) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const uint2 r = leaf[i];
+    const uint32_t e0 = scan[r.x], e1 = scan[r.x + r.y];
+    first[i] = e0;
+    if (i == n - 1) first[n] = e1;
+    if (single) single[leaf_key[i]] = e1 - e0;
+    if (!(e0 < e1)) return;
+    float lo0 = INFINITY, lo1 = INFINITY, lo2 = INFINITY, hi0 = -INFINITY, hi1 = -INFINITY, hi2 = -INFINITY;
+    for (uint32_t e = e0; e < e1; ++e) {
+        const float4 q = own[2 * (size_t)e];
+        lo0 = fminf(lo0, q.x);
+        lo1 = fminf(lo1, q.y);
+        lo2 = fminf(lo2, q.z);
+        hi0 = fmaxf(hi0, q.x);
+        hi1 = fmaxf(hi1, q.y);
+        hi2 = fmaxf(hi2, q.z);
+    }
+    lbox[e0] = make_float4(0.5f * (lo0 + hi0), 0.5f * (lo1 + hi1), 0.5f * (lo2 + hi2), 0.f);
+}
+
+// Own entries before each cell of every leaves' parent ([n3 + 1] per parent).
+__global__ void k_own_cells(const uint64_t* mask, const uint32_t* base, const uint32_t* first, int nw, uint32_t n3,
+                            uint64_t n, uint32_t* cells) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const uint64_t P = i / (n3 + 1);
+    const uint32_t p = (uint32_t)(i - P * (n3 + 1));
+    // the end of a brick is counted from its last cell
+    const uint32_t c = min(p, n3 - 1);
+    const size_t w = (size_t)P * nw + (c >> 6);
+    const uint64_t below = p < n3 ? (uint64_t(1) << (c & 63u)) - 1ull : ~0ull >> (63u - (c & 63u));
+    cells[i] = first[base[w] + (uint32_t)__popcll(mask[w] & below)];
 }
 
 // 8 bits spread to the even bits of 16.
@@ -243,208 +396,236 @@ __global__ void k_sdf_keys(const float* o, const float* d, uint32_t n, float3 lo
     idx[j] = j;
 }
 
-template <int NL>
-__device__ __forceinline__ void sdf_first_hit(const SdfArgs& a, const float o[3], const float d[3], float t_lo,
-                                              float t_hi, float& best, float bn[3], int bc[3], uint32_t& evals,
-                                              uint32_t& reads) {
-    const SceneView& v = a.v;
-    best = INFINITY;
-    bn[0] = bn[1] = bn[2] = 0.f;
-    bc[0] = bc[1] = bc[2] = -1;
-    Seg S;
-    bool walking = !a.empty && t_lo <= t_hi && seg_begin(v, o, d, S);
-    float t_in = 0.f;  // where the ray enters the current cell
-    if (walking) {
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            float tf = -INFINITY;
-            if (d[ax] > 0.f) tf = ((float)S.c[ax] * v.h + v.org[ax] - o[ax]) * S.inv[ax];
-            else if (d[ax] < 0.f) tf = ((float)(S.c[ax] + 1) * v.h + v.org[ax] - o[ax]) * S.inv[ax];
-            t_in = fmaxf(t_in, tf);
+// Id and label of the point nearest to x among those within h (smallest
+// distance, then smallest id); false if none.
+template <int NL, bool FAST>
+__device__ __forceinline__ bool nearest_own(const float x[3], SdfRuns& runs, uint32_t& id, uint32_t& label) {
+    const uint32_t lane = lane_id();
+    uint32_t reads = 0;
+    uint32_t todo = sdf_runs<NL, FAST>(x, runs, reads);
+    const SdfArgs& a = reread_sdf();
+    float bd = a.h2;
+    uint32_t best = 0;
+    bool found = false;
+    while (todo) {
+        const uint2 run = runs[__ffs((int)todo) - 1][lane];
+        todo &= todo - 1u;
+        for (uint32_t e = run.x; e < run.y; ++e) {
+            const float4 Q = a.own[2 * (size_t)e];
+            const float ex = Q.x - x[0], ey = Q.y - x[1], ez = Q.z - x[2];
+            const float d2 = dot3(ex, ey, ez, ex, ey, ez);
+            const uint32_t pid = __float_as_uint(Q.w);
+            if (d2 < bd || (d2 == bd && found && pid < id)) {
+                bd = d2;
+                id = pid;
+                best = e;
+                found = true;
+            }
         }
     }
+    if (found) label = __float_as_uint(a.own[2 * (size_t)best + 1].w);
+    return found;
+}
+
+// One lane's march: the leaf walk, the march of the current leaf, and the
+// nearest intersection so far.
+struct SdfMarch {
+    Seg S;
+    float t_in;           // where the ray enters the current cell
+    float best, bn[3];
+    int bc[3];
+    // the current leaf's march
+    float t, tb, fp, tp;
+    int s;
+    bool in_leaf, shared, prev, stop;
     // Every leaf whose segment starts at or before t_lo marches from t_lo: the
     // same samples, cut at different far ends.  One shared march serves them
     // all: a leaf whose far end it has already passed, or after it found an
     // intersection or stopped (step limit, nothing nearer possible), adds
     // nothing; a leaf reaching further resumes it.  Exact: the nearest over
     // these leaves is unchanged.
-    float c_t = t_lo, c_fp = 0.f, c_tp = 0.f, c_tb = -INFINITY;
-    bool c_prev = false, c_done = false;
-    int c_s = 0;
-    while (walking) {
-        DdaCell k;
-        dda_cell_reset(k);
-        dda_locate<NL>(v, S, k);
-        const bool at_leaf = k.lvl == NL;
-        float c[3];
-        uint32_t o0 = 0u, o1 = 0u;
-        if (at_leaf && t_in <= t_hi) {
-            o0 = a.oscan[k.range.x];
-            o1 = a.oscan[k.range.x + k.range.y];
-        }
-        if (at_leaf && t_in <= t_hi && own_box_centre(a, o0, o1, c)) {
-            reads += o1 - o0;
-            const float tc = (c[0] - o[0]) * d[0] + (c[1] - o[1]) * d[1] + (c[2] - o[2]) * d[2];
-            const bool shared = tc - a.half_diam <= t_lo;
-            float t = fmaxf(tc - a.half_diam, t_lo);
-            const float tb = fminf(tc + a.half_diam, t_hi);
-            float fp = 0.f, tp = 0.f;
-            bool prev = false;
-            int s = 0;
-            bool stop = false;  // the march ended by an intersection, the step limit or `best`
-            if (shared) {
-                if (c_done || tb <= c_tb) s = a.max_steps;  // nothing new from this leaf
-                t = c_t;
-                fp = c_fp;
-                tp = c_tp;
-                prev = c_prev;
-                if (s < a.max_steps) s = c_s;
-            }
-            for (; s < a.max_steps && t <= tb; ++s) {
-                // every later result of this leaf lies at or beyond t
-                if (t >= best && !(prev && tp < best)) {
-                    stop = true;
-                    break;
-                }
-                const float x[3] = {o[0] + t * d[0], o[1] + t * d[1], o[2] + t * d[2]};
-                float f, n[3];
-                ++evals;
-                if (!sdf_eval<NL>(a, x, f, n, reads)) {
-                    prev = false;
-                    t += a.half_h;
-                    continue;
-                }
-                float th = t;
-                bool found = fabsf(f) <= a.eps;
-                if (!found && prev && ((f < 0.f) != (fp < 0.f))) {
-                    th = tp + (t - tp) * fp / (fp - f);
-                    found = true;
-                }
-                if (found) {
-                    if (th < best) {
-                        best = th;
-                        bn[0] = n[0];
-                        bn[1] = n[1];
-                        bn[2] = n[2];
-                        bc[0] = S.c[0];
-                        bc[1] = S.c[1];
-                        bc[2] = S.c[2];
-                    }
-                    stop = true;
-                    break;
-                }
-                prev = true;
-                fp = f;
-                tp = t;
-                t += fabsf(f);
-            }
-            if (shared && !c_done && tb > c_tb) {
-                c_t = t;
-                c_fp = fp;
-                c_tp = tp;
-                c_prev = prev;
-                c_s = s;
-                c_tb = tb;
-                c_done = stop || s >= a.max_steps;
-            }
-        }
-        float te;
-        dda_advance<NL>(v, walking, o, d, S, k, at_leaf, fminf(best + a.reach, t_hi), te);
-        t_in = te;
+    float c_t, c_fp, c_tp, c_tb;
+    int c_s;
+    bool c_prev, c_done;
+};
+
+// Start the march of the ray (o, d) from t_lo; false when it meets no cell.
+__device__ __forceinline__ bool march_begin(SdfMarch& M, const float o[3], const float d[3], float t_lo, float t_hi) {
+    const SdfArgs& a = reread_sdf();
+    const SceneView& v = a.v;
+    M.best = INFINITY;
+    M.bn[0] = M.bn[1] = M.bn[2] = 0.f;
+    M.bc[0] = M.bc[1] = M.bc[2] = -1;
+    M.in_leaf = false;
+    M.c_t = t_lo;
+    M.c_fp = M.c_tp = 0.f;
+    M.c_tb = -INFINITY;
+    M.c_s = 0;
+    M.c_prev = M.c_done = false;
+    M.t_in = 0.f;
+    if (a.empty || !(t_lo <= t_hi) || !seg_begin(v, o, d, M.S)) return false;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        float tf = -INFINITY;
+        if (d[ax] > 0.f) tf = (fmaf((float)M.S.c[ax], v.h, v.org[ax]) - o[ax]) * M.S.inv[ax];
+        else if (d[ax] < 0.f) tf = (fmaf((float)(M.S.c[ax] + 1), v.h, v.org[ax]) - o[ax]) * M.S.inv[ax];
+        M.t_in = fmaxf(M.t_in, tf);
     }
+    return true;
 }
 
+// Move a lane on to its next sample (at M.t) or to the end of its walk
+// (`walking` false): one step of the leaf walk or one turn of the leaf's
+// march.  Returns true when a sample is to be evaluated.
 template <int NL>
+__device__ __forceinline__ bool march_next(const SdfArgs& a, SdfMarch& M, bool& walking, const float o[3],
+                                           const float d[3], float t_lo, float t_hi, uint32_t& reads) {
+    const SceneView& v = a.v;
+    DdaCell k;
+    dda_cell_reset(k);
+    bool at_leaf = true;
+    if (!M.in_leaf) {
+        dda_locate<NL>(v, M.S, k);
+        at_leaf = k.lvl == NL;
+        if (at_leaf && M.t_in <= t_hi) {
+            const uint32_t o0 = a.oscan[k.range.x], o1 = a.oscan[k.range.x + k.range.y];
+            if (o0 < o1) {
+                reads += o1 - o0;
+                const float4 c = a.lbox[o0];
+                const float tc = dot3(c.x - o[0], c.y - o[1], c.z - o[2], d[0], d[1], d[2]);
+                M.in_leaf = true;
+                M.stop = false;
+                M.shared = tc - a.half_diam <= t_lo;
+                M.t = fmaxf(tc - a.half_diam, t_lo);
+                M.tb = fminf(tc + a.half_diam, t_hi);
+                M.fp = M.tp = 0.f;
+                M.prev = false;
+                M.s = 0;
+                if (M.shared) {
+                    const bool old = M.c_done || M.tb <= M.c_tb;  // nothing new from this leaf
+                    M.s = old ? a.max_steps : M.c_s;
+                    M.t = M.c_t;
+                    M.fp = M.c_fp;
+                    M.tp = M.c_tp;
+                    M.prev = M.c_prev;
+                }
+            }
+        }
+    }
+    if (M.in_leaf) {
+        if (!M.stop && M.s < a.max_steps && M.t <= M.tb) {
+            // every later result of this leaf lies at or beyond t
+            if (!(M.t >= M.best && !(M.prev && M.tp < M.best))) return true;
+            M.stop = true;
+        }
+        if (M.shared && !M.c_done && M.tb > M.c_tb) {
+            M.c_t = M.t;
+            M.c_fp = M.fp;
+            M.c_tp = M.tp;
+            M.c_prev = M.prev;
+            M.c_s = M.s;
+            M.c_tb = M.tb;
+            M.c_done = M.stop || M.s >= a.max_steps;
+        }
+        M.in_leaf = false;
+    }
+    float te;
+    dda_advance<NL>(v, walking, o, d, M.S, k, at_leaf, fminf(M.best + a.reach, t_hi), te);
+    M.t_in = te;
+    return false;
+}
+
+// Evaluate f at the lane's sample and move its march on.
+template <int NL, bool FAST>
+__device__ __forceinline__ void march_sample(SdfMarch& M, SdfRuns& runs, const float o[3], const float d[3],
+                                             uint32_t& reads) {
+    const float t = M.t;
+    const float x[3] = {fmaf(t, d[0], o[0]), fmaf(t, d[1], o[1]), fmaf(t, d[2], o[2])};
+    float f, n[3];
+    const bool defined = sdf_eval<NL, FAST>(x, runs, f, n, reads);
+    const SdfArgs& a = reread_sdf();
+    if (!defined) {
+        M.prev = false;
+        M.t = t + a.half_h;
+        ++M.s;
+        return;
+    }
+    float th = t;
+    bool found = fabsf(f) <= a.eps;
+    if (!found && M.prev && ((f < 0.f) != (M.fp < 0.f))) {
+        th = M.tp + (t - M.tp) * M.fp / (M.fp - f);
+        found = true;
+    }
+    if (found) {
+        if (th < M.best) {
+            M.best = th;
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                M.bn[ax] = n[ax];
+                M.bc[ax] = M.S.c[ax];
+            }
+        }
+        M.stop = true;
+        return;
+    }
+    M.prev = true;
+    M.fp = f;
+    M.tp = t;
+    M.t = t + fabsf(f);
+    ++M.s;
+}
+
+template <int NL, bool FAST>
 __global__ __launch_bounds__(SDF_BLOCK) void k_sdf(SdfArgs a) {
+    __shared__ SdfRuns runs;
     const uint32_t lane_ray = blockIdx.x * SDF_BLOCK + threadIdx.x;
-    if (lane_ray >= a.n) return;
-    const uint32_t i = a.order ? a.order[lane_ray] : lane_ray;
+    const bool in = lane_ray < a.n;
+    const uint32_t i = !in ? 0u : a.order ? a.order[lane_ray] : lane_ray;
     const size_t i3 = 3 * (size_t)i, i2 = 2 * (size_t)i;  // n may exceed 2^32 / 3
     const float o[3] = {a.o[i3], a.o[i3 + 1], a.o[i3 + 2]};
     float d[3] = {a.d[i3], a.d[i3 + 1], a.d[i3 + 2]};
     const float t_lo = a.tr ? a.tr[i2] : 0.f;
     const float t_hi = a.tr ? a.tr[i2 + 1] : INFINITY;
-    const float len = sqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-    const bool ok = len > 0.f && isfinite(len) && isfinite(o[0]) && isfinite(o[1]) && isfinite(o[2]);
-    float best = INFINITY, bn[3] = {0.f, 0.f, 0.f};
-    int bc[3] = {-1, -1, -1};
+    const float len = sqrtf(dot3(d[0], d[1], d[2], d[0], d[1], d[2]));
+    const bool ok = in && len > 0.f && isfinite(len) && isfinite(o[0]) && isfinite(o[1]) && isfinite(o[2]);
     uint32_t evals = 0, reads = 0;
+    SdfMarch M;
+    M.best = INFINITY;
+    M.bn[0] = M.bn[1] = M.bn[2] = 0.f;
+    M.bc[0] = M.bc[1] = M.bc[2] = -1;
+    bool walking = false;
     if (ok) {
         const float il = 1.0f / len;
         d[0] *= il;
         d[1] *= il;
         d[2] *= il;
-        sdf_first_hit<NL>(a, o, d, t_lo, t_hi, best, bn, bc, evals, reads);
+        walking = march_begin(M, o, d, t_lo, t_hi);
     }
-    a.t[i] = best;
-    const bool hit = bc[0] >= 0;
+    for (;;) {
+        bool want = false;
+        {
+            const SdfArgs& w = reread_sdf();
+            while (walking && !want) want = march_next<NL>(w, M, walking, o, d, t_lo, t_hi, reads);
+        }
+        if (!__ballot(want)) break;
+        if (want) {
+            ++evals;
+            march_sample<NL, FAST>(M, runs, o, d, reads);
+        }
+    }
+    if (!in) return;
+    a.t[i] = M.best;
+    const bool hit = M.bc[0] >= 0;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        a.pt[i3 + ax] = hit ? o[ax] + best * d[ax] : NAN;
-        a.nrm[i3 + ax] = bn[ax];
-        if (a.cell) a.cell[i3 + ax] = bc[ax];
+        a.pt[i3 + ax] = hit ? fmaf(M.best, d[ax], o[ax]) : NAN;
+        a.nrm[i3 + ax] = M.bn[ax];
+        if (a.cell) a.cell[i3 + ax] = M.bc[ax];
     }
     if (a.stats) {
         atomicAdd(&a.stats[0], (unsigned long long)evals);
         atomicAdd(&a.stats[1], (unsigned long long)reads);
     }
-}
-
-// Id and label of the point nearest to x among those within h (smallest
-// distance, then smallest id); false if none.
-template <int NL>
-__device__ __forceinline__ bool nearest_own(const SdfArgs& a, const float x[3], uint32_t& id, uint32_t& label) {
-    const SceneView& v = a.v;
-    int lc[3];
-    float fr[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const float u = (x[k] - v.org[k]) * v.inv_h;
-        lc[k] = (int)floorf(u);
-        fr[k] = u - (float)lc[k];
-    }
-    float bd = a.h2;
-    bool found = false;
-    Seg N;
-    N.cq[0] = N.cq[1] = N.cq[2] = -1;
-    N.cres = 0;
-    N.cskip0 = 1;
-    N.cbox = NO_BOX;
-    N.cnode = 0;
-    N.oct_shift = 0;
-#pragma unroll 1
-    for (int q = 0; q < 27; ++q) {
-        const int dx = q % 3 - 1, dy = (q / 3) % 3 - 1, dz = q / 9 - 1;
-        const float gx = dx < 0 ? fr[0] : (dx > 0 ? 1.f - fr[0] : 0.f);
-        const float gy = dy < 0 ? fr[1] : (dy > 0 ? 1.f - fr[1] : 0.f);
-        const float gz = dz < 0 ? fr[2] : (dz > 0 ? 1.f - fr[2] : 0.f);
-        if (gx * gx + gy * gy + gz * gz >= a.hl2) continue;
-        N.c[0] = lc[0] + dx;
-        N.c[1] = lc[1] + dy;
-        N.c[2] = lc[2] + dz;
-        if (N.c[0] < 0 || N.c[1] < 0 || N.c[2] < 0 || N.c[0] >= v.dim[0] || N.c[1] >= v.dim[1] ||
-            N.c[2] >= v.dim[2])
-            continue;
-        DdaCell k;
-        dda_cell_reset(k);
-        dda_locate<NL>(a.ov, N, k);
-        if (k.lvl != NL || k.range.y == 0u) continue;
-        const uint32_t e1 = k.range.x + k.range.y;
-        for (uint32_t e = k.range.x; e < e1; ++e) {
-            const float4 P = a.opos[e];
-            const float ex = P.x - x[0], ey = P.y - x[1], ez = P.z - x[2];
-            const float d2 = ex * ex + ey * ey + ez * ez;
-            const uint32_t pid = __float_as_uint(P.w);
-            if (d2 < bd || (d2 == bd && found && pid < id)) {
-                bd = d2;
-                id = pid;
-                label = __float_as_uint(a.onrm[e].w);
-                found = true;
-            }
-        }
-    }
-    return found;
 }
 
 // A launch whose intersections are those of the implicit surface (launch_rays
@@ -481,67 +662,92 @@ __device__ __forceinline__ void wave_add(uint32_t* p, uint32_t x) {
 // intersection (from t_lo: 0 from the TX, after a reflection 4 eps / |d.n|
 // so that the march starts outside the |f| <= eps band it left); the RX
 // spheres are tested on [0, t]; at the intersection the ray reflects about
-// n(x) and records the label of the nearest point.
-template <int NL>
+// n(x) and records the label of the nearest point.  A lane goes on to its
+// next segment at once, so the wave ends with its longest ray, not with the
+// longest of every segment.
+template <int NL, bool FAST>
 __global__ __launch_bounds__(SDF_BLOCK) void k_sdf_launch(SdfLaunchArgs A) {
+    __shared__ SdfRuns runs;
     const uint32_t lane_ray = blockIdx.x * SDF_BLOCK + threadIdx.x;
-    if (lane_ray >= A.n_total) return;
-    const uint32_t g = A.order ? A.order[lane_ray] : lane_ray;
+    bool alive = lane_ray < A.n_total;
+    const uint32_t g = !alive ? 0u : A.order ? A.order[lane_ray] : lane_ray;
     const SdfArgs& a = A.s;
     const uint32_t ti = g / A.n_rays, j = g - ti * A.n_rays;
     float o[3] = {A.tx[3 * ti], A.tx[3 * ti + 1], A.tx[3 * ti + 2]};
     float d[3] = {A.dirs[3 * (size_t)j], A.dirs[3 * (size_t)j + 1], A.dirs[3 * (size_t)j + 2]};
     {
-        const float il = 1.0f / sqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        const float il = 1.0f / sqrtf(dot3(d[0], d[1], d[2], d[0], d[1], d[2]));
         d[0] *= il;
         d[1] *= il;
         d[2] *= il;
     }
     float L = 0.f, t_lo = 0.f;
     uint32_t* rec_counter = &A.counters[PCRL_CNT_REC(A.K)];
-    for (int b = 0; b <= A.K; ++b) {
-        wave_add(&A.counters[b], 1u);
-        float t, n[3];
-        int bc[3];
-        uint32_t ev = 0, rd = 0;
-        sdf_first_hit<NL>(a, o, d, t_lo, INFINITY, t, n, bc, ev, rd);
-        bool hit = bc[0] >= 0;
-        float q[3] = {o[0] + t * d[0], o[1] + t * d[1], o[2] + t * d[2]};
-        uint32_t pid = 0, lab = 0;
-        if (hit) hit = nearest_own<NL>(a, q, pid, lab);
-        if (!hit) t = INFINITY;
-        if (A.hit_id) {
-            const size_t idx = (size_t)g * (A.K + 1) + b;
-            A.hit_id[idx] = hit ? (int32_t)pid : -1;
-            A.hit_t[idx] = hit ? t : NAN;
-        }
-        for (int r = 0; r < A.n_rx; ++r) {
-            const float vx = A.rx[3 * r] - o[0], vy = A.rx[3 * r + 1] - o[1], vz = A.rx[3 * r + 2] - o[2];
-            const float sp = vx * d[0] + vy * d[1] + vz * d[2];
-            if (!(sp > 0.f && sp <= t)) continue;
-            const float cx = vx - sp * d[0], cy = vy - sp * d[1], cz = vz - sp * d[2];
-            const float rho = A.sig_c * (L + sp);
-            if (!(cx * cx + cy * cy + cz * cz <= rho * rho)) continue;
-            const uint32_t slot = atomicAdd(rec_counter, 1u);
-            if (slot < A.rec_cap) {
-                const float lp = L + sqrtf(vx * vx + vy * vy + vz * vz);
-                A.rec[slot] = make_uint4(g, (uint32_t)r | ((uint32_t)b << 16), __float_as_uint(lp),
-                                         __float_as_uint(L + sp));
+    uint32_t reads = 0;
+    int b = 0;
+    SdfMarch M;
+    bool walking = false;
+    if (alive) {
+        wave_add(&A.counters[0], 1u);
+        walking = march_begin(M, o, d, 0.f, INFINITY);
+    }
+    for (;;) {
+        bool want = false;
+        const SdfArgs& w = reread_sdf();
+        while (alive && !want) {
+            if (walking) {
+                want = march_next<NL>(w, M, walking, o, d, t_lo, INFINITY, reads);
+                continue;
             }
+            // the segment's end
+            float t = M.best;
+            bool hit = M.bc[0] >= 0;
+            const float q[3] = {fmaf(t, d[0], o[0]), fmaf(t, d[1], o[1]), fmaf(t, d[2], o[2])};
+            uint32_t pid = 0, lab = 0;
+            if (hit) hit = nearest_own<NL, FAST>(q, runs, pid, lab);
+            if (!hit) t = INFINITY;
+            if (A.hit_id) {
+                const size_t idx = (size_t)g * (A.K + 1) + b;
+                A.hit_id[idx] = hit ? (int32_t)pid : -1;
+                A.hit_t[idx] = hit ? t : NAN;
+            }
+            for (int r = 0; r < A.n_rx; ++r) {
+                const float vx = A.rx[3 * r] - o[0], vy = A.rx[3 * r + 1] - o[1], vz = A.rx[3 * r + 2] - o[2];
+                const float sp = dot3(vx, vy, vz, d[0], d[1], d[2]);
+                if (!(sp > 0.f && sp <= t)) continue;
+                const float cx = fmaf(-d[0], sp, vx), cy = fmaf(-d[1], sp, vy), cz = fmaf(-d[2], sp, vz);
+                const float rho = A.sig_c * (L + sp);
+                if (!(dot3(cx, cy, cz, cx, cy, cz) <= rho * rho)) continue;
+                const uint32_t slot = atomicAdd(rec_counter, 1u);
+                if (slot < A.rec_cap) {
+                    const float lp = L + sqrtf(dot3(vx, vy, vz, vx, vy, vz));
+                    A.rec[slot] = make_uint4(g, (uint32_t)r | ((uint32_t)b << 16), __float_as_uint(lp),
+                                             __float_as_uint(L + sp));
+                }
+            }
+            if (!hit || b >= A.K) {
+                alive = false;
+                break;
+            }
+            A.hist[(size_t)b * A.n_total + g] = make_float4(q[0], q[1], q[2], __uint_as_float(lab));
+            L += t;
+            const float* n = M.bn;
+            const float dn = fmaf(d[2], n[2], fmaf(d[1], n[1], d[0] * n[0])), dn2 = 2.f * dn;
+            const float ex = fmaf(-n[0], dn2, d[0]), ey = fmaf(-n[1], dn2, d[1]), ez = fmaf(-n[2], dn2, d[2]);
+            const float inv = 1.0f / sqrtf(dot3(ex, ey, ez, ex, ey, ez));
+            d[0] = ex * inv;
+            d[1] = ey * inv;
+            d[2] = ez * inv;
+            o[0] = q[0];
+            o[1] = q[1];
+            o[2] = q[2];
+            t_lo = 4.f * a.eps / fmaxf(fabsf(dn), 0.05f);
+            ++b;
+            wave_add(&A.counters[b], 1u);
+            walking = march_begin(M, o, d, t_lo, INFINITY);
         }
-        if (!hit || b >= A.K) break;
-        A.hist[(size_t)b * A.n_total + g] = make_float4(q[0], q[1], q[2], __uint_as_float(lab));
-        L += t;
-        const float dn = d[0] * n[0] + d[1] * n[1] + d[2] * n[2];
-        const float ex = d[0] - 2.f * dn * n[0], ey = d[1] - 2.f * dn * n[1], ez = d[2] - 2.f * dn * n[2];
-        const float inv = 1.0f / sqrtf(ex * ex + ey * ey + ez * ez);
-        d[0] = ex * inv;
-        d[1] = ey * inv;
-        d[2] = ez * inv;
-        o[0] = q[0];
-        o[1] = q[1];
-        o[2] = q[2];
-        t_lo = 4.f * a.eps / fmaxf(fabsf(dn), 0.05f);
+        if (!__ballot(want)) break;
+        if (want) march_sample<NL, FAST>(M, runs, o, d, reads);
     }
 }
 
@@ -560,48 +766,24 @@ __global__ void k_sdf_launch_keys(const float* tx, const float* dirs, uint32_t n
 template <int NL>
 static void launch_sdf_nl(const SdfArgs& a, hipStream_t s) {
     const unsigned grid = (a.n + SDF_BLOCK - 1) / SDF_BLOCK;
-    hipLaunchKernelGGL((k_sdf<NL>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
+    if (a.cells || a.empty) hipLaunchKernelGGL((k_sdf<NL, true>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
+    else if constexpr (NL > 1) hipLaunchKernelGGL((k_sdf<NL, false>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
 }
 
-// Entry ranges (first, count) of a leaf table or a dense cell table turned
-// into ranges of own entries; an entry with count 0 (an empty cell's skip
-// radius) is kept as it is.
-__global__ void k_own_ranges(const uint2* in, uint32_t n, const uint32_t* scan, uint2* out) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint2 r = in[i];
-    out[i] = r.y ? make_uint2(scan[r.x], scan[r.x + r.y] - scan[r.x]) : r;
-}
+// Largest table of own entries before each cell (4 bytes per leaf cell of
+// every leaves' parent); beyond it, and where the parents have no dense top
+// grid, a sample's runs are found through the bricks' masks (two more
+// dependent loads each).
+constexpr int64_t OWN_CELLS_MAX_BYTES = (int64_t)4 << 30;
 
-// The integer block of the own-point index: the scan [n_entries + 1], then
-// (8-byte aligned) the own range of every leaf and, where the scene has a
-// dense cell table, that table with own ranges.
-struct OwnLayout {
-    size_t leaf_off, n_leaves, cells_off, n_cells, bytes;
-};
-
-static OwnLayout own_layout(const PcrlScene* S) {
-    const SceneView& v = S->walk;
-    OwnLayout L{};
-    L.leaf_off = ((size_t)(S->info.n_entries + 1) * sizeof(uint32_t) + 7) / 8 * 8;
-    L.n_leaves = v.nn[v.nlev - 1];
-    L.cells_off = L.leaf_off + L.n_leaves * sizeof(uint2);
-    if (v.cells && v.nlev >= 2) {
-        const size_t r = (size_t)v.ratio[v.nlev - 2];
-        L.n_cells = (size_t)v.nn[v.nlev - 2] * r * r * r;
-    }
-    L.bytes = L.cells_off + L.n_cells * sizeof(uint2);
-    return L;
-}
-
-// The scene's view with its leaf and cell ranges pointing into the own entries.
-static SceneView own_view(const PcrlScene* S) {
-    const OwnLayout L = own_layout(S);
-    SceneView ov = S->walk;
-    char* base = (char*)S->own_scan;
-    ov.leaf = (const uint2*)(base + L.leaf_off);
-    if (L.n_cells) ov.cells = (const uint2*)(base + L.cells_off);
-    return ov;
+// The scene's arrays for the kernels (the index is built).
+static void own_args(const PcrlScene* S, SdfArgs& a) {
+    a.v = S->walk;
+    a.oscan = S->own_scan;
+    a.own = S->own;
+    a.lbox = S->own_box;
+    a.first = S->own_first;
+    a.cells = S->own_cells;
 }
 
 template <int NL>
@@ -678,32 +860,42 @@ static int own_index(PcrlScene* S, hipStream_t s) {
     DevBufs B;  // handed to the scene when complete
     B.stream = s;
     int rc = build_walk(S, s, B);
-    const OwnLayout lay = own_layout(S);
-    char* block = nullptr;
-    uint32_t* scan = nullptr;
-    float4 *pos = nullptr, *nrm = nullptr;
-    if (!rc) rc = B.alloc(&block, lay.bytes);
-    if (!rc) rc = B.alloc(&pos, (size_t)(np > 0 ? np : 1));
-    if (!rc) rc = B.alloc(&nrm, (size_t)(np > 0 ? np : 1));
-    scan = (uint32_t*)block;
+    const SceneView& v = S->walk;
+    const uint32_t n_leaves = v.nn[v.nlev - 1];
+    const int P = v.nlev - 2;
+    const uint32_t n3 = P < 0 ? 0u : (uint32_t)v.ratio[P] * v.ratio[P] * v.ratio[P];
+    const int64_t n_cells = P < 0 ? (int64_t)v.dim[0] * v.dim[1] * v.dim[2] + 1 : (int64_t)v.nn[P] * (n3 + 1);
+    const bool table = P < 0 || (v.depth == 0 && n_cells * 4 <= OWN_CELLS_MAX_BYTES);
+    uint32_t *scan = nullptr, *first = nullptr, *cells = nullptr;
+    float4 *own = nullptr, *box = nullptr;
+    const size_t slots = (size_t)(np > 0 ? np : 1);
+    if (!rc) rc = B.alloc(&scan, (size_t)m + 1);
+    if (!rc) rc = B.alloc(&own, 2 * slots);
+    if (!rc) rc = B.alloc(&box, slots);
+    if (!rc) rc = B.alloc(&first, (size_t)n_leaves + 1);
+    if (!rc && table) rc = B.alloc(&cells, (size_t)n_cells);
+    if (!rc && P < 0) rc = fill_u32(cells, 0u, n_cells, s);
     if (!rc) {
-        switch (S->view.nlev) {
-        case 1: launch_own_flags<1>(S->walk, (uint32_t)m, scan, s); break;
-        case 2: launch_own_flags<2>(S->walk, (uint32_t)m, scan, s); break;
-        case 3: launch_own_flags<3>(S->walk, (uint32_t)m, scan, s); break;
-        default: launch_own_flags<4>(S->walk, (uint32_t)m, scan, s); break;
+        switch (v.nlev) {
+        case 1: launch_own_flags<1>(v, (uint32_t)m, scan, s); break;
+        case 2: launch_own_flags<2>(v, (uint32_t)m, scan, s); break;
+        case 3: launch_own_flags<3>(v, (uint32_t)m, scan, s); break;
+        default: launch_own_flags<4>(v, (uint32_t)m, scan, s); break;
         }
         rc = hipGetLastError() == hipSuccess ? scan_u32(scan, scan, m, scan + m, s) : PCRL_EHIP;
     }
     if (!rc) {
-        hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, S->view.spos,
-                           S->view.snrm, scan, (uint32_t)m, (uint32_t)np, pos, nrm);
-        hipLaunchKernelGGL(k_own_ranges, dim3((unsigned)((lay.n_leaves + 255) / 256)), dim3(256), 0, s,
-                           S->walk.leaf, (uint32_t)lay.n_leaves, scan, (uint2*)(block + lay.leaf_off));
-        if (lay.n_cells)
-            hipLaunchKernelGGL(k_own_ranges, dim3((unsigned)((lay.n_cells + 255) / 256)), dim3(256), 0, s,
-                               S->walk.cells, (uint32_t)lay.n_cells, scan, (uint2*)(block + lay.cells_off));
-        rc = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? PCRL_OK : PCRL_EHIP;
+        hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, v.spos, v.snrm, scan,
+                           (uint32_t)m, (uint32_t)np, own);
+        hipLaunchKernelGGL(k_own_leaves, dim3((n_leaves + 255) / 256), dim3(256), 0, s, v.leaf, n_leaves, scan,
+                           (const float4*)own, first, box, P < 0 ? cells : (uint32_t*)nullptr,
+                           (const uint64_t*)S->leaf_key);
+        if (P < 0)
+            rc = scan_u32(cells, cells, n_cells, nullptr, s);
+        else if (table)
+            hipLaunchKernelGGL(k_own_cells, dim3((unsigned)((n_cells + 255) / 256)), dim3(256), 0, s, v.mask[P],
+                               v.base[P], (const uint32_t*)first, v.nw[P], n3, (uint64_t)n_cells, cells);
+        if (!rc) rc = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? PCRL_OK : PCRL_EHIP;
     }
     if (rc) {
         B.release();
@@ -711,9 +903,11 @@ static int own_index(PcrlScene* S, hipStream_t s) {
         return rc;
     }
     S->bufs.ptrs.insert(S->bufs.ptrs.end(), B.ptrs.begin(), B.ptrs.end());
+    S->own = own;
+    S->own_box = box;
+    S->own_first = first;
+    S->own_cells = cells;
     S->own_scan = scan;
-    S->own_pos = pos;
-    S->own_nrm = nrm;
     return PCRL_OK;
 }
 
@@ -726,6 +920,7 @@ static void sdf_defaults(const PcrlScene* scene, SdfArgs& a) {
     const float h = 0.95f * leaf;
     a.max_steps = 64;
     a.h2 = h * h;
+    a.rh2 = 1.0f / a.h2;
     a.hl2 = (h / leaf + 1e-3f) * (h / leaf + 1e-3f);
     a.half_h = 0.5f * h;
     a.eps = 1e-3f * leaf;
@@ -738,7 +933,8 @@ static void sdf_defaults(const PcrlScene* scene, SdfArgs& a) {
 template <int NL>
 static void launch_sdf_launch_nl(const SdfLaunchArgs& A, hipStream_t s) {
     const unsigned grid = (A.n_total + SDF_BLOCK - 1) / SDF_BLOCK;
-    hipLaunchKernelGGL((k_sdf_launch<NL>), dim3(grid), dim3(SDF_BLOCK), 0, s, A);
+    if (A.s.cells || A.s.empty) hipLaunchKernelGGL((k_sdf_launch<NL, true>), dim3(grid), dim3(SDF_BLOCK), 0, s, A);
+    else if constexpr (NL > 1) hipLaunchKernelGGL((k_sdf_launch<NL, false>), dim3(grid), dim3(SDF_BLOCK), 0, s, A);
 }
 
 int sdf_launch_run(PcrlLaunch* L, const TraceArgs& t) {
@@ -752,11 +948,7 @@ int sdf_launch_run(PcrlLaunch* L, const TraceArgs& t) {
     sdf_defaults(scene, A.s);
     if (!A.s.empty) {
         PCRL_TRY(own_index(const_cast<PcrlScene*>(scene), s));
-        A.s.oscan = scene->own_scan;
-        A.s.opos = scene->own_pos;
-        A.s.onrm = scene->own_nrm;
-        A.s.v = scene->walk;
-        A.s.ov = own_view(scene);
+        own_args(scene, A.s);
     }
     A.tx = t.tx;
     A.rx = t.rx;
@@ -844,6 +1036,7 @@ extern "C" int sdf_intersect(const PcrlScene* scene, const float* o, const float
     a.n = (uint32_t)n_rays;
     a.max_steps = max_steps;
     a.h2 = h * h;
+    a.rh2 = 1.0f / a.h2;
     a.hl2 = (h / leaf + 1e-3f) * (h / leaf + 1e-3f);
     a.half_h = 0.5f * h;
     a.eps = eps;
@@ -861,11 +1054,7 @@ extern "C" int sdf_intersect(const PcrlScene* scene, const float* o, const float
         // the index is a cache of the scene's data: building it does not change the scene
         const int rc = own_index(const_cast<PcrlScene*>(scene), s);
         if (rc) return rc;
-        a.oscan = scene->own_scan;
-        a.opos = scene->own_pos;
-        a.onrm = scene->own_nrm;
-        a.v = scene->walk;
-        a.ov = own_view(scene);
+        own_args(scene, a);
     }
     DevBufs T;
     T.stream = s;

@@ -181,7 +181,8 @@ __device__ __forceinline__ void leaf_tests(const SceneView& v, WaveLds& W, uint2
         const float qx = fmaf(t, Dd.x, -wx), qy = fmaf(t, Dd.y, -wy), qz = fmaf(t, Dd.z, -wz);
         const float dist2 = fmaf(qz, qz, fmaf(qx, qx, qy * qy));
         // no short circuit: the id is then loaded with the position
-        const bool ok = (fabsf(den) > 1e-7f) & (t > v.t_eps) & (id != __float_as_uint(O.w)) & (dist2 <= v.rs2);
+        const bool ok = ((int)(fabsf(den) > 1e-7f) & (int)(t > v.t_eps) & (int)(id != __float_as_uint(O.w)) &
+                         (int)(dist2 <= v.rs2)) != 0;
         const unsigned long long cand = hit_word(t, id);
         if (ok) atomicMin(&W.best[own], cand);
         if (ballot(ok)) {
