@@ -60,6 +60,13 @@ struct SdfArgs {
     float* nrm;            // [n][3]
     int32_t* cell;         // [n][3] or null
     unsigned long long* stats;  // null, or [2]: evaluations of f, entries read
+    // rays left to the tail kernel (one wave each)
+    uint32_t budget;       // samples of one segment after which a lane leaves its ray to it
+    uint32_t tail_cap;     // most of them; further rays stay with their lanes
+    uint32_t* tail;        // their ray ids
+    uint32_t* tail_cnt;    // [0] their number, [1] the next to be taken
+    float4* tail_ray;      // launches: per ray (o, L), (d, t_lo)
+    uint32_t* tail_b;      // launches: its segment
 };
 
 // a . b with the fused form written out (results must not depend on the
@@ -575,11 +582,33 @@ __device__ __forceinline__ void march_sample(SdfMarch& M, SdfRuns& runs, const f
     ++M.s;
 }
 
+// This lane's slot in the tail list (one atomic per wave).
+__device__ __forceinline__ uint32_t tail_slot(uint32_t* cnt) {
+    const uint64_t m = __ballot(1);
+    const int leader = __ffsll((long long)m) - 1;
+    uint32_t first = 0;
+    if ((int)lane_id() == leader) first = atomicAdd(cnt, (uint32_t)__popcll(m));
+    return __shfl(first, leader, 64) + (uint32_t)__popcll(m & lanemask_lt());
+}
+
+__device__ __forceinline__ void sdf_write(const SdfArgs& a, uint32_t i, const float o[3], const float d[3], float best,
+                                          const float bn[3], const int bc[3]) {
+    const size_t i3 = 3 * (size_t)i;
+    a.t[i] = best;
+    const bool hit = bc[0] >= 0;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        a.pt[i3 + ax] = hit ? fmaf(best, d[ax], o[ax]) : NAN;
+        a.nrm[i3 + ax] = bn[ax];
+        if (a.cell) a.cell[i3 + ax] = bc[ax];
+    }
+}
+
 template <int NL, bool FAST>
 __global__ __launch_bounds__(SDF_BLOCK) void k_sdf(SdfArgs a) {
     __shared__ SdfRuns runs;
     const uint32_t lane_ray = blockIdx.x * SDF_BLOCK + threadIdx.x;
-    const bool in = lane_ray < a.n;
+    bool in = lane_ray < a.n;
     const uint32_t i = !in ? 0u : a.order ? a.order[lane_ray] : lane_ray;
     const size_t i3 = 3 * (size_t)i, i2 = 2 * (size_t)i;  // n may exceed 2^32 / 3
     const float o[3] = {a.o[i3], a.o[i3 + 1], a.o[i3 + 2]};
@@ -609,19 +638,19 @@ __global__ __launch_bounds__(SDF_BLOCK) void k_sdf(SdfArgs a) {
         }
         if (!__ballot(want)) break;
         if (want) {
-            ++evals;
+            if (evals++ == a.budget) {
+                const uint32_t slot = tail_slot(a.tail_cnt);
+                if (slot < a.tail_cap) {
+                    a.tail[slot] = i;
+                    in = walking = false;
+                    continue;
+                }
+            }
             march_sample<NL, FAST>(M, runs, o, d, reads);
         }
     }
     if (!in) return;
-    a.t[i] = M.best;
-    const bool hit = M.bc[0] >= 0;
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        a.pt[i3 + ax] = hit ? fmaf(M.best, d[ax], o[ax]) : NAN;
-        a.nrm[i3 + ax] = M.bn[ax];
-        if (a.cell) a.cell[i3 + ax] = M.bc[ax];
-    }
+    sdf_write(a, i, o, d, M.best, M.bn, M.bc);
     if (a.stats) {
         atomicAdd(&a.stats[0], (unsigned long long)evals);
         atomicAdd(&a.stats[1], (unsigned long long)reads);
@@ -657,6 +686,66 @@ __device__ __forceinline__ void wave_add(uint32_t* p, uint32_t x) {
     if ((int)lane_id() == leader) atomicAdd(p, (uint32_t)__popcll(m) * x);
 }
 
+__device__ __forceinline__ void launch_ray(const SdfLaunchArgs& A, uint32_t g, float o[3], float d[3]) {
+    const uint32_t ti = g / A.n_rays, j = g - ti * A.n_rays;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        o[k] = A.tx[3 * ti + k];
+        d[k] = A.dirs[3 * (size_t)j + k];
+    }
+    const float il = 1.0f / sqrtf(dot3(d[0], d[1], d[2], d[0], d[1], d[2]));
+    d[0] *= il;
+    d[1] *= il;
+    d[2] *= il;
+}
+
+// End of segment b of ray g at its first intersection (t = best, normal n):
+// hit log, receptions, history, and the reflected ray (o, d, L, t_lo).  False
+// when the ray ends.  Only lanes with `write` store.
+template <int NL, bool FAST>
+__device__ __forceinline__ bool segment_end(const SdfLaunchArgs& A, SdfRuns& runs, uint32_t g, int b, float o[3],
+                                            float d[3], float& L, float& t_lo, float best, const float n[3], bool hit,
+                                            bool write = true) {
+    float t = best;
+    const float q[3] = {fmaf(t, d[0], o[0]), fmaf(t, d[1], o[1]), fmaf(t, d[2], o[2])};
+    uint32_t pid = 0, lab = 0;
+    if (hit) hit = nearest_own<NL, FAST>(q, runs, pid, lab);
+    if (!hit) t = INFINITY;
+    if (A.hit_id && write) {
+        const size_t idx = (size_t)g * (A.K + 1) + b;
+        A.hit_id[idx] = hit ? (int32_t)pid : -1;
+        A.hit_t[idx] = hit ? t : NAN;
+    }
+    for (int r = 0; r < A.n_rx; ++r) {
+        const float vx = A.rx[3 * r] - o[0], vy = A.rx[3 * r + 1] - o[1], vz = A.rx[3 * r + 2] - o[2];
+        const float sp = dot3(vx, vy, vz, d[0], d[1], d[2]);
+        if (!(sp > 0.f && sp <= t)) continue;
+        const float cx = fmaf(-d[0], sp, vx), cy = fmaf(-d[1], sp, vy), cz = fmaf(-d[2], sp, vz);
+        const float rho = A.sig_c * (L + sp);
+        if (!(dot3(cx, cy, cz, cx, cy, cz) <= rho * rho) || !write) continue;
+        const uint32_t slot = atomicAdd(&A.counters[PCRL_CNT_REC(A.K)], 1u);
+        if (slot < A.rec_cap) {
+            const float lp = L + sqrtf(dot3(vx, vy, vz, vx, vy, vz));
+            A.rec[slot] = make_uint4(g, (uint32_t)r | ((uint32_t)b << 16), __float_as_uint(lp),
+                                     __float_as_uint(L + sp));
+        }
+    }
+    if (!hit || b >= A.K) return false;
+    if (write) A.hist[(size_t)b * A.n_total + g] = make_float4(q[0], q[1], q[2], __uint_as_float(lab));
+    L += t;
+    const float dn = fmaf(d[2], n[2], fmaf(d[1], n[1], d[0] * n[0])), dn2 = 2.f * dn;
+    const float ex = fmaf(-n[0], dn2, d[0]), ey = fmaf(-n[1], dn2, d[1]), ez = fmaf(-n[2], dn2, d[2]);
+    const float inv = 1.0f / sqrtf(dot3(ex, ey, ez, ex, ey, ez));
+    d[0] = ex * inv;
+    d[1] = ey * inv;
+    d[2] = ez * inv;
+    o[0] = q[0];
+    o[1] = q[1];
+    o[2] = q[2];
+    t_lo = 4.f * A.s.eps / fmaxf(fabsf(dn), 0.05f);
+    return true;
+}
+
 // Every segment of a ray, as the launcher's bounce kernels do with surfels:
 // the segment from o along d ends at the implicit surface's first
 // intersection (from t_lo: 0 from the TX, after a reflection 4 eps / |d.n|
@@ -672,18 +761,10 @@ __global__ __launch_bounds__(SDF_BLOCK) void k_sdf_launch(SdfLaunchArgs A) {
     bool alive = lane_ray < A.n_total;
     const uint32_t g = !alive ? 0u : A.order ? A.order[lane_ray] : lane_ray;
     const SdfArgs& a = A.s;
-    const uint32_t ti = g / A.n_rays, j = g - ti * A.n_rays;
-    float o[3] = {A.tx[3 * ti], A.tx[3 * ti + 1], A.tx[3 * ti + 2]};
-    float d[3] = {A.dirs[3 * (size_t)j], A.dirs[3 * (size_t)j + 1], A.dirs[3 * (size_t)j + 2]};
-    {
-        const float il = 1.0f / sqrtf(dot3(d[0], d[1], d[2], d[0], d[1], d[2]));
-        d[0] *= il;
-        d[1] *= il;
-        d[2] *= il;
-    }
+    float o[3], d[3];
+    launch_ray(A, g, o, d);
     float L = 0.f, t_lo = 0.f;
-    uint32_t* rec_counter = &A.counters[PCRL_CNT_REC(A.K)];
-    uint32_t reads = 0;
+    uint32_t evals = 0, reads = 0;
     int b = 0;
     SdfMarch M;
     bool walking = false;
@@ -699,55 +780,240 @@ __global__ __launch_bounds__(SDF_BLOCK) void k_sdf_launch(SdfLaunchArgs A) {
                 want = march_next<NL>(w, M, walking, o, d, t_lo, INFINITY, reads);
                 continue;
             }
-            // the segment's end
-            float t = M.best;
-            bool hit = M.bc[0] >= 0;
-            const float q[3] = {fmaf(t, d[0], o[0]), fmaf(t, d[1], o[1]), fmaf(t, d[2], o[2])};
-            uint32_t pid = 0, lab = 0;
-            if (hit) hit = nearest_own<NL, FAST>(q, runs, pid, lab);
-            if (!hit) t = INFINITY;
-            if (A.hit_id) {
-                const size_t idx = (size_t)g * (A.K + 1) + b;
-                A.hit_id[idx] = hit ? (int32_t)pid : -1;
-                A.hit_t[idx] = hit ? t : NAN;
-            }
-            for (int r = 0; r < A.n_rx; ++r) {
-                const float vx = A.rx[3 * r] - o[0], vy = A.rx[3 * r + 1] - o[1], vz = A.rx[3 * r + 2] - o[2];
-                const float sp = dot3(vx, vy, vz, d[0], d[1], d[2]);
-                if (!(sp > 0.f && sp <= t)) continue;
-                const float cx = fmaf(-d[0], sp, vx), cy = fmaf(-d[1], sp, vy), cz = fmaf(-d[2], sp, vz);
-                const float rho = A.sig_c * (L + sp);
-                if (!(dot3(cx, cy, cz, cx, cy, cz) <= rho * rho)) continue;
-                const uint32_t slot = atomicAdd(rec_counter, 1u);
-                if (slot < A.rec_cap) {
-                    const float lp = L + sqrtf(dot3(vx, vy, vz, vx, vy, vz));
-                    A.rec[slot] = make_uint4(g, (uint32_t)r | ((uint32_t)b << 16), __float_as_uint(lp),
-                                             __float_as_uint(L + sp));
-                }
-            }
-            if (!hit || b >= A.K) {
+            if (!segment_end<NL, FAST>(A, runs, g, b, o, d, L, t_lo, M.best, M.bn, M.bc[0] >= 0)) {
                 alive = false;
                 break;
             }
-            A.hist[(size_t)b * A.n_total + g] = make_float4(q[0], q[1], q[2], __uint_as_float(lab));
-            L += t;
-            const float* n = M.bn;
-            const float dn = fmaf(d[2], n[2], fmaf(d[1], n[1], d[0] * n[0])), dn2 = 2.f * dn;
-            const float ex = fmaf(-n[0], dn2, d[0]), ey = fmaf(-n[1], dn2, d[1]), ez = fmaf(-n[2], dn2, d[2]);
-            const float inv = 1.0f / sqrtf(dot3(ex, ey, ez, ex, ey, ez));
-            d[0] = ex * inv;
-            d[1] = ey * inv;
-            d[2] = ez * inv;
-            o[0] = q[0];
-            o[1] = q[1];
-            o[2] = q[2];
-            t_lo = 4.f * a.eps / fmaxf(fabsf(dn), 0.05f);
+            evals = 0;
             ++b;
             wave_add(&A.counters[b], 1u);
             walking = march_begin(M, o, d, t_lo, INFINITY);
         }
         if (!__ballot(want)) break;
-        if (want) march_sample<NL, FAST>(M, runs, o, d, reads);
+        if (want) {
+            if (evals++ == a.budget) {
+                const uint32_t slot = tail_slot(a.tail_cnt);
+                if (slot < a.tail_cap) {
+                    a.tail[slot] = g;
+                    a.tail_ray[2 * (size_t)slot] = make_float4(o[0], o[1], o[2], L);
+                    a.tail_ray[2 * (size_t)slot + 1] = make_float4(d[0], d[1], d[2], t_lo);
+                    a.tail_b[slot] = (uint32_t)b;
+                    alive = false;
+                    continue;
+                }
+            }
+            march_sample<NL, FAST>(M, runs, o, d, reads);
+        }
+    }
+}
+
+// First intersection of one ray found by a whole wave (every lane holds the
+// same ray): the walk hands its leaves out to the lanes, up to 64 at a time,
+// and every lane marches its own.  The nearest over the leaves is the same as
+// marching them one after another, the earliest leaf of the walk among equals:
+// a march is only ever cut where no nearer result can follow.  Leaves of the
+// shared march from t_lo continue each other's samples, so every lane marches
+// those alike.
+// The walk waits in LDS (`keep`) meanwhile: it is the same in every lane, and
+// registers are what the marches lack.
+template <int NL, bool FAST>
+__device__ __forceinline__ void wave_first_hit(SdfRuns& runs, SdfMarch& keep, const float o[3], const float d[3], float t_lo, float t_hi,
+                                               float& best, float bn[3], int bc[3]) {
+    const uint32_t lane = lane_id();
+    uint32_t reads = 0;  // not counted here
+    SdfMarch M;
+    bool walking = march_begin(M, o, d, t_lo, t_hi);
+    while (walking) {
+        // hand out leaves
+        uint32_t n = 0;
+        float jt = 0.f, jtb = -INFINITY;
+        int jc[3] = {-1, -1, -1};
+        {
+            const SdfArgs& a = reread_sdf();
+            const SceneView& v = a.v;
+            while (walking && n < 64) {
+                DdaCell k;
+                dda_cell_reset(k);
+                dda_locate<NL>(v, M.S, k);
+                const bool at_leaf = k.lvl == NL;
+                if (at_leaf && M.t_in <= t_hi) {
+                    const uint32_t o0 = a.oscan[k.range.x], o1 = a.oscan[k.range.x + k.range.y];
+                    if (o0 < o1) {
+                        const float4 c = a.lbox[o0];
+                        const float tc = dot3(c.x - o[0], c.y - o[1], c.z - o[2], d[0], d[1], d[2]);
+                        if (tc - a.half_diam <= t_lo) {
+                            // a leaf of the shared march: after the leaves handed out before it
+                            if (n) break;
+                            M.in_leaf = M.shared = true;
+                            M.stop = false;
+                            M.tb = fminf(tc + a.half_diam, t_hi);
+                            M.s = M.c_done || M.tb <= M.c_tb ? a.max_steps : M.c_s;
+                            M.t = M.c_t;
+                            M.fp = M.c_fp;
+                            M.tp = M.c_tp;
+                            M.prev = M.c_prev;
+                            break;
+                        }
+                        if (lane == n) {
+                            jt = fmaxf(tc - a.half_diam, t_lo);
+                            jtb = fminf(tc + a.half_diam, t_hi);
+                            jc[0] = M.S.c[0];
+                            jc[1] = M.S.c[1];
+                            jc[2] = M.S.c[2];
+                        }
+                        ++n;
+                    }
+                }
+                float te;
+                dda_advance<NL>(v, walking, o, d, M.S, k, at_leaf, fminf(M.best + a.reach, t_hi), te);
+                M.t_in = te;
+            }
+        }
+        if (M.in_leaf) {
+            bool at_sample = true;
+            while (at_sample) {
+                at_sample = march_next<NL>(reread_sdf(), M, walking, o, d, t_lo, t_hi, reads);
+                if (!at_sample) break;  // the leaf is done and the walk one step further
+                march_sample<NL, FAST>(M, runs, o, d, reads);
+            }
+            continue;
+        }
+        // march the lane's leaf
+        const float best0 = M.best;
+        keep = M;
+        __syncthreads();
+        float fp = 0.f, tp = 0.f, th = INFINITY, nn[3] = {0.f, 0.f, 0.f};
+        bool prev = false, go = lane < n;
+        int s = 0;
+        for (;;) {
+            const SdfArgs& a = reread_sdf();
+            go = go && s < a.max_steps && jt <= jtb && !(jt >= best0 && !(prev && tp < best0));
+            if (!__ballot(go)) break;
+            if (!go) continue;
+            const float x[3] = {fmaf(jt, d[0], o[0]), fmaf(jt, d[1], o[1]), fmaf(jt, d[2], o[2])};
+            float f, nv[3];
+            ++s;
+            if (!sdf_eval<NL, FAST>(x, runs, f, nv, reads)) {
+                prev = false;
+                jt += reread_sdf().half_h;
+                continue;
+            }
+            bool found = fabsf(f) <= reread_sdf().eps;
+            float h = jt;
+            if (!found && prev && ((f < 0.f) != (fp < 0.f))) {
+                h = tp + (jt - tp) * fp / (fp - f);
+                found = true;
+            }
+            if (found) {
+                th = h;
+                nn[0] = nv[0];
+                nn[1] = nv[1];
+                nn[2] = nv[2];
+                go = false;
+            }
+            prev = true;
+            fp = f;
+            tp = jt;
+            jt += fabsf(f);
+        }
+        __syncthreads();
+        M = keep;
+        float m = th;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) m = fminf(m, __shfl_xor(m, off, 64));
+        if (m < M.best) {
+            const int src = __ffsll((long long)__ballot(th == m)) - 1;
+            M.best = m;
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                M.bn[ax] = __shfl(nn[ax], src, 64);
+                M.bc[ax] = __shfl(jc[ax], src, 64);
+            }
+        }
+    }
+    best = M.best;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        bn[ax] = M.bn[ax];
+        bc[ax] = M.bc[ax];
+    }
+}
+
+// The next item of the tail list for this wave, or false when none is left.
+__device__ __forceinline__ bool tail_next(const SdfArgs& a, uint32_t& item) {
+    uint32_t q = 0;
+    if (lane_id() == 0) q = atomicAdd(&a.tail_cnt[1], 1u);
+    item = (uint32_t)__builtin_amdgcn_readfirstlane((int)q);
+    return item < min(a.tail_cnt[0], a.tail_cap);
+}
+
+// The rays left over by k_sdf, one wave each.
+template <int NL, bool FAST>
+__global__ __launch_bounds__(SDF_BLOCK) void k_sdf_tail(SdfArgs a) {
+    __shared__ SdfRuns runs;
+    __shared__ SdfMarch keep;
+    uint32_t item;
+    while (tail_next(a, item)) {
+        const uint32_t i = a.tail[item];
+        const size_t i3 = 3 * (size_t)i, i2 = 2 * (size_t)i;
+        const float o[3] = {a.o[i3], a.o[i3 + 1], a.o[i3 + 2]};
+        float d[3] = {a.d[i3], a.d[i3 + 1], a.d[i3 + 2]};
+        const float t_lo = a.tr ? a.tr[i2] : 0.f;
+        const float t_hi = a.tr ? a.tr[i2 + 1] : INFINITY;
+        const float len = sqrtf(dot3(d[0], d[1], d[2], d[0], d[1], d[2]));
+        const bool ok = len > 0.f && isfinite(len) && isfinite(o[0]) && isfinite(o[1]) && isfinite(o[2]);
+        float best = INFINITY, bn[3] = {0.f, 0.f, 0.f};
+        int bc[3] = {-1, -1, -1};
+        if (ok) {
+            const float il = 1.0f / len;
+            d[0] *= il;
+            d[1] *= il;
+            d[2] *= il;
+            wave_first_hit<NL, FAST>(runs, keep, o, d, t_lo, t_hi, best, bn, bc);
+        }
+        if (lane_id() == 0) sdf_write(a, i, o, d, best, bn, bc);
+    }
+}
+
+// The rays left over by k_sdf_launch, one wave each from the segment they had
+// reached.
+template <int NL, bool FAST>
+__global__ __launch_bounds__(SDF_BLOCK) void k_sdf_launch_tail(SdfLaunchArgs A) {
+    __shared__ SdfRuns runs;
+    __shared__ SdfMarch keep;
+    __shared__ float path;      // L, the ray and its segment, in LDS between the segments' ends
+    __shared__ uint32_t at[2];
+    const SdfArgs& a = A.s;
+    uint32_t item;
+    while (tail_next(a, item)) {
+        float o[3], d[3], t_lo;
+        const float4 O = a.tail_ray[2 * (size_t)item], D = a.tail_ray[2 * (size_t)item + 1];
+        o[0] = O.x;
+        o[1] = O.y;
+        o[2] = O.z;
+        d[0] = D.x;
+        d[1] = D.y;
+        d[2] = D.z;
+        t_lo = D.w;
+        path = O.w;
+        at[0] = a.tail[item];
+        at[1] = a.tail_b[item];
+        __syncthreads();
+        for (;;) {
+            float best, bn[3];
+            int bc[3];
+            wave_first_hit<NL, FAST>(runs, keep, o, d, t_lo, INFINITY, best, bn, bc);
+            // every lane ends the segment alike; lane 0 writes
+            const uint32_t b = at[1];
+            float L = path;
+            if (!segment_end<NL, FAST>(A, runs, at[0], (int)b, o, d, L, t_lo, best, bn, bc[0] >= 0, lane_id() == 0)) break;
+            __syncthreads();
+            path = L;
+            at[1] = b + 1u;
+            __syncthreads();
+            if (lane_id() == 0) atomicAdd(&A.counters[b + 1u], 1u);
+        }
+        __syncthreads();
     }
 }
 
@@ -763,11 +1029,47 @@ __global__ void k_sdf_launch_keys(const float* tx, const float* dirs, uint32_t n
     idx[g] = g;
 }
 
+// Samples of one segment after which a lane leaves its ray to the tail kernel
+// (at its first sample in bundles of at most SDF_TAIL_ALL rays), and room for
+// at least so many rays (a sixteenth of larger bundles; the rest stay with
+// their lanes).  A lane marches a ray's samples one after another at about
+// 20 us each, so a kernel lasts as long as its longest ray: of 500 k rays in a
+// 1M-point room the median takes 15 samples, 0.7 % more than 100 and the
+// longest, along a wall, 1,122.  A wave on one ray marches 64 of its leaves at
+// once, but also leaves behind the first hit.  The 500 k rays take 23.1 ms
+// without the tail and 31.5, 11.6, 9.7 and 12.8 ms with a budget of 24, 48, 96
+// and 192 (k_sdf 7.0, k_sdf_tail 2.1 ms at 96); a launch of 150 k rays with
+// two reflections (400 k points) 36.3, then 44.3, 24.7, 21.5 and 24.1 ms.
+constexpr uint32_t SDF_BUDGET = 96, SDF_TAIL_ALL = 4096, SDF_TAIL_MIN = 65536;
+
+// Waves of the tail kernel: four per SIMD stay resident.
+static unsigned tail_waves(uint32_t n) { return std::min<unsigned>(std::max(n, 1u), (unsigned)device_cus() * 16); }
+
+template <int NL, bool FAST>
+static void launch_sdf_fast(const SdfArgs& a, hipStream_t s) {
+    const unsigned grid = (a.n + SDF_BLOCK - 1) / SDF_BLOCK;
+    hipLaunchKernelGGL((k_sdf<NL, FAST>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
+    hipLaunchKernelGGL((k_sdf_tail<NL, FAST>), dim3(tail_waves(a.n)), dim3(SDF_BLOCK), 0, s, a);
+}
+
 template <int NL>
 static void launch_sdf_nl(const SdfArgs& a, hipStream_t s) {
-    const unsigned grid = (a.n + SDF_BLOCK - 1) / SDF_BLOCK;
-    if (a.cells || a.empty) hipLaunchKernelGGL((k_sdf<NL, true>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
-    else if constexpr (NL > 1) hipLaunchKernelGGL((k_sdf<NL, false>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
+    if (NL == 1 || a.cells || a.empty) launch_sdf_fast<NL, true>(a, s);
+    else launch_sdf_fast<NL, NL == 1>(a, s);
+}
+
+// The tail list of n rays (in T), empty; launches keep their rays' state too.
+static int tail_alloc(SdfArgs& a, uint32_t n, bool launch, DevBufs& T, hipStream_t s) {
+    // counted runs march every ray on its lane: the counts are those of the serial march
+    a.budget = a.stats ? ~0u : n <= SDF_TAIL_ALL ? 0u : SDF_BUDGET;
+    a.tail_cap = std::min(n, std::max(n / 16, SDF_TAIL_MIN));
+    n = std::max(a.tail_cap, 1u);
+    PCRL_TRY(T.alloc(&a.tail_cnt, 2));
+    PCRL_TRY(fill_u32(a.tail_cnt, 0u, 2, s));
+    PCRL_TRY(T.alloc(&a.tail, (size_t)n));
+    if (!launch) return PCRL_OK;
+    PCRL_TRY(T.alloc(&a.tail_ray, 2 * (size_t)n));
+    return T.alloc(&a.tail_b, (size_t)n);
 }
 
 // Largest table of own entries before each cell (4 bytes per leaf cell of
@@ -930,11 +1232,17 @@ static void sdf_defaults(const PcrlScene* scene, SdfArgs& a) {
     a.empty = scene->info.n_points == 0;
 }
 
+template <int NL, bool FAST>
+static void launch_sdf_launch_fast(const SdfLaunchArgs& A, hipStream_t s) {
+    const unsigned grid = (A.n_total + SDF_BLOCK - 1) / SDF_BLOCK;
+    hipLaunchKernelGGL((k_sdf_launch<NL, FAST>), dim3(grid), dim3(SDF_BLOCK), 0, s, A);
+    hipLaunchKernelGGL((k_sdf_launch_tail<NL, FAST>), dim3(tail_waves(A.n_total)), dim3(SDF_BLOCK), 0, s, A);
+}
+
 template <int NL>
 static void launch_sdf_launch_nl(const SdfLaunchArgs& A, hipStream_t s) {
-    const unsigned grid = (A.n_total + SDF_BLOCK - 1) / SDF_BLOCK;
-    if (A.s.cells || A.s.empty) hipLaunchKernelGGL((k_sdf_launch<NL, true>), dim3(grid), dim3(SDF_BLOCK), 0, s, A);
-    else if constexpr (NL > 1) hipLaunchKernelGGL((k_sdf_launch<NL, false>), dim3(grid), dim3(SDF_BLOCK), 0, s, A);
+    if (NL == 1 || A.s.cells || A.s.empty) launch_sdf_launch_fast<NL, true>(A, s);
+    else launch_sdf_launch_fast<NL, NL == 1>(A, s);
 }
 
 int sdf_launch_run(PcrlLaunch* L, const TraceArgs& t) {
@@ -980,6 +1288,7 @@ int sdf_launch_run(PcrlLaunch* L, const TraceArgs& t) {
         PCRL_TRY(radix_sort_u64_bits(keys, idx, (int64_t)A.n_total, 0, 28, s));
         A.order = idx;
     }
+    PCRL_TRY(tail_alloc(A.s, A.n_total, true, L->bufs, s));
     const bool timing = !L->events.empty();
     if (timing) PCRL_TRY_HIP(hipEventRecord(L->events[0], s));
     switch (scene->view.nlev) {
@@ -1081,6 +1390,10 @@ extern "C" int sdf_intersect(const PcrlScene* scene, const float* o, const float
             return rc;
         }
         a.order = idx;
+    }
+    if (const int rc = tail_alloc(a, (uint32_t)n_rays, false, T, s)) {
+        T.release();
+        return rc;
     }
     switch (scene->view.nlev) {
     case 1: launch_sdf_nl<1>(a, s); break;
