@@ -26,12 +26,13 @@
 // converged path is kept if every interaction has both neighbours on one
 // side of its surfel and the last segment reaches the RX unblocked.
 //
-// Lane = path, with few paths per wave (one, unless the paths outnumber the
-// GPU's SIMDs): a wave iterates in lockstep until all its paths are done, and
-// all 64 lanes share the leaf tests of its rays (traversal and leaf tests are
-// the launcher's own, trace_core.h).  The per-path interaction state lives
-// in global arrays [k][path] (a dynamically indexed private array would be
-// placed in scratch memory).
+// A group of 64, 32, 16 or 8 lanes per path, the fewer the more paths there
+// are; a wave iterates in lockstep until all its paths are done.  A path is a
+// chain of up to 2000 iterations of dependent rays, so what counts is the time
+// of one ray: its lanes walk parts of it side by side, and all 64 lanes share
+// the leaf tests of the wave's rays (traversal and leaf tests are the
+// launcher's own, trace_core.h).  Lane k of a group steps interaction k.  The
+// interactions' state lies in LDS.
 //
 // Dedup of the valid paths of one (TX, RX, number of reflections) group, in
 // order of increasing length: a path whose label sequence already occurred
@@ -59,15 +60,12 @@ struct RefineArgs {
     const int32_t* p_n;         // per path: reflections N
     const float* p_pts;         // [n][K][3] coarse interaction points
     uint32_t n;
-    uint32_t ppw;               // paths per wave (lanes 0..ppw-1 hold one each; the others help the leaf tests)
+    uint32_t group;             // log2 of the lanes per path (3..6)
     int32_t K;
     int32_t max_iters;
     float grad_tol;
     float step;
     float smooth_h2;            // > 0: surface normals averaged over this squared radius
-    float4* cpos;               // [K][n] current point, surfel id (bits)
-    float4* cnrm;               // [K][n] its surfel's normal, label (bits)
-    float4* tgt;                // [K][n] point the next trace aims at
     int32_t* status;
     int32_t* iters;
     float* grad;
@@ -84,13 +82,15 @@ struct RefineArgs {
     float clear;                // r_s: the clearance at a diffraction point
 };
 
-__device__ __forceinline__ int edge_at(const RefineArgs& a, uint32_t p, int k) {
-    return a.p_edge ? a.p_edge[(size_t)p * a.K + k] : -1;
+// The fused forms are written out: a descent amplifies a last bit, so results
+// must not depend on the compiler's choice.
+__device__ __forceinline__ float dot3f(float ax, float ay, float az, float bx, float by, float bz) {
+    return fmaf(az, bz, fmaf(ax, bx, ay * by));
 }
 
 __device__ __forceinline__ float dist3(const float a[3], const float b[3]) {
     const float x = a[0] - b[0], y = a[1] - b[1], z = a[2] - b[2];
-    return sqrtf(x * x + y * y + z * z);
+    return sqrtf(dot3f(x, y, z, x, y, z));
 }
 
 // The largest value of x over the wave (x >= 0).
@@ -98,10 +98,71 @@ __device__ __forceinline__ int wave_max(int x) {
     return __builtin_amdgcn_readlane(wave_scan_max_dpp(x), 63);
 }
 
-// Trace every lane's ray from o towards `target`, starting `skip` along its
-// direction (lanes with `act` false only help with the leaf tests).  Returns
+// State of the wave's paths: interaction k of the path of lanes
+// [g << group, (g + 1) << group) at 8 g + k.
+struct PathLds {
+    float4 pos[64];   // current point, surfel id (bits)
+    float4 nrm[64];   // its surfel's normal, label (bits)
+    float4 tgt[64];   // point the next trace aims at (diffractions: t along the edge in w)
+    int32_t edge[64]; // its edge, -1 a reflection
+    float gg[64];     // its part of the squared gradient
+    uint32_t first[8][28];  // smooth normals: entries before each of the 27 leaves, and of all
+    uint32_t begin[8][27];  // their first entries
+};
+
+// The nearest hit of each group's ray (staged in every lane of the group)
+// between t0 and t1 of each of its walking lanes, nearer than `hit` so far.
+// Exact: the launcher's walk finds every hit nearer than its start value from
+// the cell at its start on, and the nearest over the lanes' parts is that of
+// the whole.
+template <int TD, bool OVL>
+__device__ __forceinline__ void trace_parts(const uint64_t* ahead, WaveLds& W, uint32_t lead, bool walks, float t0, float t1,
+                                            Hit& hit) {
+    const TraceArgs& a = reread(kernel_args());
+    const SceneView& v = OVL ? a.ov : a.v;
+    const uint32_t lane = lane_id();
+    const unsigned long long old = hit_word(hit.t, hit.id), end = hit_word(t1, NO_HIT);
+    const unsigned long long before = old < end ? old : end;
+    W.best[lane] = before;
+    wave_sync();
+    walk<false, TD>(v, ahead, W, walks, nullptr, t0);
+    const unsigned long long b = W.best[lane];
+    const uint32_t entry = W.entry[lane];
+    const bool mine = walks && b != before;
+    wave_sync();
+    W.best[lane] = ~0ull;
+    wave_sync();
+    if (mine) atomicMin(&W.best[lead], b);
+    wave_sync();
+    if (mine && W.best[lead] == b) W.entry[lead] = entry;  // equal (t, id): the same point
+    wave_sync();
+    const unsigned long long B = W.best[lead];
+    if (B < old) {
+        const float4 N = v.snrm[W.entry[lead]];
+        hit.t = __uint_as_float((uint32_t)(B >> 32));
+        hit.id = (uint32_t)B;
+        hit.nx = N.x;
+        hit.ny = N.y;
+        hit.nz = N.z;
+        hit.lab = __float_as_uint(N.w);
+    }
+    wave_sync();
+}
+
+// Leaves of a ray that one lane walks, at least.  Bound by the latency of one
+// path's chain of rays (a room's 611 paths occupy 611 of 1,024 SIMDs): about
+// 5.6 us a ray, four steps of the walk and three passes of leaf tests.  1M
+// points, 16 RX, three reflections: 33.6, 38.6, 40.0, 45.5 ms with 1, 2, 4, 8
+// leaves (34.9 with half a leaf); 87.1 ms when one lane walked each ray and
+// the interactions lay in global memory.
+constexpr float PART_LEAVES = 1.f;
+
+// Trace every group's ray from o towards `target`, starting `skip` along its
+// direction (groups with `act` false only help with the leaf tests).  Returns
 // the hit in `hit` (t from the start os = o + skip d); `len` is the distance
-// from o to the target (0: the target is o, no ray).
+// from o to the target (0: the target is o, no ray).  The target lies at or
+// near a surface: the lanes of a group walk parts of the ray up to a little
+// beyond it, and the first lane goes on from there if none finds a hit.
 template <int TD, bool OV>
 __device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_t* ahead, WaveLds& W, bool act, const float o[3],
                                               const float target[3], uint32_t last, float skip, Hit& hit, float d[3],
@@ -109,7 +170,7 @@ __device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_
     d[0] = target[0] - o[0];
     d[1] = target[1] - o[1];
     d[2] = target[2] - o[2];
-    len = sqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+    len = sqrtf(fmaf(d[2], d[2], fmaf(d[1], d[1], d[0] * d[0])));
     const bool go = act && len > 0.f;
     if (go) {
         const float inv = 1.0f / len;
@@ -120,13 +181,25 @@ __device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_
         d[0] = 1.f;
         d[1] = d[2] = 0.f;
     }
-    os[0] = o[0] + skip * d[0];
-    os[1] = o[1] + skip * d[1];
-    os[2] = o[2] + skip * d[2];
+    os[0] = fmaf(skip, d[0], o[0]);
+    os[1] = fmaf(skip, d[1], o[1]);
+    os[2] = fmaf(skip, d[2], o[2]);
     hit_reset(hit);
     stage_ray(W, os, d, last);
-    trace_segment<false, TD, false>(kernel_args(), ahead, W, go, hit, nullptr);
-    if (OV) trace_segment<false, TD, true>(kernel_args(), ahead, W, go, hit, nullptr);
+    const uint32_t G = 1u << a.group, j = lane_id() & (G - 1u), lead = lane_id() - j;
+    const float near = fmaf(len, 1.001f, 2.f * a.t.v.h);
+    // a non-finite ray walks nowhere
+    const float parts = fminf(fmaxf(ceilf(near * a.t.v.inv_h * (1.f / PART_LEAVES)), 1.f), (float)G);
+    const float part = near / parts, t0 = (float)j * part, t1 = (float)(j + 1u) * part;
+    const bool walks = go && (float)j < parts;
+    trace_parts<TD, false>(ahead, W, lead, walks, t0, t1, hit);
+    if (OV) trace_parts<TD, true>(ahead, W, lead, walks, t0, t1, hit);
+    const bool on = go && hit.id == NO_HIT;
+    if (ballot(on)) {
+        const float from = parts * part;
+        trace_parts<TD, false>(ahead, W, lead, on && j == 0, from, INFINITY, hit);
+        if (OV) trace_parts<TD, true>(ahead, W, lead, on && j == 0, from, INFINITY, hit);
+    }
 }
 
 // Add the weighted normals of the points of hierarchy v within sqrt(h2) of c
@@ -134,39 +207,71 @@ __device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_
 // with nh).  h2 is below one leaf edge squared, so the points lie in the 27
 // leaves around c's; a point is taken from the leaf holding its centre only
 // (every leaf its disk meets lists it).
+// The lanes of a group (c and nh are the same in all) look one leaf each up
+// and test the points between them; the accepted ones are added in the order
+// of the leaves and of their entries.
 template <int TD>
-__device__ __forceinline__ void gather_normals(const SceneView& v, const float c[3], float h2, const float nh[3],
-                                               float acc[3]) {
+__device__ __forceinline__ void gather_normals(const SceneView& v, WaveLds& W, PathLds& S, uint32_t group, const float c[3],
+                                               float h2, const float nh[3], float acc[3]) {
+    const uint32_t G = 1u << group, lane = lane_id(), j = lane & (G - 1u), lead = lane - j, g = lane >> group;
+    uint32_t* const first = S.first[g];
+    uint32_t* const begin = S.begin[g];
     int lc[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) lc[a] = (int)floorf((c[a] - v.org[a]) * v.inv_h);
-    for (int dz = -1; dz <= 1; ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int cell[3] = {lc[0] + dx, lc[1] + dy, lc[2] + dz};
-                if (cell[0] < 0 || cell[1] < 0 || cell[2] < 0 || cell[0] >= v.dim[0] || cell[1] >= v.dim[1] ||
-                    cell[2] >= v.dim[2])
-                    continue;
-                const uint2 r = leaf_range<TD>(v, cell[0], cell[1], cell[2]);
-                for (uint32_t e = r.x; e < r.x + r.y; ++e) {
-                    const float4 P = v.spos[e];
-                    const float x = P.x - c[0], y = P.y - c[1], z = P.z - c[2];
-                    const float d2 = x * x + y * y + z * z;
-                    if (!(d2 < h2)) continue;
-                    if ((int)floorf((P.x - v.org[0]) * v.inv_h) != cell[0] ||
-                        (int)floorf((P.y - v.org[1]) * v.inv_h) != cell[1] ||
-                        (int)floorf((P.z - v.org[2]) * v.inv_h) != cell[2])
-                        continue;
-                    const float4 N = v.snrm[e];
-                    float w = 1.0f - d2 / h2;
-                    w *= w;
-                    w *= w;
-                    if (N.x * nh[0] + N.y * nh[1] + N.z * nh[2] < 0.f) w = -w;
-                    acc[0] += w * N.x;
-                    acc[1] += w * N.y;
-                    acc[2] += w * N.z;
-                }
-            }
+    for (int q = (int)j; q < 27; q += (int)G) {
+        const int cell[3] = {lc[0] + q % 3 - 1, lc[1] + q / 3 % 3 - 1, lc[2] + q / 9 - 1};
+        uint2 r = make_uint2(0u, 0u);
+        if (cell[0] >= 0 && cell[1] >= 0 && cell[2] >= 0 && cell[0] < v.dim[0] && cell[1] < v.dim[1] &&
+            cell[2] < v.dim[2])
+            r = leaf_range<TD>(v, cell[0], cell[1], cell[2]);
+        begin[q] = r.x;
+        first[q + 1] = r.y;
+    }
+    wave_sync();
+    if (j == 0) {
+        uint32_t sum = 0;
+        first[0] = 0;
+        for (int q = 1; q <= 27; ++q) {
+            sum += first[q];
+            first[q] = sum;
+        }
+    }
+    wave_sync();
+    const uint32_t total = first[27];
+    for (uint32_t base = 0; base < total; base += G) {
+        const uint32_t f = min(base + j, total - 1u);
+        uint32_t lo = 0, hi = 26;  // the leaf holding entry f: the last with first[leaf] <= f
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1u) >> 1;
+            if (first[mid] <= f) lo = mid;
+            else hi = mid - 1u;
+        }
+        const uint32_t e = begin[lo] + (f - first[lo]);
+        const float4 P = v.spos[e], N = v.snrm[e];
+        const float x = P.x - c[0], y = P.y - c[1], z = P.z - c[2];
+        const float d2 = dot3f(x, y, z, x, y, z);
+        const int cell[3] = {lc[0] + (int)(lo % 3u) - 1, lc[1] + (int)(lo / 3u % 3u) - 1, lc[2] + (int)(lo / 9u) - 1};
+        const bool ok = base + j < total && d2 < h2 && (int)floorf((P.x - v.org[0]) * v.inv_h) == cell[0] &&
+                        (int)floorf((P.y - v.org[1]) * v.inv_h) == cell[1] &&
+                        (int)floorf((P.z - v.org[2]) * v.inv_h) == cell[2];
+        float w = 1.0f - d2 / h2;
+        w *= w;
+        w *= w;
+        if (dot3f(nh[0], nh[1], nh[2], N.x, N.y, N.z) < 0.f) w = -w;
+        wave_sync();
+        W.o[lane] = make_float4(N.x, N.y, N.z, w);
+        wave_sync();
+        uint64_t m = (ballot(ok) >> lead) & (~0ull >> (64u - G));
+        while (m) {
+            const float4 A = W.o[lead + (uint32_t)__ffsll((long long)m) - 1u];
+            m &= m - 1ull;
+            acc[0] = fmaf(A.x, A.w, acc[0]);
+            acc[1] = fmaf(A.y, A.w, acc[1]);
+            acc[2] = fmaf(A.z, A.w, acc[2]);
+        }
+    }
+    wave_sync();
 }
 
 __device__ __forceinline__ void load3(const float4* p, float x[3]) {
@@ -179,11 +284,12 @@ __device__ __forceinline__ void load3(const float4* p, float x[3]) {
 template <int TD, bool OV>
 __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     __shared__ TraceLds<1> lds;
+    __shared__ PathLds S;
     ahead_init(lds.ahead, threadIdx.x, REFINE_BLOCK);
     __syncthreads();
-    const uint32_t p = blockIdx.x * a.ppw + threadIdx.x;
-    const bool in = threadIdx.x < a.ppw && p < a.n;
-    const size_t n = a.n;
+    const uint32_t G = 1u << a.group, j = lane_id() & (G - 1u), s0 = 8u * (lane_id() >> a.group);
+    const uint32_t p = (blockIdx.x << (6u - a.group)) + (lane_id() >> a.group);
+    const bool in = p < a.n;
     int N = 0;
     float T[3] = {0.f, 0.f, 0.f}, R[3] = {0.f, 0.f, 0.f};
     if (in) {
@@ -195,16 +301,17 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         R[0] = a.rx[3 * ri];
         R[1] = a.rx[3 * ri + 1];
         R[2] = a.rx[3 * ri + 2];
-        for (int k = 0; k < N; ++k) {
-            const float* q = a.p_pts + ((size_t)p * a.K + k) * 3;
+        if ((int)j < N) {
+            const float* q = a.p_pts + ((size_t)p * a.K + j) * 3;
             // a diffraction point starts at the coarse point's projection onto its edge (t in w)
             float t = 0.f;
-            const int e = edge_at(a, p, k);
+            const int e = a.p_edge ? a.p_edge[(size_t)p * a.K + j] : -1;
             if (e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
-                t = (q[0] - A.x) * Wd.x + (q[1] - A.y) * Wd.y + (q[2] - A.z) * Wd.z;
+                t = dot3f(q[0] - A.x, q[1] - A.y, q[2] - A.z, Wd.x, Wd.y, Wd.z);
             }
-            a.tgt[k * n + p] = make_float4(q[0], q[1], q[2], t);
+            S.tgt[s0 + j] = make_float4(q[0], q[1], q[2], t);
+            S.edge[s0 + j] = e;
         }
     }
     const int nmax = wave_max(N);
@@ -212,7 +319,8 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     int it = 0;
     float gnorm = 0.f;
     bool run = in && N > 0;
-    while (__ballot(run)) {
+    wave_sync();
+    while (ballot(run)) {
         // the interaction points: diffraction points on their edges, reflection points where the
         // rays towards the targets hit
         float o[3] = {T[0], T[1], T[2]};
@@ -220,21 +328,21 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         float skip = 0.f;
         for (int k = 0; k < nmax; ++k) {
             const bool act = run && k < N;
-            const int e = act ? edge_at(a, p, k) : -1;
+            const int e = act ? S.edge[s0 + k] : -1;
             float tg[3] = {0.f, 0.f, 0.f}, d[3], os[3], len;
-            if (act) load3(&a.tgt[k * n + p], tg);
+            if (act) load3(&S.tgt[s0 + k], tg);
             Hit hit;
             trace_towards<TD, OV>(a, lds.ahead, lds.w[0], act && e < 0, o, tg, last, skip, hit, d, os, len);
             if (act && e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
-                const float t = a.tgt[k * n + p].w;
-                o[0] = A.x + t * Wd.x;
-                o[1] = A.y + t * Wd.y;
-                o[2] = A.z + t * Wd.z;
+                const float t = S.tgt[s0 + k].w;
+                o[0] = fmaf(t, Wd.x, A.x);
+                o[1] = fmaf(t, Wd.y, A.y);
+                o[2] = fmaf(t, Wd.z, A.z);
                 last = NO_HIT;
                 skip = a.clear;
-                a.cpos[k * n + p] = make_float4(o[0], o[1], o[2], __uint_as_float(NO_HIT));
-                a.cnrm[k * n + p] = make_float4(0.f, 0.f, 0.f, Wd.w);
+                S.pos[s0 + k] = make_float4(o[0], o[1], o[2], __uint_as_float(NO_HIT));
+                S.nrm[s0 + k] = make_float4(0.f, 0.f, 0.f, Wd.w);
             } else if (act) {
                 if (!(len > 0.f)) {
                     status = PCRL_REFINE_DEGENERATE;
@@ -243,78 +351,77 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                     status = PCRL_REFINE_MISS;
                     run = false;
                 } else {
-                    o[0] = os[0] + hit.t * d[0];
-                    o[1] = os[1] + hit.t * d[1];
-                    o[2] = os[2] + hit.t * d[2];
+                    o[0] = fmaf(hit.t, d[0], os[0]);
+                    o[1] = fmaf(hit.t, d[1], os[1]);
+                    o[2] = fmaf(hit.t, d[2], os[2]);
                     last = hit.id;
                     skip = 0.f;
                     float nr[3] = {hit.nx, hit.ny, hit.nz};
                     if (a.smooth_h2 > 0.f) {
                         float acc[3] = {0.f, 0.f, 0.f};
-                        gather_normals<TD>(a.t.v, o, a.smooth_h2, nr, acc);
-                        if (OV) gather_normals<TD>(a.t.ov, o, a.smooth_h2, nr, acc);
-                        const float l = sqrtf(acc[0] * acc[0] + acc[1] * acc[1] + acc[2] * acc[2]);
+                        gather_normals<TD>(a.t.v, lds.w[0], S, a.group, o, a.smooth_h2, nr, acc);
+                        if (OV) gather_normals<TD>(a.t.ov, lds.w[0], S, a.group, o, a.smooth_h2, nr, acc);
+                        const float l = sqrtf(dot3f(acc[0], acc[1], acc[2], acc[0], acc[1], acc[2]));
                         if (l > 0.f) {
                             nr[0] = acc[0] / l;
                             nr[1] = acc[1] / l;
                             nr[2] = acc[2] / l;
                         }
                     }
-                    a.cpos[k * n + p] = make_float4(o[0], o[1], o[2], __uint_as_float(hit.id));
-                    a.cnrm[k * n + p] = make_float4(nr[0], nr[1], nr[2], __uint_as_float(hit.lab));
+                    S.pos[s0 + k] = make_float4(o[0], o[1], o[2], __uint_as_float(hit.id));
+                    S.nrm[s0 + k] = make_float4(nr[0], nr[1], nr[2], __uint_as_float(hit.lab));
                 }
             }
         }
-        if (!run) continue;
+        wave_sync();
         // gradient of the path length (tangent planes of reflections, edge directions of
-        // diffractions) and the next targets
-        float prev[3] = {T[0], T[1], T[2]}, cur[3], next[3];
-        load3(&a.cpos[p], cur);
-        float gg = 0.f;
-        bool off = false;
-        for (int k = 0; k < N; ++k) {
-            if (k + 1 < N) load3(&a.cpos[(k + 1) * n + p], next);
-            else {
-                next[0] = R[0];
-                next[1] = R[1];
-                next[2] = R[2];
-            }
+        // diffractions) and the next targets: lane k's of interaction k
+        bool off = false, degenerate = false;
+        if (run && (int)j < N) {
+            const int k = (int)j;
+            float prev[3] = {T[0], T[1], T[2]}, cur[3], next[3] = {R[0], R[1], R[2]};
+            load3(&S.pos[s0 + k], cur);
+            if (k > 0) load3(&S.pos[s0 + k - 1], prev);
+            if (k + 1 < N) load3(&S.pos[s0 + k + 1], next);
             const float lp = dist3(cur, prev), ln = dist3(cur, next);
-            if (!(lp > 0.f) || !(ln > 0.f)) {
-                status = PCRL_REFINE_DEGENERATE;
-                run = false;
-                break;
-            }
-            float G[3];
+            degenerate = !(lp > 0.f) || !(ln > 0.f);
+            float G3[3];
 #pragma unroll
-            for (int j = 0; j < 3; ++j) G[j] = (cur[j] - prev[j]) / lp + (cur[j] - next[j]) / ln;
+            for (int x = 0; x < 3; ++x) G3[x] = (cur[x] - prev[x]) / lp + (cur[x] - next[x]) / ln;
             const float ak = a.step / (1.0f / lp + 1.0f / ln);
-            const int e = edge_at(a, p, k);
+            const int e = S.edge[s0 + k];
             if (e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
-                const float gw = G[0] * Wd.x + G[1] * Wd.y + G[2] * Wd.z;
-                gg += gw * gw;
-                const float4 tq = a.tgt[k * n + p];
-                const float t = tq.w - ak * gw;
-                off = off || !(t >= 0.f && t <= A.w);
-                a.tgt[k * n + p] = make_float4(tq.x, tq.y, tq.z, t);
+                const float gw = dot3f(G3[0], G3[1], G3[2], Wd.x, Wd.y, Wd.z);
+                S.gg[s0 + k] = gw * gw;
+                const float4 tq = S.tgt[s0 + k];
+                const float t = fmaf(-ak, gw, tq.w);
+                off = !(t >= 0.f && t <= A.w);
+                S.tgt[s0 + k] = make_float4(tq.x, tq.y, tq.z, t);
             } else {
                 float nrm[3];
-                load3(&a.cnrm[k * n + p], nrm);
-                const float gn = G[0] * nrm[0] + G[1] * nrm[1] + G[2] * nrm[2];
+                load3(&S.nrm[s0 + k], nrm);
+                const float gn = dot3f(G3[0], G3[1], G3[2], nrm[0], nrm[1], nrm[2]);
                 float g[3];
 #pragma unroll
-                for (int j = 0; j < 3; ++j) g[j] = G[j] - gn * nrm[j];
-                gg += g[0] * g[0] + g[1] * g[1] + g[2] * g[2];
-                a.tgt[k * n + p] = make_float4(cur[0] - ak * g[0], cur[1] - ak * g[1], cur[2] - ak * g[2], 0.f);
-            }
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                prev[j] = cur[j];
-                cur[j] = next[j];
+                for (int x = 0; x < 3; ++x) g[x] = fmaf(-gn, nrm[x], G3[x]);
+                S.gg[s0 + k] = dot3f(g[0], g[1], g[2], g[0], g[1], g[2]);
+                S.tgt[s0 + k] = make_float4(fmaf(-ak, g[0], cur[0]), fmaf(-ak, g[1], cur[1]), fmaf(-ak, g[2], cur[2]), 0.f);
             }
         }
+        const uint64_t mine = ~0ull >> (64u - G);
+        const uint32_t lead = lane_id() - j;
+        degenerate = ((ballot(degenerate) >> lead) & mine) != 0;
+        off = ((ballot(off) >> lead) & mine) != 0;
+        wave_sync();
         if (!run) continue;
+        if (degenerate) {
+            status = PCRL_REFINE_DEGENERATE;
+            run = false;
+            continue;
+        }
+        float gg = 0.f;
+        for (int k = 0; k < N; ++k) gg += S.gg[s0 + k];
         gnorm = sqrtf(gg);
         if (gnorm < a.grad_tol) {
             run = false;  // converged
@@ -332,15 +439,15 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     // outside its edge's wedge
     if (in && status == PCRL_REFINE_VALID && N > 0) {
         float prev[3] = {T[0], T[1], T[2]}, cur[3], next[3], nrm[3];
-        load3(&a.cpos[p], cur);
+        load3(&S.pos[s0], cur);
         for (int k = 0; k < N; ++k) {
-            if (k + 1 < N) load3(&a.cpos[(k + 1) * n + p], next);
+            if (k + 1 < N) load3(&S.pos[s0 + k + 1], next);
             else {
                 next[0] = R[0];
                 next[1] = R[1];
                 next[2] = R[2];
             }
-            const int e = edge_at(a, p, k);
+            const int e = S.edge[s0 + k];
             bool ok;
             if (e >= 0) {
                 const float4 N1 = a.e_n1[e], N2 = a.e_n2[e];
@@ -350,12 +457,12 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                 const float q2 = (next[0] - cur[0]) * N2.x + (next[1] - cur[1]) * N2.y + (next[2] - cur[2]) * N2.z;
                 ok = (p1 > 0.f || p2 > 0.f) && (q1 > 0.f || q2 > 0.f);
             } else {
-                load3(&a.cnrm[k * n + p], nrm);
+                load3(&S.nrm[s0 + k], nrm);
                 float sp = 0.f, sn = 0.f;
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    sp += (prev[j] - cur[j]) * nrm[j];
-                    sn += (next[j] - cur[j]) * nrm[j];
+                for (int x = 0; x < 3; ++x) {
+                    sp += (prev[x] - cur[x]) * nrm[x];
+                    sn += (next[x] - cur[x]) * nrm[x];
                 }
                 ok = sp * sn > 0.f;
             }
@@ -364,27 +471,27 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                 break;
             }
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                prev[j] = cur[j];
-                cur[j] = next[j];
+            for (int x = 0; x < 3; ++x) {
+                prev[x] = cur[x];
+                cur[x] = next[x];
             }
         }
     }
     // segments arriving at a diffraction point: blocked by a hit more than r_s before it
     if (a.p_edge) {
         for (int k = 0; k < nmax; ++k) {
-            const bool act = in && status == PCRL_REFINE_VALID && k < N && edge_at(a, p, k) >= 0;
+            const bool act = in && status == PCRL_REFINE_VALID && k < N && S.edge[s0 + k] >= 0;
             float o[3] = {T[0], T[1], T[2]}, tg[3] = {0.f, 0.f, 0.f};
             uint32_t last = NO_HIT;
             float skip = 0.f;
             if (act) {
-                load3(&a.cpos[k * n + p], tg);
+                load3(&S.pos[s0 + k], tg);
                 if (k > 0) {
-                    const float4 c = a.cpos[(k - 1) * n + p];
+                    const float4 c = S.pos[s0 + k - 1];
                     o[0] = c.x;
                     o[1] = c.y;
                     o[2] = c.z;
-                    if (edge_at(a, p, k - 1) >= 0) skip = a.clear;
+                    if (S.edge[s0 + k - 1] >= 0) skip = a.clear;
                     else last = __float_as_uint(c.w);
                 }
             }
@@ -404,11 +511,11 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         uint32_t last = NO_HIT;
         float skip = 0.f;
         if (act && N > 0) {
-            const float4 c = a.cpos[(N - 1) * n + p];
+            const float4 c = S.pos[s0 + N - 1];
             o[0] = c.x;
             o[1] = c.y;
             o[2] = c.z;
-            if (edge_at(a, p, N - 1) >= 0) skip = a.clear;
+            if (S.edge[s0 + N - 1] >= 0) skip = a.clear;
             else last = __float_as_uint(c.w);
         }
         float d[3], os[3], len;
@@ -421,34 +528,31 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     }
     if (!in) return;
     const bool finite = status != PCRL_REFINE_MISS && status != PCRL_REFINE_DEGENERATE;
+    if ((int)j < a.K) {
+        const size_t r = (size_t)p * a.K + j;
+        const bool has = finite && (int)j < N;
+        const float4 c = has ? S.pos[s0 + j] : make_float4(NAN, NAN, NAN, __uint_as_float(0xFFFFFFFFu));
+        float* q = a.out_pts + r * 3;
+        q[0] = c.x;
+        q[1] = c.y;
+        q[2] = c.z;
+        const int e = has ? S.edge[s0 + j] : -1;
+        a.out_id[r] = e >= 0 ? -2 - e : (int32_t)__float_as_uint(c.w);
+        a.out_key[r] = has ? (int64_t)__float_as_uint(S.nrm[s0 + j].w) : -1;
+    }
+    if (j != 0) return;
     float f = 0.f;
     if (finite) {
         float prev[3] = {T[0], T[1], T[2]}, cur[3];
         for (int k = 0; k < N; ++k) {
-            const float4 c = a.cpos[k * n + p];
-            const float4 m = a.cnrm[k * n + p];
-            cur[0] = c.x;
-            cur[1] = c.y;
-            cur[2] = c.z;
+            load3(&S.pos[s0 + k], cur);
             f += dist3(cur, prev);
             prev[0] = cur[0];
             prev[1] = cur[1];
             prev[2] = cur[2];
-            float* q = a.out_pts + ((size_t)p * a.K + k) * 3;
-            q[0] = c.x;
-            q[1] = c.y;
-            q[2] = c.z;
-            const int e = edge_at(a, p, k);
-            a.out_id[(size_t)p * a.K + k] = e >= 0 ? -2 - e : (int32_t)__float_as_uint(c.w);
-            a.out_key[(size_t)p * a.K + k] = (int64_t)__float_as_uint(m.w);
         }
-        f += dist3(R, prev);
-    }
-    for (int k = finite ? N : 0; k < a.K; ++k) {
-        float* q = a.out_pts + ((size_t)p * a.K + k) * 3;
-        q[0] = q[1] = q[2] = NAN;
-        a.out_id[(size_t)p * a.K + k] = -1;
-        a.out_key[(size_t)p * a.K + k] = -1;
+        const float x = R[0] - prev[0], y = R[1] - prev[1], z = R[2] - prev[2];
+        f += sqrtf(fmaf(z, z, fmaf(y, y, x * x)));
     }
     a.status[p] = status;
     a.iters[p] = it;
@@ -575,7 +679,8 @@ __global__ __launch_bounds__(64) void k_refine_sweep(const uint64_t* skey, const
 
 template <int TD>
 static void launch_refine_td(const RefineArgs& a, hipStream_t s) {
-    const unsigned grid = (a.n + a.ppw - 1) / a.ppw;
+    const uint32_t ppw = 64u >> a.group;
+    const unsigned grid = (a.n + ppw - 1) / ppw;
     if (a.t.has_ov) hipLaunchKernelGGL((k_refine<TD, true>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
     else hipLaunchKernelGGL((k_refine<TD, false>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
 }
@@ -681,12 +786,10 @@ extern "C" int refine_paths(const PcrlScene* scene, const float* tx, int32_t n_t
     a.p_n = paths->n_refl;
     a.p_pts = paths->points;
     a.n = (uint32_t)n;
-    // paths per wave: a path's iterations run in lockstep with the wave's other paths, so
-    // few paths per wave (down to one) as long as the waves still fill the GPU (one per SIMD)
-    {
-        const int64_t waves = (int64_t)device_cus() * 4;
-        a.ppw = (uint32_t)std::min<int64_t>(REFINE_BLOCK, std::max<int64_t>(1, (n + waves - 1) / waves));
-    }
+    // lanes per path: a wave each as long as the waves find room at once (three per SIMD: 13 KB of
+    // LDS each), since a wave's paths wait for its slowest; eight lanes at least (one per interaction)
+    a.group = 6;
+    while (a.group > 3 && n > ((int64_t)device_cus() * 12 << (6 - a.group))) --a.group;
     a.K = k_stride;
     a.max_iters = max_iters;
     a.grad_tol = grad_tol;
@@ -702,11 +805,7 @@ extern "C" int refine_paths(const PcrlScene* scene, const float* tx, int32_t n_t
     uint64_t* keys = nullptr;
     uint32_t *idx = nullptr, *counters = nullptr;
     int rc = PCRL_OK;
-    if (k_stride > 0) {
-        const size_t m = (size_t)k_stride * n;
-        if (!(rc = T.alloc(&a.cpos, m)) && !(rc = T.alloc(&a.cnrm, m))) rc = T.alloc(&a.tgt, m);
-    }
-    if (!rc && !(rc = T.alloc(&keys, n)) && !(rc = T.alloc(&idx, n))) rc = T.alloc(&counters, 2);
+    if (!(rc = T.alloc(&keys, n)) && !(rc = T.alloc(&idx, n))) rc = T.alloc(&counters, 2);
     if (!rc) rc = fill_u32(counters, 0u, 2, s);
     if (!rc) rc = fill_u32((uint32_t*)out->kept, 0u, n, s);
     if (!rc && has_edges) {

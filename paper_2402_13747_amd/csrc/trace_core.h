@@ -207,7 +207,8 @@ __device__ __forceinline__ size_t top_index(const SceneView& v, uint32_t x, uint
 // Walk every active lane's ray (staged in W) through one hierarchy, testing
 // the surfels of the leaves it crosses until no nearer hit can follow.  The
 // lane's nearest hit so far is W.best; ANY: a lane stops at its first hit
-// nearer than that.  Called by every lane of the wave.
+// nearer than that; t_from: the walk starts at this distance.  Called by every
+// lane of the wave.
 //
 // The walk runs in units of leaves, mirrored along every axis on which the
 // ray moves backwards, so it only moves towards larger coordinates: a step
@@ -237,9 +238,10 @@ __device__ __forceinline__ size_t top_index(const SceneView& v, uint32_t x, uint
 // 48 of them did (fuller tests) took 1.53, 1.66 and 1.90 ms in the room
 // against 1.49.
 template <bool STATS, int TD, bool ANY = false>
-__device__ __forceinline__ void walk(const SceneView& v, const uint64_t* ahead, WaveLds& W, bool active, stat_t* cnt) {
+__device__ __forceinline__ void walk(const SceneView& v, const uint64_t* ahead, WaveLds& W, bool active, stat_t* cnt,
+                                     float t_from = 0.f) {
     const uint32_t lane = lane_id();
-    float og[3], dg[3], ig[3], c[3], te = 0.f, ts;
+    float og[3], dg[3], ig[3], c[3], te = t_from, ts;
     bool neg[3], walking;
     {
         const float4 O = W.o[lane], Dd = W.d[lane];
