@@ -348,14 +348,34 @@ struct HierOut {
 
 // Node starts of every level from the sorted keys: an entry opens a node of
 // level l when its key differs from the previous entry's above bit sh[l].
-// A wave owns a tile of LINK_TILE consecutive entries, read in LINK_ROUNDS
-// coalesced rounds of 64 (lane j of round r: entry tile + 64 r + j).
-constexpr int LINK_ROUNDS = 16;
-constexpr int LINK_TILE = 64 * LINK_ROUNDS;
+// A wave owns a tile of 64 ROUNDS consecutive entries, read in coalesced
+// rounds of 64 (lane j of round r: entry tile + 64 r + j), up to LINK_BATCH of
+// them before any is used.  Few entries are dealt out in tiles of two rounds:
+// the waves' chains of rounds are what counts there: 60 k entries take 34 us
+// in k_link and 9.5 in k_link_count with 16 rounds, 7.4 and 3.7 with two (3 M:
+// 31 and 10 us with 16; two would need three kernels to scan the counts).
+constexpr int LINK_ROUNDS = 16, LINK_ROUNDS_FEW = 2, LINK_BATCH = 8;
+constexpr int64_t LINK_FEW = 64 * LINK_ROUNDS_FEW * 4096;  // whose tiles' counts one block scans
 
-__device__ __forceinline__ uint32_t link_flags(const uint64_t* keys, int64_t e, const LevelShifts& ls) {
-    const uint64_t k = keys[e];
-    const uint64_t prev = e > 0 ? keys[e - 1] : 0ull;
+// The keys of a batch's rounds r0, r0 + 1, ..: entries from e0 on, 0 past m.
+template <int B>
+__device__ __forceinline__ void link_load(const uint64_t* keys, int64_t m, int64_t e0, uint64_t (&k)[B]) {
+#pragma unroll
+    for (int r = 0; r < B; ++r) {
+        const int64_t e = e0 + 64 * r + lane_id();
+        k[r] = e < m ? keys[e] : 0ull;
+    }
+}
+
+// The key before this lane's in round r of a batch (`last`: before the batch).
+template <int B>
+__device__ __forceinline__ uint64_t link_prev(const uint64_t (&k)[B], int r, uint64_t last) {
+    const uint64_t up = __shfl_up((unsigned long long)k[r], 1, 64);
+    const uint64_t before = r > 0 ? (uint64_t)__shfl((unsigned long long)k[r > 0 ? r - 1 : 0], 63, 64) : last;
+    return lane_id() == 0 ? before : up;
+}
+
+__device__ __forceinline__ uint32_t link_flags(uint64_t k, uint64_t prev, int64_t e, const LevelShifts& ls) {
     uint32_t f = 0;
 #pragma unroll
     for (int l = 0; l < PCRL_MAX_LEVELS; ++l)
@@ -364,16 +384,27 @@ __device__ __forceinline__ uint32_t link_flags(const uint64_t* keys, int64_t e, 
 }
 
 // Per wave tile and level: the nodes that start in the tile ([level][tile]).
+template <int ROUNDS>
 __global__ __launch_bounds__(BUILD_BLOCK) void k_link_count(const uint64_t* keys, int64_t m, LevelShifts ls,
                                                             uint32_t* tile_cnt, uint32_t n_tiles) {
     const uint32_t tile = blockIdx.x * (BUILD_BLOCK / 64) + (threadIdx.x >> 6);
     if (tile >= n_tiles) return;
     uint32_t c[PCRL_MAX_LEVELS] = {0u, 0u, 0u, 0u};
-    for (int r = 0; r < LINK_ROUNDS; ++r) {
-        const int64_t e = (int64_t)tile * LINK_TILE + 64 * r + lane_id();
-        const uint32_t f = e < m ? link_flags(keys, e, ls) : 0u;
+    constexpr int B = ROUNDS < LINK_BATCH ? ROUNDS : LINK_BATCH;
+    const int64_t first = (int64_t)tile * (64 * ROUNDS);
+    uint64_t last = first > 0 ? keys[first - 1] : 0ull;
+    for (int r0 = 0; r0 < ROUNDS; r0 += B) {
+        uint64_t k[B];
+        link_load<B>(keys, m, first + 64 * r0, k);
 #pragma unroll
-        for (int l = 0; l < PCRL_MAX_LEVELS; ++l) c[l] += (f >> l) & 1u;
+        for (int r = 0; r < B; ++r) {
+            const int64_t e = first + 64 * (r0 + r) + lane_id();
+            const uint64_t prev = link_prev<B>(k, r, last);
+            const uint32_t f = e < m ? link_flags(k[r], prev, e, ls) : 0u;
+#pragma unroll
+            for (int l = 0; l < PCRL_MAX_LEVELS; ++l) c[l] += (f >> l) & 1u;
+        }
+        last = __shfl((unsigned long long)k[B - 1], 63, 64);
     }
 #pragma unroll
     for (int l = 0; l < PCRL_MAX_LEVELS; ++l) {
@@ -387,6 +418,7 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_link_count(const uint64_t* keys
 // and the leaf's first entry and key.  tile_off[l][t] is the exclusive scan
 // of the tiles' node counts, so the node of level l holding entry e is the
 // number of level-l nodes opened up to and including e, minus one.
+template <int ROUNDS>
 __global__ __launch_bounds__(BUILD_BLOCK) void k_link(const uint64_t* keys, int64_t m, LevelShifts ls, SceneView v,
                                                       const uint32_t* tile_off, uint32_t n_tiles, HierOut h,
                                                       int id_bits) {
@@ -395,11 +427,20 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_link(const uint64_t* keys, int6
     const int L = ls.nlev;
     uint32_t carry[PCRL_MAX_LEVELS] = {0u, 0u, 0u, 0u};
     for (int l = 0; l < L; ++l) carry[l] = tile_off[(size_t)l * n_tiles + tile];
-    for (int r = 0; r < LINK_ROUNDS; ++r) {
-        const int64_t e = (int64_t)tile * LINK_TILE + 64 * r + lane_id();
+    constexpr int B = ROUNDS < LINK_BATCH ? ROUNDS : LINK_BATCH;
+    const int64_t first = (int64_t)tile * (64 * ROUNDS);
+    uint64_t last = first > 0 ? keys[first - 1] : 0ull, kr[B] = {};
+#pragma unroll
+    for (int r0 = 0; r0 < ROUNDS; ++r0) {
+        const int r = r0 % B;
+        if (r == 0) {
+            if (r0 > 0) last = __shfl((unsigned long long)kr[B - 1], 63, 64);
+            link_load<B>(keys, m, first + 64 * r0, kr);
+        }
+        const int64_t e = first + 64 * r0 + lane_id();
         const bool in = e < m;
-        const uint32_t f = in ? link_flags(keys, e, ls) : 0u;
-        const uint64_t k = in ? keys[e] : 0ull;
+        const uint64_t k = kr[r], prev = link_prev<B>(kr, r, last);
+        const uint32_t f = in ? link_flags(k, prev, e, ls) : 0u;
         // the levels' flags in 8-bit fields of one word (at most 64 per field): one wave scan
         uint32_t fp = 0;
 #pragma unroll
@@ -992,12 +1033,18 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
     hb.entry_point = ids;
 
     // per-level node boundaries: node starts counted per tile, the tiles' counts scanned
-    const int64_t n_tiles64 = (m + LINK_TILE - 1) / LINK_TILE;
+    const bool few = m <= LINK_FEW;
+    const int64_t link_tile = 64 * (few ? LINK_ROUNDS_FEW : LINK_ROUNDS);
+    const int64_t n_tiles64 = (m + link_tile - 1) / link_tile;
     const uint32_t n_tiles = (uint32_t)n_tiles64;
     uint32_t *tiles = nullptr, *ltot = nullptr;
     if ((rc = T.alloc(&tiles, (size_t)L * n_tiles)) || (rc = T.alloc(&ltot, PCRL_MAX_LEVELS))) return rc;
     const unsigned link_blocks = (unsigned)((n_tiles64 + BUILD_BLOCK / 64 - 1) / (BUILD_BLOCK / 64));
-    hipLaunchKernelGGL(k_link_count, dim3(link_blocks), dim3(BUILD_BLOCK), 0, s, keys, m, ls, tiles, n_tiles);
+    if (few)
+        hipLaunchKernelGGL(k_link_count<LINK_ROUNDS_FEW>, dim3(link_blocks), dim3(BUILD_BLOCK), 0, s, keys, m, ls, tiles,
+                           n_tiles);
+    else
+        hipLaunchKernelGGL(k_link_count<LINK_ROUNDS>, dim3(link_blocks), dim3(BUILD_BLOCK), 0, s, keys, m, ls, tiles, n_tiles);
     for (int l = 0; l < L; ++l)
         if ((rc = scan_u32(tiles + (size_t)l * n_tiles, tiles + (size_t)l * n_tiles, n_tiles, ltot + l, s))) return rc;
     uint32_t host_nodes[PCRL_MAX_LEVELS] = {0, 0, 0, 0};
@@ -1046,8 +1093,12 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
     ho.top = top;
     ho.occ = occ;
     ho.tcell = tcell;
-    hipLaunchKernelGGL(k_link, dim3(link_blocks), dim3(BUILD_BLOCK), 0, s, keys, m, ls, v, tiles, n_tiles, ho,
-                       packed ? id_bits : 0);
+    if (few)
+        hipLaunchKernelGGL(k_link<LINK_ROUNDS_FEW>, dim3(link_blocks), dim3(BUILD_BLOCK), 0, s, keys, m, ls, v, tiles, n_tiles,
+                           ho, packed ? id_bits : 0);
+    else
+        hipLaunchKernelGGL(k_link<LINK_ROUNDS>, dim3(link_blocks), dim3(BUILD_BLOCK), 0, s, keys, m, ls, v, tiles, n_tiles, ho,
+                           packed ? id_bits : 0);
     // the brick levels between the top grid and the leaves' parents
     for (int i = 0; i < v.depth; ++i) {
         uint32_t* bs = nullptr;
