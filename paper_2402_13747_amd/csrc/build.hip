@@ -734,28 +734,29 @@ __global__ void k_split_leaf(const uint2* r, int64_t n, uint32_t* b, uint32_t* c
 }
 
 // With packed items (`packed` non-null) the point index is taken from their
-// low id_bits, else from ids (the sort's values).
-__global__ void k_gather_surfels(uint32_t* ids, const uint64_t* packed, int id_bits, int64_t m, const float* xyz,
-                                 const float4* un, const uint32_t* label, const uint32_t* gid, float4* spos,
-                                 float4* snrm) {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= m) return;
-    uint32_t i;
-    if (packed) {
-        i = (uint32_t)(packed[e] & ((uint64_t(1) << id_bits) - 1));
-    } else {
-        i = ids[e];
+// low id_bits, else from ids (the sort's values).  The block's entries pass
+// through LDS, so that a wave stores 1 KB in a row.
+__global__ __launch_bounds__(BUILD_BLOCK) void k_gather_surfels(uint32_t* ids, const uint64_t* packed, int id_bits, int64_t m,
+                                                                const float* xyz, const float4* un, const uint32_t* label,
+                                                                const uint32_t* gid, float4* surf) {
+    __shared__ float4 out[2 * BUILD_BLOCK];
+    const int64_t first = (int64_t)blockIdx.x * BUILD_BLOCK, e = first + threadIdx.x;
+    if (e < m) {
+        const uint32_t i = packed ? (uint32_t)(packed[e] & ((uint64_t(1) << id_bits) - 1)) : ids[e];
+        out[2 * threadIdx.x] = make_float4(xyz[3 * (size_t)i], xyz[3 * (size_t)i + 1], xyz[3 * (size_t)i + 2],
+                                           __uint_as_float(gid ? gid[i] : i));
+        const float4 nn = un[i];
+        out[2 * threadIdx.x + 1] = make_float4(nn.x, nn.y, nn.z, __uint_as_float(label[i]));
     }
-    const uint32_t g = gid ? gid[i] : i;
-    spos[e] = make_float4(xyz[3 * (size_t)i], xyz[3 * (size_t)i + 1], xyz[3 * (size_t)i + 2], __uint_as_float(g));
-    const float4 nn = un[i];
-    snrm[e] = make_float4(nn.x, nn.y, nn.z, __uint_as_float(label[i]));
+    __syncthreads();
+    const uint32_t n = 2u * (uint32_t)min((int64_t)BUILD_BLOCK, m - first);
+    for (uint32_t h = threadIdx.x; h < n; h += BUILD_BLOCK) surf[2 * first + h] = out[h];
 }
 
 // Entry -> point table of a scene from its surfel stream.
-__global__ void k_entry_points(const float4* spos, int64_t m, uint32_t* out) {
+__global__ void k_entry_points(const float4* surf, int64_t m, uint32_t* out) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < m) out[e] = __float_as_uint(spos[e].w);
+    if (e < m) out[e] = __float_as_uint(surf[2 * e].w);
 }
 
 // ---------------------------------------------------------------------------
@@ -1158,13 +1159,12 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
     }
 
     // surfel streams in leaf order
-    float4 *spos = nullptr, *snrm = nullptr;
-    if ((rc = B.alloc(&spos, (size_t)m)) || (rc = B.alloc(&snrm, (size_t)m))) return rc;
+    float4* surf = nullptr;
+    if ((rc = B.alloc(&surf, 2 * (size_t)m))) return rc;
     hipLaunchKernelGGL(k_gather_surfels, dim3(blocks_for(m)), dim3(BUILD_BLOCK), 0, s, ids,
                        packed ? (const uint64_t*)keys : (const uint64_t*)nullptr, packed ? id_bits : 0, m, xyz,
-                       unit_nrm, label, gid, spos, snrm);
-    v.spos = spos;
-    v.snrm = snrm;
+                       unit_nrm, label, gid, surf);
+    v.surf = surf;
     if (hipGetLastError() != hipSuccess) {
         set_error("build_voxels: kernel launch failed");
         return PCRL_EHIP;
@@ -1287,7 +1287,7 @@ static int overlay_impl(PcrlScene* S, const uint32_t* gid, const float* xyz, con
     v.blk = nullptr;
     v.pbox = nullptr;
     v.leaf = nullptr;
-    v.spos = v.snrm = nullptr;
+    v.surf = nullptr;
     HierBuild hb;
     if ((rc = build_hierarchy(xyz, unit_nrm, label, gid, n, s, v, ov->bufs, T, hb))) return fail(rc);
     ov->view = v;
@@ -1373,7 +1373,7 @@ extern "C" int scene_leaf_table(const PcrlScene* scene, uint64_t* leaf_key, uint
             PCRL_TRY_HIP(hipMemcpyAsync(entry_point, scene->entry_point, (size_t)m * 4, hipMemcpyDeviceToDevice, s));
         } else {
             // the point id rides in the surfel stream (x, y, z, id)
-            hipLaunchKernelGGL(k_entry_points, dim3(blocks_for(m)), dim3(BUILD_BLOCK), 0, s, scene->view.spos, m,
+            hipLaunchKernelGGL(k_entry_points, dim3(blocks_for(m)), dim3(BUILD_BLOCK), 0, s, scene->view.surf, m,
                                entry_point);
             PCRL_TRY_HIP(hipGetLastError());
         }

@@ -261,8 +261,7 @@ struct SceneView {
     const uint8_t* dist0;            // null, or per level-0 cell its empty-space skip radius (level-0 cells)
     const uint2* cells;              // null, or per leaf cell of every parent brick: (first entry, count) of
                                      // an occupied leaf, or (skip radius, 0) of an empty one
-    const float4* spos;              // per entry: x, y, z, point id (bits)
-    const float4* snrm;              // per entry: unit normal, label (bits)
+    const float4* surf;              // per entry two: x, y, z, point id (bits); unit normal, label (bits)
 };
 
 // x / span for 0 <= x < 2^22 and span <= 2^18 with a precomputed ceil(2^40 / span):
@@ -317,7 +316,7 @@ struct PcrlScene {
     pcrl::DevBufs bufs;
     PcrlSceneInfo info{};
     uint64_t* leaf_key = nullptr;     // per leaf hierarchical key
-    uint32_t* entry_point = nullptr;  // per entry: point id (leaf order); null: read from spos.w
+    uint32_t* entry_point = nullptr;  // per entry: point id (leaf order); null: read from surf
     uint2* leaf_range = nullptr;
     uint32_t* first_child[PCRL_MAX_LEVELS - 1] = {};  // per node of level i: its first child
     uint32_t max_label = 0;

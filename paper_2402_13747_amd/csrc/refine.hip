@@ -138,7 +138,7 @@ __device__ __forceinline__ void trace_parts(const uint64_t* ahead, WaveLds& W, u
     wave_sync();
     const unsigned long long B = W.best[lead];
     if (B < old) {
-        const float4 N = v.snrm[W.entry[lead]];
+        const float4 N = v.surf[2 * (size_t)W.entry[lead] + 1];
         hit.t = __uint_as_float((uint32_t)(B >> 32));
         hit.id = (uint32_t)B;
         hit.nx = N.x;
@@ -248,7 +248,7 @@ __device__ __forceinline__ void gather_normals(const SceneView& v, WaveLds& W, P
             else hi = mid - 1u;
         }
         const uint32_t e = begin[lo] + (f - first[lo]);
-        const float4 P = v.spos[e], N = v.snrm[e];
+        const float4 P = v.surf[2 * (size_t)e], N = v.surf[2 * (size_t)e + 1];
         const float x = P.x - c[0], y = P.y - c[1], z = P.z - c[2];
         const float d2 = dot3f(x, y, z, x, y, z);
         const int cell[3] = {lc[0] + (int)(lo % 3u) - 1, lc[1] + (int)(lo / 3u % 3u) - 1, lc[2] + (int)(lo / 9u) - 1};

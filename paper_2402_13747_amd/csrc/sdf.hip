@@ -295,7 +295,7 @@ template <int NL>
 __global__ void k_own_flags(SceneView v, uint32_t m, uint32_t* flag) {
     const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= m) return;
-    const float4 P = v.spos[e];
+    const float4 P = v.surf[2 * (size_t)e];
     Seg N;
     N.c[0] = (int)floorf((P.x - v.org[0]) * v.inv_h);
     N.c[1] = (int)floorf((P.y - v.org[1]) * v.inv_h);
@@ -317,14 +317,14 @@ __global__ void k_own_flags(SceneView v, uint32_t m, uint32_t* flag) {
 }
 
 // Copy the own entries to their compacted slots.
-__global__ void k_own_scatter(const float4* spos, const float4* snrm, const uint32_t* scan, uint32_t m, uint32_t cap,
+__global__ void k_own_scatter(const float4* surf, const uint32_t* scan, uint32_t m, uint32_t cap,
                               float4* own) {
     const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const uint32_t j = scan[e];
     if (scan[e + 1] == j || j >= cap) return;
-    own[2 * (size_t)j] = spos[e];
-    own[2 * (size_t)j + 1] = snrm[e];
+    own[2 * (size_t)j] = surf[2 * (size_t)e];
+    own[2 * (size_t)j + 1] = surf[2 * (size_t)e + 1];
 }
 
 // Own entries before each leaf, and the centre of the box around each leaf's
@@ -1187,7 +1187,7 @@ static int own_index(PcrlScene* S, hipStream_t s) {
         rc = hipGetLastError() == hipSuccess ? scan_u32(scan, scan, m, scan + m, s) : PCRL_EHIP;
     }
     if (!rc) {
-        hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, v.spos, v.snrm, scan,
+        hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, v.surf, scan,
                            (uint32_t)m, (uint32_t)np, own);
         hipLaunchKernelGGL(k_own_leaves, dim3((n_leaves + 255) / 256), dim3(256), 0, s, v.leaf, n_leaves, scan,
                            (const float4*)own, first, box, P < 0 ? cells : (uint32_t*)nullptr,

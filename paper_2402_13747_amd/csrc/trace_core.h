@@ -150,6 +150,11 @@ __device__ __forceinline__ unsigned long long hit_word(float t, uint32_t id) {
 // previous hit and all accepted pairs: the same result as testing the
 // leaf's entries one after another in the owner's lane.  Called by every
 // lane of the wave (r.y 0: no leaf).
+//
+// A large scene's reflected rays are bound by what their leaves (four entries
+// on average) make HBM read: with an entry's two 16-byte halves in one array
+// instead of two, a bounce of 12 M rays in a 20M-point street canyon reads 6.4
+// GB instead of 8.5, and the launch's kernels take 8.8 ms instead of 9.1.
 template <bool STATS>
 __device__ __forceinline__ void leaf_tests(const SceneView& v, WaveLds& W, uint2 r, stat_t* cnt) {
     const uint32_t lane = lane_id();
@@ -168,8 +173,8 @@ __device__ __forceinline__ void leaf_tests(const SceneView& v, WaveLds& W, uint2
         // lanes past the last pair repeat it (same loads, no branch)
         const uint32_t pi = min(base + lane, total - 1u);
         const uint32_t k = W.delta[own] + pi;
-        const float4 P = v.spos[k];
-        const float4 N = v.snrm[k];
+        const float4 P = v.surf[2 * (size_t)k];
+        const float4 N = v.surf[2 * (size_t)k + 1];
         const float4 O = W.o[own];
         const float4 Dd = W.d[own];
         const uint32_t id = __float_as_uint(P.w);
@@ -232,11 +237,11 @@ __device__ __forceinline__ size_t top_index(const SceneView& v, uint32_t x, uint
 // loads, and by instruction issue.  Against a per-step descent through the
 // levels with 64-bit divisions (36 then 16 steps a segment, 250 instructions
 // each, spilled scalar registers): street canyon, 4 x 4 M rays, 10.2 steps a
-// segment, 21.6 -> 11.1 ms of kernels a launch; furnished room, 1 M rays, 9.5
-// steps, 2.25 -> 1.41 ms; 16 k rays in a room 0.74 -> 0.30 ms.  The leaves of
-// a step are tested at once: letting lanes wait at their leaves until 8, 24 or
-// 48 of them did (fuller tests) took 1.53, 1.66 and 1.90 ms in the room
-// against 1.49.
+// segment, 21.6 -> 11.1 ms of kernels a launch (8.8 with what came later);
+// furnished room, 1 M rays, 9.5 steps, 2.25 -> 1.41 ms; 16 k rays in a room
+// 0.74 -> 0.30 ms.  The leaves of a step are tested at once: letting lanes wait
+// at their leaves until 8, 24 or 48 of them did (fuller tests) took 1.53, 1.66
+// and 1.90 ms in the room against 1.49.
 template <bool STATS, int TD, bool ANY = false>
 __device__ __forceinline__ void walk(const SceneView& v, const uint64_t* ahead, WaveLds& W, bool active, stat_t* cnt,
                                      float t_from = 0.f) {
@@ -538,7 +543,7 @@ __device__ __forceinline__ void trace_segment(ArgsPtr args, const uint64_t* ahea
     walk<STATS, TD, ANY>(v, ahead, W, active, cnt);
     const unsigned long long b = W.best[lane];
     if (active && b != before) {
-        const float4 N = v.snrm[W.entry[lane]];
+        const float4 N = v.surf[2 * (size_t)W.entry[lane] + 1];
         hit.t = __uint_as_float((uint32_t)(b >> 32));
         hit.id = (uint32_t)b;
         hit.nx = N.x;
