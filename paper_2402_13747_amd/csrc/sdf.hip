@@ -102,7 +102,8 @@ __device__ __forceinline__ uint32_t own_before(const SdfArgs& a, int P, uint32_t
 // this lane in runs[s][lane] for every bit s of the result, [first, end).
 // NL voxel levels; FAST: bricks from the dense top grid and per-cell prefixes
 // (one load each); else by descent and the bricks' masks (scenes whose
-// prefixes would be too large).
+// prefixes would be too large).  The leaves' parents hold at least two leaves
+// an axis (build_walk), so three cells next to each other lie in at most two.
 template <int NL, bool FAST>
 __device__ __forceinline__ uint32_t sdf_runs(const float x[3], SdfRuns& runs, uint32_t& reads) {
     constexpr int P = NL - 2;
@@ -330,14 +331,14 @@ __global__ void k_own_scatter(const float4* surf, const uint32_t* scan, uint32_t
 // Own entries before each leaf, and the centre of the box around each leaf's
 // own points (at its first own entry).
 __global__ void k_own_leaves(const uint2* leaf, uint32_t n, const uint32_t* scan, const float4* own, uint32_t* first,
-                             float4* lbox, uint32_t* single, const uint64_t* leaf_key) {
+                             float4* lbox, uint32_t* single, const uint64_t* leaf_key, int key_shift) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const uint2 r = leaf[i];
     const uint32_t e0 = scan[r.x], e1 = scan[r.x + r.y];
     first[i] = e0;
     if (i == n - 1) first[n] = e1;
-    if (single) single[leaf_key[i]] = e1 - e0;
+    if (single) single[leaf_key[i] >> key_shift] = e1 - e0;
     if (!(e0 < e1)) return;
     float lo0 = INFINITY, lo1 = INFINITY, lo2 = INFINITY, hi0 = -INFINITY, hi1 = -INFINITY, hi2 = -INFINITY;
     for (uint32_t e = e0; e < e1; ++e) {
@@ -1095,10 +1096,17 @@ static void launch_own_flags(const SceneView& v, uint32_t m, uint32_t* flag, hip
 
 // The structures of the leaf walk for scene S (S->walk), owned by B: child
 // bases and boxes of every brick, the leaves' skip radii (a dense cell table
-// where it fits, else isotropic radii) and those of the level-0 grid.
+// where it fits, else isotropic radii) and those of the level-0 grid.  A last
+// level that divides nothing (ratio 1) is left out: the nodes above it are the
+// leaves, one by one in the same order.
 static int build_walk(PcrlScene* S, hipStream_t s, DevBufs& B) {
     SceneView v = S->view;
+    while (v.nlev > 1 && v.ratio[v.nlev - 2] == 1) --v.nlev;
     const int L = v.nlev;
+    if (L >= 2) {
+        v.pinv = 1.0f / (float)v.ratio[L - 2];
+        v.phalf = 0.5f / (float)v.ratio[L - 2];
+    }
     int rc;
     auto blocks = [](int64_t n, int block) { return dim3((unsigned)std::max<int64_t>(1, (n + block - 1) / block)); };
     for (int l = 0; l + 1 < L; ++l) {
@@ -1167,7 +1175,10 @@ static int own_index(PcrlScene* S, hipStream_t s) {
     const int P = v.nlev - 2;
     const uint32_t n3 = P < 0 ? 0u : (uint32_t)v.ratio[P] * v.ratio[P] * v.ratio[P];
     const int64_t n_cells = P < 0 ? (int64_t)v.dim[0] * v.dim[1] * v.dim[2] + 1 : (int64_t)v.nn[P] * (n3 + 1);
-    const bool table = P < 0 || (v.depth == 0 && n_cells * 4 <= OWN_CELLS_MAX_BYTES);
+    const int F = std::max(S->view.nlev - 2 - v.depth, 0);  // level of the top grid
+    const bool table = P < 0 || (F == P && n_cells * 4 <= OWN_CELLS_MAX_BYTES);
+    int key_shift = 0;  // key bits of the levels left out
+    for (int l = v.nlev; l < S->view.nlev; ++l) key_shift += v.lbits[l];
     uint32_t *scan = nullptr, *first = nullptr, *cells = nullptr;
     float4 *own = nullptr, *box = nullptr;
     const size_t slots = (size_t)(np > 0 ? np : 1);
@@ -1191,7 +1202,7 @@ static int own_index(PcrlScene* S, hipStream_t s) {
                            (uint32_t)m, (uint32_t)np, own);
         hipLaunchKernelGGL(k_own_leaves, dim3((n_leaves + 255) / 256), dim3(256), 0, s, v.leaf, n_leaves, scan,
                            (const float4*)own, first, box, P < 0 ? cells : (uint32_t*)nullptr,
-                           (const uint64_t*)S->leaf_key);
+                           (const uint64_t*)S->leaf_key, key_shift);
         if (P < 0)
             rc = scan_u32(cells, cells, n_cells, nullptr, s);
         else if (table)
@@ -1291,7 +1302,7 @@ int sdf_launch_run(PcrlLaunch* L, const TraceArgs& t) {
     PCRL_TRY(tail_alloc(A.s, A.n_total, true, L->bufs, s));
     const bool timing = !L->events.empty();
     if (timing) PCRL_TRY_HIP(hipEventRecord(L->events[0], s));
-    switch (scene->view.nlev) {
+    switch (A.s.empty ? 1 : A.s.v.nlev) {
     case 1: launch_sdf_launch_nl<1>(A, s); break;
     case 2: launch_sdf_launch_nl<2>(A, s); break;
     case 3: launch_sdf_launch_nl<3>(A, s); break;
@@ -1395,7 +1406,7 @@ extern "C" int sdf_intersect(const PcrlScene* scene, const float* o, const float
         T.release();
         return rc;
     }
-    switch (scene->view.nlev) {
+    switch (a.empty ? 1 : a.v.nlev) {
     case 1: launch_sdf_nl<1>(a, s); break;
     case 2: launch_sdf_nl<2>(a, s); break;
     case 3: launch_sdf_nl<3>(a, s); break;
