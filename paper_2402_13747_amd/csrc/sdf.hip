@@ -679,12 +679,16 @@ struct SdfLaunchArgs {
     float* hit_t;
 };
 
-// Add x (the same on every lane) to *p for each lane active here, with one
-// atomic per wave.
-__device__ __forceinline__ void wave_add(uint32_t* p, uint32_t x) {
-    const uint64_t m = __ballot(1);
-    const int leader = __ffsll((long long)m) - 1;
-    if ((int)lane_id() == leader) atomicAdd(p, (uint32_t)__popcll(m) * x);
+// Add 1 to counters[b] for each lane active here: one atomic per wave and
+// different b (the lanes stand at different segments).
+__device__ __forceinline__ void wave_count(uint32_t* counters, int b) {
+    for (bool left = true; left;) {
+        const int first = __builtin_amdgcn_readfirstlane(b);
+        const uint64_t same = __ballot(b == first);  // of the lanes left
+        if (b != first) continue;
+        if ((int)lane_id() == __ffsll((long long)same) - 1) atomicAdd(&counters[first], (uint32_t)__popcll(same));
+        left = false;
+    }
 }
 
 __device__ __forceinline__ void launch_ray(const SdfLaunchArgs& A, uint32_t g, float o[3], float d[3]) {
@@ -770,7 +774,7 @@ __global__ __launch_bounds__(SDF_BLOCK) void k_sdf_launch(SdfLaunchArgs A) {
     SdfMarch M;
     bool walking = false;
     if (alive) {
-        wave_add(&A.counters[0], 1u);
+        wave_count(A.counters, 0);
         walking = march_begin(M, o, d, 0.f, INFINITY);
     }
     for (;;) {
@@ -787,7 +791,7 @@ __global__ __launch_bounds__(SDF_BLOCK) void k_sdf_launch(SdfLaunchArgs A) {
             }
             evals = 0;
             ++b;
-            wave_add(&A.counters[b], 1u);
+            wave_count(A.counters, b);
             walking = march_begin(M, o, d, t_lo, INFINITY);
         }
         if (!__ballot(want)) break;
