@@ -1098,13 +1098,13 @@ static void launch_own_flags(const SceneView& v, uint32_t m, uint32_t* flag, hip
     hipLaunchKernelGGL((k_own_flags<NL>), dim3((unsigned)(((uint64_t)m + 255) / 256)), dim3(256), 0, s, v, m, flag);
 }
 
-// The structures of the leaf walk for scene S (S->walk), owned by B: child
+// The structures of the leaf walk for scene S in its view v, owned by B: child
 // bases and boxes of every brick, the leaves' skip radii (a dense cell table
 // where it fits, else isotropic radii) and those of the level-0 grid.  A last
 // level that divides nothing (ratio 1) is left out: the nodes above it are the
 // leaves, one by one in the same order.
-static int build_walk(PcrlScene* S, hipStream_t s, DevBufs& B) {
-    SceneView v = S->view;
+static int build_walk(const PcrlScene* S, hipStream_t s, DevBufs& B, SceneView& v) {
+    v = S->view;
     while (v.nlev > 1 && v.ratio[v.nlev - 2] == 1) --v.nlev;
     const int L = v.nlev;
     if (L >= 2) {
@@ -1160,7 +1160,6 @@ static int build_walk(PcrlScene* S, hipStream_t s, DevBufs& B) {
                        v.dim0[0], v.dim0[1], v.dim0[2], 2);
     v.dist0 = d0;
     dfree(tmp, s);
-    S->walk = v;
     return hipGetLastError() == hipSuccess ? PCRL_OK : PCRL_EHIP;
 }
 
@@ -1173,8 +1172,13 @@ static int own_index(PcrlScene* S, hipStream_t s) {
     const int64_t m = S->info.n_entries, np = S->info.n_points;
     DevBufs B;  // handed to the scene when complete
     B.stream = s;
-    int rc = build_walk(S, s, B);
-    const SceneView& v = S->walk;
+    SceneView v{};
+    int rc = build_walk(S, s, B, v);
+    if (rc) {
+        B.release();
+        if (rc == PCRL_EHIP) set_error("sdf_intersect: building the leaf walk failed");
+        return rc;
+    }
     const uint32_t n_leaves = v.nn[v.nlev - 1];
     const int P = v.nlev - 2;
     const uint32_t n3 = P < 0 ? 0u : (uint32_t)v.ratio[P] * v.ratio[P] * v.ratio[P];
@@ -1220,6 +1224,7 @@ static int own_index(PcrlScene* S, hipStream_t s) {
         return rc;
     }
     S->bufs.ptrs.insert(S->bufs.ptrs.end(), B.ptrs.begin(), B.ptrs.end());
+    S->walk = v;
     S->own = own;
     S->own_box = box;
     S->own_first = first;
