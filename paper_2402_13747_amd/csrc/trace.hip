@@ -21,24 +21,6 @@
 
 namespace pcrl {
 
-// Rays a wave traces together when n rays are active.  A wave lasts as long as
-// its longest ray and tests its lanes' leaves together, so while the waves do
-// not fill the GPU fewer rays per wave end sooner; once they do, every extra
-// wave costs its own instructions.  The line is at 8,192 waves (8 per SIMD).
-// 16 k rays in a room, four segments: 0.391 ms with 64 rays a wave, 0.352
-// with 32, 0.318 with 16, 0.304 with 8, 0.357 with 4.  766 k rays in a street:
-// 0.338 ms with 64, 0.452 with 32; 196 k: 0.525 and 0.401 ms.  Every wave
-// culls and tests the receivers once, so many receivers move the line down:
-// 200 k rays and 1,024 of them take 0.94 ms by the line moved so, 1.02 by the
-// line as it is for few.
-constexpr uint32_t RPW_MIN = 8, RPW_WAVES = 8192, RPW_RX = 512;
-__host__ __device__ __forceinline__ uint32_t rays_per_wave(uint32_t n, uint32_t n_rx) {
-    const uint32_t waves = RPW_WAVES * RPW_RX / (RPW_RX + n_rx);
-    uint32_t r = 64;
-    while (r > RPW_MIN && n / (r / 2) <= waves) r /= 2;
-    return r;
-}
-
 // Specialised on the depth TD of the traversal's top grid and on the presence
 // of an overlay OV, so every level index in the traversal is a compile-time
 // constant.  Each wave traces `rpw` consecutive slots in lockstep
@@ -48,21 +30,6 @@ __host__ __device__ __forceinline__ uint32_t rays_per_wave(uint32_t n, uint32_t 
 // slots need are spread over all 8 XCDs (workgroups are dispatched to them
 // round-robin), each XCD working on one contiguous range of slots so that
 // neighbouring, coherent rays share its L2; the other blocks end at once.
-// Consecutive blocks that go to one XCD before the next one's turn: an eighth
-// of the blocks, or in large launches of an eighth's share in up to 8 turns of
-// at least PIECE_BLOCKS: neighbouring blocks need much the same lines, but an
-// XCD whose eighth of the directions is dear keeps the others waiting.  Street
-// canyon, 16 M rays, five segments: 11.0 ms of kernels in one turn, 10.5 with
-// turns of 256 blocks, 10.3 with 64, 10.4 with up to 32 turns; its 300 k rays
-// with an overlay lose by turns: 0.84 ms in one, 0.86 and 0.90 with turns of
-// 64 and 32 blocks.
-constexpr uint32_t PIECES = 8, PIECE_BLOCKS = 256;
-__host__ __device__ __forceinline__ uint32_t xcd_piece(uint32_t blocks) {
-    const uint32_t per = (blocks + 7) / 8, turns = per / PIECE_BLOCKS;
-    const uint32_t n = turns < 1 ? 1 : turns > PIECES ? PIECES : turns;
-    return (per + n - 1) / n;
-}
-
 template <bool FIRST, bool STATS, int TD, bool OV>
 __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(TraceArgs a, int b, uint32_t cap) {
     constexpr uint32_t WAVES = TRACE_BLOCK / 64;
@@ -70,8 +37,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(TraceArgs a, int b, uint3
     const uint32_t n_act = FIRST ? a.n_total : a.counters[b];
     const uint32_t rpw = rays_per_wave(n_act, (uint32_t)a.n_rx);
     const uint32_t blocks = min(cap, (n_act + rpw * WAVES - 1) / (rpw * WAVES));
-    const uint32_t piece = xcd_piece(blocks), k = blockIdx.x >> 3, turn = k / piece;
-    const uint32_t block = (8u * turn + (blockIdx.x & 7u)) * piece + (k - turn * piece);
+    const uint32_t block = xcd_turn(blocks, blockIdx.x);
     if (block >= blocks) return;
     ahead_init(lds.ahead, threadIdx.x, TRACE_BLOCK);
     __syncthreads();
@@ -156,8 +122,7 @@ __global__ void k_unpack_records(const uint4* rec, const uint32_t* count, uint32
 
 template <bool FIRST, bool STATS, int TD>
 static void launch_trace_td(const TraceArgs& a, int b, unsigned grid, hipStream_t s) {
-    // whole turns of pieces over the XCDs, for any number of blocks up to `grid`
-    const unsigned full = (grid + 7) / 8 * 8 + 8 * xcd_piece(grid);
+    const unsigned full = xcd_groups(grid);
     if (a.has_ov)
         hipLaunchKernelGGL((k_trace<FIRST, STATS, TD, true>), dim3(full), dim3(TRACE_BLOCK), 0, s, a, b, grid);
     else

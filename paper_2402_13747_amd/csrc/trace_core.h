@@ -54,6 +54,52 @@ struct TraceArgs {
     unsigned long long* stats;
 };
 
+// Rays a wave traces together when n rays are active.  A wave lasts as long as
+// its longest ray and tests its lanes' leaves together, so while the waves do
+// not fill the GPU fewer rays per wave end sooner; once they do, every extra
+// wave costs its own instructions.  The line is at 8,192 waves (8 per SIMD).
+// 16 k rays in a room, four segments: 0.391 ms with 64 rays a wave, 0.352
+// with 32, 0.318 with 16, 0.304 with 8, 0.357 with 4.  766 k rays in a street:
+// 0.338 ms with 64, 0.452 with 32; 196 k: 0.525 and 0.401 ms.  Every wave
+// culls and tests the receivers once, so many receivers move the line down:
+// 200 k rays and 1,024 of them take 0.94 ms by the line moved so, 1.02 by the
+// line as it is for few.
+constexpr uint32_t RPW_MIN = 8, RPW_WAVES = 8192, RPW_RX = 512;
+__host__ __device__ __forceinline__ uint32_t rays_per_wave(uint32_t n, uint32_t n_rx) {
+    const uint32_t waves = RPW_WAVES * RPW_RX / (RPW_RX + n_rx);
+    uint32_t r = 64;
+    while (r > RPW_MIN && n / (r / 2) <= waves) r /= 2;
+    return r;
+}
+
+// Consecutive blocks that go to one XCD before the next one's turn: an eighth
+// of the blocks, or in large launches of an eighth's share in up to 8 turns of
+// at least PIECE_BLOCKS: neighbouring blocks need much the same lines, but an
+// XCD whose eighth of the directions is dear keeps the others waiting.  Street
+// canyon, 16 M rays, five segments: 11.0 ms of kernels in one turn, 10.5 with
+// turns of 256 blocks, 10.3 with 64, 10.4 with up to 32 turns; its 300 k rays
+// with an overlay lose by turns: 0.84 ms in one, 0.86 and 0.90 with turns of
+// 64 and 32 blocks.
+constexpr uint32_t PIECES = 8, PIECE_BLOCKS = 256;
+__host__ __device__ __forceinline__ uint32_t xcd_piece(uint32_t blocks) {
+    const uint32_t per = (blocks + 7) / 8, turns = per / PIECE_BLOCKS;
+    const uint32_t n = turns < 1 ? 1 : turns > PIECES ? PIECES : turns;
+    return per < n ? 1 : (per + n - 1) / n;  // no block at all: pieces of one
+}
+
+// The block that workgroup g of a grid works as when `blocks` are needed (a
+// number from `blocks` on: none).
+__host__ __device__ __forceinline__ uint32_t xcd_turn(uint32_t blocks, uint32_t g) {
+    const uint32_t piece = xcd_piece(blocks), k = g >> 3, turn = k / piece;
+    return (8u * turn + (g & 7u)) * piece + (k - turn * piece);
+}
+
+// Workgroups that hold whole turns of pieces over the XCDs for any number of
+// blocks up to `most`.
+__host__ __device__ __forceinline__ uint32_t xcd_groups(uint32_t most) {
+    return (most + 7) / 8 * 8 + 8 * xcd_piece(most);
+}
+
 // Ping-pong ray buffers of bounce b, chosen by selects: a runtime index into
 // the argument struct's arrays would force the whole struct into scratch.
 __device__ __forceinline__ float4* ray_o(const TraceArgs& a, int k) { return (k & 1) ? a.buf_o[1] : a.buf_o[0]; }
