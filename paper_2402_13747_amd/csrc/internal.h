@@ -322,12 +322,13 @@ struct PcrlScene {
     uint32_t max_label = 0;
     bool compact = false;             // PCRL_VOXEL_COMPACT: no dense cell table for the implicit surface's walk
     std::shared_ptr<pcrl::Overlay> overlay;  // current epoch of dynamic points (may be null)
-    // own-point index of the implicit-surface intersection (sdf_intersect), built
-    // on first use: every point once, in the leaf holding its centre, in leaf order
+    // own-point index, built on first use (ie_build, sdf_intersect): every point
+    // once, in the leaf holding its centre, in leaf order
     std::mutex own_mu;
-    pcrl::SceneView walk{};           // `view` with the structures of the implicit surface's leaf walk
     uint32_t* own_scan = nullptr;     // [n_entries + 1] own entries before each entry
     float4* own = nullptr;            // [n_points] pairs: position (w: point id bits), unit normal (w: label bits)
+    // the implicit surface's part of it, built by its own first call
+    pcrl::SceneView walk{};           // `view` with the structures of the implicit surface's leaf walk
     float4* own_box = nullptr;        // [n_points] at a leaf's first own entry: centre of the box around its points
     uint32_t* own_first = nullptr;    // [n_leaves + 1] own entries before each leaf
     uint32_t* own_cells = nullptr;    // null, or own entries before each leaf cell (sdf.hip)

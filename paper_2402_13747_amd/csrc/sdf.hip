@@ -292,29 +292,16 @@ __device__ __forceinline__ bool sdf_eval(const float x[3], SdfRuns& runs, float&
 
 // 1 for each entry of the hierarchy listed in the leaf that holds its point's
 // centre (the cell taken in FP32 as everywhere else), else 0.
-template <int NL>
+template <int TD>
 __global__ void k_own_flags(SceneView v, uint32_t m, uint32_t* flag) {
     const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const float4 P = v.surf[2 * (size_t)e];
-    Seg N;
-    N.c[0] = (int)floorf((P.x - v.org[0]) * v.inv_h);
-    N.c[1] = (int)floorf((P.y - v.org[1]) * v.inv_h);
-    N.c[2] = (int)floorf((P.z - v.org[2]) * v.inv_h);
-    uint32_t own = 0u;
-    if (N.c[0] >= 0 && N.c[1] >= 0 && N.c[2] >= 0 && N.c[0] < v.dim[0] && N.c[1] < v.dim[1] && N.c[2] < v.dim[2]) {
-        N.cq[0] = N.cq[1] = N.cq[2] = -1;
-        N.cres = 0;
-        N.cskip0 = 1;
-        N.cbox = NO_BOX;
-        N.cnode = 0;
-        N.oct_shift = 0;
-        DdaCell k;
-        dda_cell_reset(k);
-        dda_locate<NL>(v, N, k);
-        own = (k.lvl == NL && k.range.x <= e && e - k.range.x < k.range.y) ? 1u : 0u;
-    }
-    flag[e] = own;
+    const int x = (int)floorf((P.x - v.org[0]) * v.inv_h), y = (int)floorf((P.y - v.org[1]) * v.inv_h),
+              z = (int)floorf((P.z - v.org[2]) * v.inv_h);
+    uint2 r = make_uint2(0u, 0u);
+    if (x >= 0 && y >= 0 && z >= 0 && x < v.dim[0] && y < v.dim[1] && z < v.dim[2]) r = leaf_range<TD>(v, x, y, z);
+    flag[e] = r.x <= e && e - r.x < r.y ? 1u : 0u;
 }
 
 // Copy the own entries to their compacted slots.
@@ -1093,9 +1080,9 @@ static void own_args(const PcrlScene* S, SdfArgs& a) {
     a.cells = S->own_cells;
 }
 
-template <int NL>
+template <int TD>
 static void launch_own_flags(const SceneView& v, uint32_t m, uint32_t* flag, hipStream_t s) {
-    hipLaunchKernelGGL((k_own_flags<NL>), dim3((unsigned)(((uint64_t)m + 255) / 256)), dim3(256), 0, s, v, m, flag);
+    hipLaunchKernelGGL((k_own_flags<TD>), dim3((unsigned)(((uint64_t)m + 255) / 256)), dim3(256), 0, s, v, m, flag);
 }
 
 // The structures of the leaf walk for scene S in its view v, owned by B: child
@@ -1163,13 +1150,55 @@ static int build_walk(const PcrlScene* S, hipStream_t s, DevBufs& B, SceneView& 
     return hipGetLastError() == hipSuccess ? PCRL_OK : PCRL_EHIP;
 }
 
-// The scene's own-point index, built on the first call (under the scene's
-// lock) and kept with the scene.  The build waits for its stream, so calls on
-// any stream find the index complete.
-static int own_index(PcrlScene* S, hipStream_t s) {
-    std::lock_guard<std::mutex> lock(S->own_mu);
+// Every point once, in the leaf that holds its centre (under the scene's lock).
+static int own_points(PcrlScene* S, hipStream_t s) {
     if (S->own_scan) return PCRL_OK;
+    const SceneView& v = S->view;
     const int64_t m = S->info.n_entries, np = S->info.n_points;
+    DevBufs B;  // handed to the scene when complete
+    B.stream = s;
+    uint32_t* scan = nullptr;
+    float4* own = nullptr;
+    int rc = B.alloc(&scan, (size_t)m + 1);
+    if (!rc) rc = B.alloc(&own, 2 * (size_t)(np > 0 ? np : 1));
+    if (!rc) {
+        switch (v.depth) {
+        case -1: launch_own_flags<-1>(v, (uint32_t)m, scan, s); break;
+        case 0: launch_own_flags<0>(v, (uint32_t)m, scan, s); break;
+        case 1: launch_own_flags<1>(v, (uint32_t)m, scan, s); break;
+        default: launch_own_flags<2>(v, (uint32_t)m, scan, s); break;
+        }
+        rc = hipGetLastError() == hipSuccess ? scan_u32(scan, scan, m, scan + m, s) : PCRL_EHIP;
+    }
+    if (!rc) {
+        hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, v.surf, scan,
+                           (uint32_t)m, (uint32_t)np, own);
+        rc = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? PCRL_OK : PCRL_EHIP;
+    }
+    if (rc) {
+        B.release();
+        if (rc == PCRL_EHIP) set_error("building the scene's own-point index failed");
+        return rc;
+    }
+    S->bufs.ptrs.insert(S->bufs.ptrs.end(), B.ptrs.begin(), B.ptrs.end());
+    S->own = own;
+    S->own_scan = scan;
+    return PCRL_OK;
+}
+
+int scene_own_index(PcrlScene* S, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(S->own_mu);
+    return own_points(S, s);
+}
+
+// The implicit surface's index of the scene (the own points, their leaves'
+// boxes and prefixes, and the leaf walk), built on the first call (under the
+// scene's lock) and kept with the scene.  The build waits for its stream, so
+// calls on any stream find the index complete.
+static int sdf_index(PcrlScene* S, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(S->own_mu);
+    if (S->own_first) return PCRL_OK;
+    PCRL_TRY(own_points(S, s));
     DevBufs B;  // handed to the scene when complete
     B.stream = s;
     SceneView v{};
@@ -1187,30 +1216,17 @@ static int own_index(PcrlScene* S, hipStream_t s) {
     const bool table = P < 0 || (F == P && n_cells * 4 <= OWN_CELLS_MAX_BYTES);
     int key_shift = 0;  // key bits of the levels left out
     for (int l = v.nlev; l < S->view.nlev; ++l) key_shift += v.lbits[l];
-    uint32_t *scan = nullptr, *first = nullptr, *cells = nullptr;
-    float4 *own = nullptr, *box = nullptr;
-    const size_t slots = (size_t)(np > 0 ? np : 1);
-    if (!rc) rc = B.alloc(&scan, (size_t)m + 1);
-    if (!rc) rc = B.alloc(&own, 2 * slots);
-    if (!rc) rc = B.alloc(&box, slots);
+    uint32_t *first = nullptr, *cells = nullptr;
+    float4* box = nullptr;
+    const int64_t np = S->info.n_points;
+    rc = B.alloc(&box, (size_t)(np > 0 ? np : 1));
     if (!rc) rc = B.alloc(&first, (size_t)n_leaves + 1);
     if (!rc && table) rc = B.alloc(&cells, (size_t)n_cells);
     if (!rc && P < 0) rc = fill_u32(cells, 0u, n_cells, s);
     if (!rc) {
-        switch (v.nlev) {
-        case 1: launch_own_flags<1>(v, (uint32_t)m, scan, s); break;
-        case 2: launch_own_flags<2>(v, (uint32_t)m, scan, s); break;
-        case 3: launch_own_flags<3>(v, (uint32_t)m, scan, s); break;
-        default: launch_own_flags<4>(v, (uint32_t)m, scan, s); break;
-        }
-        rc = hipGetLastError() == hipSuccess ? scan_u32(scan, scan, m, scan + m, s) : PCRL_EHIP;
-    }
-    if (!rc) {
-        hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, v.surf, scan,
-                           (uint32_t)m, (uint32_t)np, own);
-        hipLaunchKernelGGL(k_own_leaves, dim3((n_leaves + 255) / 256), dim3(256), 0, s, v.leaf, n_leaves, scan,
-                           (const float4*)own, first, box, P < 0 ? cells : (uint32_t*)nullptr,
-                           (const uint64_t*)S->leaf_key, key_shift);
+        hipLaunchKernelGGL(k_own_leaves, dim3((n_leaves + 255) / 256), dim3(256), 0, s, v.leaf, n_leaves,
+                           (const uint32_t*)S->own_scan, (const float4*)S->own, first, box,
+                           P < 0 ? cells : (uint32_t*)nullptr, (const uint64_t*)S->leaf_key, key_shift);
         if (P < 0)
             rc = scan_u32(cells, cells, n_cells, nullptr, s);
         else if (table)
@@ -1225,15 +1241,11 @@ static int own_index(PcrlScene* S, hipStream_t s) {
     }
     S->bufs.ptrs.insert(S->bufs.ptrs.end(), B.ptrs.begin(), B.ptrs.end());
     S->walk = v;
-    S->own = own;
     S->own_box = box;
-    S->own_first = first;
     S->own_cells = cells;
-    S->own_scan = scan;
+    S->own_first = first;
     return PCRL_OK;
 }
-
-int scene_own_index(PcrlScene* S, hipStream_t s) { return own_index(S, s); }
 
 // Defaults of the implicit surface for a scene (h, eps, max_steps as
 // sdf_intersect's when its parameters are not given).
@@ -1275,7 +1287,7 @@ int sdf_launch_run(PcrlLaunch* L, const TraceArgs& t) {
     SdfLaunchArgs A{};
     sdf_defaults(scene, A.s);
     if (!A.s.empty) {
-        PCRL_TRY(own_index(const_cast<PcrlScene*>(scene), s));
+        PCRL_TRY(sdf_index(const_cast<PcrlScene*>(scene), s));
         own_args(scene, A.s);
     }
     A.tx = t.tx;
@@ -1381,7 +1393,7 @@ extern "C" int sdf_intersect(const PcrlScene* scene, const float* o, const float
     hipStream_t s = (hipStream_t)stream;
     if (!a.empty) {
         // the index is a cache of the scene's data: building it does not change the scene
-        const int rc = own_index(const_cast<PcrlScene*>(scene), s);
+        const int rc = sdf_index(const_cast<PcrlScene*>(scene), s);
         if (rc) return rc;
         own_args(scene, a);
     }

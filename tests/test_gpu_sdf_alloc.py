@@ -73,3 +73,24 @@ def test_index_that_runs_out_of_memory(levels, compact):
         scene.release()
         torch.cuda.synchronize()
         assert not A.sizes  # nothing of the attempts is left
+
+
+def test_ie_table_keeps_the_points_index_alone():
+    """A table of intersectable entities leaves each point of the scene once (32 B) and 4 B per entry with it, not
+    what only the implicit surface reads (blocks have less than half of slack)."""
+    import torch
+    import paper_2402_13747_amd as pcrl
+    s = scenes.box_room()
+    with Limited(torch, pcrl._lib) as A:
+        scene = pcrl.build_voxels(s.xyz, s.normal, s.label, (1.0, 0.1), float(np.float32(s.surfel_radius)))
+        held = sum(A.sizes.values())
+        info = scene.info()
+        ies = pcrl.ie_build(scene, (-0.55, -0.45, -0.6), 0.5, 2, (23, 19, 9))
+        assert ies.info()["n_ies"] > 100
+        ies.release()
+        torch.cuda.synchronize()
+        kept = sum(A.sizes.values()) - held
+        assert 32 * info["n_points"] <= kept <= 1.5 * (32 * info["n_points"] + 4 * info["n_entries"] + 1024), kept
+        scene.release()
+        torch.cuda.synchronize()
+        assert not A.sizes
