@@ -1065,9 +1065,9 @@ static int tail_alloc(SdfArgs& a, uint32_t n, bool launch, DevBufs& T, hipStream
 }
 
 // Largest table of own entries before each cell (4 bytes per leaf cell of
-// every leaves' parent); beyond it, and where the parents have no dense top
-// grid, a sample's runs are found through the bricks' masks (two more
-// dependent loads each).
+// every leaves' parent); beyond it, in compact scenes, where the parents have
+// no dense top grid and where the table finds no memory, a sample's runs are
+// found through the bricks' masks (two more dependent loads each).
 constexpr int64_t OWN_CELLS_MAX_BYTES = (int64_t)4 << 30;
 
 // The scene's arrays for the kernels (the index is built).
@@ -1213,7 +1213,7 @@ static int sdf_index(PcrlScene* S, hipStream_t s) {
     const uint32_t n3 = P < 0 ? 0u : (uint32_t)v.ratio[P] * v.ratio[P] * v.ratio[P];
     const int64_t n_cells = P < 0 ? (int64_t)v.dim[0] * v.dim[1] * v.dim[2] + 1 : (int64_t)v.nn[P] * (n3 + 1);
     const int F = std::max(S->view.nlev - 2 - v.depth, 0);  // level of the top grid
-    const bool table = P < 0 || (F == P && n_cells * 4 <= OWN_CELLS_MAX_BYTES);
+    const bool table = P < 0 || (F == P && !S->compact && n_cells * 4 <= OWN_CELLS_MAX_BYTES);
     int key_shift = 0;  // key bits of the levels left out
     for (int l = v.nlev; l < S->view.nlev; ++l) key_shift += v.lbits[l];
     uint32_t *first = nullptr, *cells = nullptr;
@@ -1221,7 +1221,14 @@ static int sdf_index(PcrlScene* S, hipStream_t s) {
     const int64_t np = S->info.n_points;
     rc = B.alloc(&box, (size_t)(np > 0 ? np : 1));
     if (!rc) rc = B.alloc(&first, (size_t)n_leaves + 1);
-    if (!rc && table) rc = B.alloc(&cells, (size_t)n_cells);
+    if (!rc && table) {
+        rc = B.alloc(&cells, (size_t)n_cells);
+        if (rc == PCRL_ENOMEM && P >= 0) {
+            clear_error();
+            cells = nullptr;
+            rc = PCRL_OK;
+        }
+    }
     if (!rc && P < 0) rc = fill_u32(cells, 0u, n_cells, s);
     if (!rc) {
         hipLaunchKernelGGL(k_own_leaves, dim3((n_leaves + 255) / 256), dim3(256), 0, s, v.leaf, n_leaves,
@@ -1229,7 +1236,7 @@ static int sdf_index(PcrlScene* S, hipStream_t s) {
                            P < 0 ? cells : (uint32_t*)nullptr, (const uint64_t*)S->leaf_key, key_shift);
         if (P < 0)
             rc = scan_u32(cells, cells, n_cells, nullptr, s);
-        else if (table)
+        else if (cells)
             hipLaunchKernelGGL(k_own_cells, dim3((unsigned)((n_cells + 255) / 256)), dim3(256), 0, s, v.mask[P],
                                v.base[P], (const uint32_t*)first, v.nw[P], n3, (uint64_t)n_cells, cells);
         if (!rc) rc = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? PCRL_OK : PCRL_EHIP;

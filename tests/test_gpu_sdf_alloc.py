@@ -94,3 +94,31 @@ def test_ie_table_keeps_the_points_index_alone():
         scene.release()
         torch.cuda.synchronize()
         assert not A.sizes
+
+
+@pytest.mark.parametrize("levels", [(1.0, 0.1), (2.0, 1.0, 0.1)])
+def test_compact_scene_keeps_no_table_of_leaf_cells(levels):
+    """The implicit surface of a compact scene reads the bricks' masks: no table of the leaves' parents' cells, not even
+    of prefixes (4 B a cell), is kept with the scene; a skip radius (1 B a cell) is."""
+    import torch
+    import paper_2402_13747_amd as pcrl
+    s = scenes.box_room()
+    o = torch.tensor([[5.0, 4.0, 1.5]]).expand(200, 3).contiguous().cuda()
+    d = torch.randn(200, 3, generator=torch.Generator().manual_seed(3)).cuda()
+    kept, out = [], []
+    for compact in (False, True):
+        with Limited(torch, pcrl._lib) as A:
+            scene = pcrl.build_voxels(s.xyz, s.normal, s.label, levels, float(np.float32(s.surfel_radius)), compact=compact)
+            held = sum(A.sizes.values())
+            out.append(pcrl.sdf_intersect(scene, o, d))
+            torch.cuda.synchronize()
+            kept.append(sum(A.sizes.values()) - held)
+            parents, leaves = scene.info()["n_nodes"][len(levels) - 2:len(levels)]
+            points, entries = scene.info()["n_points"], scene.info()["n_entries"]
+            cells = 1000 * parents
+            scene.release()
+    assert kept[0] >= 12 * cells
+    # per parent cell the skip radius and 4 B per 64 for the masks' child counts; the points' index
+    assert kept[1] <= 1.5 * (1.1 * cells + 48 * points + 4 * entries + 4 * leaves + 64 * 1024), (kept, cells)
+    for k in ("t", "point", "normal"):
+        assert torch.equal(out[0][k].nan_to_num(-1.0, 1e30), out[1][k].nan_to_num(-1.0, 1e30)), k
