@@ -101,11 +101,11 @@ typedef struct {
 } PcrlVoxelParams;
 
 /* PcrlVoxelParams.flags: the implicit surface (sdf_intersect, PCRL_LAUNCH_SDF)
- * keeps no dense cell table of the leaves' parent bricks (8 bytes per leaf
- * cell of every occupied parent) but walks the bricks' occupancy masks (less
- * device memory, slower).  The table is also left out when the
- * parent-to-leaf ratio exceeds 16 or it would exceed 256 MiB.  The launcher
- * keeps no such table. */
+ * keeps no dense tables of the leaves' parent bricks (ranges, 8 bytes, and
+ * prefixes, 4 bytes per leaf cell of every occupied parent) but reads the
+ * bricks' occupancy masks (less device memory, slower).  The ranges are also
+ * left out when the parent-to-leaf ratio exceeds 16 or they would exceed 256
+ * MiB.  The launcher keeps no such table. */
 #define PCRL_VOXEL_COMPACT 1
 
 typedef struct {
@@ -122,7 +122,8 @@ typedef struct {
     float   surfel_radius;
     float   t_eps;                        /* effective self-intersection distance */
     float   aabb[6];                      /* point AABB: min xyz, max xyz */
-    int64_t device_bytes;                 /* device memory held by the scene */
+    int64_t device_bytes;                 /* device memory held by the scene, its dynamic overlay and the
+                                             index of its points (ie_build, sdf_intersect) included */
     int32_t key_bits;                     /* bits of the hierarchical leaf key */
     int32_t reserved;
     int64_t n_dynamic;                    /* points of the current dynamic overlay (update_points) */
@@ -471,8 +472,14 @@ typedef struct {
  * A ray with a zero or non-finite direction or origin, or t_lo > t_hi, has
  * no intersection.  Asynchronous on `stream`, except that the first call on
  * a scene builds and keeps with the scene an index of each point in the leaf
- * of its centre (16 B per point twice, 4 B per entry) with the structures of its leaf
- * walk (a table or skip radii of the leaf cells), and waits for it.  Calls
+ * of its centre and waits for it: 48 B per point, 4 B per entry and per leaf,
+ * and the structures of its leaf walk.  Those are, per leaf cell of the
+ * leaves' parents, 4 B of prefixes (unless compact, above 4 GiB, without
+ * memory for them, or where the parents' own grid exceeds 64 M cells) and 8 B
+ * of a dense table or 1 B of a skip radius (see PCRL_VOXEL_COMPACT); per brick
+ * 4 B and 4 B per 64 children; 1 B per coarsest cell.  A single-level scene
+ * has 5 B per leaf cell instead.  ie_build keeps 32 B per point and 4 B per
+ * entry of it.  Calls
  * of 65536 rays or more sort the rays by origin and direction first (outputs
  * stay in the caller's order).  PCRL_EINVAL on NULL arrays, out-of-range
  * parameters, or a scene holding dynamic points (update_points): the surface

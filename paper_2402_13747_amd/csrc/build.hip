@@ -1347,6 +1347,7 @@ extern "C" int scene_info(const PcrlScene* scene, PcrlSceneInfo* out) {
         return PCRL_EINVAL;
     }
     *out = scene->info;
+    out->device_bytes += scene->index_bytes;
     if (scene->overlay) out->device_bytes += scene->overlay->bytes;
     return PCRL_OK;
 }

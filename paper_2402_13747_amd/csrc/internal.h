@@ -10,6 +10,7 @@
 
 #include <cstdarg>
 #include <cstdint>
+#include <atomic>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -78,6 +79,7 @@ struct ArenaScope {
 // Owns a list of device allocations released together (stream ordered).
 struct DevBufs {
     std::vector<void*> ptrs;
+    int64_t bytes = 0;  // asked for
     hipStream_t stream = nullptr;
     template <typename T>
     int alloc(T** p, size_t count) {
@@ -85,12 +87,14 @@ struct DevBufs {
         int rc = dalloc(&q, count * sizeof(T), stream);
         if (rc != PCRL_OK) return rc;
         ptrs.push_back(q);
+        bytes += (int64_t)(count * sizeof(T));
         *p = static_cast<T*>(q);
         return PCRL_OK;
     }
     void release() {
         for (void* q : ptrs) dfree(q, stream);
         ptrs.clear();
+        bytes = 0;
     }
 };
 
@@ -325,6 +329,7 @@ struct PcrlScene {
     // own-point index, built on first use (ie_build, sdf_intersect): every point
     // once, in the leaf holding its centre, in leaf order
     std::mutex own_mu;
+    std::atomic<int64_t> index_bytes{0};  // device bytes of the index built so far
     uint32_t* own_scan = nullptr;     // [n_entries + 1] own entries before each entry
     float4* own = nullptr;            // [n_points] pairs: position (w: point id bits), unit normal (w: label bits)
     // the implicit surface's part of it, built by its own first call

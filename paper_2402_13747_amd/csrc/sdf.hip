@@ -1181,6 +1181,7 @@ static int own_points(PcrlScene* S, hipStream_t s) {
         return rc;
     }
     S->bufs.ptrs.insert(S->bufs.ptrs.end(), B.ptrs.begin(), B.ptrs.end());
+    S->index_bytes += B.bytes;
     S->own = own;
     S->own_scan = scan;
     return PCRL_OK;
@@ -1247,6 +1248,7 @@ static int sdf_index(PcrlScene* S, hipStream_t s) {
         return rc;
     }
     S->bufs.ptrs.insert(S->bufs.ptrs.end(), B.ptrs.begin(), B.ptrs.end());
+    S->index_bytes += B.bytes;
     S->walk = v;
     S->own_box = box;
     S->own_cells = cells;

@@ -122,3 +122,23 @@ def test_compact_scene_keeps_no_table_of_leaf_cells(levels):
     assert kept[1] <= 1.5 * (1.1 * cells + 48 * points + 4 * entries + 4 * leaves + 64 * 1024), (kept, cells)
     for k in ("t", "point", "normal"):
         assert torch.equal(out[0][k].nan_to_num(-1.0, 1e30), out[1][k].nan_to_num(-1.0, 1e30)), k
+
+
+@pytest.mark.parametrize("levels,compact", [((0.2,), False), ((1.0, 0.1), False), ((1.0, 0.1), True), ((2.0, 1.0, 0.1), False)])
+def test_device_bytes_hold_the_index(levels, compact):
+    """scene_info's device_bytes grow by the blocks that the scene's index keeps (each block is asked for rounded up by
+    less than half, and to 512 bytes)."""
+    import torch
+    import paper_2402_13747_amd as pcrl
+    s = scenes.box_room()
+    o = torch.tensor([[5.0, 4.0, 1.5]]).cuda()
+    with Limited(torch, pcrl._lib) as A:
+        scene = pcrl.build_voxels(s.xyz, s.normal, s.label, levels, float(np.float32(s.surfel_radius)), compact=compact)
+        for use in (lambda: pcrl.ie_build(scene, (-0.55, -0.45, -0.6), 0.5, 2, (23, 19, 9)).release(),
+                    lambda: pcrl.sdf_intersect(scene, o, o)):
+            held, said, blocks = sum(A.sizes.values()), scene.info()["device_bytes"], len(A.sizes)
+            use()
+            torch.cuda.synchronize()
+            kept, grown = sum(A.sizes.values()) - held, scene.info()["device_bytes"] - said
+            assert 0 < grown <= kept <= 1.5 * grown + 512 * (len(A.sizes) - blocks), (grown, kept)
+        scene.release()
