@@ -275,7 +275,8 @@ typedef struct {
 } PcrlQuery;
 
 typedef struct {
-    int32_t tile_rays;          /* ray slots per work item (multiple of 64); <= 0 -> 64..1024, eight per wave */
+    int32_t tile_rays;          /* most ray slots per work item (multiple of 64); <= 0 -> 1024; fewer (down to
+                                   64) where the batch's rays would not give every wave eight items */
     float   compact_threshold;  /* theta: a bounce keeps survivors in place when the predicted density of live
                                    rays is >= theta, else compacts them; > 1 always compacts; < 0 -> 0.6 */
     int32_t waves_per_cu;       /* persistent waves per compute unit; <= 0 -> 16 */

@@ -269,17 +269,22 @@ static int run_graph(const std::vector<BatchCtl>& host_ctl, const std::vector<Ba
     return PCRL_OK;
 }
 
-// Slots per work item of a group of `rays` rays on `waves` persistent waves
-// when the caller gives none.  A wave works through a tile's 64-slot chunks
-// one after another at up to 0.2 ms each, so the bounce lasts as long as the
-// waves with one tile more than the others: every wave should pop several
-// tiles (8), down to one chunk each.  Past 1024 slots the queue's atomics are
-// negligible.  Ten scenes of 31k-500k rays (1.9 M together, 4096 waves): 28.7 ms
-// a pass with 1024-slot tiles (1,860 tiles: half of the waves idle), 12.6 ms
-// with the 64-slot ones chosen here (both from one queue).
-static uint32_t batch_tile(int64_t rays, int64_t waves) {
+// Slots per work item of a group of `rays` rays on `waves` persistent waves,
+// at most `most` (the caller's, else 1024).  A wave works through a tile's
+// 64-slot chunks one after another at up to 0.2 ms each, so the bounce lasts
+// as long as the waves with one tile more than the others: every wave should
+// pop several tiles (8), down to one chunk each.  Past 1024 slots the queue's
+// atomics are negligible.  Ten scenes of 31k-500k rays (1.9 M together, 4096
+// waves): 28.7 ms a pass with 1024-slot tiles (1,860 tiles: half of the waves
+// idle), 12.6 ms with the 64-slot ones chosen here (both from one queue).  The
+// caller's tiles are cut down too: those scenes with tiles of 256, 1024 and
+// 4096 as given took 5.2, 10.2 and 25.8 ms of kernels, and 4.1 with all of
+// them cut to 64 (eight queues); 15 M rays lose nothing: 16.9, 22.1 and 38.3
+// as given, 16.9, 17.8 and 17.9 cut.
+static uint32_t batch_tile(int64_t rays, int64_t waves, int32_t most) {
     const int64_t t = rays / std::max<int64_t>(1, waves * 8) / 64 * 64;
-    return (uint32_t)std::min<int64_t>(1024, std::max<int64_t>(64, t));
+    const int64_t cap = most > 0 ? std::max(64, most / 64 * 64) : 1024;
+    return (uint32_t)std::min<int64_t>(cap, std::max<int64_t>(64, t));
 }
 
 static int batch_impl(const PcrlQuery* q, int32_t n_q, const PcrlBatchParams* bp, hipStream_t s, PcrlLaunch** out) {
@@ -352,8 +357,7 @@ static int batch_impl(const PcrlQuery* q, int32_t n_q, const PcrlBatchParams* bp
         c.n_q = g_count[g];
         int64_t rays = 0;
         for (uint32_t k = 0; k < c.n_q; ++k) rays += args[(size_t)f + k].n_total;
-        c.tile = bp->tile_rays > 0 ? (uint32_t)std::max(64, (bp->tile_rays / 64) * 64)
-                                   : batch_tile(rays, (int64_t)grid * (TRACE_BLOCK / 64));
+        c.tile = batch_tile(rays, (int64_t)grid * (TRACE_BLOCK / 64), bp->tile_rays);
         c.theta = bp->compact_threshold;
         c.tile_off = tile_off + f + g;  // n_q + 1 entries per group
         c.range = range + f;
