@@ -212,7 +212,8 @@ typedef struct {
     int64_t surfel_tests;                          /* ray-disk tests */
     int64_t hits;                                  /* segments ending on a surfel */
     int64_t algo_bytes;                            /* algorithmic bytes of the trace kernels: hierarchy
-                                                      reads (8 B per top cell, 16 B per block, 8 B per
+                                                      reads (8 B per top cell, 16 B per block, between
+                                                      them 12 B per brick word and 4 B per box, 8 B per
                                                       leaf), 32 B per surfel tested, 36 B ray state read per
                                                       later segment, 52 B per reflection, 16 B per record */
     int64_t empty_leaf_steps;                      /* DDA steps into empty leaves of occupied parents */

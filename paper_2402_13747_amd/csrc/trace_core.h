@@ -14,7 +14,7 @@ constexpr uint32_t NO_HIT = 0xFFFFFFFFu;
 
 // Statistics of the PCRL_LAUNCH_STATS kernel variant.  ST_BYTES is the exact
 // algorithmic traffic of the trace kernels: 8 B per top cell and 16 B per block
-// record read (12 B per brick word between), 8 B per leaf range, 32 B per
+// record read (between them 12 B per brick word and 4 B per box), 8 B per leaf range, 32 B per
 // surfel tested, 36 B of ray state read per segment after the first, 36 B of
 // ray state + 16 B of history per reflection, 16 B per record.
 enum StatSlot {
@@ -390,7 +390,10 @@ __device__ __forceinline__ void walk(const SceneView& v, const uint64_t* ahead, 
                                 q[a] = qi[a];
                             }
                         }
-                        if (found) box = v.pbox[node];
+                        if (found) {
+                            box = v.pbox[node];
+                            if (STATS) cnt[ST_BYTES] += 4;
+                        }
                     }
                     if (found) {
                         // to the box of the brick's occupied leaves, or past the brick
