@@ -386,11 +386,14 @@ static unsigned nblk(uint32_t n) { return std::max(1u, (n + 255u) / 256u); }
 
 // Scratch bytes collect_impl needs for n records with W-word keys: the
 // per-record arrays (W key words, a 64-bit and seven 32-bit arrays), the
-// radix sort's double buffer and tile histograms, the scan's block sums,
-// and 256-byte alignment of every block.
+// radix sort's, the scan's block sums, and 256-byte alignment of every block.
+// For the sort at least 12 bytes a record and 1 KB per 2048 are counted,
+// whatever its tiles need, so that what a launch may hold does not move with
+// them.
 static size_t collect_scratch_bytes(uint64_t n, int W) {
     const uint64_t tiles = (n + 2047) / 2048;
-    return (size_t)(n * (8ull * W + 8 + 28) + n * 12 + tiles * 256 * 4 + (n / 512 + 64) * 4 + 64 * 256);
+    const size_t sort = std::max<size_t>(radix_sort_scratch_bytes((int64_t)n, 12), (size_t)(n * 12 + tiles * 1024));
+    return (size_t)(n * (8ull * W + 8 + 28) + (n / 512 + 64) * 4 + 64 * 256) + sort;
 }
 
 // scratch_limit > 0: the call may use at most that many bytes of temporaries

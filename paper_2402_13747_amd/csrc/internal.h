@@ -113,6 +113,8 @@ int radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int bits, hipStrea
 int radix_sort_u32(uint32_t* keys, uint32_t* vals, int64_t n, int bits, hipStream_t s);
 // The same on key bits [lo_bit, lo_bit + bits) only (lower bits ride along).
 int radix_sort_u64_bits(uint64_t* keys, uint32_t* vals, int64_t n, int lo_bit, int bits, hipStream_t s);
+// Device bytes that a sort of n items of `item` bytes (key and value) takes beside them.
+size_t radix_sort_scratch_bytes(int64_t n, size_t item);
 
 // order[0 .. n) = the indices j < n of `keys` grouped by key (ascending
 // buckets, any order inside a bucket: one counting pass with atomics), where

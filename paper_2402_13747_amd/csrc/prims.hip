@@ -3,9 +3,9 @@
 // The radix sort is the voxel build's dominant step (sorting (leaf key,
 // point id) pairs) and also orders reception records for deduplication.
 // Design: the digit counts of all passes in one read of the keys, then one
-// kernel per pass: each block ranks a tile of 1024 or 8192 keys (stable
-// in-wave ranks from 8 ballots per key, running digit counts in LDS) and hand
-// the tiles' digit prefixes on to each other in tile order.  A sort that fits
+// kernel per pass: each block ranks a tile of 2048 or 8192 keys (stable
+// in-wave ranks from 8 ballots per key, running digit counts in LDS), and the
+// tiles hand their digit prefixes on to each other in tile order.  A sort that fits
 // one tile is one kernel.  Tiles and the keys within them keep their order,
 // so the whole sort is stable.
 #include "internal.h"
@@ -822,6 +822,15 @@ static void launch_sweeps(K* ka, uint32_t* va, K* kb, uint32_t* vb, int64_t n, i
 // 133.
 constexpr int64_t SORT_SMALL = 1 << 18;
 
+// Keys of a tile of a sort of n > SORT_TILE keys.
+static int64_t sort_tile_keys(int64_t n) { return 512 * (n <= SORT_SMALL ? 4 : 16); }
+
+size_t radix_sort_scratch_bytes(int64_t n, size_t item) {
+    if (n <= SORT_TILE) return 0;
+    const int64_t tile = sort_tile_keys(n), n_tiles = (n + tile - 1) / tile;
+    return (size_t)n * item + sizeof(SortAux) + (size_t)n_tiles * SORT_R * sizeof(uint64_t);
+}
+
 template <typename K>
 static int radix_sort_impl(K* keys, uint32_t* vals, int64_t n, int bits, hipStream_t s, int lo_bit = 0) {
     if (n <= 1 || bits <= 0) return PCRL_OK;
@@ -842,7 +851,7 @@ static int radix_sort_impl(K* keys, uint32_t* vals, int64_t n, int bits, hipStre
         set_error("radix sort kernel failed");
         return PCRL_EHIP;
     }
-    const int64_t tile = 512 * (n <= SORT_SMALL ? 4 : 16);
+    const int64_t tile = sort_tile_keys(n);
     const uint32_t n_tiles = (uint32_t)((n + tile - 1) / tile);
     const int64_t n_state = (int64_t)n_tiles * SORT_R;
     K* k2 = nullptr;
