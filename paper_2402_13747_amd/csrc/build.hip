@@ -655,11 +655,9 @@ struct BlockArgs {
     uint32_t* pbox;
 };
 
-__global__ __launch_bounds__(64) void k_brick_blocks(BlockArgs a) {
-    extern __shared__ uint64_t bmask[];  // [nblk^3] masks, then [nblk^3] first ranges (32 bits)
+__device__ __forceinline__ void brick_blocks(const BlockArgs& a, int64_t P, uint64_t* bmask) {
     const int B = a.nblk, B3 = B * B * B, r = a.r;
     uint32_t* bfirst = reinterpret_cast<uint32_t*>(bmask + B3);
-    const int64_t P = blockIdx.x;
     const int lane = (int)lane_id();
     const uint64_t* mask = a.mask + (size_t)P * a.nw;
     const uint32_t first = a.first[P];
@@ -722,6 +720,14 @@ __global__ __launch_bounds__(64) void k_brick_blocks(BlockArgs a) {
         const uint32_t e1 = g + 1 < (uint32_t)a.n_leaves ? a.leaf[g + 1].x : (uint32_t)a.m;
         a.leaf[g].y = e1 - e0;
         a.rng[bfirst[b] + (uint32_t)__popcll(bmask[b] & ((uint64_t(1) << bit) - 1))] = make_uint2(e0, e1 - e0);
+    }
+}
+
+__global__ __launch_bounds__(64) void k_brick_blocks(BlockArgs a) {
+    extern __shared__ uint64_t bmask[];  // [nblk^3] masks, then [nblk^3] first ranges (32 bits)
+    for (int64_t P = blockIdx.x; P < a.n_parents; P += gridDim.x) {
+        brick_blocks(a, P, bmask);
+        __syncthreads();
     }
 }
 
@@ -1151,7 +1157,8 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
         ba.tcell = tcell;
         ba.top = top;
         ba.pbox = pbox;
-        hipLaunchKernelGGL(k_brick_blocks, dim3(host_nodes[P]), dim3(64), (size_t)v.nblk3 * 12, s, ba);
+        hipLaunchKernelGGL(k_brick_blocks, dim3((unsigned)std::min<int64_t>(host_nodes[P], WAVES_MAX)), dim3(64),
+                           (size_t)v.nblk3 * 12, s, ba);
         v.blk = blk;
         v.rng = rng;
         v.pbox = pbox;

@@ -116,6 +116,10 @@ int radix_sort_u64_bits(uint64_t* keys, uint32_t* vals, int64_t n, int lo_bit, i
 // Device bytes that a sort of n items of `item` bytes (key and value) takes beside them.
 size_t radix_sort_scratch_bytes(int64_t n, size_t item);
 
+// Most waves of a launch of one wave an item (each then takes every so many):
+// a grid of 2^32 threads or more is cut off at its low 32 bits without an error.
+constexpr int64_t WAVES_MAX = (int64_t)1 << 22;
+
 // order[0 .. n) = the indices j < n of `keys` grouped by key (ascending
 // buckets, any order inside a bucket: one counting pass with atomics), where
 // n = min(*n_dev, n_max) when n_dev (device) is given, else n_max.
