@@ -744,7 +744,7 @@ __device__ __forceinline__ void cone_ranges(const ConeArgs& a, ConeLds& W, uint3
     }
 }
 
-// One cone per wave: march the axis voxel by voxel (Amanatides and Woo; every
+// One cone of a wave: march the axis voxel by voxel (Amanatides and Woo; every
 // boundary distance computed from the origin, no accumulation) up to the voxel
 // holding t_end; at every voxel the neighbours it adds to the union of 3x3x3
 // blocks along the march are evaluated (all 27 at the first voxel, then the 9
@@ -757,12 +757,8 @@ __device__ __forceinline__ void cone_ranges(const ConeArgs& a, ConeLds& W, uint3
 // up together, their targets dealt out over the lanes.  Bound by the latency of
 // these chains.  1M-point room, 16 RX, three generations: 0.47 ms, 5.95 with
 // one cone per thread (every RX against every voxel, an atomic per target).
-__global__ __launch_bounds__(CONE_BLOCK) void k_cones(ConeArgs a) {
-    __shared__ ConeLds lds[CONE_BLOCK / 64];
+__device__ __forceinline__ void cone_march(const ConeArgs& a, ConeLds& W, uint32_t q) {
     const uint32_t lane = lane_id();
-    const uint32_t q = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (CONE_BLOCK / 64) + (threadIdx.x >> 6)));
-    if (q >= a.cones.n) return;
-    ConeLds& W = lds[threadIdx.x >> 6];
     const IeGrid& g = a.g;
     const uint32_t node = a.cones.node[q];
     const float4 A = a.gen.apex[node];
@@ -864,6 +860,13 @@ __global__ __launch_bounds__(CONE_BLOCK) void k_cones(ConeArgs a) {
             look(src >= 0, w);
         }
     }
+}
+
+__global__ __launch_bounds__(CONE_BLOCK) void k_cones(ConeArgs a) {
+    __shared__ ConeLds lds[CONE_BLOCK / 64];
+    constexpr uint32_t WAVES = CONE_BLOCK / 64;
+    uint32_t q = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * WAVES + (threadIdx.x >> 6)));
+    for (; q < a.cones.n; q += gridDim.x * WAVES) cone_march(a, lds[threadIdx.x >> 6], q);
 }
 
 // ---------------------------------------------------------------------------
@@ -1499,7 +1502,8 @@ static int cone_launch_impl(const PcrlIes* I, const float* tx, int32_t n_tx, con
             c.n_cand = counters;
             c.cand_node = cnode;
             c.cand_target = ctarget;
-            hipLaunchKernelGGL(k_cones, dim3(blocks(cs.n, CONE_BLOCK / 64)), dim3(CONE_BLOCK), 0, s, c);
+            hipLaunchKernelGGL(k_cones, dim3(blocks(std::min<int64_t>(cs.n, WAVES_MAX), CONE_BLOCK / 64)), dim3(CONE_BLOCK),
+                               0, s, c);
             if (hipGetLastError() != hipSuccess || read_u32(counters, &n_cand, s)) {
                 set_error("cone_launch: cone kernel failed: %s", hipGetErrorString(hipGetLastError()));
                 return fail(PCRL_EHIP);
