@@ -1125,7 +1125,7 @@ static int build_walk(const PcrlScene* S, hipStream_t s, DevBufs& B, SceneView& 
         } else if (r >= 3 && r <= 16) {
             uint8_t* ld = nullptr;
             if ((rc = B.alloc(&ld, (size_t)n_cells))) return rc;
-            const dim3 g = blocks(nb, WALK_BLOCK / 64);
+            const dim3 g = blocks(std::min(nb, WAVES_MAX), WALK_BLOCK / 64);
             if (r == 10)
                 hipLaunchKernelGGL(k_brick_dist<10>, g, dim3(WALK_BLOCK), 0, s, v.mask[L - 2], v.nw[L - 2], r, nb, ld);
             else if (r == 8)

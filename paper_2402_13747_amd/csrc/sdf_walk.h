@@ -416,60 +416,62 @@ __global__ __launch_bounds__(WALK_BLOCK) void k_brick_dist(const uint64_t* mask,
     const int n2 = r * r, n3 = n2 * r;
     const int w = threadIdx.x >> 6;
     const int lane = (int)lane_id();
-    const int64_t P = (int64_t)blockIdx.x * (WALK_BLOCK / 64) + w;
-    if (P >= n_bricks) return;  // the whole wave: no block-wide barrier follows
     uint32_t* cur = rows_s[w][0];
     uint32_t* tmp = rows_s[w][1];
     uint8_t* D = d_s[w];
     const uint32_t full = (1u << r) - 1u;
-    // row j holds bits [r j, r j + r) of the brick's mask
-    for (int j = lane; j < n2; j += 64) {
-        const int b0 = r * j;
-        const uint64_t* m = mask + (size_t)P * nw + (b0 >> 6);
-        uint64_t bits = m[0] >> (b0 & 63);
-        if ((b0 & 63) + r > 64) bits |= m[1] << (64 - (b0 & 63));
-        cur[j] = (uint32_t)bits & full;
-    }
-    walk_wave_sync();
-    for (int c = lane; c < n3; c += 64) D[c] = ((cur[c / r] >> (c % r)) & 1u) ? 0 : 255;
-    const int K = (r - 1) / 2 + 1;
-    for (int k = 1; k <= K; ++k) {
-        // along x, then y
+    // whole waves go on or end: no block-wide barrier in here
+    for (int64_t P = (int64_t)blockIdx.x * (WALK_BLOCK / 64) + w; P < n_bricks; P += (int64_t)gridDim.x * (WALK_BLOCK / 64)) {
+        // row j holds bits [r j, r j + r) of the brick's mask
         for (int j = lane; j < n2; j += 64) {
-            const int y = j % r;
-            const uint32_t a = cur[j];
-            uint32_t t = a | (a << 1) | (a >> 1);
-            if (y > 0) {
-                const uint32_t b = cur[j - 1];
-                t |= b | (b << 1) | (b >> 1);
-            }
-            if (y < r - 1) {
-                const uint32_t b = cur[j + 1];
-                t |= b | (b << 1) | (b >> 1);
-            }
-            tmp[j] = t & full;
+            const int b0 = r * j;
+            const uint64_t* m = mask + (size_t)P * nw + (b0 >> 6);
+            uint64_t bits = m[0] >> (b0 & 63);
+            if ((b0 & 63) + r > 64) bits |= m[1] << (64 - (b0 & 63));
+            cur[j] = (uint32_t)bits & full;
         }
         walk_wave_sync();
-        // along z; the cells reached now are at distance k
-        for (int j = lane; j < n2; j += 64) {
-            const int z = j / r;
-            uint32_t t = tmp[j];
-            if (z > 0) t |= tmp[j - r];
-            if (z < r - 1) t |= tmp[j + r];
-            uint32_t nb = t & ~cur[j];
-            while (nb) {
-                const int x = __ffs(nb) - 1;
-                nb &= nb - 1u;
-                D[x + r * j] = (uint8_t)k;
+        for (int c = lane; c < n3; c += 64) D[c] = ((cur[c / r] >> (c % r)) & 1u) ? 0 : 255;
+        const int K = (r - 1) / 2 + 1;
+        for (int k = 1; k <= K; ++k) {
+            // along x, then y
+            for (int j = lane; j < n2; j += 64) {
+                const int y = j % r;
+                const uint32_t a = cur[j];
+                uint32_t t = a | (a << 1) | (a >> 1);
+                if (y > 0) {
+                    const uint32_t b = cur[j - 1];
+                    t |= b | (b << 1) | (b >> 1);
+                }
+                if (y < r - 1) {
+                    const uint32_t b = cur[j + 1];
+                    t |= b | (b << 1) | (b >> 1);
+                }
+                tmp[j] = t & full;
             }
-            cur[j] = t;
+            walk_wave_sync();
+            // along z; the cells reached now are at distance k
+            for (int j = lane; j < n2; j += 64) {
+                const int z = j / r;
+                uint32_t t = tmp[j];
+                if (z > 0) t |= tmp[j - r];
+                if (z < r - 1) t |= tmp[j + r];
+                uint32_t nb = t & ~cur[j];
+                while (nb) {
+                    const int x = __ffs(nb) - 1;
+                    nb &= nb - 1u;
+                    D[x + r * j] = (uint8_t)k;
+                }
+                cur[j] = t;
+            }
+            walk_wave_sync();
+        }
+        for (int c = lane; c < n3; c += 64) {
+            const int x = c % r, y = (c / r) % r, z = c / n2;
+            const int db = min(min(min(x, r - 1 - x), min(y, r - 1 - y)), min(z, r - 1 - z));
+            dist[P * n3 + c] = (uint8_t)min((int)D[c], db + 1);
         }
         walk_wave_sync();
-    }
-    for (int c = lane; c < n3; c += 64) {
-        const int x = c % r, y = (c / r) % r, z = c / n2;
-        const int db = min(min(min(x, r - 1 - x), min(y, r - 1 - y)), min(z, r - 1 - z));
-        dist[P * n3 + c] = (uint8_t)min((int)D[c], db + 1);
     }
 }
 
