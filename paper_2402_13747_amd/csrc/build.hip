@@ -540,6 +540,8 @@ __global__ void k_leaf_counts(uint2* leaf, int64_t n_leaves, int64_t m) {
 //   k_top_codes the same along z per octant, then one 4-bit code s - 1 per
 //               octant and cell.
 // Cells outside the grid count as empty (a ray that reaches them has left).
+// Both work on the rows of y0 <= y < y0 + ny of every slab: a large grid is
+// done in turns, so that the planes (224 B a word) stay small.
 // Bound by the loads of the rows (each word read 16 times from the caches) and
 // the 8 B written per cell.  8 M cells (a 20M-point street's 1 m cells): 33 us
 // and 97 us; the isotropic radii of every leaf cell and the bricks' boxes that
@@ -547,18 +549,19 @@ __global__ void k_leaf_counts(uint2* leaf, int64_t n_leaves, int64_t m) {
 constexpr int TOP_NS = 7;
 __device__ constexpr int TOP_SIZES[TOP_NS] = {2, 3, 4, 6, 8, 12, 16};
 
-__global__ __launch_bounds__(BUILD_BLOCK) void k_top_rows(const uint64_t* occ, int words, int dy, int dz,
+__global__ __launch_bounds__(BUILD_BLOCK) void k_top_rows(const uint64_t* occ, int words, int dy, int dz, int y0, int ny,
                                                           uint64_t* plane) {
-    const int64_t n = (int64_t)words * dy * dz;
+    const int64_t n = (int64_t)words * ny * dz;
     const int64_t i = (int64_t)blockIdx.x * BUILD_BLOCK + threadIdx.x;
     const int q = blockIdx.y;  // bit 0: towards -x, bit 1: towards -y
     if (i >= n) return;
-    const int w = (int)(i % words), y = (int)((i / words) % dy);
-    const int64_t row0 = i - w;  // first word of the row
+    const int64_t r = i / words;
+    const int w = (int)(i - r * words), z = (int)(r / ny), y = y0 + (int)(r - (int64_t)z * ny);
+    const int64_t row0 = ((int64_t)z * dy + y) * words;  // first word of the row
     uint64_t acc[TOP_NS] = {0, 0, 0, 0, 0, 0, 0};
-    const bool nx = q & 1, ny = q & 2;
+    const bool nx = q & 1, my = q & 2;
     for (int j = 0; j < TOP_SIZES[TOP_NS - 1]; ++j) {
-        const int yy = ny ? y - j : y + j;
+        const int yy = my ? y - j : y + j;
         if (yy < 0 || yy >= dy) break;
         const uint64_t* row = occ + row0 + (int64_t)(yy - y) * words;
         const uint64_t cur = row[w];
@@ -580,16 +583,15 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_top_rows(const uint64_t* occ, i
 constexpr int TOP_WORDS = BUILD_BLOCK / 8;  // words per block: one thread per (word, octant)
 
 __global__ __launch_bounds__(BUILD_BLOCK) void k_top_codes(const uint64_t* occ, const uint64_t* plane, int words,
-                                                           int dx, int dy, int dz, uint2* top) {
+                                                           int dx, int dy, int dz, int y0, int ny, uint2* top) {
     __shared__ uint64_t bits[TOP_WORDS][8][4];
-    const int64_t n = (int64_t)words * dy * dz;
+    const int64_t slab = (int64_t)words * ny, n = slab * dz;
     const int64_t i0 = (int64_t)blockIdx.x * TOP_WORDS;
     {
         const int o = threadIdx.x / TOP_WORDS, wl = threadIdx.x % TOP_WORDS;
         const int64_t i = i0 + wl;
         uint64_t e[TOP_NS] = {0, 0, 0, 0, 0, 0, 0};  // cells with a free box of the size
         if (i < n) {
-            const int64_t slab = (int64_t)words * dy;
             const int z = (int)(i / slab);
             const bool nz = o & 4;
             uint64_t above = ~0ull;
@@ -615,24 +617,16 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_top_codes(const uint64_t* occ, 
     for (int wl = threadIdx.x >> 6; wl < TOP_WORDS; wl += BUILD_BLOCK / 64) {
         const int64_t i = i0 + wl;
         if (i >= n) break;
-        const int x = (int)(i % words) * 64 + lane;
-        if (x >= dx || ((occ[i] >> lane) & 1ull)) continue;
+        const int64_t r = i / words, z = r / ny, row = z * dy + y0 + (r - z * ny);
+        const int w = (int)(i - r * words), x = w * 64 + lane;
+        if (x >= dx || ((occ[row * words + w] >> lane) & 1ull)) continue;
         uint32_t code = 0;
 #pragma unroll
         for (int o = 0; o < 8; ++o)
 #pragma unroll
             for (int b = 0; b < 4; ++b) code |= (uint32_t)((bits[wl][o][b] >> lane) & 1ull) << (4 * o + b);
-        top[(i / words) * dx + x] = make_uint2(0xFFFFFFFFu, code);
+        top[row * dx + x] = make_uint2(0xFFFFFFFFu, code);
     }
-}
-
-// Top cells of a grid without skip codes.
-__global__ void k_top_plain(const uint64_t* occ, int words, int dx, int64_t n, uint2* top) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n) return;
-    const int64_t row = c / dx;
-    const int x = (int)(c - row * dx);
-    if (!((occ[row * words + (x >> 6)] >> (x & 63)) & 1ull)) top[c] = make_uint2(0xFFFFFFFFu, 0u);
 }
 
 // One wave per leaves' parent: the occupancy of its blocks of 4 x 4 x 4
@@ -806,9 +800,8 @@ static int validate_params(const PcrlVoxelParams* p, int32_t ratio[PCRL_MAX_LEVE
 // a leaf's brick with one load) while their grid has at most this many cells
 // (8 bytes each), else the finest coarser level that has, or level 0.
 constexpr int64_t TOP_MAX_CELLS = (int64_t)64 << 20;
-// Grids beyond this many cells (only a level-0 grid can be) keep no skip
-// codes: every empty cell is crossed by itself.
-constexpr int64_t TOP_CODES_MAX_CELLS = (int64_t)512 << 20;
+// Words of occupancy whose skip codes are made at a time (0.94 GB of planes).
+constexpr int64_t TOP_PLANE_WORDS = (int64_t)4 << 20;
 
 static int64_t top_cells(const SceneView& v) { return (int64_t)v.tdim[0] * v.tdim[1] * v.tdim[2]; }
 
@@ -1115,16 +1108,19 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
         v.mbase[i] = bs;
         hb.bytes += (int64_t)host_nodes[F + i] * v.nw[F + i] * 4;
     }
-    if (cells <= TOP_CODES_MAX_CELLS) {
+    {
+        const int64_t per_row = (int64_t)words * v.tdim[2];
+        const int rows = (int)std::min<int64_t>(v.tdim[1], std::max<int64_t>(1, TOP_PLANE_WORDS / per_row));
         uint64_t* plane = nullptr;
-        if ((rc = T.alloc(&plane, (size_t)(4 * TOP_NS * occ_words)))) return rc;
-        hipLaunchKernelGGL(k_top_rows, dim3(blocks_for(occ_words), 4), dim3(BUILD_BLOCK), 0, s, (const uint64_t*)occ,
-                           words, v.tdim[1], v.tdim[2], plane);
-        hipLaunchKernelGGL(k_top_codes, dim3(blocks_for(occ_words, TOP_WORDS)), dim3(BUILD_BLOCK), 0, s,
-                           (const uint64_t*)occ, (const uint64_t*)plane, words, v.tdim[0], v.tdim[1], v.tdim[2], top);
-    } else {
-        hipLaunchKernelGGL(k_top_plain, dim3(blocks_for(cells)), dim3(BUILD_BLOCK), 0, s, (const uint64_t*)occ, words,
-                           v.tdim[0], cells, top);
+        if ((rc = T.alloc(&plane, (size_t)(4 * TOP_NS * per_row * rows)))) return rc;
+        for (int y0 = 0; y0 < v.tdim[1]; y0 += rows) {
+            const int ny = std::min(rows, v.tdim[1] - y0);
+            hipLaunchKernelGGL(k_top_rows, dim3(blocks_for(per_row * ny), 4), dim3(BUILD_BLOCK), 0, s, (const uint64_t*)occ,
+                               words, v.tdim[1], v.tdim[2], y0, ny, plane);
+            hipLaunchKernelGGL(k_top_codes, dim3(blocks_for(per_row * ny, TOP_WORDS)), dim3(BUILD_BLOCK), 0, s,
+                               (const uint64_t*)occ, (const uint64_t*)plane, words, v.tdim[0], v.tdim[1], v.tdim[2], y0, ny,
+                               top);
+        }
     }
     v.leaf = leaf;
     hb.leaf_range = leaf;
