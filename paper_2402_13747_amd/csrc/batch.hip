@@ -103,15 +103,15 @@ __global__ __launch_bounds__(TILE_BLOCK) void k_batch_tiles(BatchCtl* c, int b) 
     if (threadIdx.x < (uint32_t)XCDS) c->next[threadIdx.x][0] = 0;
 }
 
-// One persistent kernel per group of queries with the same top-grid depth TD
-// and overlay presence OV (the specialisations of the bounce body).  Every XCD
+// One persistent kernel per group of queries with the same top-grid depths of
+// scene and overlay (the specialisations of the bounce body).  Every XCD
 // (workgroups are dispatched to them round-robin) has a queue of its own, one
 // contiguous eighth of the tiles, so that its L2 holds the part of one scene
 // that neighbouring rays share; waves that find it empty go on with the next
 // XCD's.  Ten scenes of 31k-500k rays (1.9 M together), four bounces: 9.1 ms
 // of kernels (14 % of the VALU's cycles used: a scene's lines went through all
 // eight L2s) from one queue, 3.3 ms from eight; 10.9 -> 5.5 ms a pass.
-template <bool FIRST, bool STATS, int TD, bool OV>
+template <bool FIRST, bool STATS, int TD, int OTD>
 __global__ __launch_bounds__(TRACE_BLOCK) void k_trace_batch(BatchCtl* c, int b) {
     __shared__ TraceLds<TRACE_BLOCK / 64> lds;
     ahead_init(lds.ahead, threadIdx.x, TRACE_BLOCK);
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace_batch(BatchCtl* c, int b)
         const uint32_t start = (t - c->tile_off[q]) * tile;
         const uint32_t end = min(start + tile, range);
         for (uint32_t base = start; base < end; base += 64)
-            trace_chunk<FIRST, STATS, TD, OV>(args, lds.ahead, lds.w[threadIdx.x >> 6], b, base, 64, range, ip, cnt);
+            trace_chunk<FIRST, STATS, TD, OTD>(args, lds.ahead, lds.w[threadIdx.x >> 6], b, base, 64, range, ip, cnt);
         if (STATS) flush_stats<STATS>(cnt, a.stats ? a.stats + (size_t)b * PCRL_NSTATS : nullptr);
     }
 }
@@ -170,24 +170,15 @@ struct BatchShared {
 // Queries of one kernel specialisation, contiguous in the query table.
 struct BatchGroup {
     int depth;
-    bool ov;
+    int ov;  // the overlays' depth, or NO_OV
 };
-
-template <bool FIRST, bool STATS, int TD>
-static void launch_group_td(bool ov, BatchCtl* ctl, int b, unsigned grid, hipStream_t s) {
-    if (ov) hipLaunchKernelGGL((k_trace_batch<FIRST, STATS, TD, true>), dim3(grid), dim3(TRACE_BLOCK), 0, s, ctl, b);
-    else hipLaunchKernelGGL((k_trace_batch<FIRST, STATS, TD, false>), dim3(grid), dim3(TRACE_BLOCK), 0, s, ctl, b);
-}
 
 template <bool FIRST, bool STATS>
 static void launch_group(const BatchGroup& g, BatchCtl* ctl, int b, unsigned grid, hipStream_t s) {
-    static_assert(PCRL_MAX_LEVELS == 4, "one kernel specialisation per top-grid depth");
-    switch (g.depth) {
-    case -1: launch_group_td<FIRST, STATS, -1>(g.ov, ctl, b, grid, s); break;
-    case 0: launch_group_td<FIRST, STATS, 0>(g.ov, ctl, b, grid, s); break;
-    case 1: launch_group_td<FIRST, STATS, 1>(g.ov, ctl, b, grid, s); break;
-    default: launch_group_td<FIRST, STATS, 2>(g.ov, ctl, b, grid, s); break;
-    }
+    with_depths(g.depth, g.ov, [&](auto td, auto otd) {
+        hipLaunchKernelGGL((k_trace_batch<FIRST, STATS, decltype(td)::value, decltype(otd)::value>), dim3(grid),
+                           dim3(TRACE_BLOCK), 0, s, ctl, b);
+    });
 }
 
 // A captured bounce loop: replayable for any batch with the same maximum K,
@@ -224,7 +215,7 @@ static int run_graph(const std::vector<BatchCtl>& host_ctl, const std::vector<Ba
         char head[96];
         snprintf(head, sizeof head, "%d/%p/%d/%u/%d", dev, (void*)s, kmax, grid, stats ? 1 : 0);
         key = head;
-        for (const auto& g : groups) key += "/" + std::to_string(g.depth) + (g.ov ? "o" : "b");
+        for (const auto& g : groups) key += "/" + std::to_string(g.depth) + "o" + std::to_string(g.ov);
     }
     std::lock_guard<std::mutex> lock(g_graph_mu);
     GraphEntry& e = g_graphs[key];
@@ -310,20 +301,20 @@ static int batch_impl(const PcrlQuery* q, int32_t n_q, const PcrlBatchParams* bp
             set_error("%s", msg);
         }
     }
-    // query table ordered by kernel specialisation (top-grid depth, overlay); one group per run
+    // query table ordered by kernel specialisation (top-grid depths); one group per run
     std::vector<BatchGroup> groups;
     std::vector<uint32_t> g_first, g_count;
     if (!rc) {
         std::vector<int> order((size_t)n_q);
         for (int i = 0; i < n_q; ++i) order[(size_t)i] = i;
-        auto cls = [&](int i) { return (args[(size_t)i].v.depth + 1) * 2 + (args[(size_t)i].has_ov ? 1 : 0); };
+        auto cls = [&](int i) { return (args[(size_t)i].v.depth + 1) * 8 + overlay_depth(args[(size_t)i]) - NO_OV; };
         std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cls(x) < cls(y); });
         std::vector<TraceArgs> sorted((size_t)n_q);
         for (int k = 0; k < n_q; ++k) {
             const TraceArgs& a = args[(size_t)order[(size_t)k]];
             sorted[(size_t)k] = a;
             if (k == 0 || cls(order[(size_t)k]) != cls(order[(size_t)k - 1])) {
-                groups.push_back(BatchGroup{a.v.depth, a.has_ov != 0});
+                groups.push_back(BatchGroup{a.v.depth, overlay_depth(a)});
                 g_first.push_back((uint32_t)k);
                 g_count.push_back(0);
             }

@@ -334,7 +334,7 @@ struct LevelShifts {
 struct HierOut {
     const uint32_t* unmap0;   // rank of an occupied level-0 cell -> the cell (null: keys hold the cell)
     int32_t g_sh0;            // bits below the level-0 part of a key (without the packed point index)
-    int32_t* map0;
+    int32_t* map0;            // or null
     uint64_t* mask[PCRL_MAX_LEVELS - 1];
     uint32_t* first_child[PCRL_MAX_LEVELS - 1];
     uint2* leaf;
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_link(const uint64_t* keys, int6
             if (!((f >> l) & 1u)) continue;
             if (l == 0) {
                 const uint64_t top = k >> ls.sh[0];
-                h.map0[h.unmap0 ? (uint64_t)h.unmap0[top] : top] = (int32_t)node[0];
+                if (h.map0) h.map0[h.unmap0 ? (uint64_t)h.unmap0[top] : top] = (int32_t)node[0];
             }
             if (l == h.F) {
                 // the node's cell of the top grid: its level-0 cell, then the local cells down to level F
@@ -803,17 +803,26 @@ constexpr int64_t TOP_MAX_CELLS = (int64_t)64 << 20;
 // Words of occupancy whose skip codes are made at a time (0.94 GB of planes).
 constexpr int64_t TOP_PLANE_WORDS = (int64_t)4 << 20;
 
+// An overlay is built anew for every frame: its own top grid has at most this
+// many cells, or so many a point when they are more, so that few points cost
+// little in a large scene.  Frame and launch (300 k or 1 M rays) in a 20M-point
+// street, 8 M cells: of 1.4 k points 0.42 + 1.55 ms and 64.5 MB with the grid of
+// its 1 m cells, 0.35 + 1.50 ms and 0.6 MB with that of its 8 m cells; of 50 k
+// points 0.50 + 2.19 ms and 81.5 MB, 0.41 + 2.15 ms and 17.6 MB.
+constexpr int64_t OVERLAY_TOP_CELLS = (int64_t)1 << 18, OVERLAY_CELLS_PER_POINT = 16;
+
 static int64_t top_cells(const SceneView& v) { return (int64_t)v.tdim[0] * v.tdim[1] * v.tdim[2]; }
 
-// The top grid, the brick levels below it and the blocks' layout of a frame.
-static void set_top(SceneView& v) {
+// The top grid (of at most `most` cells where a level has so few), the brick
+// levels below it and the blocks' layout of a frame.
+static void set_top(SceneView& v, int64_t most) {
     const int P = v.nlev - 2;  // the leaves' parents
     int F = std::max(P, 0);
     auto dims = [&](int l) {
         for (int a = 0; a < 3; ++a) v.tdim[a] = v.dim[a] / v.span[l];
         return top_cells(v);
     };
-    while (dims(F) > TOP_MAX_CELLS && F > 0) --F;
+    while (dims(F) > most && F > 0) --F;
     // depth counts at most two brick levels: with four voxel levels a top grid on level 0 leaves two above the parents
     v.depth = P < 0 ? -1 : P - F;
     const float span = (float)v.span[F];
@@ -896,7 +905,7 @@ static int make_frame(const PcrlVoxelParams* params, const int32_t ratio[PCRL_MA
         return PCRL_EINVAL;
     }
     v.key_bits = key_bits;
-    set_top(v);
+    set_top(v, TOP_MAX_CELLS);
     const double diag = std::sqrt((double)(io.hi[0] - io.lo[0]) * (io.hi[0] - io.lo[0]) +
                                   (double)(io.hi[1] - io.lo[1]) * (io.hi[1] - io.lo[1]) +
                                   (double)(io.hi[2] - io.lo[2]) * (io.hi[2] - io.lo[2]));
@@ -917,9 +926,10 @@ struct HierBuild {
 };
 
 // Voxelise n ingested points into the frame already set in v (level-0 map,
-// bricks, leaves, surfel streams).  gid: global point ids (null: 0..n-1).
+// bricks, leaves, surfel streams).  gid: global point ids (null: 0..n-1);
+// base: with the level-0 map (the implicit surface's, which overlays have not).
 static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint32_t* label, const uint32_t* gid,
-                           int64_t n, hipStream_t s, SceneView& v, DevBufs& B, DevBufs& T,
+                           int64_t n, hipStream_t s, bool base, SceneView& v, DevBufs& B, DevBufs& T,
                            HierBuild& hb) {
     const int L = v.nlev;
     int rc = PCRL_OK;
@@ -934,11 +944,13 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
     }
     const uint64_t cells0 = (uint64_t)v.dim0[0] * v.dim0[1] * v.dim0[2];
     int32_t* map0 = nullptr;
-    if ((rc = B.alloc(&map0, (size_t)cells0))) return rc;
-    if ((rc = fill_u32((uint32_t*)map0, 0xFFFFFFFFu, (int64_t)cells0, s))) return rc;
+    if (base) {
+        if ((rc = B.alloc(&map0, (size_t)cells0))) return rc;
+        if ((rc = fill_u32((uint32_t*)map0, 0xFFFFFFFFu, (int64_t)cells0, s))) return rc;
+    }
     v.map0 = map0;
     for (int l = 0; l < PCRL_MAX_LEVELS; ++l) v.nn[l] = 0;
-    hb.bytes = (int64_t)cells0 * 4;
+    hb.bytes = base ? (int64_t)cells0 * 4 : 0;
     const int64_t cells = top_cells(v);
     uint2* top = nullptr;
     if ((rc = B.alloc(&top, (size_t)cells))) return rc;
@@ -1226,7 +1238,7 @@ static int build_impl(const float* xyz, const float* nrm, const uint32_t* label,
     if ((rc = make_frame(params, ratio, io, v))) return fail(rc);
     HierBuild hb;
     S->compact = (params->flags & PCRL_VOXEL_COMPACT) != 0;
-    if ((rc = build_hierarchy(xyz, unit_nrm, label, nullptr, n, s, v, S->bufs, T, hb))) return fail(rc);
+    if ((rc = build_hierarchy(xyz, unit_nrm, label, nullptr, n, s, true, v, S->bufs, T, hb))) return fail(rc);
     S->max_label = io.max_label;
     S->leaf_key = hb.leaf_key;
     S->entry_point = hb.entry_point;
@@ -1280,6 +1292,8 @@ static int overlay_impl(PcrlScene* S, const uint32_t* gid, const float* xyz, con
         }
     }
     SceneView v = bv;  // same frame: origin, levels, padding, t_eps
+    // never a finer top grid than the base's (with_depths)
+    set_top(v, std::min(top_cells(bv), std::max(OVERLAY_TOP_CELLS, OVERLAY_CELLS_PER_POINT * n)));
     v.map0 = nullptr;
     for (int l = 0; l + 1 < PCRL_MAX_LEVELS; ++l) v.mask[l] = nullptr;
     for (int i = 0; i < 2; ++i) {
@@ -1292,7 +1306,7 @@ static int overlay_impl(PcrlScene* S, const uint32_t* gid, const float* xyz, con
     v.leaf = nullptr;
     v.surf = nullptr;
     HierBuild hb;
-    if ((rc = build_hierarchy(xyz, unit_nrm, label, gid, n, s, v, ov->bufs, T, hb))) return fail(rc);
+    if ((rc = build_hierarchy(xyz, unit_nrm, label, gid, n, s, false, v, ov->bufs, T, hb))) return fail(rc);
     ov->view = v;
     ov->n_points = n;
     ov->n_entries = hb.n_entries;

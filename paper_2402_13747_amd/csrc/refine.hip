@@ -163,7 +163,7 @@ constexpr float PART_LEAVES = 1.f;
 // from o to the target (0: the target is o, no ray).  The target lies at or
 // near a surface: the lanes of a group walk parts of the ray up to a little
 // beyond it, and the first lane goes on from there if none finds a hit.
-template <int TD, bool OV>
+template <int TD, int OTD>
 __device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_t* ahead, WaveLds& W, bool act, const float o[3],
                                               const float target[3], uint32_t last, float skip, Hit& hit, float d[3],
                                               float os[3], float& len) {
@@ -193,12 +193,12 @@ __device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_
     const float part = near / parts, t0 = (float)j * part, t1 = (float)(j + 1u) * part;
     const bool walks = go && (float)j < parts;
     trace_parts<TD, false>(ahead, W, lead, walks, t0, t1, hit);
-    if (OV) trace_parts<TD, true>(ahead, W, lead, walks, t0, t1, hit);
+    if constexpr (OTD != NO_OV) trace_parts<OTD, true>(ahead, W, lead, walks, t0, t1, hit);
     const bool on = go && hit.id == NO_HIT;
     if (ballot(on)) {
         const float from = parts * part;
         trace_parts<TD, false>(ahead, W, lead, on && j == 0, from, INFINITY, hit);
-        if (OV) trace_parts<TD, true>(ahead, W, lead, on && j == 0, from, INFINITY, hit);
+        if constexpr (OTD != NO_OV) trace_parts<OTD, true>(ahead, W, lead, on && j == 0, from, INFINITY, hit);
     }
 }
 
@@ -281,7 +281,7 @@ __device__ __forceinline__ void load3(const float4* p, float x[3]) {
     x[2] = v.z;
 }
 
-template <int TD, bool OV>
+template <int TD, int OTD>
 __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     __shared__ TraceLds<1> lds;
     __shared__ PathLds S;
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
             float tg[3] = {0.f, 0.f, 0.f}, d[3], os[3], len;
             if (act) load3(&S.tgt[s0 + k], tg);
             Hit hit;
-            trace_towards<TD, OV>(a, lds.ahead, lds.w[0], act && e < 0, o, tg, last, skip, hit, d, os, len);
+            trace_towards<TD, OTD>(a, lds.ahead, lds.w[0], act && e < 0, o, tg, last, skip, hit, d, os, len);
             if (act && e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
                 const float t = S.tgt[s0 + k].w;
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                     if (a.smooth_h2 > 0.f) {
                         float acc[3] = {0.f, 0.f, 0.f};
                         gather_normals<TD>(a.t.v, lds.w[0], S, a.group, o, a.smooth_h2, nr, acc);
-                        if (OV) gather_normals<TD>(a.t.ov, lds.w[0], S, a.group, o, a.smooth_h2, nr, acc);
+                        if constexpr (OTD != NO_OV) gather_normals<OTD>(a.t.ov, lds.w[0], S, a.group, o, a.smooth_h2, nr, acc);
                         const float l = sqrtf(dot3f(acc[0], acc[1], acc[2], acc[0], acc[1], acc[2]));
                         if (l > 0.f) {
                             nr[0] = acc[0] / l;
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
             }
             float d[3], os[3], len;
             Hit hit;
-            trace_towards<TD, OV>(a, lds.ahead, lds.w[0], act, o, tg, last, skip, hit, d, os, len);
+            trace_towards<TD, OTD>(a, lds.ahead, lds.w[0], act, o, tg, last, skip, hit, d, os, len);
             if (act) {
                 if (!(len > 0.f)) status = PCRL_REFINE_DEGENERATE;
                 else if (hit.id != NO_HIT && skip + hit.t < len - a.clear) status = PCRL_REFINE_OCCLUDED;
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         }
         float d[3], os[3], len;
         Hit hit;
-        trace_towards<TD, OV>(a, lds.ahead, lds.w[0], act, o, R, last, skip, hit, d, os, len);
+        trace_towards<TD, OTD>(a, lds.ahead, lds.w[0], act, o, R, last, skip, hit, d, os, len);
         if (act) {
             if (!(len > 0.f)) status = PCRL_REFINE_DEGENERATE;
             else if (hit.id != NO_HIT && skip + hit.t < len) status = PCRL_REFINE_OCCLUDED;
@@ -677,14 +677,6 @@ __global__ __launch_bounds__(64) void k_refine_sweep(const uint64_t* skey, const
     }
 }
 
-template <int TD>
-static void launch_refine_td(const RefineArgs& a, hipStream_t s) {
-    const uint32_t ppw = 64u >> a.group;
-    const unsigned grid = (a.n + ppw - 1) / ppw;
-    if (a.t.has_ov) hipLaunchKernelGGL((k_refine<TD, true>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
-    else hipLaunchKernelGGL((k_refine<TD, false>), dim3(grid), dim3(REFINE_BLOCK), 0, s, a);
-}
-
 }  // namespace pcrl
 
 using namespace pcrl;
@@ -838,12 +830,11 @@ extern "C" int refine_paths(const PcrlScene* scene, const float* tx, int32_t n_t
         T.release();
         return rc;
     }
-    switch (scene->view.depth) {
-    case -1: launch_refine_td<-1>(a, s); break;
-    case 0: launch_refine_td<0>(a, s); break;
-    case 1: launch_refine_td<1>(a, s); break;
-    default: launch_refine_td<2>(a, s); break;
-    }
+    const uint32_t ppw = 64u >> a.group;
+    with_depths(a.t.v.depth, overlay_depth(a.t), [&](auto td, auto otd) {
+        hipLaunchKernelGGL((k_refine<decltype(td)::value, decltype(otd)::value>), dim3((a.n + ppw - 1) / ppw),
+                           dim3(REFINE_BLOCK), 0, s, a);
+    });
     const unsigned g = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_refine_keys, dim3(g), dim3(256), 0, s, paths->tx, paths->rx, paths->n_refl, out->status,
                        out->length, (uint32_t)n, keys, idx);

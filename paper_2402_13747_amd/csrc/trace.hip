@@ -21,16 +21,15 @@
 
 namespace pcrl {
 
-// Specialised on the depth TD of the traversal's top grid and on the presence
-// of an overlay OV, so every level index in the traversal is a compile-time
-// constant.  Each wave traces `rpw` consecutive slots in lockstep
+// Specialised on the depths of the base's and the overlay's top grid, so every
+// level index in the traversal is a compile-time constant.  Each wave traces `rpw` consecutive slots in lockstep
 // (neighbouring slots hold coherent rays: their lookups share cache lines),
 // grid-stride over the active slots; with an overlay, the base hierarchy and
 // then the overlay.  The grid is a multiple of 8: the blocks that the active
 // slots need are spread over all 8 XCDs (workgroups are dispatched to them
 // round-robin), each XCD working on one contiguous range of slots so that
 // neighbouring, coherent rays share its L2; the other blocks end at once.
-template <bool FIRST, bool STATS, int TD, bool OV>
+template <bool FIRST, bool STATS, int TD, int OTD>
 __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(TraceArgs a, int b, uint32_t cap) {
     constexpr uint32_t WAVES = TRACE_BLOCK / 64;
     __shared__ TraceLds<WAVES> lds;
@@ -44,7 +43,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(TraceArgs a, int b, uint3
     const uint32_t wave = block * WAVES + (threadIdx.x >> 6);
     stat_t cnt[ST_COUNT] = {};
     for (uint32_t base = wave * rpw; base < n_act; base += blocks * WAVES * rpw)
-        trace_chunk<FIRST, STATS, TD, OV>(kernel_args(), lds.ahead, lds.w[threadIdx.x >> 6], b, base, rpw, n_act, false,
+        trace_chunk<FIRST, STATS, TD, OTD>(kernel_args(), lds.ahead, lds.w[threadIdx.x >> 6], b, base, rpw, n_act, false,
                                           cnt);
     flush_stats<STATS>(cnt, a.stats ? a.stats + (size_t)b * PCRL_NSTATS : nullptr);
 }
@@ -120,24 +119,12 @@ __global__ void k_unpack_records(const uint4* rec, const uint32_t* count, uint32
 // host side
 // ---------------------------------------------------------------------------
 
-template <bool FIRST, bool STATS, int TD>
-static void launch_trace_td(const TraceArgs& a, int b, unsigned grid, hipStream_t s) {
-    const unsigned full = xcd_groups(grid);
-    if (a.has_ov)
-        hipLaunchKernelGGL((k_trace<FIRST, STATS, TD, true>), dim3(full), dim3(TRACE_BLOCK), 0, s, a, b, grid);
-    else
-        hipLaunchKernelGGL((k_trace<FIRST, STATS, TD, false>), dim3(full), dim3(TRACE_BLOCK), 0, s, a, b, grid);
-}
-
 template <bool FIRST, bool STATS>
 static void launch_trace(const TraceArgs& a, int b, unsigned grid, hipStream_t s) {
-    static_assert(PCRL_MAX_LEVELS == 4, "one kernel specialisation per top-grid depth");
-    switch (a.v.depth) {
-    case -1: launch_trace_td<FIRST, STATS, -1>(a, b, grid, s); break;
-    case 0: launch_trace_td<FIRST, STATS, 0>(a, b, grid, s); break;
-    case 1: launch_trace_td<FIRST, STATS, 1>(a, b, grid, s); break;
-    default: launch_trace_td<FIRST, STATS, 2>(a, b, grid, s); break;
-    }
+    with_depths(a.v.depth, overlay_depth(a), [&](auto td, auto otd) {
+        hipLaunchKernelGGL((k_trace<FIRST, STATS, decltype(td)::value, decltype(otd)::value>), dim3(xcd_groups(grid)),
+                           dim3(TRACE_BLOCK), 0, s, a, b, grid);
+    });
 }
 
 void destroy_launch(PcrlLaunch* L) {

@@ -7,6 +7,8 @@
 
 #include "internal.h"
 
+#include <type_traits>
+
 namespace pcrl {
 
 constexpr int TRACE_BLOCK = 256;
@@ -26,7 +28,7 @@ static_assert(ST_COUNT <= PCRL_NSTATS, "device statistics buffer too small");
 
 struct TraceArgs {
     SceneView v;
-    SceneView ov;           // overlay of dynamic points (valid when has_ov)
+    SceneView ov;           // overlay of dynamic points (valid when has_ov; its top grid may lie deeper than v's)
     int32_t has_ov;
     const float* tx;
     const float* rx;
@@ -98,6 +100,37 @@ __host__ __device__ __forceinline__ uint32_t xcd_turn(uint32_t blocks, uint32_t 
 // blocks up to `most`.
 __host__ __device__ __forceinline__ uint32_t xcd_groups(uint32_t most) {
     return (most + 7) / 8 * 8 + 8 * xcd_piece(most);
+}
+
+// Kernels that trace are specialised on the depths TD and OTD of the top grids
+// of the base and of the overlay (NO_OV: none).  An overlay shares the base's
+// levels and its top grid is as fine or coarser (build.hip).
+constexpr int NO_OV = -2;
+template <int N>
+using Depth = std::integral_constant<int, N>;
+
+static inline int overlay_depth(const TraceArgs& a) { return a.has_ov ? a.ov.depth : NO_OV; }
+
+template <int TD, typename F>
+static void with_overlay_depth(int otd, F&& f) {
+    static_assert(PCRL_MAX_LEVELS == 4, "depths reach from -1 to 2");
+    if (otd == NO_OV) return f(Depth<TD>{}, Depth<NO_OV>{});
+    if constexpr (TD == 0)
+        if (otd == 1) return f(Depth<0>{}, Depth<1>{});
+    if constexpr (TD == 0 || TD == 1)
+        if (otd == 2) return f(Depth<TD>{}, Depth<2>{});
+    f(Depth<TD>{}, Depth<TD>{});
+}
+
+// f(Depth<TD>, Depth<OTD>) for a base and an overlay of these depths.
+template <typename F>
+static void with_depths(int td, int otd, F&& f) {
+    switch (td) {
+    case -1: return with_overlay_depth<-1>(otd, f);
+    case 0: return with_overlay_depth<0>(otd, f);
+    case 1: return with_overlay_depth<1>(otd, f);
+    default: return with_overlay_depth<2>(otd, f);
+    }
 }
 
 // Ping-pong ray buffers of bounce b, chosen by selects: a runtime index into
@@ -837,7 +870,7 @@ __device__ __forceinline__ void finish_segment(const TraceArgs& a, int b, bool d
 // or past `range` are idle; a slot whose ray id is NO_HIT (left by an
 // in-place bounce) is idle too.  Every lane of the wave must call this
 // (ballots).
-template <bool FIRST, bool STATS, int TD, bool OV>
+template <bool FIRST, bool STATS, int TD, int OTD>
 __device__ __forceinline__ void trace_chunk(ArgsPtr args, const uint64_t* ahead, WaveLds& W, int b, uint32_t base,
                                             uint32_t rpw, uint32_t range, bool in_place, stat_t* cnt) {
     const uint32_t i = base + lane_id();
@@ -855,7 +888,7 @@ __device__ __forceinline__ void trace_chunk(ArgsPtr args, const uint64_t* ahead,
     // dynamic points: the nearest hit over base and overlay is the nearest
     // hit of the union (ties again by point id); the overlay shares the
     // base's frame and levels
-    if (OV) trace_segment<STATS, TD, true>(args, ahead, W, act, hit, cnt);
+    if constexpr (OTD != NO_OV) trace_segment<STATS, OTD, true>(args, ahead, W, act, hit, cnt);
     const float4 O = W.o[lane_id()], Dd = W.d[lane_id()];
     float o[3] = {O.x, O.y, O.z}, d[3] = {Dd.x, Dd.y, Dd.z};
     finish_segment<FIRST, STATS>(reread(args), b, act, in_place, i, W.g[lane_id()], o, d, Dd.w, __float_as_uint(O.w), hit,
