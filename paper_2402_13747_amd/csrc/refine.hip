@@ -98,17 +98,25 @@ __device__ __forceinline__ int wave_max(int x) {
     return __builtin_amdgcn_readlane(wave_scan_max_dpp(x), 63);
 }
 
-// State of the wave's paths: interaction k of the path of lanes
-// [g << group, (g + 1) << group) at 8 g + k.
-struct PathLds {
-    float4 pos[64];   // current point, surfel id (bits)
-    float4 nrm[64];   // its surfel's normal, label (bits)
-    float4 tgt[64];   // point the next trace aims at (diffractions: t along the edge in w)
-    int32_t edge[64]; // its edge, -1 a reflection
-    float gg[64];     // its part of the squared gradient
-    uint32_t first[8][28];  // smooth normals: entries before each of the 27 leaves, and of all
-    uint32_t begin[8][27];  // their first entries
+// State of an interaction of one of the wave's paths (dynamic LDS): that of
+// interaction k of the path of lanes [g << group, (g + 1) << group) at K g + k.
+struct alignas(16) PathPoint {
+    float4 pos;     // current point, surfel id (bits)
+    float4 nrm;     // its surfel's normal, label (bits)
+    float4 tgt;     // point the next trace aims at (diffractions: t along the edge in w)
+    int32_t edge;   // its edge, -1 a reflection
+    float gg;       // its part of the squared gradient
 };
+// Smooth normals, per path behind them: entries before each of the 27 leaves,
+// and of all; their first entries.
+struct PathLeaves {
+    uint32_t first[28], begin[27];
+};
+
+// Bytes of it for `paths` paths of K interactions.
+static size_t path_lds_bytes(uint32_t paths, int32_t K, bool smooth) {
+    return paths * ((size_t)K * sizeof(PathPoint) + (smooth ? sizeof(PathLeaves) : 0));
+}
 
 // The nearest hit of each group's ray (staged in every lane of the group)
 // between t0 and t1 of each of its walking lanes, nearer than `hit` so far.
@@ -211,11 +219,11 @@ __device__ __forceinline__ void trace_towards(const RefineArgs& a, const uint64_
 // and test the points between them; the accepted ones are added in the order
 // of the leaves and of their entries.
 template <int TD>
-__device__ __forceinline__ void gather_normals(const SceneView& v, WaveLds& W, PathLds& S, uint32_t group, const float c[3],
+__device__ __forceinline__ void gather_normals(const SceneView& v, WaveLds& W, PathLeaves* leaves, uint32_t group, const float c[3],
                                                float h2, const float nh[3], float acc[3]) {
     const uint32_t G = 1u << group, lane = lane_id(), j = lane & (G - 1u), lead = lane - j, g = lane >> group;
-    uint32_t* const first = S.first[g];
-    uint32_t* const begin = S.begin[g];
+    uint32_t* const first = leaves[g].first;
+    uint32_t* const begin = leaves[g].begin;
     int lc[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) lc[a] = (int)floorf((c[a] - v.org[a]) * v.inv_h);
@@ -284,10 +292,11 @@ __device__ __forceinline__ void load3(const float4* p, float x[3]) {
 template <int TD, int OTD>
 __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     __shared__ TraceLds<1> lds;
-    __shared__ PathLds S;
+    extern __shared__ PathPoint S[];
     ahead_init(lds.ahead, threadIdx.x, REFINE_BLOCK);
     __syncthreads();
-    const uint32_t G = 1u << a.group, j = lane_id() & (G - 1u), s0 = 8u * (lane_id() >> a.group);
+    const uint32_t G = 1u << a.group, j = lane_id() & (G - 1u), s0 = (uint32_t)a.K * (lane_id() >> a.group);
+    PathLeaves* const leaves = reinterpret_cast<PathLeaves*>(S + (uint32_t)a.K * (64u >> a.group));
     const uint32_t p = (blockIdx.x << (6u - a.group)) + (lane_id() >> a.group);
     const bool in = p < a.n;
     int N = 0;
@@ -310,8 +319,8 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
                 t = dot3f(q[0] - A.x, q[1] - A.y, q[2] - A.z, Wd.x, Wd.y, Wd.z);
             }
-            S.tgt[s0 + j] = make_float4(q[0], q[1], q[2], t);
-            S.edge[s0 + j] = e;
+            S[s0 + j].tgt = make_float4(q[0], q[1], q[2], t);
+            S[s0 + j].edge = e;
         }
     }
     const int nmax = wave_max(N);
@@ -328,21 +337,21 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         float skip = 0.f;
         for (int k = 0; k < nmax; ++k) {
             const bool act = run && k < N;
-            const int e = act ? S.edge[s0 + k] : -1;
+            const int e = act ? S[s0 + k].edge : -1;
             float tg[3] = {0.f, 0.f, 0.f}, d[3], os[3], len;
-            if (act) load3(&S.tgt[s0 + k], tg);
+            if (act) load3(&S[s0 + k].tgt, tg);
             Hit hit;
             trace_towards<TD, OTD>(a, lds.ahead, lds.w[0], act && e < 0, o, tg, last, skip, hit, d, os, len);
             if (act && e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
-                const float t = S.tgt[s0 + k].w;
+                const float t = S[s0 + k].tgt.w;
                 o[0] = fmaf(t, Wd.x, A.x);
                 o[1] = fmaf(t, Wd.y, A.y);
                 o[2] = fmaf(t, Wd.z, A.z);
                 last = NO_HIT;
                 skip = a.clear;
-                S.pos[s0 + k] = make_float4(o[0], o[1], o[2], __uint_as_float(NO_HIT));
-                S.nrm[s0 + k] = make_float4(0.f, 0.f, 0.f, Wd.w);
+                S[s0 + k].pos = make_float4(o[0], o[1], o[2], __uint_as_float(NO_HIT));
+                S[s0 + k].nrm = make_float4(0.f, 0.f, 0.f, Wd.w);
             } else if (act) {
                 if (!(len > 0.f)) {
                     status = PCRL_REFINE_DEGENERATE;
@@ -359,8 +368,8 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                     float nr[3] = {hit.nx, hit.ny, hit.nz};
                     if (a.smooth_h2 > 0.f) {
                         float acc[3] = {0.f, 0.f, 0.f};
-                        gather_normals<TD>(a.t.v, lds.w[0], S, a.group, o, a.smooth_h2, nr, acc);
-                        if constexpr (OTD != NO_OV) gather_normals<OTD>(a.t.ov, lds.w[0], S, a.group, o, a.smooth_h2, nr, acc);
+                        gather_normals<TD>(a.t.v, lds.w[0], leaves, a.group, o, a.smooth_h2, nr, acc);
+                        if constexpr (OTD != NO_OV) gather_normals<OTD>(a.t.ov, lds.w[0], leaves, a.group, o, a.smooth_h2, nr, acc);
                         const float l = sqrtf(dot3f(acc[0], acc[1], acc[2], acc[0], acc[1], acc[2]));
                         if (l > 0.f) {
                             nr[0] = acc[0] / l;
@@ -368,8 +377,8 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                             nr[2] = acc[2] / l;
                         }
                     }
-                    S.pos[s0 + k] = make_float4(o[0], o[1], o[2], __uint_as_float(hit.id));
-                    S.nrm[s0 + k] = make_float4(nr[0], nr[1], nr[2], __uint_as_float(hit.lab));
+                    S[s0 + k].pos = make_float4(o[0], o[1], o[2], __uint_as_float(hit.id));
+                    S[s0 + k].nrm = make_float4(nr[0], nr[1], nr[2], __uint_as_float(hit.lab));
                 }
             }
         }
@@ -380,33 +389,33 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         if (run && (int)j < N) {
             const int k = (int)j;
             float prev[3] = {T[0], T[1], T[2]}, cur[3], next[3] = {R[0], R[1], R[2]};
-            load3(&S.pos[s0 + k], cur);
-            if (k > 0) load3(&S.pos[s0 + k - 1], prev);
-            if (k + 1 < N) load3(&S.pos[s0 + k + 1], next);
+            load3(&S[s0 + k].pos, cur);
+            if (k > 0) load3(&S[s0 + k - 1].pos, prev);
+            if (k + 1 < N) load3(&S[s0 + k + 1].pos, next);
             const float lp = dist3(cur, prev), ln = dist3(cur, next);
             degenerate = !(lp > 0.f) || !(ln > 0.f);
             float G3[3];
 #pragma unroll
             for (int x = 0; x < 3; ++x) G3[x] = (cur[x] - prev[x]) / lp + (cur[x] - next[x]) / ln;
             const float ak = a.step / (1.0f / lp + 1.0f / ln);
-            const int e = S.edge[s0 + k];
+            const int e = S[s0 + k].edge;
             if (e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
                 const float gw = dot3f(G3[0], G3[1], G3[2], Wd.x, Wd.y, Wd.z);
-                S.gg[s0 + k] = gw * gw;
-                const float4 tq = S.tgt[s0 + k];
+                S[s0 + k].gg = gw * gw;
+                const float4 tq = S[s0 + k].tgt;
                 const float t = fmaf(-ak, gw, tq.w);
                 off = !(t >= 0.f && t <= A.w);
-                S.tgt[s0 + k] = make_float4(tq.x, tq.y, tq.z, t);
+                S[s0 + k].tgt = make_float4(tq.x, tq.y, tq.z, t);
             } else {
                 float nrm[3];
-                load3(&S.nrm[s0 + k], nrm);
+                load3(&S[s0 + k].nrm, nrm);
                 const float gn = dot3f(G3[0], G3[1], G3[2], nrm[0], nrm[1], nrm[2]);
                 float g[3];
 #pragma unroll
                 for (int x = 0; x < 3; ++x) g[x] = fmaf(-gn, nrm[x], G3[x]);
-                S.gg[s0 + k] = dot3f(g[0], g[1], g[2], g[0], g[1], g[2]);
-                S.tgt[s0 + k] = make_float4(fmaf(-ak, g[0], cur[0]), fmaf(-ak, g[1], cur[1]), fmaf(-ak, g[2], cur[2]), 0.f);
+                S[s0 + k].gg = dot3f(g[0], g[1], g[2], g[0], g[1], g[2]);
+                S[s0 + k].tgt = make_float4(fmaf(-ak, g[0], cur[0]), fmaf(-ak, g[1], cur[1]), fmaf(-ak, g[2], cur[2]), 0.f);
             }
         }
         const uint64_t mine = ~0ull >> (64u - G);
@@ -421,7 +430,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
             continue;
         }
         float gg = 0.f;
-        for (int k = 0; k < N; ++k) gg += S.gg[s0 + k];
+        for (int k = 0; k < N; ++k) gg += S[s0 + k].gg;
         gnorm = sqrtf(gg);
         if (gnorm < a.grad_tol) {
             run = false;  // converged
@@ -439,15 +448,15 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     // outside its edge's wedge
     if (in && status == PCRL_REFINE_VALID && N > 0) {
         float prev[3] = {T[0], T[1], T[2]}, cur[3], next[3], nrm[3];
-        load3(&S.pos[s0], cur);
+        load3(&S[s0].pos, cur);
         for (int k = 0; k < N; ++k) {
-            if (k + 1 < N) load3(&S.pos[s0 + k + 1], next);
+            if (k + 1 < N) load3(&S[s0 + k + 1].pos, next);
             else {
                 next[0] = R[0];
                 next[1] = R[1];
                 next[2] = R[2];
             }
-            const int e = S.edge[s0 + k];
+            const int e = S[s0 + k].edge;
             bool ok;
             if (e >= 0) {
                 const float4 N1 = a.e_n1[e], N2 = a.e_n2[e];
@@ -457,7 +466,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                 const float q2 = (next[0] - cur[0]) * N2.x + (next[1] - cur[1]) * N2.y + (next[2] - cur[2]) * N2.z;
                 ok = (p1 > 0.f || p2 > 0.f) && (q1 > 0.f || q2 > 0.f);
             } else {
-                load3(&S.nrm[s0 + k], nrm);
+                load3(&S[s0 + k].nrm, nrm);
                 float sp = 0.f, sn = 0.f;
 #pragma unroll
                 for (int x = 0; x < 3; ++x) {
@@ -480,18 +489,18 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     // segments arriving at a diffraction point: blocked by a hit more than r_s before it
     if (a.p_edge) {
         for (int k = 0; k < nmax; ++k) {
-            const bool act = in && status == PCRL_REFINE_VALID && k < N && S.edge[s0 + k] >= 0;
+            const bool act = in && status == PCRL_REFINE_VALID && k < N && S[s0 + k].edge >= 0;
             float o[3] = {T[0], T[1], T[2]}, tg[3] = {0.f, 0.f, 0.f};
             uint32_t last = NO_HIT;
             float skip = 0.f;
             if (act) {
-                load3(&S.pos[s0 + k], tg);
+                load3(&S[s0 + k].pos, tg);
                 if (k > 0) {
-                    const float4 c = S.pos[s0 + k - 1];
+                    const float4 c = S[s0 + k - 1].pos;
                     o[0] = c.x;
                     o[1] = c.y;
                     o[2] = c.z;
-                    if (S.edge[s0 + k - 1] >= 0) skip = a.clear;
+                    if (S[s0 + k - 1].edge >= 0) skip = a.clear;
                     else last = __float_as_uint(c.w);
                 }
             }
@@ -511,11 +520,11 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         uint32_t last = NO_HIT;
         float skip = 0.f;
         if (act && N > 0) {
-            const float4 c = S.pos[s0 + N - 1];
+            const float4 c = S[s0 + N - 1].pos;
             o[0] = c.x;
             o[1] = c.y;
             o[2] = c.z;
-            if (S.edge[s0 + N - 1] >= 0) skip = a.clear;
+            if (S[s0 + N - 1].edge >= 0) skip = a.clear;
             else last = __float_as_uint(c.w);
         }
         float d[3], os[3], len;
@@ -531,21 +540,21 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     if ((int)j < a.K) {
         const size_t r = (size_t)p * a.K + j;
         const bool has = finite && (int)j < N;
-        const float4 c = has ? S.pos[s0 + j] : make_float4(NAN, NAN, NAN, __uint_as_float(0xFFFFFFFFu));
+        const float4 c = has ? S[s0 + j].pos : make_float4(NAN, NAN, NAN, __uint_as_float(0xFFFFFFFFu));
         float* q = a.out_pts + r * 3;
         q[0] = c.x;
         q[1] = c.y;
         q[2] = c.z;
-        const int e = has ? S.edge[s0 + j] : -1;
+        const int e = has ? S[s0 + j].edge : -1;
         a.out_id[r] = e >= 0 ? -2 - e : (int32_t)__float_as_uint(c.w);
-        a.out_key[r] = has ? (int64_t)__float_as_uint(S.nrm[s0 + j].w) : -1;
+        a.out_key[r] = has ? (int64_t)__float_as_uint(S[s0 + j].nrm.w) : -1;
     }
     if (j != 0) return;
     float f = 0.f;
     if (finite) {
         float prev[3] = {T[0], T[1], T[2]}, cur[3];
         for (int k = 0; k < N; ++k) {
-            load3(&S.pos[s0 + k], cur);
+            load3(&S[s0 + k].pos, cur);
             f += dist3(cur, prev);
             prev[0] = cur[0];
             prev[1] = cur[1];
@@ -778,8 +787,11 @@ extern "C" int refine_paths(const PcrlScene* scene, const float* tx, int32_t n_t
     a.p_n = paths->n_refl;
     a.p_pts = paths->points;
     a.n = (uint32_t)n;
-    // lanes per path: a wave each as long as the waves find room at once (three per SIMD: 13 KB of
-    // LDS each), since a wave's paths wait for its slowest; eight lanes at least (one per interaction)
+    // lanes per path: a wave each as long as the waves find room at once (three per SIMD), since a
+    // wave's paths wait for its slowest; eight lanes at least (one per interaction).  Very many paths
+    // are bound by the instructions of all their rays, so by how many waves hide each other's latency:
+    // 764 k paths of an empty room, 100 iterations, 57.3 ms with a lane per path, 67.0 with eight and
+    // 13 KB of LDS a wave (three per SIMD), 51.7 with the 9 KB that three interactions take (four)
     a.group = 6;
     while (a.group > 3 && n > ((int64_t)device_cus() * 12 << (6 - a.group))) --a.group;
     a.K = k_stride;
@@ -833,7 +845,7 @@ extern "C" int refine_paths(const PcrlScene* scene, const float* tx, int32_t n_t
     const uint32_t ppw = 64u >> a.group;
     with_depths(a.t.v.depth, overlay_depth(a.t), [&](auto td, auto otd) {
         hipLaunchKernelGGL((k_refine<decltype(td)::value, decltype(otd)::value>), dim3((a.n + ppw - 1) / ppw),
-                           dim3(REFINE_BLOCK), 0, s, a);
+                           dim3(REFINE_BLOCK), path_lds_bytes(ppw, a.K, a.smooth_h2 > 0.f), s, a);
     });
     const unsigned g = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_refine_keys, dim3(g), dim3(256), 0, s, paths->tx, paths->rx, paths->n_refl, out->status,
