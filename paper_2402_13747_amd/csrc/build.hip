@@ -14,7 +14,7 @@
 //                    ratio^3 children (linear order)
 //   leaves           (first entry, count) ranges into leaf-ordered surfels, in
 //                    key order and once more block by block
-//   surfels          two 16-byte streams per entry, in leaf order:
+//   surfels          two 16-byte halves per entry, together, in leaf order:
 //                    (x, y, z, point id) and (unit normal, label rank)
 //
 // A point is listed in EVERY leaf that the axis-aligned box of its disk
@@ -163,8 +163,7 @@ struct KeyParams {
 
 // Hierarchical key of leaf (x, y, z) with level 0 numbered by `c0` (rank of
 // the level-0 cell among the occupied ones) or by its linear index (c0
-// null); the quotients use the traversal's magic divisions.  Equal to
-// leaf_key_of when c0 is null.
+// null); the quotients use magic divisions.
 __host__ __device__ __forceinline__ uint64_t leaf_key_fast(const SceneView& v, const uint32_t* c0, int x, int y, int z) {
     int p[3] = {span_div(x, v.mspan[0]), span_div(y, v.mspan[0]), span_div(z, v.mspan[0])};
     const uint32_t cell0 = (uint32_t)p[0] + (uint32_t)v.dim0[0] * ((uint32_t)p[1] + (uint32_t)v.dim0[1] * (uint32_t)p[2]);
@@ -753,7 +752,7 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_gather_surfels(uint32_t* ids, c
     for (uint32_t h = threadIdx.x; h < n; h += BUILD_BLOCK) surf[2 * first + h] = out[h];
 }
 
-// Entry -> point table of a scene from its surfel stream.
+// Entry -> point table of a scene from its surfels.
 __global__ void k_entry_points(const float4* surf, int64_t m, uint32_t* out) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < m) out[e] = __float_as_uint(surf[2 * e].w);
@@ -926,7 +925,7 @@ struct HierBuild {
 };
 
 // Voxelise n ingested points into the frame already set in v (level-0 map,
-// bricks, leaves, surfel streams).  gid: global point ids (null: 0..n-1);
+// bricks, leaves, surfels).  gid: global point ids (null: 0..n-1);
 // base: with the level-0 map (the implicit surface's, which overlays have not).
 static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint32_t* label, const uint32_t* gid,
                            int64_t n, hipStream_t s, bool base, SceneView& v, DevBufs& B, DevBufs& T,
@@ -1173,7 +1172,7 @@ static int build_hierarchy(const float* xyz, const float4* unit_nrm, const uint3
         hb.bytes += (int64_t)nb * 16 + n_leaves * 8 + (pbox ? (int64_t)host_nodes[P] * 4 : 0);
     }
 
-    // surfel streams in leaf order
+    // surfels in leaf order
     float4* surf = nullptr;
     if ((rc = B.alloc(&surf, 2 * (size_t)m))) return rc;
     hipLaunchKernelGGL(k_gather_surfels, dim3(blocks_for(m)), dim3(BUILD_BLOCK), 0, s, ids,
@@ -1390,7 +1389,7 @@ extern "C" int scene_leaf_table(const PcrlScene* scene, uint64_t* leaf_key, uint
         if (scene->entry_point) {
             PCRL_TRY_HIP(hipMemcpyAsync(entry_point, scene->entry_point, (size_t)m * 4, hipMemcpyDeviceToDevice, s));
         } else {
-            // the point id rides in the surfel stream (x, y, z, id)
+            // the point id rides in the surfel (x, y, z, id)
             hipLaunchKernelGGL(k_entry_points, dim3(blocks_for(m)), dim3(BUILD_BLOCK), 0, s, scene->view.surf, m,
                                entry_point);
             PCRL_TRY_HIP(hipGetLastError());

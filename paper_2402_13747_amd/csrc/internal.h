@@ -281,18 +281,6 @@ __host__ __device__ __forceinline__ int span_div(int x, uint64_t m) {
     return (int)(((uint64_t)(uint32_t)x * m) >> 40);
 }
 
-__host__ __device__ inline uint64_t leaf_key_of(const SceneView& v, int ix, int iy, int iz) {
-    const int s0 = v.span[0];
-    uint64_t k = (uint64_t)((ix / s0) + v.dim0[0] * ((iy / s0) + v.dim0[1] * (iz / s0)));
-    for (int i = 1; i < v.nlev; ++i) {
-        const int s = v.span[i];
-        const int r = v.ratio[i - 1];
-        const int lx = (ix / s) % r, ly = (iy / s) % r, lz = (iz / s) % r;
-        k = (k << v.lbits[i]) | (uint64_t)(lx + r * (ly + r * lz));
-    }
-    return k;
-}
-
 }  // namespace pcrl
 
 // ---------------------------------------------------------------------------

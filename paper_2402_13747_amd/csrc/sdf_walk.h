@@ -486,8 +486,8 @@ constexpr int DIST0_CAP = 15;
 
 // Largest dense cell table built: the table pays off while it stays resident
 // in the 256 MB last-level (MALL) cache; a larger one (3.3 GB for a 20M-point
-// street canyon) turns every DDA step into an HBM round trip and doubled that
-// scene's trace time.  Beyond it the traversal reads the bricks' masks.
+// street canyon) turns every step into an HBM round trip.  Beyond it the walk
+// reads the bricks' masks.
 constexpr int64_t CELL_TABLE_MAX_BYTES = (int64_t)256 << 20;
 
 __global__ void k_dist0_pass(const int32_t* map0, const uint8_t* in, uint8_t* out, int dx, int dy, int dz, int axis) {

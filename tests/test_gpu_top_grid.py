@@ -1,6 +1,8 @@
 """Top grids whose skip codes are made in several turns (more than 4 M words of occupancy: thin grids and those of more
 than 512 M cells): rays cross their empty cells and hit what they hit in a scene with a small top grid, and the codes
 take no memory by the cell of a thin grid."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -48,19 +50,11 @@ def test_a_thin_grid_takes_no_memory_by_the_word():
     import torch
     import paper_2402_13747_amd as pcrl
     xyz, nrm, lab = _disks(np.float32([0.0, 900.0, 900.0]), 64, 3)
+    most = []
     with Limited(torch, pcrl._lib) as A:
-        most = []
-        plain = A.alloc
-        scene = None
-
-        def alloc(size, stream, ctx):
-            most.append(size)
-            return plain(size, stream, ctx)
-
-        fns = (pcrl._lib.ALLOC_FN(alloc), A.fns[1])
-        a = pcrl._lib.PcrlAllocator(fns[0], fns[1], None)
-        import ctypes as C
-        assert pcrl._lib.lib.set_allocator(C.byref(a)) == 0
+        fns = (pcrl._lib.ALLOC_FN(lambda size, stream, ctx: most.append(size) or A.alloc(size, stream, ctx)), A.fns[1])
+        counted = pcrl._lib.PcrlAllocator(fns[0], fns[1], None)
+        assert pcrl._lib.lib.set_allocator(C.byref(counted)) == 0
         scene = pcrl.build_voxels(xyz, nrm, lab, (0.2,), 0.05)
         cells = int(np.prod([int(x) for x in scene.info()["dims"]]))
         scene.release()
