@@ -292,11 +292,12 @@ __device__ __forceinline__ void load3(const float4* p, float x[3]) {
 template <int TD, int OTD>
 __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     __shared__ TraceLds<1> lds;
-    extern __shared__ PathPoint S[];
+    extern __shared__ PathPoint points[];
     ahead_init(lds.ahead, threadIdx.x, REFINE_BLOCK);
     __syncthreads();
-    const uint32_t G = 1u << a.group, j = lane_id() & (G - 1u), s0 = (uint32_t)a.K * (lane_id() >> a.group);
-    PathLeaves* const leaves = reinterpret_cast<PathLeaves*>(S + (uint32_t)a.K * (64u >> a.group));
+    const uint32_t G = 1u << a.group, j = lane_id() & (G - 1u);
+    PathPoint* const S = points + (uint32_t)a.K * (lane_id() >> a.group);  // the path's
+    PathLeaves* const leaves = reinterpret_cast<PathLeaves*>(points + (uint32_t)a.K * (64u >> a.group));
     const uint32_t p = (blockIdx.x << (6u - a.group)) + (lane_id() >> a.group);
     const bool in = p < a.n;
     int N = 0;
@@ -319,8 +320,8 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
                 t = dot3f(q[0] - A.x, q[1] - A.y, q[2] - A.z, Wd.x, Wd.y, Wd.z);
             }
-            S[s0 + j].tgt = make_float4(q[0], q[1], q[2], t);
-            S[s0 + j].edge = e;
+            S[j].tgt = make_float4(q[0], q[1], q[2], t);
+            S[j].edge = e;
         }
     }
     const int nmax = wave_max(N);
@@ -337,21 +338,21 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         float skip = 0.f;
         for (int k = 0; k < nmax; ++k) {
             const bool act = run && k < N;
-            const int e = act ? S[s0 + k].edge : -1;
+            const int e = act ? S[k].edge : -1;
             float tg[3] = {0.f, 0.f, 0.f}, d[3], os[3], len;
-            if (act) load3(&S[s0 + k].tgt, tg);
+            if (act) load3(&S[k].tgt, tg);
             Hit hit;
             trace_towards<TD, OTD>(a, lds.ahead, lds.w[0], act && e < 0, o, tg, last, skip, hit, d, os, len);
             if (act && e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
-                const float t = S[s0 + k].tgt.w;
+                const float t = S[k].tgt.w;
                 o[0] = fmaf(t, Wd.x, A.x);
                 o[1] = fmaf(t, Wd.y, A.y);
                 o[2] = fmaf(t, Wd.z, A.z);
                 last = NO_HIT;
                 skip = a.clear;
-                S[s0 + k].pos = make_float4(o[0], o[1], o[2], __uint_as_float(NO_HIT));
-                S[s0 + k].nrm = make_float4(0.f, 0.f, 0.f, Wd.w);
+                S[k].pos = make_float4(o[0], o[1], o[2], __uint_as_float(NO_HIT));
+                S[k].nrm = make_float4(0.f, 0.f, 0.f, Wd.w);
             } else if (act) {
                 if (!(len > 0.f)) {
                     status = PCRL_REFINE_DEGENERATE;
@@ -377,8 +378,8 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                             nr[2] = acc[2] / l;
                         }
                     }
-                    S[s0 + k].pos = make_float4(o[0], o[1], o[2], __uint_as_float(hit.id));
-                    S[s0 + k].nrm = make_float4(nr[0], nr[1], nr[2], __uint_as_float(hit.lab));
+                    S[k].pos = make_float4(o[0], o[1], o[2], __uint_as_float(hit.id));
+                    S[k].nrm = make_float4(nr[0], nr[1], nr[2], __uint_as_float(hit.lab));
                 }
             }
         }
@@ -389,33 +390,33 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         if (run && (int)j < N) {
             const int k = (int)j;
             float prev[3] = {T[0], T[1], T[2]}, cur[3], next[3] = {R[0], R[1], R[2]};
-            load3(&S[s0 + k].pos, cur);
-            if (k > 0) load3(&S[s0 + k - 1].pos, prev);
-            if (k + 1 < N) load3(&S[s0 + k + 1].pos, next);
+            load3(&S[k].pos, cur);
+            if (k > 0) load3(&S[k - 1].pos, prev);
+            if (k + 1 < N) load3(&S[k + 1].pos, next);
             const float lp = dist3(cur, prev), ln = dist3(cur, next);
             degenerate = !(lp > 0.f) || !(ln > 0.f);
             float G3[3];
 #pragma unroll
             for (int x = 0; x < 3; ++x) G3[x] = (cur[x] - prev[x]) / lp + (cur[x] - next[x]) / ln;
             const float ak = a.step / (1.0f / lp + 1.0f / ln);
-            const int e = S[s0 + k].edge;
+            const int e = S[k].edge;
             if (e >= 0) {
                 const float4 A = a.e_a[e], Wd = a.e_w[e];
                 const float gw = dot3f(G3[0], G3[1], G3[2], Wd.x, Wd.y, Wd.z);
-                S[s0 + k].gg = gw * gw;
-                const float4 tq = S[s0 + k].tgt;
+                S[k].gg = gw * gw;
+                const float4 tq = S[k].tgt;
                 const float t = fmaf(-ak, gw, tq.w);
                 off = !(t >= 0.f && t <= A.w);
-                S[s0 + k].tgt = make_float4(tq.x, tq.y, tq.z, t);
+                S[k].tgt = make_float4(tq.x, tq.y, tq.z, t);
             } else {
                 float nrm[3];
-                load3(&S[s0 + k].nrm, nrm);
+                load3(&S[k].nrm, nrm);
                 const float gn = dot3f(G3[0], G3[1], G3[2], nrm[0], nrm[1], nrm[2]);
                 float g[3];
 #pragma unroll
                 for (int x = 0; x < 3; ++x) g[x] = fmaf(-gn, nrm[x], G3[x]);
-                S[s0 + k].gg = dot3f(g[0], g[1], g[2], g[0], g[1], g[2]);
-                S[s0 + k].tgt = make_float4(fmaf(-ak, g[0], cur[0]), fmaf(-ak, g[1], cur[1]), fmaf(-ak, g[2], cur[2]), 0.f);
+                S[k].gg = dot3f(g[0], g[1], g[2], g[0], g[1], g[2]);
+                S[k].tgt = make_float4(fmaf(-ak, g[0], cur[0]), fmaf(-ak, g[1], cur[1]), fmaf(-ak, g[2], cur[2]), 0.f);
             }
         }
         const uint64_t mine = ~0ull >> (64u - G);
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
             continue;
         }
         float gg = 0.f;
-        for (int k = 0; k < N; ++k) gg += S[s0 + k].gg;
+        for (int k = 0; k < N; ++k) gg += S[k].gg;
         gnorm = sqrtf(gg);
         if (gnorm < a.grad_tol) {
             run = false;  // converged
@@ -448,15 +449,15 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     // outside its edge's wedge
     if (in && status == PCRL_REFINE_VALID && N > 0) {
         float prev[3] = {T[0], T[1], T[2]}, cur[3], next[3], nrm[3];
-        load3(&S[s0].pos, cur);
+        load3(&S[0].pos, cur);
         for (int k = 0; k < N; ++k) {
-            if (k + 1 < N) load3(&S[s0 + k + 1].pos, next);
+            if (k + 1 < N) load3(&S[k + 1].pos, next);
             else {
                 next[0] = R[0];
                 next[1] = R[1];
                 next[2] = R[2];
             }
-            const int e = S[s0 + k].edge;
+            const int e = S[k].edge;
             bool ok;
             if (e >= 0) {
                 const float4 N1 = a.e_n1[e], N2 = a.e_n2[e];
@@ -466,7 +467,7 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
                 const float q2 = (next[0] - cur[0]) * N2.x + (next[1] - cur[1]) * N2.y + (next[2] - cur[2]) * N2.z;
                 ok = (p1 > 0.f || p2 > 0.f) && (q1 > 0.f || q2 > 0.f);
             } else {
-                load3(&S[s0 + k].nrm, nrm);
+                load3(&S[k].nrm, nrm);
                 float sp = 0.f, sn = 0.f;
 #pragma unroll
                 for (int x = 0; x < 3; ++x) {
@@ -489,18 +490,18 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     // segments arriving at a diffraction point: blocked by a hit more than r_s before it
     if (a.p_edge) {
         for (int k = 0; k < nmax; ++k) {
-            const bool act = in && status == PCRL_REFINE_VALID && k < N && S[s0 + k].edge >= 0;
+            const bool act = in && status == PCRL_REFINE_VALID && k < N && S[k].edge >= 0;
             float o[3] = {T[0], T[1], T[2]}, tg[3] = {0.f, 0.f, 0.f};
             uint32_t last = NO_HIT;
             float skip = 0.f;
             if (act) {
-                load3(&S[s0 + k].pos, tg);
+                load3(&S[k].pos, tg);
                 if (k > 0) {
-                    const float4 c = S[s0 + k - 1].pos;
+                    const float4 c = S[k - 1].pos;
                     o[0] = c.x;
                     o[1] = c.y;
                     o[2] = c.z;
-                    if (S[s0 + k - 1].edge >= 0) skip = a.clear;
+                    if (S[k - 1].edge >= 0) skip = a.clear;
                     else last = __float_as_uint(c.w);
                 }
             }
@@ -520,11 +521,11 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
         uint32_t last = NO_HIT;
         float skip = 0.f;
         if (act && N > 0) {
-            const float4 c = S[s0 + N - 1].pos;
+            const float4 c = S[N - 1].pos;
             o[0] = c.x;
             o[1] = c.y;
             o[2] = c.z;
-            if (S[s0 + N - 1].edge >= 0) skip = a.clear;
+            if (S[N - 1].edge >= 0) skip = a.clear;
             else last = __float_as_uint(c.w);
         }
         float d[3], os[3], len;
@@ -540,21 +541,21 @@ __global__ __launch_bounds__(REFINE_BLOCK) void k_refine(RefineArgs a) {
     if ((int)j < a.K) {
         const size_t r = (size_t)p * a.K + j;
         const bool has = finite && (int)j < N;
-        const float4 c = has ? S[s0 + j].pos : make_float4(NAN, NAN, NAN, __uint_as_float(0xFFFFFFFFu));
+        const float4 c = has ? S[j].pos : make_float4(NAN, NAN, NAN, __uint_as_float(0xFFFFFFFFu));
         float* q = a.out_pts + r * 3;
         q[0] = c.x;
         q[1] = c.y;
         q[2] = c.z;
-        const int e = has ? S[s0 + j].edge : -1;
+        const int e = has ? S[j].edge : -1;
         a.out_id[r] = e >= 0 ? -2 - e : (int32_t)__float_as_uint(c.w);
-        a.out_key[r] = has ? (int64_t)__float_as_uint(S[s0 + j].nrm.w) : -1;
+        a.out_key[r] = has ? (int64_t)__float_as_uint(S[j].nrm.w) : -1;
     }
     if (j != 0) return;
     float f = 0.f;
     if (finite) {
         float prev[3] = {T[0], T[1], T[2]}, cur[3];
         for (int k = 0; k < N; ++k) {
-            load3(&S[s0 + k].pos, cur);
+            load3(&S[k].pos, cur);
             f += dist3(cur, prev);
             prev[0] = cur[0];
             prev[1] = cur[1];
