@@ -59,18 +59,21 @@ struct TraceArgs {
 // Rays a wave traces together when n rays are active.  A wave lasts as long as
 // its longest ray and tests its lanes' leaves together, so while the waves do
 // not fill the GPU fewer rays per wave end sooner; once they do, every extra
-// wave costs its own instructions.  The line is at 8,192 waves (8 per SIMD).
-// 16 k rays in a room, four segments: 0.391 ms with 64 rays a wave, 0.352
-// with 32, 0.318 with 16, 0.304 with 8, 0.357 with 4.  766 k rays in a street:
-// 0.338 ms with 64, 0.452 with 32; 196 k: 0.525 and 0.401 ms.  Every wave
-// culls and tests the receivers once, so many receivers move the line down:
-// 200 k rays and 1,024 of them take 0.94 ms by the line moved so, 1.02 by the
-// line as it is for few.
+// wave costs its own instructions.  The line is at 8,192 waves (8 per SIMD) for
+// 32 rays a wave, and at 4,096 for fewer, which leave most lanes idle.  16 k
+// rays in a room, four segments: 0.391 ms with 64 rays a wave, 0.352 with 32,
+// 0.318 with 16, 0.304 with 8, 0.357 with 4.  766 k rays in a street: 0.338 ms
+// with 64, 0.452 with 32; 196 k: 0.525 and 0.401 ms.  80 k rays, a whole launch:
+// of 40 TX in an empty room 338 us with 64 and the walk before this one, 362
+// with 16, 293 with 32; in a furnished room 440 and 423, in a street 562 and
+// 545.  Every wave culls and tests the receivers once, so many receivers move
+// the line down: 200 k rays and 1,024 of them take 0.94 ms by the line moved
+// so, 1.02 by the line as it is for few.
 constexpr uint32_t RPW_MIN = 8, RPW_WAVES = 8192, RPW_RX = 512;
 __host__ __device__ __forceinline__ uint32_t rays_per_wave(uint32_t n, uint32_t n_rx) {
     const uint32_t waves = RPW_WAVES * RPW_RX / (RPW_RX + n_rx);
     uint32_t r = 64;
-    while (r > RPW_MIN && n / (r / 2) <= waves) r /= 2;
+    while (r > RPW_MIN && n / (r / 2) <= (r > 32 ? waves : waves / 2)) r /= 2;
     return r;
 }
 
