@@ -542,9 +542,10 @@ __global__ void k_leaf_counts(uint2* leaf, int64_t n_leaves, int64_t m) {
 // Both work on the rows of y0 <= y < y0 + ny of every slab: a large grid is
 // done in turns, so that the planes (224 B a word) stay small.
 // Bound by the loads of the rows (each word read 16 times from the caches) and
-// the 8 B written per cell.  8 M cells (a 20M-point street's 1 m cells): 33 us
-// and 97 us; the isotropic radii of every leaf cell and the bricks' boxes that
-// they replace took 1.1 ms.
+// the 8 B written per cell.  8 M cells (a 20M-point street's 1 m cells): 31 us
+// and 96 us; the isotropic radii of every leaf cell and the bricks' boxes that
+// they replace took 1.1 ms.  Small grids by the latency of the loads, which are
+// batched: 360 k cells 13 and 20 us (16 and 24 one after another).
 constexpr int TOP_NS = 7;
 __device__ constexpr int TOP_SIZES[TOP_NS] = {2, 3, 4, 6, 8, 12, 16};
 
@@ -559,20 +560,29 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_top_rows(const uint64_t* occ, i
     const int64_t row0 = ((int64_t)z * dy + y) * words;  // first word of the row
     uint64_t acc[TOP_NS] = {0, 0, 0, 0, 0, 0, 0};
     const bool nx = q & 1, my = q & 2;
-    for (int j = 0; j < TOP_SIZES[TOP_NS - 1]; ++j) {
-        const int yy = my ? y - j : y + j;
-        if (yy < 0 || yy >= dy) break;
-        const uint64_t* row = occ + row0 + (int64_t)(yy - y) * words;
-        const uint64_t cur = row[w];
-        const uint64_t nb = nx ? (w > 0 ? row[w - 1] : 0ull) : (w + 1 < words ? row[w + 1] : 0ull);
-        if (!(cur | nb)) continue;
-        uint64_t d = cur;
-        int k = 1;
+    // eight rows are loaded before any is used
+    for (int j0 = 0; j0 < TOP_SIZES[TOP_NS - 1]; j0 += 8) {
+        uint64_t cur[8], nb[8];
 #pragma unroll
-        for (int s = 0; s < TOP_NS; ++s) {
-            for (; k < TOP_SIZES[s]; ++k)
-                d |= nx ? (cur << k) | (nb >> (64 - k)) : (cur >> k) | (nb << (64 - k));
-            if (j < TOP_SIZES[s]) acc[s] |= d;
+        for (int j = 0; j < 8; ++j) {
+            const int yy = my ? y - (j0 + j) : y + (j0 + j);
+            const bool in = yy >= 0 && yy < dy;
+            const uint64_t* row = occ + row0 + (int64_t)(in ? yy - y : 0) * words;
+            const int wn = nx ? w - 1 : w + 1;
+            cur[j] = in ? row[w] : 0ull;
+            nb[j] = in && wn >= 0 && wn < words ? row[wn] : 0ull;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (!(cur[j] | nb[j])) continue;
+            uint64_t d = cur[j];
+            int k = 1;
+#pragma unroll
+            for (int s = 0; s < TOP_NS; ++s) {
+                for (; k < TOP_SIZES[s]; ++k)
+                    d |= nx ? (cur[j] << k) | (nb[j] >> (64 - k)) : (cur[j] >> k) | (nb[j] << (64 - k));
+                if (j0 + j < TOP_SIZES[s]) acc[s] |= d;
+            }
         }
     }
 #pragma unroll
@@ -594,13 +604,15 @@ __global__ __launch_bounds__(BUILD_BLOCK) void k_top_codes(const uint64_t* occ, 
             const int z = (int)(i / slab);
             const bool nz = o & 4;
             uint64_t above = ~0ull;
-            for (int s = 0; s < TOP_NS && above; ++s) {
+#pragma unroll
+            for (int s = 0; s < TOP_NS; ++s) {
+                if (!above) break;
                 const uint64_t* pl = plane + ((int64_t)(o & 3) * TOP_NS + s) * n + i;
                 uint64_t occd = 0;
+#pragma unroll
                 for (int k = 0; k < TOP_SIZES[s]; ++k) {
                     const int zz = nz ? z - k : z + k;
-                    if (zz < 0 || zz >= dz) break;
-                    occd |= pl[(int64_t)(zz - z) * slab];
+                    if (zz >= 0 && zz < dz) occd |= pl[(int64_t)(zz - z) * slab];
                 }
                 above = e[s] = ~occd;
             }
