@@ -939,14 +939,14 @@ __device__ __forceinline__ bool tail_next(const SdfArgs& a, uint32_t& item) {
     return item < min(a.tail_cnt[0], a.tail_cap);
 }
 
-// The rays left over by k_sdf, one wave each.
+// The rays left over by k_sdf, or all rays (no list), one wave each.
 template <int NL, bool FAST>
 __global__ __launch_bounds__(SDF_BLOCK) void k_sdf_tail(SdfArgs a) {
     __shared__ SdfRuns runs;
     __shared__ SdfMarch keep;
-    uint32_t item;
-    while (tail_next(a, item)) {
-        const uint32_t i = a.tail[item];
+    uint32_t item = blockIdx.x;
+    for (; a.tail ? tail_next(a, item) : item < a.n; item += gridDim.x) {
+        const uint32_t i = a.tail ? a.tail[item] : item;
         const size_t i3 = 3 * (size_t)i, i2 = 2 * (size_t)i;
         const float o[3] = {a.o[i3], a.o[i3 + 1], a.o[i3 + 2]};
         float d[3] = {a.d[i3], a.d[i3 + 1], a.d[i3 + 2]};
@@ -1022,7 +1022,7 @@ __global__ void k_sdf_launch_keys(const float* tx, const float* dirs, uint32_t n
 }
 
 // Samples of one segment after which a lane leaves its ray to the tail kernel
-// (at its first sample in bundles of at most SDF_TAIL_ALL rays), and room for
+// (bundles of at most SDF_TAIL_ALL rays are its from the start), and room for
 // at least so many rays (a sixteenth of larger bundles; the rest stay with
 // their lanes).  A lane marches a ray's samples one after another at about
 // 20 us each, so a kernel lasts as long as its longest ray: of 500 k rays in a
@@ -1040,7 +1040,7 @@ static unsigned tail_waves(uint32_t n) { return std::min<unsigned>(std::max(n, 1
 template <int NL, bool FAST>
 static void launch_sdf_fast(const SdfArgs& a, hipStream_t s) {
     const unsigned grid = (a.n + SDF_BLOCK - 1) / SDF_BLOCK;
-    hipLaunchKernelGGL((k_sdf<NL, FAST>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
+    if (a.tail) hipLaunchKernelGGL((k_sdf<NL, FAST>), dim3(grid), dim3(SDF_BLOCK), 0, s, a);
     hipLaunchKernelGGL((k_sdf_tail<NL, FAST>), dim3(tail_waves(a.n)), dim3(SDF_BLOCK), 0, s, a);
 }
 
@@ -1054,6 +1054,7 @@ static void launch_sdf_nl(const SdfArgs& a, hipStream_t s) {
 static int tail_alloc(SdfArgs& a, uint32_t n, bool launch, DevBufs& T, hipStream_t s) {
     // counted runs march every ray on its lane: the counts are those of the serial march
     a.budget = a.stats ? ~0u : n <= SDF_TAIL_ALL ? 0u : SDF_BUDGET;
+    if (a.budget == 0u && !launch) return PCRL_OK;  // no list: all rays
     a.tail_cap = std::min(n, std::max(n / 16, SDF_TAIL_MIN));
     n = std::max(a.tail_cap, 1u);
     PCRL_TRY(T.alloc(&a.tail_cnt, 2));
@@ -1150,7 +1151,8 @@ static int build_walk(const PcrlScene* S, hipStream_t s, DevBufs& B, SceneView& 
     return hipGetLastError() == hipSuccess ? PCRL_OK : PCRL_EHIP;
 }
 
-// Every point once, in the leaf that holds its centre (under the scene's lock).
+// Every point once, in the leaf that holds its centre (under the scene's
+// lock; the caller waits for the stream).
 static int own_points(PcrlScene* S, hipStream_t s) {
     if (S->own_scan) return PCRL_OK;
     const SceneView& v = S->view;
@@ -1173,7 +1175,7 @@ static int own_points(PcrlScene* S, hipStream_t s) {
     if (!rc) {
         hipLaunchKernelGGL(k_own_scatter, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, v.surf, scan,
                            (uint32_t)m, (uint32_t)np, own);
-        rc = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? PCRL_OK : PCRL_EHIP;
+        if (hipGetLastError() != hipSuccess) rc = PCRL_EHIP;
     }
     if (rc) {
         B.release();
@@ -1189,7 +1191,10 @@ static int own_points(PcrlScene* S, hipStream_t s) {
 
 int scene_own_index(PcrlScene* S, hipStream_t s) {
     std::lock_guard<std::mutex> lock(S->own_mu);
-    return own_points(S, s);
+    if (S->own_scan) return PCRL_OK;
+    PCRL_TRY(own_points(S, s));
+    PCRL_TRY_HIP(hipStreamSynchronize(s));
+    return PCRL_OK;
 }
 
 // The implicit surface's index of the scene (the own points, their leaves'
@@ -1205,6 +1210,7 @@ static int sdf_index(PcrlScene* S, hipStream_t s) {
     SceneView v{};
     int rc = build_walk(S, s, B, v);
     if (rc) {
+        (void)hipStreamSynchronize(s);  // the own points stay
         B.release();
         if (rc == PCRL_EHIP) set_error("sdf_intersect: building the leaf walk failed");
         return rc;
@@ -1243,6 +1249,7 @@ static int sdf_index(PcrlScene* S, hipStream_t s) {
         if (!rc) rc = hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? PCRL_OK : PCRL_EHIP;
     }
     if (rc) {
+        (void)hipStreamSynchronize(s);
         B.release();
         if (rc == PCRL_EHIP) set_error("sdf_intersect: building the own-point index failed");
         return rc;
