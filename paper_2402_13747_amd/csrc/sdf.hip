@@ -63,6 +63,7 @@ struct SdfArgs {
     // rays left to the tail kernel (one wave each)
     uint32_t budget;       // samples of one segment after which a lane leaves its ray to it
     uint32_t tail_cap;     // most of them; further rays stay with their lanes
+    uint32_t leaves;       // leaves handed out at first (then four times as many, up to 64)
     uint32_t* tail;        // their ray ids
     uint32_t* tail_cnt;    // [0] their number, [1] the next to be taken
     float4* tail_ray;      // launches: per ray (o, L), (d, t_lo)
@@ -800,8 +801,8 @@ __global__ __launch_bounds__(SDF_BLOCK) void k_sdf_launch(SdfLaunchArgs A) {
 }
 
 // First intersection of one ray found by a whole wave (every lane holds the
-// same ray): the walk hands its leaves out to the lanes, up to 64 at a time,
-// and every lane marches its own.  The nearest over the leaves is the same as
+// same ray): the walk hands its leaves out to the lanes, `leaves` of them, then
+// four times as many, up to 64 at a time, and every lane marches its own.  The nearest over the leaves is the same as
 // marching them one after another, the earliest leaf of the walk among equals:
 // a march is only ever cut where no nearer result can follow.  Leaves of the
 // shared march from t_lo continue each other's samples, so every lane marches
@@ -815,7 +816,7 @@ __device__ __forceinline__ void wave_first_hit(SdfRuns& runs, SdfMarch& keep, co
     uint32_t reads = 0;  // not counted here
     SdfMarch M;
     bool walking = march_begin(M, o, d, t_lo, t_hi);
-    while (walking) {
+    for (uint32_t most = reread_sdf().leaves; walking; most = min(64u, most * 4u)) {
         // hand out leaves
         uint32_t n = 0;
         float jt = 0.f, jtb = -INFINITY;
@@ -823,7 +824,7 @@ __device__ __forceinline__ void wave_first_hit(SdfRuns& runs, SdfMarch& keep, co
         {
             const SdfArgs& a = reread_sdf();
             const SceneView& v = a.v;
-            while (walking && n < 64) {
+            while (walking && n < most) {
                 DdaCell k;
                 dda_cell_reset(k);
                 dda_locate<NL>(v, M.S, k);
@@ -1032,7 +1033,13 @@ __global__ void k_sdf_launch_keys(const float* tx, const float* dirs, uint32_t n
 // without the tail and 31.5, 11.6, 9.7 and 12.8 ms with a budget of 24, 48, 96
 // and 192 (k_sdf 7.0, k_sdf_tail 2.1 ms at 96); a launch of 150 k rays with
 // two reflections (400 k points) 36.3, then 44.3, 24.7, 21.5 and 24.1 ms.
-constexpr uint32_t SDF_BUDGET = 96, SDF_TAIL_ALL = 4096, SDF_TAIL_MIN = 65536;
+// Up to SDF_SOON rays a wave hands four leaves out at first: most of a few rays
+// end at one of them.  One ray, mean of 64: 160 us against 208 with 64 leaves
+// (294 marched on a lane) in the room, 128 against 151 (218) in a street, 266
+// against 341 (237) there with bricks of 40^3 leaves, whose walk is long; in more
+// rays, and among the stragglers, the longest one counts, which loses a tenth
+// by it.
+constexpr uint32_t SDF_BUDGET = 96, SDF_TAIL_ALL = 4096, SDF_TAIL_MIN = 65536, SDF_SOON = 8;
 
 // Waves of the tail kernel: four per SIMD stay resident.
 static unsigned tail_waves(uint32_t n) { return std::min<unsigned>(std::max(n, 1u), (unsigned)device_cus() * 16); }
@@ -1054,6 +1061,7 @@ static void launch_sdf_nl(const SdfArgs& a, hipStream_t s) {
 static int tail_alloc(SdfArgs& a, uint32_t n, bool launch, DevBufs& T, hipStream_t s) {
     // counted runs march every ray on its lane: the counts are those of the serial march
     a.budget = a.stats ? ~0u : n <= SDF_TAIL_ALL ? 0u : SDF_BUDGET;
+    a.leaves = n <= SDF_SOON && !launch ? 4u : 64u;
     if (a.budget == 0u && !launch) return PCRL_OK;  // no list: all rays
     a.tail_cap = std::min(n, std::max(n / 16, SDF_TAIL_MIN));
     n = std::max(a.tail_cap, 1u);
