@@ -45,7 +45,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(TraceArgs a, int b, uint3
     for (uint32_t base = wave * rpw; base < n_act; base += blocks * WAVES * rpw)
         trace_chunk<FIRST, STATS, TD, OTD>(kernel_args(), lds.ahead, lds.w[threadIdx.x >> 6], b, base, rpw, n_act, false,
                                           cnt);
-    flush_stats<STATS>(cnt, a.stats ? a.stats + (size_t)b * PCRL_NSTATS : nullptr);
+    flush_stats_block<STATS>(cnt, a.stats ? a.stats + (size_t)b * PCRL_NSTATS : nullptr);
 }
 
 // Fibonacci-lattice direction j of n (FP64, rounded to FP32).
