@@ -819,8 +819,10 @@ constexpr int64_t TOP_PLANE_WORDS = (int64_t)4 << 20;
 // little in a large scene.  Frame and launch (300 k or 1 M rays) in a 20M-point
 // street, 8 M cells: of 1.4 k points 0.42 + 1.55 ms and 64.5 MB with the grid of
 // its 1 m cells, 0.35 + 1.50 ms and 0.6 MB with that of its 8 m cells; of 50 k
-// points 0.50 + 2.19 ms and 81.5 MB, 0.41 + 2.15 ms and 17.6 MB.
-constexpr int64_t OVERLAY_TOP_CELLS = (int64_t)1 << 18, OVERLAY_CELLS_PER_POINT = 16;
+// points 0.50 + 2.19 ms and 81.5 MB, 0.41 + 2.15 ms and 17.6 MB.  100 k points
+// in a grid of 2.1 M cells of 1 m (launches of 65 k to 1 M rays): 1.37 ms a
+// launch with that grid, 1.40 with the coarser one that 16 a point would take.
+constexpr int64_t OVERLAY_TOP_CELLS = (int64_t)1 << 18, OVERLAY_CELLS_PER_POINT = 32;
 
 static int64_t top_cells(const SceneView& v) { return (int64_t)v.tdim[0] * v.tdim[1] * v.tdim[2]; }
 
